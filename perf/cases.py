@@ -1,0 +1,192 @@
+"""The calls that a user of this library makes, as cases to time: vla_forward over whole sequences (prefill) and
+vla_decode_step (generation, one token on a resident state).
+
+A case is a dict: kind ("forward" or "decode"), B, H, d_k, d_v, dtype ("f32" or "bf16": q, k, v and o), T (forward),
+values ("gaussian" or "recall"), std of the Gaussian values, lambda0, carried (the call continues from a given S, A)
+and the optional lines of Algorithm 1 (u, refresh, normalise, feature_map).
+"""
+import math
+
+import torch
+
+import paper_2605_11196_amd as vla
+
+DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
+RING = 32   # tokens that a decode case steps through
+
+
+def _case(kind, B, H, d, dtype, *, T=1, d_v=None, std=1.0, lambda0=0.1, values="gaussian", carried=False, u=False,
+          refresh=0, normalise=False, feature_map=False, name=None):
+    c = dict(kind=kind, B=B, H=H, T=T, d_k=d, d_v=d if d_v is None else d_v, dtype=dtype, std=std, lambda0=lambda0,
+             values=values, carried=carried, u=u, refresh=refresh, normalise=normalise, feature_map=feature_map)
+    if name:
+        c["name"] = name
+    return c
+
+
+_PAPER = dict(u=True, refresh=20, normalise=True, feature_map=True)   # every optional line of Algorithm 1
+
+
+def listed():
+    return [
+        # generation for one sequence of 16 heads: a launch and the host path
+        _case("decode", 1, 16, 64, "bf16", name="decode_few_heads"),
+        # generation for a serving batch: the state of 2048 heads through HBM once
+        _case("decode", 64, 32, 128, "bf16", std=128 ** -0.5, name="decode_large_batch"),
+        # generation with the paper's whole head, float32, an ordinary batch
+        _case("decode", 64, 4, 64, "f32", name="decode_options", **_PAPER),
+        # the smallest sequence: one head, 256 tokens
+        _case("forward", 1, 1, 16, "f32", T=256, lambda0=1.0, name="tiny"),
+        # associative recall: sparse writes and reads among zero tokens, 256 heads
+        _case("forward", 64, 4, 64, "f32", T=2048, values="recall", name="recall"),
+        # one sequence of 16 heads, short, long, and with heads of 128
+        _case("forward", 1, 16, 64, "bf16", T=4096, name="context_4096"),
+        _case("forward", 1, 16, 64, "bf16", T=131072, name="context_131072"),
+        _case("forward", 1, 16, 128, "bf16", T=32768, name="context_32768_d128"),
+        # the later part of a sequence (state carried in) of odd length, heads of unequal sizes, float32
+        _case("forward", 3, 13, 128, "f32", T=1537, d_v=64, carried=True, name="carried_ragged"),
+        # throughput over a large batch, at both head sizes that throughput is quoted for
+        _case("forward", 64, 32, 128, "bf16", T=8192, std=128 ** -0.5, name="large_batch"),
+        _case("forward", 64, 32, 64, "bf16", T=8192, std=64 ** -0.5, name="large_batch_d64"),
+        # the same with every optional line of Algorithm 1
+        _case("forward", 64, 32, 128, "bf16", T=8192, std=128 ** -0.5, name="large_batch_options", **_PAPER),
+    ]
+
+
+def _log(rng, lo, hi):
+    return max(lo, min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def draw(rng):
+    d = rng.choice((16, 32, 64, 64, 96, 128, 128))
+    d_v = d if rng.random() < 0.75 else rng.choice((16, 32, 64, 96, 128))
+    dtype = rng.choice(("f32", "bf16", "bf16"))
+    std = rng.choice((1.0, d ** -0.5))
+    options = rng.random()
+    opt = {}
+    if options < 0.15:
+        opt = dict(_PAPER)
+    elif options < 0.3:
+        opt = dict(u=True, normalise=True, feature_map=True)
+    elif options < 0.4:
+        opt = dict(feature_map=True)
+    B, H = _log(rng, 1, 64), rng.randint(1, 32)
+    if rng.random() < 0.25:
+        return _case("decode", B, H, d, dtype, d_v=d_v, std=std, **opt)
+    # no longer than the largest listed call: sequences that only the block kernels take run token block after block
+    serial = d == 16 or opt.get("refresh", 0) > 0
+    T = _log(rng, 16, 16384 if serial else 131072)
+    T = max(16, min(T, int(1.5e11 / (B * H * max(d, 64) * max(d, d_v, 64)))))
+    return _case("forward", B, H, d, dtype, T=T, d_v=d_v, std=std, carried=rng.random() < 0.25, **opt)
+
+
+def _gaussian(shape, std, dtype, gen):
+    return torch.randn(shape, generator=gen, device="cuda", dtype=dtype).mul_(std)
+
+
+def _recall(B, H, T, d, dtype, gen):
+    """n (16, 32, 48, 64 by batch index) unit keys written once in the first half of the sequence and read back in
+    another order in the second half; every other token is zero."""
+    n_max, half, heads = 64, T // 2, B * H
+    keys = torch.randn((heads, n_max, d), generator=gen, device="cuda")
+    keys /= keys.norm(dim=-1, keepdim=True)
+    vals = torch.randn((heads, n_max, d), generator=gen, device="cuda")
+    n = torch.tensor((16, 32, 48, 64), device="cuda")[torch.arange(B, device="cuda") % 4].repeat_interleave(H)
+    live = (torch.arange(n_max, device="cuda") < n[:, None]).unsqueeze(-1)
+
+    def positions(length):
+        return torch.rand((heads, length), generator=gen, device="cuda").argsort(dim=1)[:, :n_max]
+
+    def scatter(pos, rows):
+        x = torch.zeros((heads, T, d), device="cuda")
+        x.scatter_(1, pos.unsqueeze(-1).expand(-1, -1, d), rows * live)
+        return x.view(B, H, T, d).to(dtype)
+
+    write, read = positions(half), half + positions(T - half)
+    return scatter(read, keys), scatter(write, keys), scatter(write, vals)
+
+
+def _options(case, u):
+    o = {}
+    if case["u"]:
+        o.update(u=u, u_scale=case["d_k"] ** -0.5)
+    if case["refresh"]:
+        o.update(refresh_period=case["refresh"], refresh_eta=1e-3)
+    if case["normalise"]:
+        o.update(normalise_output=True)
+    if case["feature_map"]:
+        o.update(feature_map=True)
+    return o
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    B, H, T, d, d_v, std = case["B"], case["H"], case["T"], case["d_k"], case["d_v"], case["std"]
+    dtype = DTYPES[case["dtype"]]
+
+    def tokens(T):
+        q, k = (_gaussian((B, H, T, d), std, dtype, gen) for _ in range(2))
+        v = _gaussian((B, H, T, d_v), std, dtype, gen)
+        return q, k, v, _gaussian((B, H, T, d), 1.0, dtype, gen) if case["u"] else None
+
+    S = A = None
+    if case["carried"] or case["kind"] == "decode":   # the state after the first tokens of the sequence
+        q, k, v, u = tokens(96)
+        _, S, A, z = vla.vla_forward(q, k, v, lambda0=case["lambda0"], return_zkey=True, **_options(case, u))
+    if case["kind"] == "decode":
+        ring = []
+        for _ in range(RING):
+            q, k, v, u = (None if x is None else x[:, :, 0].contiguous() for x in tokens(1))
+            opt = _options(case, u)
+            if case["normalise"]:
+                opt["zkey"] = z
+            ring.append((q, k, v, opt))
+        return dict(kind="decode", ring=ring, S=S, A=A, z=z if case["normalise"] else None, step=96,
+                    refresh=bool(case["refresh"]))
+    if case["values"] == "recall":
+        q, k, v = _recall(B, H, T, d, dtype, gen)
+        u = None
+    else:
+        q, k, v, u = tokens(T)
+    opt = _options(case, u)
+    if case["normalise"] and case["carried"]:
+        opt["zkey0"] = z
+    if case["refresh"] and case["carried"]:
+        opt["step_offset"] = 96
+    return dict(kind="forward", q=q, k=k, v=v, S=S, A=A, lambda0=case["lambda0"], opt=opt)
+
+
+def run(state):
+    if state["kind"] == "forward":
+        return vla.vla_forward(state["q"], state["k"], state["v"], state["S"], state["A"], lambda0=state["lambda0"],
+                               **state["opt"])
+    step = state["step"]
+    q, k, v, opt = state["ring"][step % RING]
+    if state["refresh"]:
+        o = vla.vla_decode_step(q, k, v, state["S"], state["A"], step_offset=step, **opt)
+    else:
+        o = vla.vla_decode_step(q, k, v, state["S"], state["A"], **opt)
+    state["step"] = step + 1
+    return o, state["S"], state["A"], state["z"]
+
+
+def work(case):
+    heads, T, d, d_v = case["B"] * case["H"], case["T"], case["d_k"], case["d_v"]
+    es = 2 if case["dtype"] == "bf16" else 4
+    rows = 2 * d + 2 * d_v + (d if case["u"] else 0)           # q, k, v, o and u of one token
+    state = 4 * (d * d + d * d_v)                              # S and A of one head
+    both = case["kind"] == "decode" or case["carried"]
+    # A: one product and the rank-1 update (two products with a separate u); S: residual, update and read-out
+    flops = (4 + (2 if case["u"] else 0)) * d * d + 6 * d * d_v
+    return {"bytes": heads * (T * rows * es + state * (2 if both else 1)), "flops": heads * T * flops}
+
+
+def tolerance(case):
+    # Four times what the modes of the library (token by token, in blocks, in segments: the same sums in other orders)
+    # differ by.  bf16: the rounding of o decides (1.1e-4 measured; single values change by a unit in the last place).
+    # f32: 2.6e-6 up to some thousand tokens; over long sequences the rounding of A gathers (A after 131072 tokens in
+    # blocks against segments that start from float64 inverses: 2.6e-5).
+    if case["dtype"] == "bf16":
+        return {"rel": 5e-4, "max": 1.6e-2}
+    return {"rel": 1e-5 if case["T"] <= 8192 else 1e-4, "max": 4e-4}
