@@ -13,6 +13,7 @@ import paper_2605_11196_amd as vla
 
 DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
 RING = 32   # tokens that a decode case steps through
+EPS = 1e-4  # the library's default floor of every denominator
 
 
 def _case(kind, B, H, d, dtype, *, T=1, d_v=None, std=1.0, lambda0=0.1, values="gaussian", carried=False, u=False,
@@ -119,6 +120,47 @@ def _options(case, u):
     return o
 
 
+def _recurrence(q, k, v, S, A, z, *, u=None, u_scale=1.0, refresh_period=0, refresh_eta=0.0, normalise_output=False,
+                feature_map=False, step=0):
+    """The recurrence token by token in float64 torch: [B,H,T,d] tensors, S and A float64 and advanced in place, z the
+    key sum; returns o."""
+    B, H, T, d = k.shape
+    flat = lambda x: x.reshape(B * H, T, x.shape[-1]).double()
+    if feature_map:
+        q, k = (torch.nn.functional.elu(x.double()) + 1 for x in (q, k))
+    q, k, v = flat(q), flat(k), flat(v)
+    kn = k / k.norm(dim=-1, keepdim=True).clamp_min(EPS)
+    un = kn if u is None else u_scale * flat(u) / flat(u).norm(dim=-1, keepdim=True).clamp_min(EPS)
+    S, A = (x.view(B * H, x.shape[-2], x.shape[-1]) for x in (S, A))
+    z = z.view(B * H, d)
+    o = torch.empty(v.shape, dtype=torch.float64, device=v.device)
+    for t in range(T):
+        kt, ut = kn[:, t, :, None], un[:, t, :, None]
+        y = A @ ut
+        delta = 1 + (ut * y).sum(1, keepdim=True)
+        A.baddbmm_(y / delta, y.transpose(1, 2), alpha=-1)
+        if refresh_period and (step + t + 1) % refresh_period == 0:
+            A.diagonal(dim1=1, dim2=2).add_(refresh_eta)
+        alpha = A @ kt
+        alpha = alpha / alpha.norm(dim=1, keepdim=True).clamp_min(EPS)
+        S.baddbmm_(v[:, t, :, None] - S @ kt, alpha.transpose(1, 2))
+        z += k[:, t]
+        ot = (S @ q[:, t, :, None])[:, :, 0]
+        if normalise_output:
+            ot = ot / (q[:, t] * z).sum(-1, keepdim=True).clamp_min(EPS)
+        o[:, t] = ot
+    return o.view(B, H, T, -1)
+
+
+def _start(case):
+    """S, A and the key sum before the first token, in float64."""
+    heads = (case["B"], case["H"])
+    S = torch.zeros((*heads, case["d_v"], case["d_k"]), dtype=torch.float64, device="cuda")
+    A = torch.zeros((*heads, case["d_k"], case["d_k"]), dtype=torch.float64, device="cuda")
+    A.diagonal(dim1=2, dim2=3).fill_(1 / case["lambda0"])
+    return S, A, torch.zeros((*heads, case["d_k"]), dtype=torch.float64, device="cuda")
+
+
 def prepare(case, seed):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
@@ -133,7 +175,10 @@ def prepare(case, seed):
     S = A = None
     if case["carried"] or case["kind"] == "decode":   # the state after the first tokens of the sequence
         q, k, v, u = tokens(96)
-        _, S, A, z = vla.vla_forward(q, k, v, lambda0=case["lambda0"], return_zkey=True, **_options(case, u))
+        S, A, z = _start(case)
+        _recurrence(q, k, v, S, A, z, **_options(case, u))
+        S, A, z = S.float(), A.float(), z.float()
+        A = 0.5 * (A + A.transpose(2, 3))
     if case["kind"] == "decode":
         ring = []
         for _ in range(RING):
@@ -169,6 +214,34 @@ def run(state):
         o = vla.vla_decode_step(q, k, v, state["S"], state["A"], **opt)
     state["step"] = step + 1
     return o, state["S"], state["A"], state["z"]
+
+
+def exact(case, seed):
+    """What run() returns, token by token in float64; not for the cases of a thousand long sequences and more."""
+    B, H, T = case["B"], case["H"], case["T"]
+    if B * H * T * case["d_k"] * case["d_v"] > 4e10 or T > 65536:
+        return None
+    state = prepare(case, seed)
+    if state["kind"] == "decode":
+        q, k, v, opt = state["ring"][state["step"] % RING]
+        q, k, v = (x.unsqueeze(2) for x in (q, k, v))
+        opt = {key: x for key, x in opt.items() if key != "zkey"}
+        if "u" in opt:
+            opt["u"] = opt["u"].unsqueeze(2)
+        S, A = state["S"].double(), state["A"].double()
+        z = torch.zeros((B, H, case["d_k"]), dtype=torch.float64, device="cuda") if state["z"] is None \
+            else state["z"].double()
+        o = _recurrence(q, k, v, S, A, z, step=state["step"], **opt)
+        return o[:, :, 0], S, A, None if state["z"] is None else z
+    S, A, z = _start(case)
+    if state["S"] is not None:
+        S, A = state["S"].double(), state["A"].double()
+    opt = dict(state["opt"])
+    step = opt.pop("step_offset", 0)
+    if "zkey0" in opt:
+        z = opt.pop("zkey0").double()
+    o = _recurrence(state["q"], state["k"], state["v"], S, A, z, step=step, **opt)
+    return o, S, A
 
 
 def work(case):
