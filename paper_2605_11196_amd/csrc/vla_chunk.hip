@@ -21,12 +21,18 @@
 // A zero key gives an all-zero row in Y, W and E, so padding the last block with zero tokens is exact.
 //
 // Work split: NW waves per (batch, head); wave w owns columns [SL*w, SL*w+SL) of A and the same rows of
-// S, as 16x16 MFMA accumulator tiles that stay in VGPRs for the whole sequence (A is symmetric, so an
+// S, as 16x16 float32 accumulator tiles that stay in VGPRs for the whole sequence (A is symmetric, so an
 // accumulator tile of A can be fed straight back as the B operand).  The C x C factorisations run on
 // one wave (rotating with the block index) with lanes = rows and v_readlane broadcasts.
 //
-// v_mfma_f32_16x16x4_f32 register layout, lane l = 16*g + c:
-//   A operand: A[m = c][k = g]      B operand: B[k = g][n = c]      C/D: reg r -> D[m = 4g + r][n = c]
+// What bounds it: instruction issue -- the matrix unit, the vector instructions that split the state, and the two
+// serial sections, of which one head hides the other's.  The five sweeps over A and S are FP32 products formed
+// from bf16 terms (vla_mfma_util.h): the state is split into three terms as it is read (11 instructions per two
+// elements, once per block: S for both of its products), bf16 keys and queries are one term each, float32 ones
+// three; W and E are split once per block.  On FP32 matrix instructions the matrix unit alone took 78 % of the time
+// (large batch: 2048 heads of 128, 8192 tokens, bf16 q, k, v: 25.1 ms); with the split products 16.5 ms, 167
+// TFLOP/s, above the FP32 matrix peak of 157.  2048 heads of 64: 8.3 -> 6.2 ms; 256 heads of 64, float32, 2048
+// tokens: 0.63 -> 0.48 ms.  Error against float64 on the latter 4.3e-7 -> 3.8e-7 (2-norm, relative).
 #include "vla_mfma_util.h"
 
 namespace vla {
@@ -59,7 +65,15 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   constexpr int NJV = kEven ? TV / NW : (TV + NW - 1) / NW;   // tile slots per wave
   static_assert(DV % 16 == 0 && NJV >= 1, "whole tiles of S");
   constexpr int NB = D / 16;       // 16-row blocks over the whole head dimension
-  constexpr int LD = D + 4;        // row stride of the token-major LDS arrays
+  constexpr int NKB = (NB + 1) / 2;   // 32-column steps of a contraction over the head dimension
+  // Head size 16 is a single tile: half of the slots of a bf16 product would be empty and nothing but the latency of
+  // the chain counts (one head of 256 tokens: 51 us with FP32 products, 55 us with split ones), so its products
+  // stay on the FP32 matrix instruction and its operands are staged as they are.
+  constexpr bool kSplit = D > 16;
+  // operand terms of k and q: bf16 numbers are exact in one, float32 ones (and mapped ones) take three
+  constexpr int KT = (sizeof(IO) == 2 && !FMAP) || !kSplit ? 1 : 3;
+  constexpr int LDK = 32 * NKB + 8;   // row stride (bf16) of the staged operands: an odd number of 16-byte pieces
+  constexpr int LDY = SL + 4;         // row stride of a wave's slab of Y^T
   constexpr int NT = 64 * NW;
   // Staging: a token row is split over TPR threads of EPT elements each.  For the power-of-two head sizes every
   // thread stages; at d = 96 a row takes 6 threads of 16 elements in a group of 8 (two lanes of each group and
@@ -68,20 +82,23 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   constexpr bool PADDED = (TPR0 & (TPR0 - 1)) != 0;
   constexpr int EPT = PADDED ? 16 : C * D / NT;  // staged elements per thread per tensor
   constexpr int TPR = PADDED ? 8 : D / EPT;      // thread slots per token row
-  static_assert(EPT % 4 == 0 && TPR <= 16 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
+  static_assert(EPT % 4 == 0 && TPR <= 32 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
-  __shared__ __align__(16) float Ksb[2][C * LD];      // K^  [t][j], double-buffered over blocks
-  __shared__ __align__(16) float Qsb[2][C * LD];      // Q   [t][j]
-  __shared__ __align__(16) float Ys[C * LD];          // Y^T [t][j] (each wave touches only its columns)
-  __shared__ __align__(16) float Wb[D * LT];          // W   [j][t]
-  __shared__ __align__(16) float Gp[NW][2][C * LT];   // per-wave partial Gram matrices G, GQ  [s][t]
+  __shared__ __align__(16) uint16_t Ksb[2][KT][C * LDK];   // k [t][slot], terms, double-buffered over blocks
+  __shared__ __align__(16) uint16_t Qsb[2][KT][C * LDK];   // q
+  __shared__ __align__(16) u4 Whm[D * 4];                  // W [j][t], terms h and m
+  __shared__ __align__(16) u2 Wl[D * 4];                   //           term l
+  __shared__ __align__(16) float Gp[NW][2][C * LT];   // per-wave partial Gram matrices G, GQ  [s][t]; first the
+                                                      // wave's slab of Y^T [t][j], which no other wave reads
   __shared__ __align__(16) float Lis[C * LT];         // L^{-1} [t][s]
   __shared__ __align__(16) float Lrs[C * LT];         // L [t][s] (rows), for the wave that forms Z
   __shared__ __align__(16) float Zs[C * LT];          // Z   [t][s]
   __shared__ __align__(16) float NQs[C * LT];         // -NQ^T [t][s]
   __shared__ __align__(16) float wn2p[NW][C];         // per-wave partial ||w_t||^2
   __shared__ __align__(16) float cvec[C];             // -c_t
+  __shared__ __align__(16) float rns[2][C];           // 1 / max(||k_t||, eps)
+  static_assert(C * LDY <= 2 * C * LT, "a slab of Y^T fits the wave's Gram tiles");
 
   const int head = blockIdx.x;
   const int tid = threadIdx.x;
@@ -175,8 +192,23 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int jn = 0; jn < NJV; ++jn) vpre[jn][r] = vh[voff + (s_row(jn) - s_row(0))];
     }
   };
-  // normalise this thread's share of the keys of the block starting at t0 and put K^, Q into LDS half `buf`
-  auto stage = [&](int t0, int buf) {
+  // four elements (j0 a multiple of 4) of this thread's row into the operand terms
+  auto put4 = [&](uint16_t (&dst)[KT][C * LDK], int j0, f4 x) {
+    u2 h, m, l;
+    const int at = srow * LDK + kslot(j0);
+    if constexpr (!kSplit) {
+      *reinterpret_cast<f4*>(&dst[0][srow * LDK + 2 * j0]) = x;
+    } else if constexpr (KT == 1) {   // exact: the low halves are zero
+      *reinterpret_cast<u2*>(&dst[0][at]) = u2{pack_tops(x[0], x[1]), pack_tops(x[2], x[3])};
+    } else {
+      split3_rne(x, h, m, l);
+      *reinterpret_cast<u2*>(&dst[0][at]) = h;
+      *reinterpret_cast<u2*>(&dst[1][at]) = m;
+      *reinterpret_cast<u2*>(&dst[2][at]) = l;
+    }
+  };
+  // put this thread's share of the keys and queries of the block starting at t0, and the key norms, into LDS half `buf`
+  auto stage = [&](int t0, int buf) __attribute__((always_inline)) {
     if (!stage_wave) return;
     float kx[EPT];
     const bool ragged = t0 + C > T;   // uniform: only the last block can hold rows past the end
@@ -210,24 +242,77 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     float rn = __builtin_amdgcn_rsqf(sm);
     rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f);
     if (!stager) return;
+    if constexpr (!kSplit) {   // FP32 products take the normalised keys themselves
 #pragma unroll
-    for (int e = 0; e < EPT; e += 4) {
-      *reinterpret_cast<f4*>(&Ksb[buf][srow * LD + sseg + e]) =
-          f4{kx[e] * rn, kx[e + 1] * rn, kx[e + 2] * rn, kx[e + 3] * rn};
+      for (int e = 0; e < EPT; ++e) kx[e] *= rn;
+      rn = 1.0f;
     }
-    qpre.unpack(kx);
+    if (sseg == 0) rns[buf][srow] = rn;
+#pragma unroll
+    for (int e = 0; e < EPT; e += 4) put4(Ksb[buf], sseg + e, f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]});
+    float qx[EPT];
+    qpre.unpack(qx);
     if constexpr (FMAP) {
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) kx[e] = elu_plus_one(kx[e]);
+      for (int e = 0; e < EPT; ++e) qx[e] = elu_plus_one(qx[e]);
     }
     if (ragged) {
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) kx[e] = live ? kx[e] : 0.0f;
+      for (int e = 0; e < EPT; ++e) qx[e] = live ? qx[e] : 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < EPT; e += 4) {
-      *reinterpret_cast<f4*>(&Qsb[buf][srow * LD + sseg + e]) = f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]};
+    for (int e = 0; e < EPT; e += 4) put4(Qsb[buf], sseg + e, f4{qx[e], qx[e + 1], qx[e + 2], qx[e + 3]});
+  };
+  // operand terms of the tokens' columns 32 kb .. 32 kb + 31
+  auto operand = [&](const uint16_t (&src)[KT][C * LDK], int kb) {
+    Terms<KT> x;
+#pragma unroll
+    for (int i = 0; i < KT; ++i) {
+      x.t[i] = *reinterpret_cast<const u4*>(&src[i][c * LDK + 32 * kb + 8 * g]);   // (kSplit or not: 16 bytes at 16 g)
     }
+    return x;
+  };
+  // acc += x X over the columns of two accumulator tiles of X (one tile without the split)
+  auto sweep = [&](const Terms<KT>& x, const auto& X, f4 acc) {
+    if constexpr (kSplit) {
+      return mfma_terms(x, X, acc);
+    } else {
+      const f4 xa = __builtin_bit_cast(f4, x.t[0]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = mfma16(xa[r], X[r], acc);
+      return acc;
+    }
+  };
+  // the LDS image of W, and updates X += W y over the block's tokens (y: four tokens per lane)
+  auto w_store = [&](int row, f4 x) {
+    if constexpr (kSplit) tok_store(Whm, Wl, row, c, g, x);
+    else Whm[4 * row + tok_chunk(c, g)] = __builtin_bit_cast(u4, x);
+  };
+  auto w_load = [&](int row) {
+    if constexpr (kSplit) return tok_load(Whm, Wl, row, c, g);
+    else return __builtin_bit_cast(f4, Whm[4 * row + tok_chunk(c, g)]);
+  };
+  auto w_neg_b = [&](int row) {
+    if constexpr (kSplit) return tok_neg_b(Whm, Wl, row, c, g);
+    else return -__builtin_bit_cast(f4, Whm[4 * row + tok_chunk(c, g)]);
+  };
+  auto tokens_b = [&](f4 x) {
+    if constexpr (kSplit) return tok_b(x);
+    else return x;
+  };
+  auto update = [&](const auto& wa, const auto& y, f4 acc) {
+    if constexpr (kSplit) {
+      return mfma_tok(wa, y, acc);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = mfma16(wa[r], y[r], acc);
+      return acc;
+    }
+  };
+  using TokenB = decltype(tokens_b(f4{}));
+  auto tiles = [&](f4 x0, f4 x1) {
+    if constexpr (kSplit) return split_tiles(x0, x1);
+    else return x0;
   };
 
   if (T > 0) {
@@ -241,77 +326,54 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   prio<kLevels, 1, -1>();
   int blk = 0;
   for (int t0 = 0; t0 < T; t0 += C, ++blk) {
-    const float* Ks = Ksb[blk & 1];
-    const float* Qs = Qsb[blk & 1];
+    const uint16_t (&Ks)[KT][C * LDK] = Ksb[blk & 1];
+    const uint16_t (&Qs)[KT][C * LDK] = Qsb[blk & 1];
     // staging of the next block (this thread's share): done where this wave is not on the critical path
     auto stage_next = [&]() {
-      if (t0 + C < T) {
-        stage(t0 + C, (blk + 1) & 1);
-        if (t0 + 2 * C < T) load_kq(t0 + 2 * C);
-      }
+      if (t0 + C < T) stage(t0 + C, (blk + 1) & 1);
     };
-    f4 ft[NJV];  // starts as -V^T, becomes -F^T = K^ S0^T - V^T
-#pragma unroll
-    for (int jn = 0; jn < NJV; ++jn)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ft[jn][r] = neg_widen(vpre[jn][r]);
-    if (t0 + C > T) {  // uniform: rows past the end of the sequence are zero tokens
-#pragma unroll
-      for (int jn = 0; jn < NJV; ++jn)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ft[jn][r] = (t0 + 4 * g + r < T) ? ft[jn][r] : 0.0f;
-    }
-    if (t0 + C < T) load_v(t0 + C);
-
-    // ================= Y^T = K^ A0 (this wave's columns); Y^T goes to LDS for the Gram products
+    auto fetch_next = [&]() {
+      if (t0 + 2 * C < T) load_kq(t0 + 2 * C);
+    };
+    // ================= Y^T = K^ A0 (this wave's columns)
     f4 yt[NJ];
-#pragma unroll
-    for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const f4 ka = lds4(&Ks[c * LD + 16 * b + 4 * g]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) yt[jn] = mfma16(ka[r], At[b][jn][r], yt[jn]);
-    }
-#pragma unroll
-    for (int jn = 0; jn < NJ; ++jn)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Ys[(4 * g + r) * LD + col0 + 16 * jn + c] = yt[jn][r];
-    // ================= -F^T = K^ S0^T - V^T  (covers the LDS round trip of Y^T)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const f4 ka = lds4(&Ks[c * LD + 16 * b + 4 * g]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int jn = 0; jn < NJV; ++jn) ft[jn] = mfma16(ka[r], St[b][jn][r], ft[jn]);
-    }
-    // ================= partial Gram matrices over this wave's columns (independent accumulators)
     {
-      f4 gg[NJ], gq[NJ];
 #pragma unroll
-      for (int jn = 0; jn < NJ; ++jn) {
-        const int o4 = c * LD + col0 + 16 * jn + 4 * g;
-        const f4 ya = lds4(&Ys[o4]);  // same-wave write -> read: LDS operations of one wave are ordered
-        const f4 kb = lds4(&Ks[o4]);
-        const f4 qb = lds4(&Qs[o4]);
-        gg[jn] = f4{0, 0, 0, 0};
-        gq[jn] = f4{0, 0, 0, 0};
+      for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          gg[jn] = mfma16(ya[r], kb[r], gg[jn]);
-          gq[jn] = mfma16(ya[r], qb[r], gq[jn]);
-        }
+      for (int kb = 0; kb < NKB; ++kb) {
+        const Terms<KT> ka = operand(Ks, kb);
+#pragma unroll
+        for (int jn = 0; jn < NJ; ++jn)
+          yt[jn] = sweep(ka, tiles(At[2 * kb][jn], At[kSplit ? 2 * kb + 1 : 0][jn]), yt[jn]);
+        if (KT > 1) __builtin_amdgcn_sched_barrier(0);
       }
+      const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
 #pragma unroll
-      for (int jn = 1; jn < NJ; ++jn) { gg[0] += gg[jn]; gq[0] += gq[jn]; }
+      for (int jn = 0; jn < NJ; ++jn) yt[jn] *= rn4;
+    }
+    // ================= partial Gram matrices over this wave's columns; Y^T turns through LDS
+    {
+      float* Yw = Gp[w][0];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        Gp[w][0][(4 * g + r) * LT + c] = gg[0][r];
-        Gp[w][1][(4 * g + r) * LT + c] = gq[0][r];
-      }
+      for (int jn = 0; jn < NJ; ++jn)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Yw[(4 * g + r) * LDY + 16 * jn + c] = yt[jn][r];
+      // same-wave write -> read: LDS operations of one wave are ordered
+      const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
+      const f4 zero{0, 0, 0, 0};
+      // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
+      f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + 16 + 4 * g]) : zero;
+      if (NJ == 1 && kSplit && (w & 1)) y1 = y0;
+      const auto ya = tiles(NJ == 1 && kSplit && (w & 1) ? zero : y0, y1);
+      // G[s][t], GQ[s][t] come out with t on the rows of the accumulator
+      const f4 gg = sweep(operand(Ks, col0 / 32), ya, zero);
+      const f4 gq = sweep(operand(Qs, col0 / 32), ya, zero);
+      const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Gp[w][0][c * LT + 4 * g + r] = gg[r] * rn4[r];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Gp[w][1][c * LT + 4 * g + r] = gq[r];
     }
     __syncthreads();  // (2) partial Grams visible
 
@@ -323,23 +385,41 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // L[j][t] serves the Cholesky trailing update and the forward substitution for L^{-1}.
     int cc = c;  // opaque copy: keeps the (c == t) masks from being hoisted into 16 registers
     asm volatile("" : "+v"(cc));
-    f4 ot[NJV];  // R^T = Q S0^T, later O^T
-    auto r_pass = [&]() {
+    // ================= -F^T = K^ S0^T - V^T and R^T = Q S0^T: one pass over S, whose split serves both; needed only
+    // after barrier (5), so it fills the serial windows
+    f4 ft[NJV], ot[NJV];
+    auto s_pass = [&]() {
 #pragma unroll
-      for (int jn = 0; jn < NJV; ++jn) ot[jn] = f4{0, 0, 0, 0};
+      for (int jn = 0; jn < NJV; ++jn) ft[jn] = ot[jn] = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const f4 qa = lds4(&Qs[c * LD + 16 * b + 4 * g]);
+      for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int jn = 0; jn < NJV; ++jn) ot[jn] = mfma16(qa[r], St[b][jn][r], ot[jn]);
+        for (int jn = 0; jn < NJV; ++jn) {
+          const auto sb = tiles(St[2 * kb][jn], St[kSplit ? 2 * kb + 1 : 0][jn]);
+          ft[jn] = sweep(operand(Ks, kb), sb, ft[jn]);
+          if (KT > 1) __builtin_amdgcn_sched_barrier(0);
+          ot[jn] = sweep(operand(Qs, kb), sb, ot[jn]);
+          __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
+        }
       }
+      const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
+      if (t0 + C > T) {  // uniform: rows past the end of the sequence are zero tokens
+#pragma unroll
+        for (int jn = 0; jn < NJV; ++jn)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) vpre[jn][r] = (t0 + 4 * g + r < T) ? vpre[jn][r] : IO(0);
+      }
+#pragma unroll
+      for (int jn = 0; jn < NJV; ++jn)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ft[jn][r] = fmaf(ft[jn][r], rn4[r], neg_widen(vpre[jn][r]));
+      if (t0 + C < T) load_v(t0 + C);
     };
-    if (w != sw) {  // the other waves use the matrix pipes while wave sw factorises
+    if (w != sw) {  // the other waves work on S while wave sw factorises
       prio<kLevels, 0, -1>();
-      r_pass();
-      stage_next();
+      stage_next();   // first, so that no staged row is held in registers over the pass
+      s_pass();
+      fetch_next();
       prio<kLevels, 1, -1>();
     }
     if (w == sw) {
@@ -380,7 +460,6 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // ================= W^T = L^{-1} Y^T, partial ||w_t||^2, W to LDS
     prio<kLevels, 2, -1>();
     const f4 la = lds4(&Lis[c * LT + 4 * g]);
-    f4 nwt[NJ];  // -W^T
     {
       f4 n2 = f4{0, 0, 0, 0};
 #pragma unroll
@@ -388,9 +467,8 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
         f4 acc = f4{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc = mfma16(la[r], yt[jn][r], acc);
-        nwt[jn] = -acc;
         n2 += acc * acc;
-        *reinterpret_cast<f4*>(&Wb[(col0 + 16 * jn + c) * LT + 4 * g]) = acc;
+        w_store(col0 + 16 * jn + c, acc);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) n2[r] = row_sum16(n2[r]);
@@ -401,13 +479,15 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 
     // ================= phase 2 (wave sw2): c_t, Z, NQ -- the other waves update A meanwhile
     auto update_A = [&]() {
+      TokenB nw[NJ];
+#pragma unroll
+      for (int jn = 0; jn < NJ; ++jn) nw[jn] = w_neg_b(col0 + 16 * jn + c);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const f4 wa = lds4(&Wb[(16 * b + c) * LT + 4 * g]);
+        const auto wa = w_load(16 * b + c);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int jn = 0; jn < NJ; ++jn) At[b][jn] = mfma16(wa[r], nwt[jn][r], At[b][jn]);
+        for (int jn = 0; jn < NJ; ++jn) At[b][jn] = update(wa, nw[jn], At[b][jn]);
+        if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two tiles' operands at a time in registers
       }
     };
     if (w != sw2) {
@@ -415,7 +495,11 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       update_A();
       prio<kLevels, 1, -1>();
     }
-    if (w == sw) stage_next();  // (sw != sw2 when NW > 1)
+    if (w == sw) {  // (sw != sw2 when NW > 1)
+      stage_next();   // first, so that no staged row is held in registers over the pass
+      s_pass();
+      fetch_next();
+    }
     if (w == sw2) {
       prio<kLevels, 3, 3>();
       float m[C];  // lane c: row c of L
@@ -466,7 +550,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 
     // ================= -E^T = Z (-F^T), R^T = Q S0^T, O^T = R^T + (-NQ^T)(-E^T), store o;
     // ce = (-c) (-E^T) = diag(c) E^T
-    f4 ce[NJV];
+    TokenB ce[NJV];
     {
       const f4 za = lds4(&Zs[c * LT + 4 * g]);
 #pragma unroll
@@ -476,14 +560,13 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
         for (int r = 0; r < 4; ++r) et = mfma16(za[r], ft[jn][r], et);
         ft[jn] = et;
       }
-      if (w == sw) r_pass();
       const f4 nqa = lds4(&NQs[c * LT + 4 * g]);
       const f4 cg = lds4(&cvec[4 * g]);
 #pragma unroll
       for (int jn = 0; jn < NJV; ++jn) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) ot[jn] = mfma16(nqa[r], ft[jn][r], ot[jn]);
-        ce[jn] = ft[jn] * cg;
+        ce[jn] = tokens_b(ft[jn] * cg);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -506,11 +589,10 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // ================= S^T += W diag(c) E^T  (and A -= W W^T on the wave that formed Z)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const f4 wa = lds4(&Wb[(16 * b + c) * LT + 4 * g]);
+      const auto wa = w_load(16 * b + c);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int jn = 0; jn < NJV; ++jn) St[b][jn] = mfma16(wa[r], ce[jn][r], St[b][jn]);
+      for (int jn = 0; jn < NJV; ++jn) St[b][jn] = update(wa, ce[jn], St[b][jn]);
+      if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
     if (w == sw2) update_A();
   }
@@ -559,21 +641,27 @@ hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
 
 bool chunk_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }
 
-// Several heads per workgroup (vla_chunk_multihead.hip) or one?  Measured on one MI355X, T = 8192:
-//   d = 64 (two-wave workgroups here, four-wave ones of two heads there; both hold 1024 heads per chip at a
-//   time): up to 256 heads one workgroup per compute unit either way, 2.5 against 2.7 ms; 257-512 heads 4.1
-//   against 2.7 ms (two two-wave workgroups on a compute unit are placed on three of its four SIMDs); 768-1024
-//   heads 4.3-4.5 against 4.1-4.2 ms; 2048 heads 8.9 against 8.3 ms, 3072: 13.2 against 12.4, 4096: 17.6 against
-//   16.5; but 1280-1536 heads 7.0 against 8.4-8.5 ms: the larger workgroups refill a draining chip two to a
-//   compute unit, so a launch that is not a whole number of full rounds pays for its tail.
-//   d = 32 (one-wave workgroups here, four heads per workgroup there): up to 1024 heads 2.3 against 2.4 ms,
-//   1280-1536 heads 3.35 against 3.25 ms, 2048 heads 4.6 against 3.25 ms, 4096: 9.2 against 6.5.
+// Waves per head.  A wave that owns 16 columns instead of 32 has half the splits and products between two serial
+// sections but as much of everything else, so it pays while it runs on a SIMD that would be idle: as long as the
+// narrow workgroups are resident in one round.  T = 512, wide / narrow waves in ms, bf16 and float32 q, k, v:
+//   d = 128 (4 / 8 waves): 256 heads 0.229 / 0.203 and 0.304 / 0.230, 512 heads 0.302 / 0.396 and 0.388 / 0.458
+//   d =  96 (3 / 6 waves): 256 heads 0.192 / 0.162 and 0.256 / 0.197, 512 heads 0.237 / 0.306 and 0.308 / 0.379
+//   d =  64 (2 / 4 waves): 768 heads 0.198 / 0.178 and 0.235 / 0.200, 1024 heads 0.212 / 0.307 and 0.422 / 0.361
+//   d =  32 (1 / 2 waves): 768 heads 0.138 / 0.133 and 0.156 / 0.138, 1024 heads 0.140 / 0.144 and 0.154 / 0.149
+//   d =  64, float32: 1536 heads 0.461 / 0.401, 2048: 0.656 / 0.554, 4096: 1.20 / 1.09 (three wide workgroups share a
+//                     compute unit's LDS, three narrow ones too)
+static bool narrow_waves(int d, int n_heads, int io_dtype) {
+  if (d == 64 && io_dtype == 0) return true;
+  return d >= 32 && n_heads <= (d >= 96 ? 256 : 768);
+}
+
+// Several heads per workgroup (vla_chunk_multihead.hip) or one?  With bf16 q, k, v one (the split products leave the
+// vector ALU free for the other heads' serial sections).  With float32 ones, T = 512, one head / several heads per workgroup in ms:
+//   d = 64: 1024 heads 0.361 / 0.283, 1536: 0.401 / 0.554, 2048: 0.576 / 0.562, 4096: 1.09 / 1.11
+//   d = 32: 1024 heads 0.149 / 0.161, 1536: 0.196 / 0.221, 2048: 0.321 / 0.226, 4096: 0.551 / 0.443
 bool prefer_multihead(int d, int n_heads) {
-  if (d == 32) return n_heads > 1024;
-  if (d == 64) {
-    const int wgs = (n_heads + 1) / 2;
-    return n_heads > 256 && (wgs <= 512 || wgs % 512 == 0 || wgs >= 4096);
-  }
+  if (d == 32) return n_heads > 1536;
+  if (d == 64) return n_heads > 768 && n_heads <= 1024;
   return false;
 }
 
@@ -582,7 +670,21 @@ bool prefer_multihead(int d, int n_heads) {
 bool chunk_supported(int d_k, int d_v) { return chunk_supported(d_k) && chunk_supported(d_v); }
 
 hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream) {
-  if (d_k == d_v && prefer_multihead(d_k, a.n_heads)) return launch_chunk_multihead(a, d_k, io_dtype, stream);
+  if (d_k == d_v && io_dtype == 0 && prefer_multihead(d_k, a.n_heads)) return launch_chunk_multihead(a, d_k, io_dtype, stream);
+  if (narrow_waves(d_k, a.n_heads, io_dtype)) {
+    switch (d_k * 1000 + d_v) {
+      case 32032: return launch_io<32, 32, 2>(a, io_dtype, stream);
+      case 64016: return launch_io<64, 16, 4>(a, io_dtype, stream);
+      case 64032: return launch_io<64, 32, 4>(a, io_dtype, stream);
+      case 64064: return launch_io<64, 64, 4>(a, io_dtype, stream);
+      case 96016: return launch_io<96, 16, 6>(a, io_dtype, stream);
+      case 96032: return launch_io<96, 32, 6>(a, io_dtype, stream);
+      case 96064: return launch_io<96, 64, 6>(a, io_dtype, stream);
+      case 96096: return launch_io<96, 96, 6>(a, io_dtype, stream);
+      case 128128: return launch_io<128, 128, 8>(a, io_dtype, stream);
+      default: break;   // d_v > d_k: narrow waves at every count, below
+    }
+  }
   switch (d_k * 1000 + d_v) {
     case 16016: return launch_io<16, 16, 1>(a, io_dtype, stream);
     case 32032: return launch_io<32, 32, 1>(a, io_dtype, stream);
@@ -591,21 +693,21 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
     case 128128: return launch_io<128, 128, 4>(a, io_dtype, stream);
     case 16032: return launch_io<16, 32, 1>(a, io_dtype, stream);
     case 32016: return launch_io<32, 16, 1>(a, io_dtype, stream);
-    case 32064: return launch_io<32, 64, 1>(a, io_dtype, stream);
+    case 32064: return launch_io<32, 64, 2>(a, io_dtype, stream);
     case 64032: return launch_io<64, 32, 2>(a, io_dtype, stream);
-    case 64128: return launch_io<64, 128, 2>(a, io_dtype, stream);
+    case 64128: return launch_io<64, 128, 4>(a, io_dtype, stream);
     case 128064: return launch_io<128, 64, 4>(a, io_dtype, stream);
     case 16064: return launch_io<16, 64, 1>(a, io_dtype, stream);
     case 16096: return launch_io<16, 96, 1>(a, io_dtype, stream);
     case 16128: return launch_io<16, 128, 1>(a, io_dtype, stream);
-    case 32096: return launch_io<32, 96, 1>(a, io_dtype, stream);
-    case 32128: return launch_io<32, 128, 1>(a, io_dtype, stream);
-    case 64096: return launch_io<64, 96, 2>(a, io_dtype, stream);
+    case 32096: return launch_io<32, 96, 2>(a, io_dtype, stream);
+    case 32128: return launch_io<32, 128, 2>(a, io_dtype, stream);
+    case 64096: return launch_io<64, 96, 4>(a, io_dtype, stream);
     case 64016: return launch_io<64, 16, 2>(a, io_dtype, stream);
     case 96016: return launch_io<96, 16, 3>(a, io_dtype, stream);
     case 96032: return launch_io<96, 32, 3>(a, io_dtype, stream);
     case 96064: return launch_io<96, 64, 3>(a, io_dtype, stream);
-    case 96128: return launch_io<96, 128, 3>(a, io_dtype, stream);
+    case 96128: return launch_io<96, 128, 6>(a, io_dtype, stream);
     case 128016: return launch_io<128, 16, 4>(a, io_dtype, stream);
     case 128032: return launch_io<128, 32, 4>(a, io_dtype, stream);
     case 128096: return launch_io<128, 96, 4>(a, io_dtype, stream);

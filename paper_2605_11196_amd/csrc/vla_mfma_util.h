@@ -27,6 +27,140 @@ __host__ __device__ constexpr size_t off_sm(int nblk, int D) { return static_cas
 __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+
+// ---- FP32 products on the bf16 matrix instruction.  A float32 value is the sum of three bf16 values (3 x 8
+// significant bits); a product of two bf16 values is exact in float32, which is what the instruction accumulates
+// in.  So a float32 matrix times a matrix of bf16 numbers is three products with nothing left out, and a float32
+// matrix times a float32 matrix is the six products of weight 2^-16 and more (what is left out is below 2^-25 of
+// the product).  Measured on one SIMD: 7.8 ns for 16x16x32 in bf16 against 14.2 ns for 16x16x4 in FP32, so three
+// products take 0.21 of the FP32 time and six 0.41; and the bf16 instruction leaves the vector ALU free for
+// other waves (32 MFMAs beside 64 FMAs of another wave 0.263 us, 0.249 and 0.116 us alone), which the FP32 one does not.
+// v_dot2_f32_bf16 would form the residuals below in fewer instructions but excludes the matrix unit (0.428 us for
+// the same pair).
+//
+// v_mfma_f32_16x16x32_bf16 register layout, lane l = 16*g + c, i = 0..7:
+//   A operand: A[m = c][k = 8g + i]     B operand: B[k = 8g + i][n = c]     C/D: reg r -> D[m = 4g + r][n = c]
+// The order of k is free as long as both operands agree.  Contractions over the head dimension take 32 columns at a
+// time in the order of two accumulator tiles: slot i of lane group g is column 4g + i of the first tile for i < 4
+// and column 4g + i - 4 of the second one from there (kslot() gives the position of a column).
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f4 mfma_bf16(u4 a, u4 b, f4 c) {
+  typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+// position of column j (a multiple of 4) in a row of operand slots
+__host__ __device__ constexpr int kslot(int j) { return (j & ~31) + 8 * ((j >> 2) & 3) + 4 * ((j >> 4) & 1); }
+
+__device__ __forceinline__ float top_half(float x) {
+  return __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+}
+// the upper halves of two float32 values, packed (x0 in the low half)
+__device__ __forceinline__ uint32_t pack_tops(float x0, float x1) {
+  return __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+}
+__device__ __forceinline__ uint32_t pack_rne(float x0, float x1) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  typedef float fl2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(fl2{x0, x1}, bf2));
+}
+// x = h + m + l exactly, each term cut off (never rounded up, so that the largest finite values split as well)
+__device__ __forceinline__ void split3_cut(f4 x, u2& h, u2& m, u2& l) {
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const float x0 = x[2 * p], x1 = x[2 * p + 1];
+    const float r0 = x0 - top_half(x0), r1 = x1 - top_half(x1);
+    const float s0 = r0 - top_half(r0), s1 = r1 - top_half(r1);
+    h[p] = pack_tops(x0, x1);
+    m[p] = pack_tops(r0, r1);
+    l[p] = pack_tops(s0, s1);
+  }
+}
+// x = h + m + l with h and m rounded to nearest: the terms that a product of two split factors leaves out
+// (m l, l m, l l) are then unbiased.
+__device__ __forceinline__ void split3_rne(f4 x, u2& h, u2& m, u2& l) {
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const float x0 = x[2 * p], x1 = x[2 * p + 1];
+    h[p] = pack_rne(x0, x1);
+    const float r0 = x0 - __uint_as_float(h[p] << 16), r1 = x1 - __uint_as_float(h[p] & 0xffff0000u);
+    m[p] = pack_rne(r0, r1);
+    const float s0 = r0 - __uint_as_float(m[p] << 16), s1 = r1 - __uint_as_float(m[p] & 0xffff0000u);
+    l[p] = pack_rne(s0, s1);
+  }
+}
+__device__ __forceinline__ u4 cat(u2 a, u2 b) { return u4{a[0], a[1], b[0], b[1]}; }
+
+// One operand of 32 columns: the NT = 1 (exact bf16 numbers) or 3 (h, m, l) terms.
+template <int NT> struct Terms { u4 t[NT]; };
+
+// Operand terms of two accumulator tiles (32 rows of the contraction).
+__device__ __forceinline__ Terms<3> split_tiles(f4 x0, f4 x1) {
+  u2 h0, m0, l0, h1, m1, l1;
+  split3_cut(x0, h0, m0, l0);
+  split3_cut(x1, h1, m1, l1);
+  return Terms<3>{{cat(h0, h1), cat(m0, m1), cat(l0, l1)}};
+}
+// acc += a b over 32 columns.  b holds three terms; a one or three.  Small products first.
+template <int NT>
+__device__ __forceinline__ f4 mfma_terms(const Terms<NT>& a, const Terms<3>& b, f4 acc) {
+  if constexpr (NT == 1) {
+    acc = mfma_bf16(a.t[0], b.t[2], acc);
+    acc = mfma_bf16(a.t[0], b.t[1], acc);
+    return mfma_bf16(a.t[0], b.t[0], acc);
+  } else {
+    acc = mfma_bf16(a.t[0], b.t[2], acc);
+    acc = mfma_bf16(a.t[2], b.t[0], acc);
+    acc = mfma_bf16(a.t[1], b.t[1], acc);
+    acc = mfma_bf16(a.t[0], b.t[1], acc);
+    acc = mfma_bf16(a.t[1], b.t[0], acc);
+    return mfma_bf16(a.t[0], b.t[0], acc);
+  }
+}
+
+// A contraction over the 16 tokens of a block fills only half of the 32 slots, so one instruction takes two of the
+// six products: slots 0-3 of a lane hold one term of its four tokens, slots 4-7 another one.
+//   [h m] x [h m] = hh + mm,   [h m] x [m h] = hm + mh,   [l h] x [h l] = lh + hl
+// For x = y the sums come out the same with the two factors exchanged (checked bit for bit on the device), so a
+// symmetric matrix stays symmetric.
+struct TokB { u4 hm, mh, hl; };   // B operand: four tokens per lane
+__device__ __forceinline__ TokB tok_b(f4 x) {
+  u2 h, m, l;
+  split3_rne(x, h, m, l);
+  return TokB{cat(h, m), cat(m, h), cat(h, l)};
+}
+// LDS image of a [rows][16 tokens] A operand: HM holds 16 bytes (h, m of four tokens) and L 8 bytes per row and
+// token group; the group index is swizzled by the row so that 16 lanes on 16 rows hit different banks.
+__device__ __forceinline__ int tok_chunk(int c, int g) { return g ^ ((c >> 2) & 3); }
+__device__ __forceinline__ void tok_store(u4* hm, u2* l, int row, int c, int g, f4 x) {
+  u2 h, m, lo;
+  split3_rne(x, h, m, lo);
+  const int i = 4 * row + tok_chunk(c, g);
+  hm[i] = cat(h, m);
+  l[i] = lo;
+}
+struct TokA { u4 hm, lh; };
+__device__ __forceinline__ TokA tok_load(const u4* hm, const u2* l, int row, int c, int g) {
+  const int i = 4 * row + tok_chunk(c, g);
+  TokA a;
+  a.hm = hm[i];
+  a.lh = cat(l[i], *reinterpret_cast<const u2*>(hm + i));
+  return a;
+}
+__device__ __forceinline__ f4 mfma_tok(const TokA& a, const TokB& b, f4 acc) {
+  acc = mfma_bf16(a.lh, b.hl, acc);
+  acc = mfma_bf16(a.hm, b.mh, acc);
+  return mfma_bf16(a.hm, b.hm, acc);
+}
+// B operand of -X from the LDS image of X (rows = columns of the product)
+__device__ __forceinline__ TokB tok_neg_b(const u4* hm, const u2* l, int row, int c, int g) {
+  const int i = 4 * row + tok_chunk(c, g);
+  const u4 x = hm[i] ^ 0x80008000u;
+  const u2 y = l[i] ^ 0x80008000u;
+  return TokB{x, u4{x[2], x[3], x[0], x[1]}, u4{x[0], x[1], y[0], y[1]}};
+}
+
 __device__ __forceinline__ float readlane(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }

@@ -516,6 +516,23 @@ def test_many_small_heads_share_a_workgroup(d, B, H, T, dtype):
     print(d, B * H, 16, dtype, errs)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,d_v,heads", [(128, 128, 256), (128, 128, 257), (96, 96, 256), (96, 64, 256), (96, 96, 257),
+                                         (64, 64, 768), (64, 16, 768), (64, 64, 769), (32, 32, 768), (32, 32, 769),
+                                         (32, 96, 3), (64, 128, 3), (96, 128, 3)])
+def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
+    """The block kernel on both sides of the head counts where a wave owns 16 instead of 32 columns, and the pairs
+    that always run with 16: 33 tokens (two blocks and one token), values over eight orders of magnitude in the state."""
+    rng = np.random.default_rng(d + heads)
+    B, T = 1, 33
+    q, k = (rng.standard_normal((B, heads, T, d)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((B, heads, T, d_v)).astype(np.float32)
+    v *= np.float32(10.0) ** rng.integers(-4, 5, size=(1, heads, 1, 1)).astype(np.float32)
+    S0 = rng.standard_normal((B, heads, d_v, d)).astype(np.float32) * np.abs(v).max(axis=(2, 3), keepdims=True)
+    errs, _, _ = check_parity(q, k, v, S0, dtype=dtype, mode=2)
+    print(d, d_v, heads, dtype, errs)
+
+
 OPTION_SETS = {
     "every option": dict(with_u=True, refresh_period=7, refresh_eta=1e-2, step_offset=3, normalise_output=True,
                          feature_map=True),
