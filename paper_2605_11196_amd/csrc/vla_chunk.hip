@@ -66,13 +66,10 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   static_assert(DV % 16 == 0 && NJV >= 1, "whole tiles of S");
   constexpr int NB = D / 16;       // 16-row blocks over the whole head dimension
   constexpr int NKB = (NB + 1) / 2;   // 32-column steps of a contraction over the head dimension
-  // Head size 16 is a single tile: half of the slots of a bf16 product would be empty and nothing but the latency of
-  // the chain counts (one head of 256 tokens: 51 us with FP32 products, 55 us with split ones), so its products
-  // stay on the FP32 matrix instruction and its operands are staged as they are.
   constexpr bool kSplit = D > 16;
   // operand terms of k and q: bf16 numbers are exact in one, float32 ones (and mapped ones) take three
   constexpr int KT = (sizeof(IO) == 2 && !FMAP) || !kSplit ? 1 : 3;
-  constexpr int LDK = 32 * NKB + 8;   // row stride (bf16) of the staged operands: an odd number of 16-byte pieces
+  using Ops = BlockOps<kSplit, KT, D>;
   constexpr int LDY = SL + 4;         // row stride of a wave's slab of Y^T
   constexpr int NT = 64 * NW;
   // Staging: a token row is split over TPR threads of EPT elements each.  For the power-of-two head sizes every
@@ -85,8 +82,8 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   static_assert(EPT % 4 == 0 && TPR <= 32 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
-  __shared__ __align__(16) uint16_t Ksb[2][KT][C * LDK];   // k [t][slot], terms, double-buffered over blocks
-  __shared__ __align__(16) uint16_t Qsb[2][KT][C * LDK];   // q
+  __shared__ __align__(16) uint16_t Ksb[2][Ops::SIZE];     // k [t][slot], terms, double-buffered over blocks
+  __shared__ __align__(16) uint16_t Qsb[2][Ops::SIZE];     // q
   __shared__ __align__(16) u4 Whm[D * 4];                  // W [j][t], terms h and m
   __shared__ __align__(16) u2 Wl[D * 4];                   //           term l
   __shared__ __align__(16) float Gp[NW][2][C * LT];   // per-wave partial Gram matrices G, GQ  [s][t]; first the
@@ -192,21 +189,6 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int jn = 0; jn < NJV; ++jn) vpre[jn][r] = vh[voff + (s_row(jn) - s_row(0))];
     }
   };
-  // four elements (j0 a multiple of 4) of this thread's row into the operand terms
-  auto put4 = [&](uint16_t (&dst)[KT][C * LDK], int j0, f4 x) {
-    u2 h, m, l;
-    const int at = srow * LDK + kslot(j0);
-    if constexpr (!kSplit) {
-      *reinterpret_cast<f4*>(&dst[0][srow * LDK + 2 * j0]) = x;
-    } else if constexpr (KT == 1) {   // exact: the low halves are zero
-      *reinterpret_cast<u2*>(&dst[0][at]) = u2{pack_tops(x[0], x[1]), pack_tops(x[2], x[3])};
-    } else {
-      split3_rne(x, h, m, l);
-      *reinterpret_cast<u2*>(&dst[0][at]) = h;
-      *reinterpret_cast<u2*>(&dst[1][at]) = m;
-      *reinterpret_cast<u2*>(&dst[2][at]) = l;
-    }
-  };
   // put this thread's share of the keys and queries of the block starting at t0, and the key norms, into LDS half `buf`
   auto stage = [&](int t0, int buf) __attribute__((always_inline)) {
     if (!stage_wave) return;
@@ -249,7 +231,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     }
     if (sseg == 0) rns[buf][srow] = rn;
 #pragma unroll
-    for (int e = 0; e < EPT; e += 4) put4(Ksb[buf], sseg + e, f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]});
+    for (int e = 0; e < EPT; e += 4) Ops::put4(Ksb[buf], srow, sseg + e, f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]});
     float qx[EPT];
     qpre.unpack(qx);
     if constexpr (FMAP) {
@@ -261,60 +243,8 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int e = 0; e < EPT; ++e) qx[e] = live ? qx[e] : 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < EPT; e += 4) put4(Qsb[buf], sseg + e, f4{qx[e], qx[e + 1], qx[e + 2], qx[e + 3]});
+    for (int e = 0; e < EPT; e += 4) Ops::put4(Qsb[buf], srow, sseg + e, f4{qx[e], qx[e + 1], qx[e + 2], qx[e + 3]});
   };
-  // operand terms of the tokens' columns 32 kb .. 32 kb + 31
-  auto operand = [&](const uint16_t (&src)[KT][C * LDK], int kb) {
-    Terms<KT> x;
-#pragma unroll
-    for (int i = 0; i < KT; ++i) {
-      x.t[i] = *reinterpret_cast<const u4*>(&src[i][c * LDK + 32 * kb + 8 * g]);   // (kSplit or not: 16 bytes at 16 g)
-    }
-    return x;
-  };
-  // acc += x X over the columns of two accumulator tiles of X (one tile without the split)
-  auto sweep = [&](const Terms<KT>& x, const auto& X, f4 acc) {
-    if constexpr (kSplit) {
-      return mfma_terms(x, X, acc);
-    } else {
-      const f4 xa = __builtin_bit_cast(f4, x.t[0]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc = mfma16(xa[r], X[r], acc);
-      return acc;
-    }
-  };
-  // the LDS image of W, and updates X += W y over the block's tokens (y: four tokens per lane)
-  auto w_store = [&](int row, f4 x) {
-    if constexpr (kSplit) tok_store(Whm, Wl, row, c, g, x);
-    else Whm[4 * row + tok_chunk(c, g)] = __builtin_bit_cast(u4, x);
-  };
-  auto w_load = [&](int row) {
-    if constexpr (kSplit) return tok_load(Whm, Wl, row, c, g);
-    else return __builtin_bit_cast(f4, Whm[4 * row + tok_chunk(c, g)]);
-  };
-  auto w_neg_b = [&](int row) {
-    if constexpr (kSplit) return tok_neg_b(Whm, Wl, row, c, g);
-    else return -__builtin_bit_cast(f4, Whm[4 * row + tok_chunk(c, g)]);
-  };
-  auto tokens_b = [&](f4 x) {
-    if constexpr (kSplit) return tok_b(x);
-    else return x;
-  };
-  auto update = [&](const auto& wa, const auto& y, f4 acc) {
-    if constexpr (kSplit) {
-      return mfma_tok(wa, y, acc);
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc = mfma16(wa[r], y[r], acc);
-      return acc;
-    }
-  };
-  using TokenB = decltype(tokens_b(f4{}));
-  auto tiles = [&](f4 x0, f4 x1) {
-    if constexpr (kSplit) return split_tiles(x0, x1);
-    else return x0;
-  };
-
   if (T > 0) {
     load_kq(0);
     load_v(0);
@@ -326,8 +256,8 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   prio<kLevels, 1, -1>();
   int blk = 0;
   for (int t0 = 0; t0 < T; t0 += C, ++blk) {
-    const uint16_t (&Ks)[KT][C * LDK] = Ksb[blk & 1];
-    const uint16_t (&Qs)[KT][C * LDK] = Qsb[blk & 1];
+    const uint16_t* Ks = Ksb[blk & 1];
+    const uint16_t* Qs = Qsb[blk & 1];
     // staging of the next block (this thread's share): done where this wave is not on the critical path
     auto stage_next = [&]() {
       if (t0 + C < T) stage(t0 + C, (blk + 1) & 1);
@@ -342,10 +272,10 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
-        const Terms<KT> ka = operand(Ks, kb);
+        const Terms<KT> ka = Ops::operand(Ks, kb, c, g);
 #pragma unroll
         for (int jn = 0; jn < NJ; ++jn)
-          yt[jn] = sweep(ka, tiles(At[2 * kb][jn], At[kSplit ? 2 * kb + 1 : 0][jn]), yt[jn]);
+          yt[jn] = Ops::sweep(ka, Ops::tiles(At[2 * kb][jn], At[kSplit ? 2 * kb + 1 : 0][jn]), yt[jn]);
         if (KT > 1) __builtin_amdgcn_sched_barrier(0);
       }
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
@@ -365,10 +295,10 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
       f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + 16 + 4 * g]) : zero;
       if (NJ == 1 && kSplit && (w & 1)) y1 = y0;
-      const auto ya = tiles(NJ == 1 && kSplit && (w & 1) ? zero : y0, y1);
+      const auto ya = Ops::tiles(NJ == 1 && kSplit && (w & 1) ? zero : y0, y1);
       // G[s][t], GQ[s][t] come out with t on the rows of the accumulator
-      const f4 gg = sweep(operand(Ks, col0 / 32), ya, zero);
-      const f4 gq = sweep(operand(Qs, col0 / 32), ya, zero);
+      const f4 gg = Ops::sweep(Ops::operand(Ks, col0 / 32, c, g), ya, zero);
+      const f4 gq = Ops::sweep(Ops::operand(Qs, col0 / 32, c, g), ya, zero);
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) Gp[w][0][c * LT + 4 * g + r] = gg[r] * rn4[r];
@@ -395,10 +325,10 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJV; ++jn) {
-          const auto sb = tiles(St[2 * kb][jn], St[kSplit ? 2 * kb + 1 : 0][jn]);
-          ft[jn] = sweep(operand(Ks, kb), sb, ft[jn]);
+          const auto sb = Ops::tiles(St[2 * kb][jn], St[kSplit ? 2 * kb + 1 : 0][jn]);
+          ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
           if (KT > 1) __builtin_amdgcn_sched_barrier(0);
-          ot[jn] = sweep(operand(Qs, kb), sb, ot[jn]);
+          ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
           __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
         }
       }
@@ -468,7 +398,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc = mfma16(la[r], yt[jn][r], acc);
         n2 += acc * acc;
-        w_store(col0 + 16 * jn + c, acc);
+        Ops::w_store(Whm, Wl, col0 + 16 * jn + c, c, g, acc);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) n2[r] = row_sum16(n2[r]);
@@ -479,14 +409,14 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 
     // ================= phase 2 (wave sw2): c_t, Z, NQ -- the other waves update A meanwhile
     auto update_A = [&]() {
-      TokenB nw[NJ];
+      decltype(Ops::tokens_b(f4{})) nw[NJ];
 #pragma unroll
-      for (int jn = 0; jn < NJ; ++jn) nw[jn] = w_neg_b(col0 + 16 * jn + c);
+      for (int jn = 0; jn < NJ; ++jn) nw[jn] = Ops::w_neg_b(Whm, Wl, col0 + 16 * jn + c, c, g);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const auto wa = w_load(16 * b + c);
+        const auto wa = Ops::w_load(Whm, Wl, 16 * b + c, c, g);
 #pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) At[b][jn] = update(wa, nw[jn], At[b][jn]);
+        for (int jn = 0; jn < NJ; ++jn) At[b][jn] = Ops::update(wa, nw[jn], At[b][jn]);
         if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two tiles' operands at a time in registers
       }
     };
@@ -550,7 +480,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 
     // ================= -E^T = Z (-F^T), R^T = Q S0^T, O^T = R^T + (-NQ^T)(-E^T), store o;
     // ce = (-c) (-E^T) = diag(c) E^T
-    TokenB ce[NJV];
+    decltype(Ops::tokens_b(f4{})) ce[NJV];
     {
       const f4 za = lds4(&Zs[c * LT + 4 * g]);
 #pragma unroll
@@ -566,7 +496,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int jn = 0; jn < NJV; ++jn) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) ot[jn] = mfma16(nqa[r], ft[jn][r], ot[jn]);
-        ce[jn] = tokens_b(ft[jn] * cg);
+        ce[jn] = Ops::tokens_b(ft[jn] * cg);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -589,9 +519,9 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // ================= S^T += W diag(c) E^T  (and A -= W W^T on the wave that formed Z)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const auto wa = w_load(16 * b + c);
+      const auto wa = Ops::w_load(Whm, Wl, 16 * b + c, c, g);
 #pragma unroll
-      for (int jn = 0; jn < NJV; ++jn) St[b][jn] = update(wa, ce[jn], St[b][jn]);
+      for (int jn = 0; jn < NJV; ++jn) St[b][jn] = Ops::update(wa, ce[jn], St[b][jn]);
       if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
     if (w == sw2) update_A();

@@ -34,14 +34,18 @@
 // the key as used before L2 normalisation, k_s = max(||k_s||, eps) k^_s; inside a block
 // q_t . zkey_t = q_t . zkey_start + sum_{s<=t} ||k_s|| (Q K^^T)[t][s].
 //
-// Work split: D/16 waves per (batch, head); wave w owns columns [16w, 16w+16) of A and the same rows of S
-// (with a value head size other than D: the row tiles w, w + D/16, ... of S) as 16x16 MFMA accumulator tiles
+// Work split: D/SL waves per (batch, head); wave w owns columns [SL w, SL w + SL) of A (SL = 16 or 32) and
+// the row tiles w, w + D/SL, ... of S as 16x16 MFMA accumulator tiles
 // resident in VGPRs for the whole sequence.  The C x C Gram matrices are
 // shared out over the waves (each one contracts over the whole head dimension), the C x C factorisations
 // run on one wave each, rotating with the block index.
 //
-// v_mfma_f32_16x16x4_f32 register layout, lane l = 16*g + c:
-//   A operand: A[m = c][k = g]      B operand: B[k = g][n = c]      C/D: reg r -> D[m = 4g + r][n = c]
+// What bounds it: the chain of five barriers of one block, of which a second workgroup on the compute unit hides
+// part.  The sweeps over A and S and the Gram matrices are FP32 products on split bf16 terms (vla_mfma_util.h); Y and X
+// share their LDS with W and Alpha and the next block is staged at the end of a block, so that two workgroups
+// of d = 128 fit a compute unit (80 KB each).  Every option on, 2048 heads of 128, 8192 tokens, bf16: 43.7 ms with FP32
+// matrix instructions and one workgroup per compute unit, 35.2 ms so.  T = 256: 2048 heads of 64 0.59 -> 0.43 ms,
+// of 32 0.33 -> 0.25, of 96 1.26 -> 1.17.
 #include "vla_mfma_util.h"
 
 namespace vla {
@@ -59,6 +63,12 @@ enum GramTile {
   kNumGram
 };
 
+// Waves per SIMD that the kernel's registers are cut for: as many workgroups as its LDS lets a compute unit hold, but
+// no more than its accumulator tiles leave registers for (value heads wider than key heads: two).
+constexpr int general_waves_per_simd(int d, int d_v, int sl, bool db) {
+  return sl == 32 || d <= 32 || d == 128 || d_v > d || db ? 2 : 3;
+}
+
 // FULL: Y and X differ (a separate u, or a refresh period): two sweeps of A and five Gram matrices.
 // SCAN: phase 1 of the two-phase and time-parallel modes: one workgroup per (head, time segment) runs the A
 //       chain only, from the A the segment starts with, and writes what the S recurrence needs into the
@@ -67,34 +77,48 @@ enum GramTile {
 // DV: head size of v and o (rows of S).  The DV / 16 row tiles of S go to the waves in turn (tile t to wave
 //     t % NW: exactly one each for square heads); a wave with fewer tiles than the others, or none, runs its spare
 //     slots on a copy of the last tile and stores nothing from them.
-template <int D, int DV, typename IO, bool FULL, bool SCAN>
-__global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_general_kernel(ForwardArgs a) {
-  constexpr int NW = D / 16;       // waves; wave w owns columns 16w..16w+15
+template <int D, int DV, int SL, typename IO, bool FULL, bool SCAN, bool DB>
+__global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL, DB)) chunk_general_kernel(ForwardArgs a) {
+  constexpr int NW = D / SL;       // waves; wave w owns columns SL w .. SL w + SL - 1 of A
+  constexpr int NJ = SL / 16;      // 16-wide tiles in a slab of A
   constexpr int TV = DV / 16;      // row tiles of S
   constexpr int NJV = (TV + NW - 1) / NW;   // tile slots per wave
   static_assert(DV % 16 == 0 && (!SCAN || DV == D), "whole tiles of S");
   constexpr int NB = D / 16;       // 16-row blocks over the head dimension
-  constexpr int LD = D + 4;        // row stride of the token-major LDS arrays
   // Staging: a token row is split over thread slots of EPT elements.  At the power-of-two head sizes every
-  // thread stages 4 elements; at d = 96 a row takes 12 threads of 8 elements in a group of 16 (the other four
-  // lanes of the group and the last two waves stage nothing), so that a row sums with a power-of-two shuffle.
+  // thread stages 4 or 8 elements; at d = 96 a row takes 12 threads of 8 elements in a group of 16, or 6 of 16 in a
+  // group of 8 (the other lanes of the group and the last waves stage nothing), so that a row sums with a
+  // power-of-two shuffle.
   constexpr bool PADDED = (D & (D - 1)) != 0;
-  constexpr int EPT = PADDED ? 8 : 4;           // staged elements per thread per tensor
-  constexpr int TPR = PADDED ? 16 : D / EPT;    // thread slots per token row (inside one wave)
-  static_assert(D % EPT == 0 && D / EPT <= TPR && C * TPR <= 4 * D, "staging layout");
-  constexpr int UROWS = FULL ? C : 1;
+  constexpr int EPT = (PADDED ? 8 : 4) * NJ;         // staged elements per thread per tensor
+  constexpr int TPR = PADDED ? 16 / NJ : D / EPT;    // thread slots per token row (inside one wave)
+  static_assert(D % EPT == 0 && D / EPT <= TPR && C * TPR <= 64 * NW, "staging layout");
   // Y = X: the Gram matrices that differ only in u against k^ coincide
   constexpr int iGK = FULL ? kGK : kG;
   constexpr int iGX = FULL ? kGX : kG;
   constexpr int iXQ = FULL ? kXQ : kGQ;
 
-  __shared__ __align__(16) float Ksb[2][C * LD];      // K^  [t][j], double-buffered over blocks
-  __shared__ __align__(16) float Qsb[2][C * LD];      // Q   [t][j]
-  __shared__ __align__(16) float Usb[UROWS * LD];     // U   [t][j] (dead after the Gram phase of its block)
-  __shared__ __align__(16) float Ys[C * LD];          // Y^T [t][j]
-  __shared__ __align__(16) float Xsb[UROWS * LD];     // X^T [t][j]
-  __shared__ __align__(16) float Wb[D * LT];          // W     [j][t]
-  __shared__ __align__(16) float Ab[D * LT];          // Alpha [j][t]
+  // Products over the head dimension and over the tokens on split bf16 terms (vla_mfma_util.h).  Keys are staged
+  // normalised and mapped, directions scaled: float32 numbers, three terms each.
+  constexpr bool kSplit = D > 16;
+  constexpr int NKB = (NB + 1) / 2;   // 32-column steps of a contraction over the head dimension
+  using Ops = BlockOps<kSplit, kSplit ? 3 : 1, D>;
+  // Y^T and X^T live until the Gram matrices are formed, W and Alpha from then to the end of the block.  DB: regions of
+  // their own, and K^ and Q double-buffered, so that the next block is staged beside the serial sections.  Otherwise
+  // one region and single buffers, at the price of staging behind one more barrier.
+  constexpr int kYX = (FULL ? 2 : 1) * Ops::SIZE * 2;            // bytes
+  constexpr int kWA = (SCAN ? 1 : 2) * D * 4 * (16 + 8);
+  __shared__ __align__(16) uint16_t Ksb[DB ? 2 : 1][Ops::SIZE]; // K^ [t][j]
+  __shared__ __align__(16) uint16_t Qsb[DB ? 2 : 1][Ops::SIZE]; // Q  [t][j]
+  __shared__ __align__(16) uint16_t Usb[FULL ? Ops::SIZE : 8];    // U  [t][j]
+  __shared__ __align__(16) unsigned char region[DB ? kYX + kWA : (kYX > kWA ? kYX : kWA)];
+  uint16_t* Ys = reinterpret_cast<uint16_t*>(region);             // Y^T [t][j]
+  uint16_t* Xs = FULL ? Ys + Ops::SIZE : Ys;                      // X^T [t][j]
+  unsigned char* const wa_region = region + (DB ? kYX : 0);
+  u4* Whm = reinterpret_cast<u4*>(wa_region);                        // W [j][t]
+  u2* Wl = reinterpret_cast<u2*>(wa_region + D * 4 * 16);
+  u4* Ahm = reinterpret_cast<u4*>(wa_region + D * 4 * 24);           // Alpha [j][t]
+  u2* Al = reinterpret_cast<u2*>(wa_region + D * 4 * 40);
   __shared__ __align__(16) float Gs[kNumGram][C * LT];
   __shared__ __align__(16) float Lis[C * LT];         // L^{-1} [t][s]
   __shared__ __align__(16) float Ps[C * LT];          // P transposed: [t][s] = alpha_s . k^_t
@@ -103,7 +127,7 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
   __shared__ __align__(16) float wn2p[NW][C];         // per-wave partial ||alpha_t||^2
   __shared__ __align__(16) float cvec[C];             // -c_t
   __shared__ __align__(16) float rdens[C];            // 1 / max(q_t . zkey_t, eps)
-  __shared__ __align__(16) float nks[2][C];           // max(||k_t||, eps), double-buffered with K^
+  __shared__ __align__(16) float nks[2][C];           // max(||k_t||, eps), double-buffered over blocks
   __shared__ __align__(16) float zks[D];              // running key sum (each wave touches its own columns)
   __shared__ __align__(16) float ens[2][C + 4];       // eta n_i, i = 0..C: refresh steps among a block's first i tokens
 
@@ -112,29 +136,26 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  const int c = lane & 15;
-  const int g = lane >> 4;
+  int c = lane & 15;
+  int g = lane >> 4;
   const int tb = SCAN ? seg * a.seg_blocks * C : 0;                 // first token of this workgroup's range
   const int T = SCAN ? min(a.T, tb + a.seg_blocks * C) : a.T;       // one past its last token
   const float eps = a.eps;
-  const int col0 = 16 * w;
+  const int col0 = SL * w;
   const int period = a.refresh_period;
   const float eta = a.refresh_eta;
   const bool norm_out = a.normalise_output != 0;
   const bool key_sum = norm_out || a.zkey_T != nullptr;
   const bool fmap = a.feature_map != 0;
   const bool has_u = a.u != nullptr;
-  const float* Us = FULL ? Usb : nullptr;   // set per block when Y = X
-  const float* Xs = FULL ? Xsb : Ys;
-
   // first S row of this wave's tile slot jn, and whether the slot holds a tile of its own
   auto s_row = [&](int jn) -> int {
     const int t = w + NW * jn;
     return 16 * (t < TV ? t : TV - 1);
   };
   auto owns = [&](int jn) -> bool { return w + NW * jn < TV; };
-  // ---- resident state: At[b][r] = A[16b + 4g + r][col0 + c],  St[jn][b][r] = S[s_row(jn) + c][16b + 4g + r]
-  f4 At[NB], St[NJV][NB];
+  // ---- resident state: At[jn][b][r] = A[16b + 4g + r][col0 + 16jn + c],  St[jn][b][r] = S[s_row(jn) + c][16b + 4g + r]
+  f4 At[NJ][NB], St[NJV][NB];
   {
     const float* A0 = (SCAN && a.seg_A) ? a.seg_A + static_cast<size_t>(blockIdx.x) * D * D
                                         : (a.A0 ? a.A0 + static_cast<size_t>(head) * D * D : nullptr);
@@ -144,12 +165,15 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     const int src = c * D + 4 * g;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      if (A0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) At[b][r] = A0[arc + (16 * b + r) * D];
-      } else {
+      for (int jn = 0; jn < NJ; ++jn) {
+        if (A0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) At[b][r] = (16 * b + 4 * g + r == col0 + c) ? diag : 0.0f;
+          for (int r = 0; r < 4; ++r) At[jn][b][r] = A0[arc + (16 * b + r) * D + 16 * jn];
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) At[jn][b][r] = (16 * b + 4 * g + r == col0 + 16 * jn + c) ? diag : 0.0f;
+        }
       }
 #pragma unroll
       for (int jn = 0; jn < NJV; ++jn) {
@@ -162,7 +186,7 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
       }
     }
   }
-  if (lane < 16) {   // key sum entering this range: the caller's, or the one the segment starts with
+  if (lane < SL) {   // key sum entering this range: the caller's, or the one the segment starts with
     const float* z0 = (SCAN && a.seg_zkey) ? a.seg_zkey + static_cast<size_t>(blockIdx.x) * D
                                            : (a.zkey0 ? a.zkey0 + static_cast<size_t>(head) * D : nullptr);
     zks[col0 + lane] = z0 ? z0[col0 + lane] : 0.0f;
@@ -222,8 +246,8 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     return rn * fmaf(-0.5f * clamped * rn, rn, 1.5f);
   };
   // this thread's share of the block of `len` live tokens that starts at token tfirst (step index idx0, 1-based,
-  // counted over the whole sequence): K^, Q (and U) into LDS half `buf`, and the refresh counts of the block
-  auto stage = [&](int len, int idx0, int buf, int tfirst) {
+  // counted over the whole sequence): K^, Q (and U) into LDS, key norms and refresh counts into half `buf`
+  auto stage = [&](int len, int idx0, int buf, int tfirst) __attribute__((always_inline)) {
     if (!stage_wave) return;
     const bool live = srow < len && stager;
     float x[EPT], kn[EPT];
@@ -271,7 +295,7 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     if (!stager) return;
 #pragma unroll
     for (int e = 0; e < EPT; e += 4) {
-      *reinterpret_cast<f4*>(&Ksb[buf][srow * LD + sseg + e]) = f4{kn[e], kn[e + 1], kn[e + 2], kn[e + 3]};
+      Ops::put4(Ksb[DB ? buf : 0], srow, sseg + e, f4{kn[e], kn[e + 1], kn[e + 2], kn[e + 3]});
     }
     if (sseg == 0) {
       nks[buf][srow] = sm * rn;  // max(||k||, eps)
@@ -285,14 +309,14 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     }
 #pragma unroll
     for (int e = 0; e < EPT; e += 4) {
-      *reinterpret_cast<f4*>(&Qsb[buf][srow * LD + sseg + e]) = f4{x[e], x[e + 1], x[e + 2], x[e + 3]};
+      Ops::put4(Qsb[DB ? buf : 0], srow, sseg + e, f4{x[e], x[e + 1], x[e + 2], x[e + 3]});
     }
     if constexpr (FULL) {
 #pragma unroll
       for (int e = 0; e < EPT; e += 4) {
-        *reinterpret_cast<f4*>(&Usb[srow * LD + sseg + e]) =
-            has_u ? f4{us[e] * su, us[e + 1] * su, us[e + 2] * su, us[e + 3] * su}
-                  : f4{kn[e], kn[e + 1], kn[e + 2], kn[e + 3]};   // u = k^ without a separate direction
+        Ops::put4(Usb, srow, sseg + e,
+                  has_u ? f4{us[e] * su, us[e + 1] * su, us[e + 2] * su, us[e + 3] * su}
+                        : f4{kn[e], kn[e + 1], kn[e + 2], kn[e + 3]});   // u = k^ without a separate direction
       }
     }
   };
@@ -301,58 +325,38 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     load_kqu(tb);
     if constexpr (!SCAN) load_v(tb);
     stage(T - tb < C ? T - tb : C, a.step_offset + tb + 1, 0, tb);
-    if (tb + C < T) load_kqu(tb + C);
+    if (DB && tb + C < T) load_kqu(tb + C);
   }
   __syncthreads();  // first block staged, zks initialised
 
   int blk = 0;
   for (int t0 = tb; t0 < T; t0 += C, ++blk) {
-    const float* Ks = Ksb[blk & 1];
-    const float* Qs = Qsb[blk & 1];
+    const uint16_t* Ks = Ksb[DB ? blk & 1 : 0];
+    const uint16_t* Qs = Qsb[DB ? blk & 1 : 0];
+    const uint16_t* Us = FULL ? Usb : Ks;
     const float* en = ens[blk & 1];
-    if constexpr (!FULL) Us = Ks;
     const int len = T - t0 < C ? T - t0 : C;
     const int tn = t0 + C;                           // start of the next block
     auto stage_next = [&]() {
-      if (tn < T) {
-        stage(T - tn < C ? T - tn : C, a.step_offset + tn + 1, (blk + 1) & 1, tn);
-        if (tn + C < T) load_kqu(tn + C);
-      }
+      if (tn < T) stage(T - tn < C ? T - tn : C, a.step_offset + tn + 1, (blk + 1) & 1, tn);
     };
+    // keeps addresses from being hoisted out of the loop, where the large heads have no registers for them
+    if constexpr (D >= 96) asm volatile("" : "+v"(c), "+v"(g));
     int cc = c;  // opaque copy: keeps lane-dependent masks from being hoisted out of the loop
     asm volatile("" : "+v"(cc));
 
-    f4 ft[NJV];  // starts as -V^T, becomes -F^T = K^ S0^T - V^T
+    // ================= Y^T = U A0, X^T = K^ A0 (this wave's columns) -> LDS
+    f4 yt[NJ], xt[NJ];
 #pragma unroll
-    for (int jn = 0; jn < NJV; ++jn) ft[jn] = f4{0, 0, 0, 0};
-    if constexpr (!SCAN) {
+    for (int jn = 0; jn < NJ; ++jn) yt[jn] = xt[jn] = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int jn = 0; jn < NJV; ++jn)
+    for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ft[jn][r] = (4 * g + r < len) ? neg_widen(vpre[jn][r]) : 0.0f;
-      if (tn < T) load_v(tn);
-    }
-
-    // ================= Y^T = U A0, X^T = K^ A0 (this wave's columns) -> LDS;  -F^T = K^ S0^T - V^T
-    f4 yt = f4{0, 0, 0, 0}, xt = f4{0, 0, 0, 0};
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const f4 ka = lds4(&Ks[c * LD + 16 * b + 4 * g]);
-      if constexpr (FULL) {
-        const f4 ua = lds4(&Us[c * LD + 16 * b + 4 * g]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) yt = mfma16(ua[r], At[b][r], yt);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) xt = mfma16(ka[r], At[b][r], xt);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) yt = mfma16(ka[r], At[b][r], yt);
-      }
-      if constexpr (!SCAN) {
-#pragma unroll
-        for (int jn = 0; jn < NJV; ++jn)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) ft[jn] = mfma16(ka[r], St[jn][b][r], ft[jn]);
+      for (int jn = 0; jn < NJ; ++jn) {
+        const auto ab = Ops::tiles(At[jn][2 * kb], At[jn][kSplit ? 2 * kb + 1 : 0]);
+        yt[jn] = Ops::sweep(Ops::operand(Us, kb, c, g), ab, yt[jn]);
+        if constexpr (FULL) xt[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), ab, xt[jn]);
+        if (NJ > 1) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
       }
     }
     if constexpr (FULL) {
@@ -360,18 +364,19 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
         const f4 e0 = lds4(&en[4 * g]);
         const f4 e1 = f4{e0[1], e0[2], e0[3], en[4 * g + 4]};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          yt[r] = fmaf(e0[r], Us[(4 * g + r) * LD + col0 + c], yt[r]);
-          xt[r] = fmaf(e1[r], Ks[(4 * g + r) * LD + col0 + c], xt[r]);
-        }
+        for (int jn = 0; jn < NJ; ++jn)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            yt[jn][r] = fmaf(e0[r], Ops::get(Us, 4 * g + r, col0 + 16 * jn + c), yt[jn][r]);
+            xt[jn][r] = fmaf(e1[r], Ops::get(Ks, 4 * g + r, col0 + 16 * jn + c), xt[jn][r]);
+          }
       }
-    } else {
-      xt = yt;
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      Ys[(4 * g + r) * LD + col0 + c] = yt[r];
-      if constexpr (FULL) Xsb[(4 * g + r) * LD + col0 + c] = xt[r];
+    for (int jn = 0; jn < NJ; ++jn) {
+      if constexpr (!FULL) xt[jn] = yt[jn];
+      Ops::put_column(Ys, 4 * g, col0 + 16 * jn + c, yt[jn]);
+      if constexpr (FULL) Ops::put_column(Xs, 4 * g, col0 + 16 * jn + c, xt[jn]);
     }
     __syncthreads();  // (1) Y^T, X^T complete
 
@@ -385,27 +390,24 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
         const bool mine = (slot % NW) == w;
         ++slot;
         if (!mine) continue;
-        const float* left = (i == kG || i == kGK || i == kGQ) ? Ys : (i == kGX || i == kXQ) ? Xs : Qs;
-        const float* right = (i == kG) ? Us : (i == kGK || i == kGX || i == kQK) ? Ks : Qs;
-        f4 acc0 = f4{0, 0, 0, 0}, acc1 = f4{0, 0, 0, 0};  // two chains: the tile is one wave's whole job here
+        const uint16_t* left = (i == kG || i == kGK || i == kGQ) ? Ys : (i == kGX || i == kXQ) ? Xs : Qs;
+        const uint16_t* right = (i == kG) ? Us : (i == kGK || i == kGX || i == kQK) ? Ks : Qs;
+        f4 acc[2] = {f4{0, 0, 0, 0}, f4{0, 0, 0, 0}};  // two chains: the tile is one wave's whole job here
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const f4 av = lds4(&left[c * LD + 16 * b + 4 * g]);
-          f4 bv;
+        for (int kb = 0; kb < NKB; ++kb) {
+          const auto av = Ops::operand(left, kb, c, g);
           if (i == kQZ) {
-            const f4 zv = lds4(&zks[16 * b + 4 * g]);
-            bv = (cc == 0) ? zv : f4{0, 0, 0, 0};
+            const f4 zero{0, 0, 0, 0};
+            const f4 z0 = cc == 0 ? lds4(&zks[32 * kb + 4 * g]) : zero;
+            const f4 z1 = cc == 0 && kSplit ? lds4(&zks[kSplit ? 32 * kb + 16 + 4 * g : 0]) : zero;
+            acc[kb & 1] = Ops::sweep(av, Ops::tiles(z0, z1), acc[kb & 1]);
           } else {
-            bv = lds4(&right[c * LD + 16 * b + 4 * g]);
+            acc[kb & 1] = Ops::sweep(av, Ops::operand(right, kb, c, g), acc[kb & 1]);
           }
-          acc0 = mfma16(av[0], bv[0], acc0);
-          acc1 = mfma16(av[1], bv[1], acc1);
-          acc0 = mfma16(av[2], bv[2], acc0);
-          acc1 = mfma16(av[3], bv[3], acc1);
         }
-        acc0 += acc1;
+        acc[0] += acc[1];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Gs[i][(4 * g + r) * LT + c] = acc0[r];
+        for (int r = 0; r < 4; ++r) Gs[i][(4 * g + r) * LT + c] = acc[0][r];
       }
     }
     __syncthreads();  // (2) Gram matrices visible
@@ -413,22 +415,46 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     // ================= phase 1 (one wave): Cholesky of I + G and L^{-1}
     const int sw = (blk + head) % NW;
     const int sw2 = (sw + (NW > 2 ? NW / 2 + 1 : 1)) % NW;  // another wave, on another SIMD, forms c, Z, NQ
-    f4 ot[NJV];  // R^T = Q S0^T, later O^T
-    auto r_pass = [&]() {
+    // -F^T = K^ S0^T - V^T and R^T = Q S0^T in one pass over S; needed only after barrier (5)
+    f4 ft[NJV], ot[NJV];
+    auto s_pass = [&]() {
 #pragma unroll
-      for (int jn = 0; jn < NJV; ++jn) ot[jn] = f4{0, 0, 0, 0};
+      for (int jn = 0; jn < NJV; ++jn) {
+        ot[jn] = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const f4 qa = lds4(&Qs[c * LD + 16 * b + 4 * g]);
+        for (int r = 0; r < 4; ++r) ft[jn][r] = (4 * g + r < len) ? neg_widen(vpre[jn][r]) : 0.0f;
+      }
+      if (tn < T) load_v(tn);
 #pragma unroll
-        for (int jn = 0; jn < NJV; ++jn)
+      for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) ot[jn] = mfma16(qa[r], St[jn][b][r], ot[jn]);
+        for (int jn = 0; jn < NJV; ++jn) {
+          const auto sb = Ops::tiles(St[jn][2 * kb], St[jn][kSplit ? 2 * kb + 1 : 0]);
+          ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
+          ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
+          if (NJ > 1) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    // zkey += sum over the block's tokens of ||k_s|| k^_s, this wave's columns (read by the Gram products only)
+    auto key_sum_pass = [&]() {
+      if (!key_sum) return;
+      const f4 nk = lds4(&nks[blk & 1][4 * g]);
+#pragma unroll
+      for (int jn = 0; jn < NJ; ++jn) {
+        float z = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z = fmaf(nk[r], Ops::get(Ks, 4 * g + r, col0 + 16 * jn + c), z);
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        if (lane < 16) zks[col0 + 16 * jn + lane] += z;
       }
     };
     if (w != sw) {
-      if constexpr (!SCAN) r_pass();
-      stage_next();
+      if constexpr (DB) stage_next();
+      if constexpr (!SCAN) s_pass();
+      key_sum_pass();
+      if (DB && tn + C < T) load_kqu(tn + C);
     } else {
       // Lanes 0-31 hold rows of I + G (-> rows of L), lanes 32-63 columns of the identity (-> columns of
       // L^{-1}); one broadcast of L[j][t] serves the trailing update and the forward substitution.
@@ -467,58 +493,71 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
 
     // ================= W^T = L^{-1} Y^T,  Hm = L^{-1} (Y K^^T),  Alpha^T = X^T - M W^T,  ||alpha_t||^2
     const f4 la = lds4(&Lis[c * LT + 4 * g]);
-    f4 nwt;   // -W^T tile
     f4 mop;   // M as an A operand: M[t = c][s = 4g + r] = Hm[s][t] for s <= t
     f4 nhm;   // -Hm in accumulator layout
     {
-      f4 acc = f4{0, 0, 0, 0};
       f4 hm = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        acc = mfma16(la[r], yt[r], acc);
-        hm = mfma16(la[r], Gs[iGK][(4 * g + r) * LT + c], hm);
-      }
-      nwt = -acc;
+      for (int r = 0; r < 4; ++r) hm = mfma16(la[r], Gs[iGK][(4 * g + r) * LT + c], hm);
       nhm = -hm;
-      *reinterpret_cast<f4*>(&Wb[(col0 + c) * LT + 4 * g]) = acc;
 #pragma unroll
       for (int r = 0; r < 4; ++r) mop[r] = (4 * g + r <= cc) ? hm[r] : 0.0f;
-      f4 at = xt;
+      f4 n2 = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) at = mfma16(mop[r], nwt[r], at);
-      f4 n2 = at * at;
+      for (int jn = 0; jn < NJ; ++jn) {
+        f4 acc = f4{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = mfma16(la[r], yt[jn][r], acc);
+        Ops::w_store(Whm, Wl, col0 + 16 * jn + c, c, g, acc);
+        f4 at = xt[jn];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) at = mfma16(mop[r], -acc[r], at);
+        n2 += at * at;
+        if constexpr (SCAN) {
+          *reinterpret_cast<f4*>(WT + (static_cast<size_t>(t0 / C) * D + col0 + 16 * jn + c) * C + 4 * g) = at;
+        } else {
+          Ops::w_store(Ahm, Al, col0 + 16 * jn + c, c, g, at);
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) n2[r] = row_sum16(n2[r]);
       if (c == 0) *reinterpret_cast<f4*>(&wn2p[w][4 * g]) = n2;
-      if constexpr (SCAN) {
-        *reinterpret_cast<f4*>(WT + (static_cast<size_t>(t0 / C) * D + col0 + c) * C + 4 * g) = at;
-      } else {
-        *reinterpret_cast<f4*>(&Ab[(col0 + c) * LT + 4 * g]) = at;
-      }
     }
     __syncthreads();  // (4) W, Alpha and the norm partials visible
 
     // ================= phase 2 (wave sw2): c_t, Z, NQ, read-out denominators -- the others update A
     auto update_A = [&]() {
+      decltype(Ops::tokens_b(f4{})) nw[NJ];
+#pragma unroll
+      for (int jn = 0; jn < NJ; ++jn) nw[jn] = Ops::w_neg_b(Whm, Wl, col0 + 16 * jn + c, c, g);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const f4 wa = lds4(&Wb[(16 * b + c) * LT + 4 * g]);
+        const auto wa = Ops::w_load(Whm, Wl, 16 * b + c, c, g);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) At[b] = mfma16(wa[r], nwt[r], At[b]);
+        for (int jn = 0; jn < NJ; ++jn) At[jn][b] = Ops::update(wa, nw[jn], At[jn][b]);
+        if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two tiles' operands at a time in registers
       }
-      if (FULL && period > 0) {  // + eta n on the diagonal (rows 16w + 4g + r against column 16w + c), n counted
+      if (FULL && period > 0) {  // + eta n on the diagonal (row 16b + 4g + r against column col0 + 16jn + c), n counted
         const float en_end = en[len];  // over the live tokens
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-          if (b == w) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) At[b][r] += (4 * g + r == cc) ? en_end : 0.0f;
+          for (int jn = 0; jn < NJ; ++jn) {
+            if (b == NJ * w + jn) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) At[jn][b][r] += (4 * g + r == cc) ? en_end : 0.0f;
+            }
           }
         }
       }
     };
     if (w != sw2) update_A();
-    if (w == sw) stage_next();
+    if (w == sw) {
+      if constexpr (DB) stage_next();
+      if constexpr (!SCAN) s_pass();
+      key_sum_pass();
+      if (DB && tn + C < T) load_kqu(tn + C);
+    }
     if (w == sw2) {
       __builtin_amdgcn_s_setprio(3);
       float wn2 = 0.0f;
@@ -593,11 +632,11 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
       }
       __builtin_amdgcn_s_setprio(0);
     }
-    __syncthreads();  // (5) Z, NQ, c, denominators visible; the next block is staged in full
+    __syncthreads();  // (5) Z, NQ, c, denominators visible; K^, Q, U no longer needed
 
     // ================= -E^T = Z (-F^T), O^T = Q S0^T + (-NQ^T)(-E^T), store o;  ce = diag(c) E^T
     if constexpr (!SCAN) {
-    f4 ce[NJV];
+    decltype(Ops::tokens_b(f4{})) ce[NJV];
     {
       const f4 za = lds4(&Zs[c * LT + 4 * g]);
       f4 et[NJV];
@@ -607,14 +646,13 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
 #pragma unroll
         for (int r = 0; r < 4; ++r) et[jn] = mfma16(za[r], ft[jn][r], et[jn]);
       }
-      if (w == sw) r_pass();
       const f4 nqa = lds4(&NQs[c * LT + 4 * g]);
       const f4 cg = lds4(&cvec[4 * g]);
 #pragma unroll
       for (int jn = 0; jn < NJV; ++jn) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) ot[jn] = mfma16(nqa[r], et[jn][r], ot[jn]);
-        ce[jn] = et[jn] * cg;
+        ce[jn] = Ops::tokens_b(et[jn] * cg);
         if (norm_out) ot[jn] *= lds4(&rdens[4 * g]);
         if (owns(jn)) {
 #pragma unroll
@@ -628,20 +666,17 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     // ================= S^T += Alpha diag(c) E^T  (and A -= W W^T on the wave that formed Z)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const f4 aa = lds4(&Ab[(16 * b + c) * LT + 4 * g]);
+      const auto aa = Ops::w_load(Ahm, Al, 16 * b + c, c, g);
 #pragma unroll
-      for (int jn = 0; jn < NJV; ++jn)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) St[jn][b] = mfma16(aa[r], ce[jn][r], St[jn][b]);
+      for (int jn = 0; jn < NJV; ++jn) St[jn][b] = Ops::update(aa, ce[jn], St[jn][b]);
+      if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
     }  // !SCAN
+    if (!DB && tn < T) load_kqu(tn);   // staged right below; not held in registers before
     if (w == sw2) update_A();
-    if (key_sum && lane < 16) {  // zkey += sum over the block's tokens of ||k_s|| k^_s, this wave's columns
-      float zk = zks[col0 + lane];
-#pragma unroll
-      for (int s = 0; s < C; ++s) zk = fmaf(nks[blk & 1][s], Ks[s * LD + col0 + lane], zk);
-      zks[col0 + lane] = zk;
-    }
+    if constexpr (DB) continue;
+    stage_next();
+    __syncthreads();  // (6) the next block is staged; W and Alpha no longer needed
   }
 
   // ---- final state (SCAN: A and the key sum after the last segment; S belongs to phase 2)
@@ -654,7 +689,9 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
     for (int b = 0; b < NB; ++b) {
       if (AT) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) AT[arc + (16 * b + r) * D] = At[b][r];
+        for (int jn = 0; jn < NJ; ++jn)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) AT[arc + (16 * b + r) * D + 16 * jn] = At[jn][b][r];
       }
       if (ST) {
 #pragma unroll
@@ -664,24 +701,37 @@ __global__ void __launch_bounds__(4 * D, (SCAN && D <= 64) ? 3 : 1) chunk_genera
                 make_float4(St[jn][b][0], St[jn][b][1], St[jn][b][2], St[jn][b][3]);
       }
     }
-    if (a.zkey_T != nullptr && lane < 16) {
+    if (a.zkey_T != nullptr && lane < SL) {
       a.zkey_T[static_cast<size_t>(head) * D + col0 + lane] = zks[col0 + lane];
     }
   }
 }
 
-template <int D, int DV, typename IO>
+template <int D, int DV, int SL, bool DB, typename IO>
 hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
   const bool full = a.u != nullptr || a.refresh_period > 0;
-  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, IO, true, false>)
-                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, IO, false, false>);
-  return hipLaunchKernel(fn, dim3(a.n_heads), dim3(4 * D), params, 0, stream);
+  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, true, false, DB>)
+                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, false, false, DB>);
+  return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * D / SL), params, 0, stream);
 }
 template <int D, int DV>
 hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
-  return io_dtype == 1 ? launch<D, DV, uint16_t>(a, stream) : launch<D, DV, float>(a, stream);
+  const bool bf = io_dtype == 1;
+  // d = 128: waves of 32 columns (two workgroups of four waves per compute unit) from the count where a compute unit
+  // gets two, waves of 16 (one of eight) below.  T = 256, every option, 16 / 32 columns: 256 heads 0.183 / 0.251 ms,
+  // 512 heads 0.34 / 0.32, 2048 heads 1.27 / 1.15.
+  if constexpr (D == 128) {
+    if (a.n_heads > 256) return bf ? launch<D, DV, 32, false, uint16_t>(a, stream) : launch<D, DV, 32, false, float>(a, stream);
+  }
+  // d <= 32: double buffers while a compute unit holds at most two workgroups (d = 32: 64 heads 0.095 ms, single
+  // buffers 0.103; 512 heads 0.114 / 0.118; 1024 heads 0.21 / 0.13).  d = 64: single ones at any count (256 heads
+  // 0.118 / 0.114, 2048 heads 0.55 / 0.43).
+  if constexpr (D <= 32 && DV <= D) {
+    if (a.n_heads <= 512) return bf ? launch<D, DV, 16, true, uint16_t>(a, stream) : launch<D, DV, 16, true, float>(a, stream);
+  }
+  return bf ? launch<D, DV, 16, false, uint16_t>(a, stream) : launch<D, DV, 16, false, float>(a, stream);
 }
 template <int D>
 hipError_t launch_dv(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t stream) {
@@ -697,14 +747,18 @@ hipError_t launch_dv(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t st
 // phase 1 of the two-phase and time-parallel modes with options: one workgroup per (head, segment)
 template <int D, typename IO>
 hipError_t launch_scan(const ForwardArgs& a, hipStream_t stream) {
+  constexpr int SL = 16;
+  // 16 heads, normalised read-out, single / double buffers: d = 64, T = 16384 0.448 / 0.418 ms, d = 128, T = 8192
+  // 0.668 / 0.643; d = 32, T = 16384 0.22 / 0.21 with and without u 0.239 / 0.28
+  constexpr bool kScanDB = D >= 64;
   ForwardArgs args = a;
   void* params[] = {&args};
   const bool full = a.u != nullptr || a.refresh_period > 0;
-  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, D, IO, true, true>)
-                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, D, IO, false, true>);
+  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, true, true, kScanDB>)
+                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, false, true, kScanDB>);
   const long long wgs = static_cast<long long>(a.n_heads) * a.n_seg;
   if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(wgs)), dim3(4 * D), params, 0, stream);
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(wgs)), dim3(64 * D / SL), params, 0, stream);
 }
 
 }  // namespace

@@ -161,6 +161,111 @@ __device__ __forceinline__ TokB tok_neg_b(const u4* hm, const u2* l, int row, in
   return TokB{x, u4{x[2], x[3], x[0], x[1]}, u4{x[0], x[1], y[0], y[1]}};
 }
 
+// The products of the block form.  SPLIT: on bf16 terms as above; otherwise on the FP32 matrix instruction, with the
+// operands staged as float32 in the same arrays (head size 16 is a single tile: half of the slots of a bf16 product
+// would be empty and nothing but the latency of the chain counts; one head of 256 tokens: 51 us with FP32 products,
+// 55 us with split ones).  NT: terms of a staged operand.  D: head size (columns of the contraction).
+template <bool SPLIT, int NT, int D>
+struct BlockOps {
+  static_assert(SPLIT || (NT == 1 && D == 16), "FP32 products: one tile");
+  static constexpr int LDK = (D + 31) / 32 * 32 + 8;   // row stride (bf16) of a term: an odd number of 16-byte pieces
+  static constexpr int TERM = C * LDK;                 // one term of 16 tokens
+  static constexpr int SIZE = NT * TERM;
+
+  // four elements of a token's row (j0 a multiple of 4)
+  static __device__ __forceinline__ void put4(uint16_t* dst, int row, int j0, f4 x) {
+    const int at = row * LDK + kslot(j0);
+    if constexpr (!SPLIT) {
+      *reinterpret_cast<f4*>(&dst[row * LDK + 2 * j0]) = x;
+    } else if constexpr (NT == 1) {   // bf16 numbers: the low halves are zero
+      *reinterpret_cast<u2*>(&dst[at]) = u2{pack_tops(x[0], x[1]), pack_tops(x[2], x[3])};
+    } else {
+      u2 h, m, l;
+      split3_rne(x, h, m, l);
+      *reinterpret_cast<u2*>(&dst[at]) = h;
+      *reinterpret_cast<u2*>(&dst[TERM + at]) = m;
+      *reinterpret_cast<u2*>(&dst[2 * TERM + at]) = l;
+    }
+  }
+  // the same element of four tokens' rows (column j of rows row0 .. row0 + 3)
+  static __device__ __forceinline__ void put_column(uint16_t* dst, int row0, int j, f4 x) {
+    if constexpr (!SPLIT) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) *reinterpret_cast<float*>(&dst[(row0 + r) * LDK + 2 * j]) = x[r];
+    } else {
+      static_assert(NT == 3 || !SPLIT, "float32 values");
+      u2 t[3];
+      split3_rne(x, t[0], t[1], t[2]);
+      const int at = row0 * LDK + kslot(j & ~3) + (j & 3);
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          dst[i * TERM + at + r * LDK] = static_cast<uint16_t>(r % 2 ? t[i][r / 2] >> 16 : t[i][r / 2] & 0xffffu);
+    }
+  }
+  // one element back (the terms sum to it exactly)
+  static __device__ __forceinline__ float get(const uint16_t* src, int row, int j) {
+    if constexpr (!SPLIT) return *reinterpret_cast<const float*>(&src[row * LDK + 2 * j]);
+    const int at = row * LDK + kslot(j & ~3) + (j & 3);
+    float x = bf16_to_f32(src[at]);
+    if constexpr (NT == 3) x = (bf16_to_f32(src[2 * TERM + at]) + bf16_to_f32(src[TERM + at])) + x;
+    return x;
+  }
+  // operand of the 16 tokens (token c on lane c), columns 32 kb .. 32 kb + 31 (16 bytes at group g either way)
+  static __device__ __forceinline__ Terms<NT> operand(const uint16_t* src, int kb, int c, int g) {
+    Terms<NT> x;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) x.t[i] = *reinterpret_cast<const u4*>(&src[i * TERM + c * LDK + 32 * kb + 8 * g]);
+    return x;
+  }
+  // two accumulator tiles (one without the split) as the other operand
+  static __device__ __forceinline__ auto tiles(f4 x0, f4 x1) {
+    if constexpr (SPLIT) return split_tiles(x0, x1);
+    else return x0;
+  }
+  template <typename X>
+  static __device__ __forceinline__ f4 sweep(const Terms<NT>& a, const X& b, f4 acc) {
+    if constexpr (SPLIT) {
+      return mfma_terms(a, b, acc);
+    } else {
+      const f4 xa = __builtin_bit_cast(f4, a.t[0]);
+      f4 xb;
+      if constexpr (sizeof(X) == sizeof(f4)) xb = __builtin_bit_cast(f4, b);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = mfma16(xa[r], xb[r], acc);
+      return acc;
+    }
+  }
+  // The LDS image of a [D][16 tokens] matrix W (hm [4 D], l [4 D]) and updates X += W y, four tokens of y per lane
+  static __device__ __forceinline__ void w_store(u4* hm, u2* l, int row, int c, int g, f4 x) {
+    if constexpr (SPLIT) tok_store(hm, l, row, c, g, x);
+    else hm[4 * row + tok_chunk(c, g)] = __builtin_bit_cast(u4, x);
+  }
+  static __device__ __forceinline__ auto w_load(const u4* hm, const u2* l, int row, int c, int g) {
+    if constexpr (SPLIT) return tok_load(hm, l, row, c, g);
+    else return __builtin_bit_cast(f4, hm[4 * row + tok_chunk(c, g)]);
+  }
+  static __device__ __forceinline__ auto w_neg_b(const u4* hm, const u2* l, int row, int c, int g) {
+    if constexpr (SPLIT) return tok_neg_b(hm, l, row, c, g);
+    else return -__builtin_bit_cast(f4, hm[4 * row + tok_chunk(c, g)]);
+  }
+  static __device__ __forceinline__ auto tokens_b(f4 x) {
+    if constexpr (SPLIT) return tok_b(x);
+    else return x;
+  }
+  template <typename WA, typename Y>
+  static __device__ __forceinline__ f4 update(const WA& wa, const Y& y, f4 acc) {
+    if constexpr (SPLIT) {
+      return mfma_tok(wa, y, acc);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = mfma16(wa[r], y[r], acc);
+      return acc;
+    }
+  }
+};
+
 __device__ __forceinline__ float readlane(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }

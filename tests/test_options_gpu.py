@@ -340,3 +340,21 @@ def test_auto_sends_a_few_head_call_with_the_papers_options_to_the_time_parallel
     got, ref = run_both(q, k, v, dtype="bf16", u=u, lambda0=0.1, u_scale=d ** -0.5, normalise_output=True,
                         feature_map=True)       # mode AUTO
     print(assert_close(got, ref, TOL["bf16"]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,heads", [(128, 256), (128, 257), (64, 257), (96, 257), (32, 512), (32, 513), (16, 513)])
+def test_option_block_kernel_on_both_sides_of_its_head_counts(d, heads, dtype):
+    """Head counts where the option kernel changes its waves per head or its staging; refresh steps inside the
+    blocks, a ragged last one, carried S, A and key sum."""
+    rng = np.random.default_rng(d + heads)
+    T = 37
+    q, k, v, u = (rng.standard_normal((1, heads, T, d)).astype(np.float32) for _ in range(4))
+    S0 = rng.standard_normal((1, heads, d, d)).astype(np.float32)
+    m = rng.standard_normal((1, heads, d, d)).astype(np.float32) / np.sqrt(d)
+    A0 = np.eye(d, dtype=np.float32) * 3.0 + m @ m.transpose(0, 1, 3, 2)
+    A0 = 0.5 * (A0 + A0.transpose(0, 1, 3, 2))
+    z0 = np.abs(rng.standard_normal((1, heads, d))).astype(np.float32)
+    got, ref = run_both(q, k, v, dtype=dtype, u=u, S0=S0, A0=A0, zkey0=z0, lambda0=0.1, u_scale=0.25, refresh_period=5,
+                        refresh_eta=1e-2, step_offset=3, normalise_output=True, feature_map=True, mode=BLOCK)
+    print(d, heads, dtype, assert_close(got, ref, TOL[dtype]))
