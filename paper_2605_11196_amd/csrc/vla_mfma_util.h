@@ -167,8 +167,10 @@ __device__ __forceinline__ TokB tok_neg_b(const u4* hm, const u2* l, int row, in
 // 55 us with split ones).  NT: terms of a staged operand.  D: head size (columns of the contraction).
 template <bool SPLIT, int NT, int D>
 struct BlockOps {
-  static_assert(SPLIT || (NT == 1 && D == 16), "FP32 products: one tile");
-  static constexpr int LDK = (D + 31) / 32 * 32 + 8;   // row stride (bf16) of a term: an odd number of 16-byte pieces
+  static_assert(SPLIT || NT == 1, "FP32 products: the values themselves");
+  // row stride (in 16 bits) of a term: an odd number of 16-byte pieces
+  static constexpr int LDK = SPLIT ? (D + 31) / 32 * 32 + 8 : 2 * D + 8;
+  static constexpr int STEP = SPLIT ? 2 : 1;           // accumulator tiles of one step of a contraction over columns
   static constexpr int TERM = C * LDK;                 // one term of 16 tokens
   static constexpr int SIZE = NT * TERM;
 
@@ -212,7 +214,7 @@ struct BlockOps {
     if constexpr (NT == 3) x = (bf16_to_f32(src[2 * TERM + at]) + bf16_to_f32(src[TERM + at])) + x;
     return x;
   }
-  // operand of the 16 tokens (token c on lane c), columns 32 kb .. 32 kb + 31 (16 bytes at group g either way)
+  // operand of the 16 tokens (token c on lane c), columns 16 STEP kb onwards (16 bytes at group g either way)
   static __device__ __forceinline__ Terms<NT> operand(const uint16_t* src, int kb, int c, int g) {
     Terms<NT> x;
 #pragma unroll

@@ -35,7 +35,15 @@ namespace {
 // one block behind the A chain, on the operands that are still in LDS (K^ and W of the previous block in a second
 // copy, Z and c from the C x C pass), instead of in a pass of their own that reads them back from the workspace.
 // The 2 d/16 row slabs of 16 rows are dealt out over the waves.
-template <int D, int NW, typename IO, bool MAPF = false>
+//
+// Products with A, S and W: split bf16 terms (vla_mfma_util.h); W is split once, as it is formed.  KT = 1: bf16 keys
+// and queries without a feature map are staged as they are, and 1 / ||k|| goes on the rows and columns of the results;
+// KT = 3 otherwise (terms of k^ and q).  With MAPF and KT = 3 the products stay on the FP32 instruction: two copies of
+// three-term keys would leave three instead of four workgroups per compute unit, and without MAPF the maps cost a pass.
+// Bound by the block's serial chain and, with the maps, the matrix pipes.  16 heads of 64, bf16, T = 131072, whole call,
+// with the S rows below already on split products: 1.89 ms with FP32 products here, 1.63 split; heads of 128,
+// T = 32768: 1.49 and 1.38.
+template <int D, int NW, typename IO, bool MAPF, int KT>
 __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_kernel(ForwardArgs a) {
   static_assert(NW >= 2, "the C x C pass of the previous block runs on a second wave");
   constexpr int NKB = MAPF ? 2 : 1;            // copies of K^ and W in LDS
@@ -46,7 +54,13 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   constexpr int SL = D / NW;
   constexpr int NJ = SL / 16;
   constexpr int NB = D / 16;
-  constexpr int LD = D + 4;
+  constexpr bool kSplit = KT == 1 || !MAPF;
+  using Prod = BlockOps<kSplit, kSplit ? KT : 1, D>;
+  constexpr int STEP = Prod::STEP;
+  constexpr bool kRawKeys = KT == 1;
+  static_assert(!kRawKeys || sizeof(IO) == 2, "one term: bf16 numbers");
+  static_assert(SL == 16 || SL == 32, "the wave's slab is a 32-column step of a contraction or half of one");
+  constexpr int LDY = SL + 4;                  // row stride of a wave's slab of Y^T
   constexpr int NT = 64 * NW;
   // Staging: a token row is split over TPR threads of EPT elements each.  For the power-of-two head sizes every
   // thread stages; at d = 96 a row takes 6 threads of 16 elements in a group of 8 (two lanes of each group and
@@ -58,17 +72,19 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   static_assert(EPT % 4 == 0 && TPR <= 16 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
-  __shared__ __align__(16) float Ksb[NKB][C * LD];
-  __shared__ __align__(16) float Qs[C * LD];
-  __shared__ __align__(16) float Ys[C * LD];
-  __shared__ __align__(16) float Wbb[NKB][D * LT];
+  __shared__ __align__(16) uint16_t Ksb[NKB][Prod::SIZE];   // terms of K^ (of k as it is: kRawKeys)
+  __shared__ __align__(16) uint16_t Qs[Prod::SIZE];
+  __shared__ __align__(16) float Ysb[NW][C * LDY];           // Y^T [t][j], a slab per wave, which no other wave reads
+  __shared__ __align__(16) u4 Whm[NKB][4 * D];               // W [j][t], split
+  __shared__ __align__(16) u2 Wl[NKB][kSplit ? 4 * D : 1];
+  __shared__ __align__(16) float rns[2][C];                  // 1 / max(||k_t||, eps) (kRawKeys)
   __shared__ __align__(16) float Gp[NW][2][C * LT];
   // MAPF: Z [t][s] and -c of the previous block live in Y^T's array, which is dead between barrier (2) of a block
   // and the first barrier of the next one: exactly the window in which they are written and read (four
   // workgroups of 40 KB share a compute unit; separate arrays would make it three)
-  static_assert(C * LD >= C * LT + C, "Z and c fit the Y^T array");
-  float* const Zs = Ys;
-  float* const cvs = Ys + C * LT;
+  static_assert(NW * C * LDY >= C * LT + C, "Z and c fit the Y^T array");
+  float* const Zs = &Ysb[0][0];
+  float* const cvs = Zs + C * LT;
   // kept for one more block (two copies, by block parity): the wave that turns them into c, Z, NQ reads the
   // previous block's while the factorisation of the current block writes its own
   __shared__ __align__(16) float Lis[2][C * LT];   // L^{-1} [t][s]
@@ -219,38 +235,38 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     }
   };
   // one block of the S recurrence on this wave's slabs: operands of the block in LDS copy `kb`
-  auto map_step = [&](int t0, int kb, const IO (&vv)[MAPF ? SPW : 1][4]) {
+  auto map_step = [&](int t0, int cp, const IO (&vv)[MAPF ? SPW : 1][4]) {
     if constexpr (MAPF) {
       const f4 za = lds4(&Zs[c * LT + 4 * g]);
       const f4 cg = lds4(&cvs[4 * g]);
+      const f4 rn4 = lds4(&rns[cp][4 * g]);
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
         f4 ft = f4{0, 0, 0, 0};
+#pragma unroll
+        for (int kb = 0; kb < NB / STEP; ++kb) {
+          ft = Prod::sweep(Prod::operand(Ksb[cp], kb, c, g),
+                           Prod::tiles(mst[i][STEP * kb], mst[i][STEP * kb + STEP - 1]), ft);
+          if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
+        }
+        if constexpr (kRawKeys) ft *= rn4;
         if (i < QSL) {   // known at compile time: the P run starts from v = 0
           if (t0 + C <= T) {   // uniform: only the ragged last block masks rows past the end
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ft[r] = neg_widen(vv[i][r]);
+            for (int r = 0; r < 4; ++r) ft[r] += neg_widen(vv[i][r]);
           } else {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ft[r] = (t0 + 4 * g + r < T) ? neg_widen(vv[i][r]) : 0.0f;
+            for (int r = 0; r < 4; ++r) ft[r] += (t0 + 4 * g + r < T) ? neg_widen(vv[i][r]) : 0.0f;
           }
-        }
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const f4 ka = lds4(&Ksb[kb][c * LD + 16 * b + 4 * g]);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) ft = mfma16(ka[r], mst[i][b][r], ft);
         }
         f4 et = f4{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 4; ++r) et = mfma16(za[r], ft[r], et);
         const f4 ce = et * cg;
+        const auto cb = Prod::tokens_b(ce);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const f4 wa = lds4(&Wbb[kb][(16 * b + c) * LT + 4 * g]);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) mst[i][b] = mfma16(wa[r], ce[r], mst[i][b]);
-        }
+        for (int b = 0; b < NB; ++b)
+          mst[i][b] = Prod::update(Prod::w_load(Whm[cp], Wl[cp], 16 * b + c, c, g), cb, mst[i][b]);
       }
     }
   };
@@ -260,8 +276,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   __builtin_amdgcn_s_setprio(1);
   for (int t0 = tb; t0 < T; t0 += C, ++blk, ++it) {
     const int pb = it & 1;
-    float* Ks = Ksb[MAPF ? pb : 0];
-    float* Wb = Wbb[MAPF ? pb : 0];
+    const int cp = MAPF ? pb : 0;
+    uint16_t* Ks = Ksb[cp];
     // ---- stage K^ and Q (LDS); 1 / max(||k||, eps) per token goes to the workspace
     if (stage_wave) {
       float kx[EPT];
@@ -292,11 +308,11 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f);
       if (stager) {
         if (sseg == 0) RN[t0 + srow] = live ? rn : 0.0f;   // rows past the end: zero keys
+        if (kRawKeys && sseg == 0) rns[pb][srow] = rn;
+        const float ks = kRawKeys ? 1.0f : rn;
 #pragma unroll
-        for (int e = 0; e < EPT; e += 4) {
-          *reinterpret_cast<f4*>(&Ks[srow * LD + sseg + e]) =
-              f4{kx[e] * rn, kx[e + 1] * rn, kx[e + 2] * rn, kx[e + 3] * rn};
-        }
+        for (int e = 0; e < EPT; e += 4)
+          Prod::put4(Ks, srow, sseg + e, f4{kx[e] * ks, kx[e + 1] * ks, kx[e + 2] * ks, kx[e + 3] * ks});
         qpre.unpack(kx);
         if (fmap) {
 #pragma unroll
@@ -308,7 +324,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
         }
 #pragma unroll
         for (int e = 0; e < EPT; e += 4)
-          *reinterpret_cast<f4*>(&Qs[srow * LD + sseg + e]) = f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]};
+          Prod::put4(Qs, srow, sseg + e, f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]});
       }
     }
     __syncthreads();  // (1)
@@ -320,36 +336,44 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
 #pragma unroll
     for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const f4 ka = lds4(&Ks[c * LD + 16 * b + 4 * g]);
+    for (int kb = 0; kb < NB / STEP; ++kb) {
+      const auto ka = Prod::operand(Ks, kb, c, g);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) yt[jn] = mfma16(ka[r], At[b][jn][r], yt[jn]);
+      for (int jn = 0; jn < NJ; ++jn)
+        yt[jn] = Prod::sweep(ka, Prod::tiles(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
+      if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one step's splits at a time in registers
     }
-#pragma unroll
-    for (int jn = 0; jn < NJ; ++jn)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Ys[(4 * g + r) * LD + col0 + 16 * jn + c] = yt[jn][r];
+    f4 rn4 = f4{1, 1, 1, 1};
+    if constexpr (kRawKeys) rn4 = lds4(&rns[pb][4 * g]);
     {
-      f4 gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
+      float* Yw = Ysb[w];
 #pragma unroll
       for (int jn = 0; jn < NJ; ++jn) {
-        const int o4 = c * LD + col0 + 16 * jn + 4 * g;
-        const f4 ya = lds4(&Ys[o4]);
-        const f4 kb = lds4(&Ks[o4]);
-        const f4 qb = lds4(&Qs[o4]);
+        if constexpr (kRawKeys) yt[jn] *= rn4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          gg = mfma16(ya[r], kb[r], gg);
-          gq = mfma16(ya[r], qb[r], gq);
+        for (int r = 0; r < 4; ++r) Yw[(4 * g + r) * LDY + 16 * jn + c] = yt[jn][r];
+      }
+      // same-wave write -> read: LDS operations of one wave are ordered
+      // G[s][t] and GQ[s][t] come out with t on the rows of the accumulator
+      f4 gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
+      if constexpr (kSplit) {
+        // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
+        const f4 zero{0, 0, 0, 0};
+        const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
+        const f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + (NJ > 1 ? 16 : 0) + 4 * g]) : (w & 1) ? y0 : zero;
+        const auto ya = Prod::tiles(NJ == 1 && (w & 1) ? zero : y0, y1);
+        gg = Prod::sweep(Prod::operand(Ks, col0 / 32, c, g), ya, gg);
+        gq = Prod::sweep(Prod::operand(Qs, col0 / 32, c, g), ya, gq);
+      } else {
+#pragma unroll
+        for (int jn = 0; jn < NJ; ++jn) {
+          const f4 y = lds4(&Yw[c * LDY + 16 * jn + 4 * g]);
+          gg = Prod::sweep(Prod::operand(Ks, col0 / 16 + jn, c, g), y, gg);
+          gq = Prod::sweep(Prod::operand(Qs, col0 / 16 + jn, c, g), y, gq);
         }
       }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        Gp[w][0][(4 * g + r) * LT + c] = gg[r];
-        Gp[w][1][(4 * g + r) * LT + c] = gq[r];
-      }
+      *reinterpret_cast<f4*>(&Gp[w][0][c * LT + 4 * g]) = gg * rn4;
+      *reinterpret_cast<f4*>(&Gp[w][1][c * LT + 4 * g]) = gq;
     }
     __syncthreads();  // (2)
 
@@ -403,7 +427,6 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
 
     // ---- W^T = L^{-1} Y^T -> LDS and workspace; partial norms
     const f4 la = lds4(&Lis[pb][c * LT + 4 * g]);
-    f4 nwt[NJ];
     {
       f4 n2 = f4{0, 0, 0, 0};
       float* wg = WT + static_cast<size_t>(blk) * D * C;
@@ -412,9 +435,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
         f4 acc = f4{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc = mfma16(la[r], yt[jn][r], acc);
-        nwt[jn] = -acc;
         n2 += acc * acc;
-        *reinterpret_cast<f4*>(&Wb[(col0 + 16 * jn + c) * LT + 4 * g]) = acc;
+        Prod::w_store(Whm[cp], Wl[cp], col0 + 16 * jn + c, c, g, acc);
         *reinterpret_cast<f4*>(wg + (col0 + 16 * jn + c) * C + 4 * g) = acc;
       }
 #pragma unroll
@@ -437,13 +459,14 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     __syncthreads();  // (4)
 
     // ---- A -= W W^T
+    decltype(Prod::tokens_b(f4{})) nw[NJ];
+#pragma unroll
+    for (int jn = 0; jn < NJ; ++jn) nw[jn] = Prod::w_neg_b(Whm[cp], Wl[cp], col0 + 16 * jn + c, c, g);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const f4 wa = lds4(&Wb[(16 * b + c) * LT + 4 * g]);
+      const auto wa = Prod::w_load(Whm[cp], Wl[cp], 16 * b + c, c, g);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) At[b][jn] = mfma16(wa[r], nwt[jn][r], At[b][jn]);
+      for (int jn = 0; jn < NJ; ++jn) At[b][jn] = Prod::update(wa, nw[jn], At[b][jn]);
     }
   }
   // c, Z, NQ of the last block: everything it needs was written before the last barrier
@@ -702,23 +725,40 @@ hipError_t launch_s_rows(const ForwardArgs& a, hipStream_t stream) {
 // D / 16 waves per run (they stage the operands, whose size follows D) and the d_v / 16 row slabs of S go to
 // them in turn: slab t to wave t % (D / 16), NJV = slots per wave; a wave with no slab in a slot skips it.
 // The P run always has D / 16 slabs, one per wave.
-template <int D, int NJV, bool RECT, typename IO, bool MAP>
-__global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 2) s_rows_lds_kernel(ForwardArgs a) {
+//
+// Products with S and W: split bf16 terms (vla_mfma_util.h), since the FP32 matrix instruction was what bounded the
+// kernel (68 % of its time).  W is split once per block as it is staged; S as it is read.  NT = 1: bf16 keys and
+// queries without a feature map go in as they are, 1 / ||k|| is applied to the residual; otherwise (float32, or
+// ELU(x) + 1) three terms of k^ and q.  Z and NQ stay FP32 products: 16 x 16, and in the block's serial chain.
+// The Z and NQ rows are unpadded (a wave reads all 1 KB of one in a row, no bank twice): so two workgroups of d = 128
+// with three-term operands fit a compute unit (81 KB each).
+// Whole calls, bf16, FP32 products against these (the A scan on FP32 ones in both): 16 heads of 128, T = 32768: 1.83
+// against 1.49 ms; 16 heads of 64, T = 131072: 2.00 against 1.89 ms, T = 4096: 0.151 against 0.146.
+//
+// kSplit = false: FP32 products, WPS: waves per SIMD (the launch below says when).
+template <int D, int NJV, bool RECT, typename IO, bool MAP, int NT_KQ, bool kSplit, int WPS>
+__global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), WPS) s_rows_lds_kernel(ForwardArgs a) {
   static_assert(RECT || NJV == 1, "square heads: one slab per wave");
   constexpr int NB = D / 16;
   constexpr int NSLAB = D / 16;                  // waves of a run
   constexpr int NT = 64 * NSLAB * (MAP ? 2 : 1);
-  constexpr int LD = D + 4;
+  using Prod = BlockOps<kSplit, kSplit ? NT_KQ : 1, D>;
+  constexpr int STEP = Prod::STEP;
+  constexpr bool kRawKeys = NT_KQ == 1;
+  constexpr bool kTight = D == 128 && kSplit && WPS == 4;   // fits 128 registers only if operands are not read ahead of their tiles
+  static_assert(!kRawKeys || sizeof(IO) == 2, "one term: bf16 numbers");
   constexpr int CH = 4 * D;                     // 16-byte pieces of K^ (and of W, and 4-element pieces of q)
   static_assert(NT == (MAP ? 2 * CH : CH), "one piece of each big operand per thread");
   constexpr int NST = 2;
   struct Stage {
-    float Ks[C * LD];      // K^ [t][j]
-    float Qs[C * LD];      // q  [t][j] widened (unused by the map pass)
-    float Wb[D * LT];      // W  [j][t]
-    float Zs[C * LT];      // Z  [t][s]
-    float NQs[C * LT];     // -NQ^T [t][s]
+    uint16_t Ks[Prod::SIZE];             // terms of K^ [t][j] (of k as it is: kRawKeys)
+    uint16_t Qs[MAP ? 8 : Prod::SIZE];   // terms of q  [t][j]
+    u4 Whm[4 * D];                       // W  [j][t], split
+    u2 Wl[kSplit ? 4 * D : 1];
+    float Zs[C * C];                     // Z  [t][s]
+    float NQs[MAP ? 4 : C * C];          // -NQ^T [t][s]
     float cv[2 * C];       // -c_t, then 1 / max(q_t . zkey_t, eps) (normalised read-out only)
+    float rn[C];           // 1 / max(||k_t||, eps), 0 past the end (kRawKeys)
   };
   __shared__ __align__(16) Stage stg[NST];
 
@@ -786,7 +826,6 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 
   const bool do_k = !MAP || tid < CH;
   const bool do_w = !MAP || tid >= CH;
   const int krow = pc / (D / 4), kcol = 4 * (pc % (D / 4));
-  const int wrow = pc / 4, wcol = 4 * (pc % 4);
   constexpr bool kSepC = NT < 136;
   const int nc = (!MAP && norm_out) ? 8 : 4;   // -c (and the read-out denominators behind it)
   const bool do_sm = tid < (MAP ? 64 : 128) || (!kSepC && tid >= 128 && tid < 128 + nc);
@@ -800,7 +839,7 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 
   // Byte offsets inside a block's records are per-thread constants (32 bits); the block's base addresses are
   // uniform (scalar registers).  Only the ragged last block has to clamp its token rows (rows past the end read
   // the last row).
-  // (krow D + kcol = wrow C + wcol = 4 pc and sm_src = 4 tid: piece pc of a row-major array of 4-element pieces.)
+  // (krow D + kcol = 4 pc and sm_src = 4 tid: piece pc of a row-major array of 4-element pieces.)
   constexpr unsigned ES = sizeof(IO);
   static_assert(C == 16, "piece arithmetic");
   const unsigned p16 = 16u * static_cast<unsigned>(pc);      // byte offset of float piece pc
@@ -859,20 +898,28 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 
     }
   };
   auto put = [&](const Regs& r, Stage& s) {
-    if (do_k) {   // k^ = k / max(||k||, eps): the same product the A scan formed it with
+    int pc = MAP ? tid % CH : tid;
+    asm volatile("" : "+v"(pc));
+    const int krow = pc / (D / 4), kcol = 4 * (pc % (D / 4));
+    const int wrow = pc / 4, wcol = 4 * (pc % 4);
+    if (do_k) {
       float x[4];
       r.kx.unpack(x);
-      if (fmap) {
+      if constexpr (kRawKeys) {
+        if (kcol == 0) s.rn[krow] = r.krn;
+        Prod::put4(s.Ks, krow, kcol, f4{x[0], x[1], x[2], x[3]});
+      } else {   // k^ = k / max(||k||, eps): the same product the A scan formed it with
+        if (fmap) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = elu_plus_one(x[i]);
+          for (int i = 0; i < 4; ++i) x[i] = elu_plus_one(x[i]);
+        }
+        Prod::put4(s.Ks, krow, kcol, f4{x[0] * r.krn, x[1] * r.krn, x[2] * r.krn, x[3] * r.krn});
       }
-      *reinterpret_cast<f4*>(&s.Ks[krow * LD + kcol]) = f4{x[0] * r.krn, x[1] * r.krn, x[2] * r.krn, x[3] * r.krn};
     }
-    if (do_w) *reinterpret_cast<f4*>(&s.Wb[wrow * LT + wcol]) = r.wx;
+    if (do_w) Prod::w_store(s.Whm, s.Wl, wrow, wrow & 15, wcol / 4, r.wx);
     if (do_sm) {
-      // Z and -NQ^T rows are 16 floats in the workspace and LT in LDS
-      if (tid < 64) *reinterpret_cast<f4*>(&s.Zs[(tid / 4) * LT + 4 * (tid % 4)]) = r.sx;
-      else if (tid < 128) *reinterpret_cast<f4*>(&s.NQs[((tid - 64) / 4) * LT + 4 * (tid % 4)]) = r.sx;
+      if (tid < 64) *reinterpret_cast<f4*>(&s.Zs[4 * tid]) = r.sx;
+      else if (!MAP && tid < 128) *reinterpret_cast<f4*>(&s.NQs[MAP ? 0 : 4 * (tid - 64)]) = r.sx;
       else *reinterpret_cast<f4*>(&s.cv[4 * (tid - 128)]) = r.sx;
     }
     if constexpr (kSepC) {
@@ -881,38 +928,44 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 
     if constexpr (!MAP) {
       float x[4];
       r.qx.unpack(x);
-      if (fmap) {
+      if constexpr (!kRawKeys) {
+        if (fmap) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = elu_plus_one(x[i]);
+          for (int i = 0; i < 4; ++i) x[i] = elu_plus_one(x[i]);
+        }
       }
-      *reinterpret_cast<f4*>(&s.Qs[krow * LD + kcol]) = f4{x[0], x[1], x[2], x[3]};
+      Prod::put4(s.Qs, krow, kcol, f4{x[0], x[1], x[2], x[3]});
     }
   };
   auto compute = [&](int blk, const Stage& s, const IO (&vv)[NJV][4]) {
     const int t0 = blk * C;
+    int c = lane & 15, g = lane >> 4;   // opaque: the LDS addresses are formed anew instead of kept in registers
+    asm volatile("" : "+v"(c), "+v"(g));
 #pragma unroll
     for (int jn = 0; jn < NJV; ++jn) {
       if (RECT && !owns(jn)) continue;   // uniform over the wave
-      f4 ft, ot = f4{0, 0, 0, 0};
+      f4 ft = f4{0, 0, 0, 0}, ot = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ft[r] = (!p_run && t0 + 4 * g + r < T) ? -widen(vv[jn][r]) : 0.0f;
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const f4 ka = lds4(&s.Ks[c * LD + 16 * b + 4 * g]);
-        f4 qa;
-        if constexpr (!MAP) qa = lds4(&s.Qs[c * LD + 16 * b + 4 * g]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          ft = mfma16(ka[r], st[jn][b][r], ft);
-          if constexpr (!MAP) ot = mfma16(qa[r], st[jn][b][r], ot);
-        }
+      for (int kb = 0; kb < NB / STEP; ++kb) {
+        const auto sb = Prod::tiles(st[jn][STEP * kb], st[jn][STEP * kb + STEP - 1]);
+        ft = Prod::sweep(Prod::operand(s.Ks, kb, c, g), sb, ft);
+        if constexpr (kTight && NT_KQ > 1) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!MAP) ot = Prod::sweep(Prod::operand(s.Qs, kb, c, g), sb, ot);
+        if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
       }
-      const f4 za = lds4(&s.Zs[c * LT + 4 * g]);
+      f4 rn4 = f4{1, 1, 1, 1};
+      if constexpr (kRawKeys) rn4 = lds4(&s.rn[4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {   // rows past the end: zero
+        const float nv = p_run ? 0.0f : -widen(vv[jn][r]);
+        ft[r] = (t0 + 4 * g + r < T) ? fmaf(ft[r], rn4[r], nv) : 0.0f;
+      }
+      const f4 za = lds4(&s.Zs[c * C + 4 * g]);
       f4 et = f4{0, 0, 0, 0};
 #pragma unroll
       for (int r = 0; r < 4; ++r) et = mfma16(za[r], ft[r], et);
       if constexpr (!MAP) {
-        const f4 nqa = lds4(&s.NQs[c * LT + 4 * g]);
+        const f4 nqa = lds4(&s.NQs[c * C + 4 * g]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) ot = mfma16(nqa[r], et[r], ot);
         if (norm_out) ot *= lds4(&s.cv[C + 4 * g]);
@@ -929,11 +982,11 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), NJV == 1 ? 4 : 
         }
       }
       const f4 ce = et * lds4(&s.cv[4 * g]);
+      const auto cb = Prod::tokens_b(ce);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const f4 wa = lds4(&s.Wb[(16 * b + c) * LT + 4 * g]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) st[jn][b] = mfma16(wa[r], ce[r], st[jn][b]);
+        st[jn][b] = Prod::update(Prod::w_load(s.Whm, s.Wl, 16 * b + c, c, g), cb, st[jn][b]);
+        if (kTight && b % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -999,8 +1052,29 @@ template <int D, int NJV, bool RECT, typename IO, bool MAP>
 hipError_t launch_s_rows_lds_n(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP>),
-                         dim3(a.n_heads * a.n_seg), dim3(64 * (D / 16) * (MAP ? 2 : 1)), params, 0, stream);
+  const long long hs = static_cast<long long>(a.n_heads) * a.n_seg;
+  constexpr int kWps = NJV == 1 ? 4 : 2;   // waves per SIMD that the registers are capped for
+  auto pick = [&](auto nt_tag) -> const void* {
+    constexpr int kNt = decltype(nt_tag)::value;
+    // One workgroup per compute unit at most: twice the registers (nothing in scratch memory, operands read ahead).
+    // 39 heads, d_v = 64, float32, T = 1537 (234 pairs): 0.289 ms against 0.312 with registers for two workgroups.
+    if constexpr (D == 128 && NJV == 1 && !MAP) {
+      if (hs <= 256) return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, true, 2>);
+    }
+    // Three-term operands of d = 64 take 44 KB, three workgroups per compute unit: beyond 768 pairs a last round that
+    // is nearly empty costs float32 calls more than the FP32 products do (33 KB, four workgroups).  16 heads, T = 65536,
+    // 1024 pairs: 1.12 to 1.13 ms against 1.17 with split products here and the maps apart; 24 heads, T = 4096, 384
+    // pairs: 0.208 against 0.190.
+    if constexpr (D == 64 && sizeof(IO) == 4 && !RECT && !MAP) {
+      if (hs > 768) return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, false, kWps>);
+    }
+    return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, true, kWps>);
+  };
+  const void* fn = pick(std::integral_constant<int, 3>{});
+  if constexpr (sizeof(IO) == 2) {   // ELU(x) + 1 of a bf16 number is none
+    if (a.feature_map == 0) fn = pick(std::integral_constant<int, 1>{});
+  }
+  return hipLaunchKernel(fn, dim3(a.n_heads * a.n_seg), dim3(64 * (D / 16) * (MAP ? 2 : 1)), params, 0, stream);
 }
 // Square heads, or (a.d_v != D) value heads of another size: slots per wave = ceil((d_v / 16) / (D / 16)).
 template <int D, typename IO, bool MAP>
@@ -1045,10 +1119,21 @@ hipError_t launch_phases(const ForwardArgs& a, hipStream_t stream) {
   // Worth it once the (head, segment) pairs fill the chip (measured at 16 heads, d = 64: 3 % faster at 1024
   // pairs, 5 % slower at 512 and below, where a block's latency counts and the maps lengthen it).
   const bool rect = a.d_v > 0 && a.d_v != D;   // value heads of another size: the A scan is the same, S has d_v rows
-  const bool fused_map = kFusedMap && !general && !rect && a.n_seg > 1 && hs >= 768;
-  const void* scan_fn = reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, false>);
-  if constexpr (kFusedMap) {
-    if (fused_map) scan_fn = reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, true>);
+  const bool raw_keys = sizeof(IO) == 2 && a.feature_map == 0;   // operands of one term
+  // Mapped bf16 heads of 64: not (16 heads, T = 65536: 1.10 ms with the maps in a pass of their own on split products,
+  // 1.12 ms with the FP32 ones that fit here; float32 input 1.17 and 1.12, d = 32 0.59 and 0.54).
+  const bool own_pass = D == 64 && sizeof(IO) == 2 && !raw_keys;
+  const bool fused_map = kFusedMap && !own_pass && !general && !rect && a.n_seg > 1 && hs >= 768;
+  auto scan_of = [&](auto kt_tag) -> const void* {
+    constexpr int kKt = decltype(kt_tag)::value;
+    if constexpr (kFusedMap) {
+      if (fused_map) return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, true, kKt>);
+    }
+    return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, false, kKt>);
+  };
+  const void* scan_fn = scan_of(std::integral_constant<int, 3>{});
+  if constexpr (sizeof(IO) == 2) {
+    if (raw_keys) scan_fn = scan_of(std::integral_constant<int, 1>{});
   }
   hipError_t err = general ? launch_a_scan_general(a, D, std::is_same<IO, uint16_t>::value ? 1 : 0, stream)
                            : hipLaunchKernel(scan_fn, dim3(static_cast<unsigned>(hs)), dim3(64 * NW), params, 0,

@@ -241,3 +241,36 @@ def test_options_on_value_heads_of_another_size_in_the_time_parallel_mode(dk, dv
         errs["z"] = slab_rel_err(to_np(out[3]), ref["zkey_T"], 1)
     print(dk, dv, optset, errs)
     assert max(errs.values()) <= 1e-4, errs
+
+
+@pytest.mark.parametrize("dtype,feature_map", [("f32", False), ("bf16", False), ("bf16", True)])
+@pytest.mark.parametrize("d,d_v,heads,segments", [
+    (128, 128, 32, 8), (128, 64, 32, 8), (128, 128, 86, 3),     # 256 and 258 (head, segment) pairs
+    (64, 64, 128, 6), (64, 64, 110, 7), (32, 32, 110, 7),       # 768 and 770
+    (64, 128, 40, 4), (96, 64, 40, 4),
+])
+def test_split_and_fp32_products_on_both_sides_of_their_pair_counts(d, d_v, heads, segments, dtype, feature_map):
+    """The pair counts where the S rows and the A scan change kernels, with and without the feature map (one- or
+    three-term operands): a one-token last block, a state over eight orders of magnitude, keys of unequal norms."""
+    import torch
+
+    import paper_2605_11196_amd as vla
+
+    rng = np.random.default_rng(d + heads + segments)
+    T = 16 * segments * 2 - 15
+    q, k = (rng.standard_normal((1, heads, T, d)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+    k *= np.float32(4.0) ** rng.integers(-3, 1 if feature_map else 4, size=(1, heads, T, 1)).astype(np.float32)
+    v *= np.float32(10.0) ** rng.integers(-4, 5, size=(1, heads, 1, 1)).astype(np.float32)
+    S0 = rng.standard_normal((1, heads, d_v, d)).astype(np.float32) * np.abs(v).max(axis=(2, 3), keepdims=True)
+    if dtype == "bf16":
+        q, k, v = (vla_inputs.round_to_bf16(x) for x in (q, k, v))
+    ref = oracle.forward(q, k, v, S0, None, lambda0=0.1, feature_map=feature_map)
+    io = torch.float32 if dtype == "f32" else torch.bfloat16
+    tq, tk, tv = (torch.from_numpy(x).cuda().to(io) for x in (q, k, v))
+    got = vla.vla_forward(tq, tk, tv, torch.from_numpy(S0).cuda(), None, lambda0=0.1, feature_map=feature_map, mode=TP,
+                          segments=segments)
+    for name, x in zip(("o", "S_T", "A_T"), got):
+        err = slab_rel_err(x.float().cpu().numpy(), ref[name], 2)
+        print(d, d_v, heads, segments, dtype, feature_map, name, err)
+        assert err <= TOL[dtype], (name, err)
