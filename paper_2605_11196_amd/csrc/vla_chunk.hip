@@ -1,4 +1,4 @@
-// Block ("chunked") form of the VLA recurrence on FP32 MFMA, 16 tokens per block.
+// Block ("chunked") form of the VLA recurrence on MFMA, 16 tokens per block.
 //
 // Same recurrence as paper Section 3.3 (eq. (sm), eq. (s-update)) and the read-out numerator of
 // eq. (output); within a block of C = 16 tokens the token-by-token matrix-vector work is regrouped

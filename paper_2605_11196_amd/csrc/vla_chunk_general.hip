@@ -1,5 +1,5 @@
 // Block form of the VLA recurrence with the optional lines of Algorithm 1 (paper, pseudocode appendix) on
-// FP32 MFMA: a penalty direction u_t supplied separately from the key (eq. (penalty)), the periodic identity
+// MFMA: a penalty direction u_t supplied separately from the key (eq. (penalty)), the periodic identity
 // refresh A += eta I, the normalised read-out of eq. (output) with its running key sum, and the ELU+1
 // feature map on q and k (Section 3.3).
 //

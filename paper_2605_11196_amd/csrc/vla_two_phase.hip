@@ -718,7 +718,7 @@ hipError_t launch_s_rows(const ForwardArgs& a, hipStream_t stream) {
 //
 // Pipeline, one barrier per block: the data of block n is requested in iteration n - 3 (two register sets),
 // written to LDS stage n % 2 in iteration n - 1 (after that iteration's barrier, which every wave reaches only
-// when it is done reading the stage for block n - 2) and consumed in iteration n.  Registers are capped at 128
+// when it is done reading the stage for block n - 2) and consumed in iteration n.  Registers are capped at 128 (WPS = 4)
 // so that four workgroups (d <= 64) share a compute unit and 1024 (head, segment) pairs run in one round.
 //
 // RECT: value heads of another size than the key heads (S has a.d_v rows, D columns).  The workgroup keeps its
