@@ -409,16 +409,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 
     // ================= phase 2 (wave sw2): c_t, Z, NQ -- the other waves update A meanwhile
     auto update_A = [&]() {
-      decltype(Ops::tokens_b(f4{})) nw[NJ];
-#pragma unroll
-      for (int jn = 0; jn < NJ; ++jn) nw[jn] = Ops::w_neg_b(Whm, Wl, col0 + 16 * jn + c, c, g);
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const auto wa = Ops::w_load(Whm, Wl, 16 * b + c, c, g);
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) At[b][jn] = Ops::update(wa, nw[jn], At[b][jn]);
-        if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two tiles' operands at a time in registers
-      }
+      Ops::template downdate<NB, NJ>(Whm, Wl, col0 + c, c, g, blk & 1, [&](int b, int jn) -> f4& { return At[b][jn]; });
     };
     if (w != sw2) {
       prio<kLevels, 0, -1>();

@@ -527,16 +527,7 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
 
     // ================= phase 2 (wave sw2): c_t, Z, NQ, read-out denominators -- the others update A
     auto update_A = [&]() {
-      decltype(Ops::tokens_b(f4{})) nw[NJ];
-#pragma unroll
-      for (int jn = 0; jn < NJ; ++jn) nw[jn] = Ops::w_neg_b(Whm, Wl, col0 + 16 * jn + c, c, g);
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const auto wa = Ops::w_load(Whm, Wl, 16 * b + c, c, g);
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) At[jn][b] = Ops::update(wa, nw[jn], At[jn][b]);
-        if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two tiles' operands at a time in registers
-      }
+      Ops::template downdate<NB, NJ>(Whm, Wl, col0 + c, c, g, blk & 1, [&](int b, int jn) -> f4& { return At[jn][b]; });
       if (FULL && period > 0) {  // + eta n on the diagonal (row 16b + 4g + r against column col0 + 16jn + c), n counted
         const float en_end = en[len];  // over the live tokens
 #pragma unroll

@@ -459,15 +459,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     __syncthreads();  // (4)
 
     // ---- A -= W W^T
-    decltype(Prod::tokens_b(f4{})) nw[NJ];
-#pragma unroll
-    for (int jn = 0; jn < NJ; ++jn) nw[jn] = Prod::w_neg_b(Whm[cp], Wl[cp], col0 + 16 * jn + c, c, g);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const auto wa = Prod::w_load(Whm[cp], Wl[cp], 16 * b + c, c, g);
-#pragma unroll
-      for (int jn = 0; jn < NJ; ++jn) At[b][jn] = Prod::update(wa, nw[jn], At[b][jn]);
-    }
+    Prod::template downdate<NB, NJ>(Whm[cp], Wl[cp], col0 + c, c, g, pb, [&](int b, int jn) -> f4& { return At[b][jn]; });
   }
   // c, Z, NQ of the last block: everything it needs was written before the last barrier
   if (it > 0 && w == it % NW) cz_pass((it - 1) & 1, SMp + static_cast<size_t>(blk - 1) * SMB);
