@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   __shared__ __align__(16) float NQs[C * LT];         // -NQ^T [t][s]
   __shared__ __align__(16) float wn2p[NW][C];         // per-wave partial ||w_t||^2
   __shared__ __align__(16) float cvec[C];             // -c_t
-  __shared__ __align__(16) float rns[2][C];           // 1 / max(||k_t||, eps)
+  __shared__ __align__(16) float rns[2][C];           // 1 / max(||k_t||, eps) over its power of two (key_scale)
   static_assert(C * LDY <= 2 * C * LT, "a slab of Y^T fits the wave's Gram tiles");
 
   const int head = blockIdx.x;
@@ -224,12 +224,11 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     float rn = __builtin_amdgcn_rsqf(sm);
     rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f);
     if (!stager) return;
-    if constexpr (!kSplit) {   // FP32 products take the normalised keys themselves
+    // FP32 products take the normalised keys themselves
+    const KeyScale ks = kSplit ? key_scale(rn) : KeyScale{rn, 1.0f};
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) kx[e] *= rn;
-      rn = 1.0f;
-    }
-    if (sseg == 0) rns[buf][srow] = rn;
+    for (int e = 0; e < EPT; ++e) kx[e] *= ks.pow2;
+    if (sseg == 0) rns[buf][srow] = ks.rest;
 #pragma unroll
     for (int e = 0; e < EPT; e += 4) Ops::put4(Ksb[buf], srow, sseg + e, f4{kx[e], kx[e + 1], kx[e + 2], kx[e + 3]});
     float qx[EPT];

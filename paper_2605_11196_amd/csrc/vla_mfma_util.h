@@ -90,6 +90,14 @@ __device__ __forceinline__ void split3_rne(f4 x, u2& h, u2& m, u2& l) {
     l[p] = pack_rne(s0, s1);
   }
 }
+// Keys that enter the products before they are normalised are staged as k 2^e, and the results multiplied by the rest of
+// 1 / max(||k||, eps) = 2^e rest, 1 <= rest < 2: k 2^e is still a bf16 (float32) number and at most 1, so that a product
+// with the state stays in range wherever k^ does (||k|| = 1e13 against a state of 1e28).
+struct KeyScale { float pow2, rest; };
+__device__ __forceinline__ KeyScale key_scale(float rn) {   // rn = 0 (no key): 0 and 0; NaN: rest NaN
+  const uint32_t p = __float_as_uint(rn) & 0x7f800000u;
+  return KeyScale{__uint_as_float(p), rn * __uint_as_float(0x7f000000u - p)};
+}
 __device__ __forceinline__ u4 cat(u2 a, u2 b) { return u4{a[0], a[1], b[0], b[1]}; }
 
 // One operand of 32 columns: the NT = 1 (exact bf16 numbers) or 3 (h, m, l) terms.

@@ -37,9 +37,10 @@ namespace {
 // The 2 d/16 row slabs of 16 rows are dealt out over the waves.
 //
 // Products with A, S and W: split bf16 terms (vla_mfma_util.h); W is split once, as it is formed.  KT = 1: bf16 keys
-// and queries without a feature map are staged as they are, and 1 / ||k|| goes on the rows and columns of the results;
-// KT = 3 otherwise (terms of k^ and q).  With MAPF and KT = 3 the products stay on the FP32 instruction: two copies of
-// three-term keys would leave three instead of four workgroups per compute unit, and without MAPF the maps cost a pass.
+// and queries without a feature map are staged as they are (keys times a power of two, key_scale), and the rest of
+// 1 / ||k|| goes on the rows and columns of the results; KT = 3 otherwise (terms of k^ and q).  With MAPF and KT = 3 the
+// products stay on the FP32 instruction: two copies of three-term keys would leave three instead of four workgroups per
+// compute unit, and without MAPF the maps cost a pass.
 // Bound by the block's serial chain and, with the maps, the matrix pipes.  16 heads of 64, bf16, T = 131072, whole call,
 // with the S rows below already on split products: 1.89 ms with FP32 products here, 1.63 split; heads of 128,
 // T = 32768: 1.49 and 1.38.
@@ -72,12 +73,12 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   static_assert(EPT % 4 == 0 && TPR <= 16 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
-  __shared__ __align__(16) uint16_t Ksb[NKB][Prod::SIZE];   // terms of K^ (of k as it is: kRawKeys)
+  __shared__ __align__(16) uint16_t Ksb[NKB][Prod::SIZE];   // terms of K^ (of k times a power of two: kRawKeys)
   __shared__ __align__(16) uint16_t Qs[Prod::SIZE];
   __shared__ __align__(16) float Ysb[NW][C * LDY];           // Y^T [t][j], a slab per wave, which no other wave reads
   __shared__ __align__(16) u4 Whm[NKB][4 * D];               // W [j][t], split
   __shared__ __align__(16) u2 Wl[NKB][kSplit ? 4 * D : 1];
-  __shared__ __align__(16) float rns[2][C];                  // 1 / max(||k_t||, eps) (kRawKeys)
+  __shared__ __align__(16) float rns[2][C];                  // 1 / max(||k_t||, eps) over its power of two (kRawKeys)
   __shared__ __align__(16) float Gp[NW][2][C * LT];
   // MAPF: Z [t][s] and -c of the previous block live in Y^T's array, which is dead between barrier (2) of a block
   // and the first barrier of the next one: exactly the window in which they are written and read (four
@@ -308,8 +309,9 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f);
       if (stager) {
         if (sseg == 0) RN[t0 + srow] = live ? rn : 0.0f;   // rows past the end: zero keys
-        if (kRawKeys && sseg == 0) rns[pb][srow] = rn;
-        const float ks = kRawKeys ? 1.0f : rn;
+        const KeyScale sc = kRawKeys ? key_scale(rn) : KeyScale{rn, 1.0f};
+        if (kRawKeys && sseg == 0) rns[pb][srow] = sc.rest;
+        const float ks = sc.pow2;
 #pragma unroll
         for (int e = 0; e < EPT; e += 4)
           Prod::put4(Ks, srow, sseg + e, f4{kx[e] * ks, kx[e + 1] * ks, kx[e + 2] * ks, kx[e + 3] * ks});
@@ -720,8 +722,9 @@ hipError_t launch_s_rows(const ForwardArgs& a, hipStream_t stream) {
 //
 // Products with S and W: split bf16 terms (vla_mfma_util.h), since the FP32 matrix instruction was what bounded the
 // kernel (68 % of its time).  W is split once per block as it is staged; S as it is read.  NT = 1: bf16 keys and
-// queries without a feature map go in as they are, 1 / ||k|| is applied to the residual; otherwise (float32, or
-// ELU(x) + 1) three terms of k^ and q.  Z and NQ stay FP32 products: 16 x 16, and in the block's serial chain.
+// queries without a feature map go in as they are (keys times a power of two, key_scale), the rest of 1 / ||k|| is
+// applied to the residual; otherwise (float32, or ELU(x) + 1) three terms of k^ and q.  Z and NQ stay FP32 products:
+// 16 x 16, and in the block's serial chain.
 // The Z and NQ rows are unpadded (a wave reads all 1 KB of one in a row, no bank twice): so two workgroups of d = 128
 // with three-term operands fit a compute unit (81 KB each).
 // Whole calls, bf16, FP32 products against these (the A scan on FP32 ones in both): 16 heads of 128, T = 32768: 1.83
@@ -743,14 +746,14 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), WPS) s_rows_lds
   static_assert(NT == (MAP ? 2 * CH : CH), "one piece of each big operand per thread");
   constexpr int NST = 2;
   struct Stage {
-    uint16_t Ks[Prod::SIZE];             // terms of K^ [t][j] (of k as it is: kRawKeys)
+    uint16_t Ks[Prod::SIZE];             // terms of K^ [t][j] (of k times a power of two: kRawKeys)
     uint16_t Qs[MAP ? 8 : Prod::SIZE];   // terms of q  [t][j]
     u4 Whm[4 * D];                       // W  [j][t], split
     u2 Wl[kSplit ? 4 * D : 1];
     float Zs[C * C];                     // Z  [t][s]
     float NQs[MAP ? 4 : C * C];          // -NQ^T [t][s]
     float cv[2 * C];       // -c_t, then 1 / max(q_t . zkey_t, eps) (normalised read-out only)
-    float rn[C];           // 1 / max(||k_t||, eps), 0 past the end (kRawKeys)
+    float rn[C];           // 1 / max(||k_t||, eps) over its power of two, 0 past the end (kRawKeys)
   };
   __shared__ __align__(16) Stage stg[NST];
 
@@ -898,8 +901,9 @@ __global__ void __launch_bounds__(64 * (D / 16) * (MAP ? 2 : 1), WPS) s_rows_lds
       float x[4];
       r.kx.unpack(x);
       if constexpr (kRawKeys) {
-        if (kcol == 0) s.rn[krow] = r.krn;
-        Prod::put4(s.Ks, krow, kcol, f4{x[0], x[1], x[2], x[3]});
+        const KeyScale sc = key_scale(r.krn);
+        if (kcol == 0) s.rn[krow] = sc.rest;
+        Prod::put4(s.Ks, krow, kcol, f4{x[0] * sc.pow2, x[1] * sc.pow2, x[2] * sc.pow2, x[3] * sc.pow2});
       } else {   // k^ = k / max(||k||, eps): the same product the A scan formed it with
         if (fmap) {
 #pragma unroll
