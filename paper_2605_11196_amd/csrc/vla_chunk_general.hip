@@ -86,12 +86,12 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
   static_assert(DV % 16 == 0 && (!SCAN || DV == D), "whole tiles of S");
   constexpr int NB = D / 16;       // 16-row blocks over the head dimension
   // Staging: a token row is split over thread slots of EPT elements.  At the power-of-two head sizes every
-  // thread stages 4 or 8 elements; at d = 96 a row takes 12 threads of 8 elements in a group of 16, or 6 of 16 in a
-  // group of 8 (the other lanes of the group and the last waves stage nothing), so that a row sums with a
-  // power-of-two shuffle.
+  // thread stages 4 or 8 elements; at d = 96 a row takes 12 threads of 8 elements in a group of 16 (the other four
+  // lanes of the group and the last two waves stage nothing), so that a row sums with a power-of-two shuffle.
   constexpr bool PADDED = (D & (D - 1)) != 0;
-  constexpr int EPT = (PADDED ? 8 : 4) * NJ;         // staged elements per thread per tensor
-  constexpr int TPR = PADDED ? 16 / NJ : D / EPT;    // thread slots per token row (inside one wave)
+  static_assert(!PADDED || NJ == 1, "d = 96: waves of 16 columns");
+  constexpr int EPT = PADDED ? 8 : 4 * NJ;      // staged elements per thread per tensor
+  constexpr int TPR = PADDED ? 16 : D / EPT;    // thread slots per token row (inside one wave)
   static_assert(D % EPT == 0 && D / EPT <= TPR && C * TPR <= 64 * NW, "staging layout");
   // Y = X: the Gram matrices that differ only in u against k^ coincide
   constexpr int iGK = FULL ? kGK : kG;
@@ -736,20 +736,33 @@ hipError_t launch_dv(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t st
   }
 }
 // phase 1 of the two-phase and time-parallel modes with options: one workgroup per (head, segment)
-template <int D, typename IO>
-hipError_t launch_scan(const ForwardArgs& a, hipStream_t stream) {
+template <int D, typename IO, bool FULL>
+hipError_t launch_scan_full(const ForwardArgs& a, hipStream_t stream) {
   constexpr int SL = 16;
-  // 16 heads, normalised read-out, single / double buffers: d = 64, T = 16384 0.448 / 0.418 ms, d = 128, T = 8192
-  // 0.668 / 0.643; d = 32, T = 16384 0.22 / 0.21 with and without u 0.239 / 0.28
-  constexpr bool kScanDB = D >= 64;
-  ForwardArgs args = a;
-  void* params[] = {&args};
-  const bool full = a.u != nullptr || a.refresh_period > 0;
-  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, true, true, kScanDB>)
-                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, false, true, kScanDB>);
   const long long wgs = static_cast<long long>(a.n_heads) * a.n_seg;
   if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
+  // Double buffers shorten the block, single ones (31 KB, with u, at d = 32; 48 at 64) let more workgroups share a
+  // compute unit's LDS: double up to the (head, segment) pairs that are resident with them in one round (with u and
+  // without: d = 32 768 and 1024, d = 64 512 and 768; from d = 96 two workgroups without u, measured better single, and
+  // one either way with u).  Whole calls, 16 heads, bf16, single / double, ms:
+  //   d = 64, T = 131072, 768 pairs: u and normalised read-out 2.65 / 3.34, normalised read-out 2.46 / 2.33;
+  //           T = 16384, 512 pairs: 0.438 / 0.420 and 0.399 / 0.379
+  //   d = 32, T = 16384, 1024 pairs: 0.221 / 0.268 and 0.205 / 0.195;  T = 4096, 256 pairs: 0.147 / 0.136
+  //   d = 96, T = 32768, 512 pairs: 1.73 / 1.69 and 1.28 / 1.51;  d = 128: 2.08 / 2.02 and 1.65 / 1.86
+  constexpr bool kAlways = FULL && D >= 96;
+  constexpr int kMostDB = D >= 96 ? 256 : (D == 64 ? (FULL ? 512 : 768) : (FULL ? 768 : 1024));
+  const void* fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, true>);
+  if constexpr (!kAlways) {
+    if (wgs > kMostDB) fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, false>);
+  }
+  ForwardArgs args = a;
+  void* params[] = {&args};
   return hipLaunchKernel(fn, dim3(static_cast<unsigned>(wgs)), dim3(64 * D / SL), params, 0, stream);
+}
+template <int D, typename IO>
+hipError_t launch_scan(const ForwardArgs& a, hipStream_t stream) {
+  return a.u != nullptr || a.refresh_period > 0 ? launch_scan_full<D, IO, true>(a, stream)
+                                                : launch_scan_full<D, IO, false>(a, stream);
 }
 
 }  // namespace

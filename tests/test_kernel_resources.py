@@ -55,3 +55,14 @@ def test_float32_io_kernels_stay_within_their_known_spills(chunk_usage):
 def test_headline_kernel_fits_two_workgroups_per_compute_unit(chunk_usage):
     r = chunk_usage[(128, 128, "bf16", False)]
     assert 2 * r["LDSSize"] <= 160 * 1024
+
+
+@pytest.mark.parametrize("io", ["short", "float"])
+def test_option_a_chain_leaves_room_for_the_workgroups_of_a_segment_plan(io):
+    """Heads of 64 with options are planned as 768 (head, segment) pairs, one round of three workgroups per compute unit:
+    single buffers with a separate u (two sweeps), double ones without."""
+    use = build.resource_usage(os.path.join(CSRC, "vla_chunk_general.hip"))
+    for full, double in (("true", "false"), ("false", "true")):
+        hits = [r for name, r in use.items() if re.search(
+            rf"chunk_general_kernel<64, 64, 16, [\w ]*{io}, {full}, true, {double}>", name)]
+        assert hits and 3 * hits[0]["LDSSize"] <= 160 * 1024 and hits[0]["Occupancy"] >= 3, (full, hits)
