@@ -46,10 +46,12 @@ __device__ __forceinline__ void prio() {
   else if constexpr (LEVELS == 1 && CHAIN >= 0) __builtin_amdgcn_s_setprio(CHAIN);
 }
 
+// SPLIT: products on split bf16 terms, else on the FP32 matrix instruction (d = 16, and where that saves a round of
+// workgroups: fp32_products below).
 // FMAP: q and k are replaced by ELU(x) + 1 while they are staged (the feature map of Section 3.3).
 // DV: head size of v and o (rows of S); the wave that owns columns [SL w, SL w + SL) of A owns rows
 // [SLV w, SLV w + SLV) of S.
-template <int D, int DV, int NW, typename IO, bool FMAP>
+template <int D, int DV, int NW, typename IO, bool FMAP, bool SPLIT>
 __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   // Measured at 2048 heads, T = 8192: the full scheme gains 5 % with four waves (d = 128), 1 % with three (d = 96),
   // 1-5 % with one (d = 16, 32); two-wave workgroups (d = 64), four of which share a compute unit, lose up to
@@ -65,11 +67,12 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   constexpr int NJV = kEven ? TV / NW : (TV + NW - 1) / NW;   // tile slots per wave
   static_assert(DV % 16 == 0 && NJV >= 1, "whole tiles of S");
   constexpr int NB = D / 16;       // 16-row blocks over the whole head dimension
-  constexpr int NKB = (NB + 1) / 2;   // 32-column steps of a contraction over the head dimension
-  constexpr bool kSplit = D > 16;
   // operand terms of k and q: bf16 numbers are exact in one, float32 ones (and mapped ones) take three
-  constexpr int KT = (sizeof(IO) == 2 && !FMAP) || !kSplit ? 1 : 3;
-  using Ops = BlockOps<kSplit, KT, D>;
+  constexpr int KT = (sizeof(IO) == 2 && !FMAP) || !SPLIT ? 1 : 3;
+  using Ops = BlockOps<SPLIT, KT, D>;
+  constexpr int STEP = Ops::STEP;
+  constexpr int NKB = NB / STEP;      // steps of a contraction over the head dimension
+  static_assert(NB % STEP == 0, "whole steps");
   constexpr int LDY = SL + 4;         // row stride of a wave's slab of Y^T
   constexpr int NT = 64 * NW;
   // Staging: a token row is split over TPR threads of EPT elements each.  For the power-of-two head sizes every
@@ -117,6 +120,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     }
   };
   auto owns = [&](int jn) -> bool { return kEven || w + NW * jn < TV; };
+  const bool has_rows = TV >= NW || w < TV;   // uniform in a wave: one without a tile leaves S to the others
 
   // ---- resident state: accumulator tiles
   // At[b][jn][r] = A[16b + 4g + r][col0 + 16jn + c]
@@ -225,7 +229,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f);
     if (!stager) return;
     // FP32 products take the normalised keys themselves
-    const KeyScale ks = kSplit ? key_scale(rn) : KeyScale{rn, 1.0f};
+    const KeyScale ks = SPLIT ? key_scale(rn) : KeyScale{rn, 1.0f};
 #pragma unroll
     for (int e = 0; e < EPT; ++e) kx[e] *= ks.pow2;
     if (sseg == 0) rns[buf][srow] = ks.rest;
@@ -274,7 +278,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
         const Terms<KT> ka = Ops::operand(Ks, kb, c, g);
 #pragma unroll
         for (int jn = 0; jn < NJ; ++jn)
-          yt[jn] = Ops::sweep(ka, Ops::tiles(At[2 * kb][jn], At[kSplit ? 2 * kb + 1 : 0][jn]), yt[jn]);
+          yt[jn] = Ops::sweep(ka, Ops::tiles(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
         if (KT > 1) __builtin_amdgcn_sched_barrier(0);
       }
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
@@ -289,15 +293,26 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) Yw[(4 * g + r) * LDY + 16 * jn + c] = yt[jn][r];
       // same-wave write -> read: LDS operations of one wave are ordered
-      const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
-      const f4 zero{0, 0, 0, 0};
-      // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
-      f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + 16 + 4 * g]) : zero;
-      if (NJ == 1 && kSplit && (w & 1)) y1 = y0;
-      const auto ya = Ops::tiles(NJ == 1 && kSplit && (w & 1) ? zero : y0, y1);
       // G[s][t], GQ[s][t] come out with t on the rows of the accumulator
-      const f4 gg = Ops::sweep(Ops::operand(Ks, col0 / 32, c, g), ya, zero);
-      const f4 gq = Ops::sweep(Ops::operand(Qs, col0 / 32, c, g), ya, zero);
+      f4 gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
+      if constexpr (SPLIT) {
+        // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
+        const f4 zero{0, 0, 0, 0};
+        const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
+        const f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + (NJ > 1 ? 16 : 0) + 4 * g]) : (w & 1) ? y0 : zero;
+        const auto ya = Ops::tiles(NJ == 1 && (w & 1) ? zero : y0, y1);
+        gg = Ops::sweep(Ops::operand(Ks, col0 / 32, c, g), ya, gg);
+        gq = Ops::sweep(Ops::operand(Qs, col0 / 32, c, g), ya, gq);
+      } else {
+        f4 y[NJ];   // all of the slab before the Gram tiles take its place
+#pragma unroll
+        for (int jn = 0; jn < NJ; ++jn) y[jn] = lds4(&Yw[c * LDY + 16 * jn + 4 * g]);
+#pragma unroll
+        for (int jn = 0; jn < NJ; ++jn) {
+          gg = Ops::sweep(Ops::operand(Ks, col0 / 16 + jn, c, g), y[jn], gg);
+          gq = Ops::sweep(Ops::operand(Qs, col0 / 16 + jn, c, g), y[jn], gq);
+        }
+      }
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) Gp[w][0][c * LT + 4 * g + r] = gg[r] * rn4[r];
@@ -318,17 +333,18 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // after barrier (5), so it fills the serial windows
     f4 ft[NJV], ot[NJV];
     auto s_pass = [&]() {
+      if (!has_rows) return;
 #pragma unroll
       for (int jn = 0; jn < NJV; ++jn) ft[jn] = ot[jn] = f4{0, 0, 0, 0};
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJV; ++jn) {
-          const auto sb = Ops::tiles(St[2 * kb][jn], St[kSplit ? 2 * kb + 1 : 0][jn]);
+          const auto sb = Ops::tiles(St[STEP * kb][jn], St[STEP * kb + STEP - 1][jn]);
           ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
-          if (KT > 1) __builtin_amdgcn_sched_barrier(0);
+          if constexpr (KT > 1) __builtin_amdgcn_sched_barrier(0);
           ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
-          __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
+          if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
         }
       }
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
@@ -468,6 +484,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     }
     __syncthreads();  // (5) Z, NQ, c visible
 
+    if (has_rows) {
     // ================= -E^T = Z (-F^T), R^T = Q S0^T, O^T = R^T + (-NQ^T)(-E^T), store o;
     // ce = (-c) (-E^T) = diag(c) E^T
     decltype(Ops::tokens_b(f4{})) ce[NJV];
@@ -514,6 +531,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       for (int jn = 0; jn < NJV; ++jn) St[b][jn] = Ops::update(wa, ce[jn], St[b][jn]);
       if (b % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
+    }
     if (w == sw2) update_A();
   }
 
@@ -544,56 +562,112 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   }
 }
 
-template <int D, int DV, int NW, typename IO>
+template <int D, int DV, int NW, typename IO, bool SPLIT>
 hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
-  const void* fn = a.feature_map ? reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, true>)
-                                 : reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, false>);
+  const void* fn = reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, true, SPLIT>);
+  // products on the FP32 instruction are for three-term operands only (d = 16 has no others)
+  if constexpr (SPLIT || D == 16 || sizeof(IO) == 4) {
+    if (a.feature_map == 0) fn = reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, false, SPLIT>);
+  }
   return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * NW), params, 0, stream);
 }
+// bf16 q and k without the feature map
 template <int D, int DV, int NW>
+hipError_t launch_one_term(const ForwardArgs& a, hipStream_t stream) {
+  ForwardArgs args = a;
+  void* params[] = {&args};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, uint16_t, false, true>), dim3(a.n_heads),
+                         dim3(64 * NW), params, 0, stream);
+}
+template <int D, int DV, int NW, bool SPLIT = (D > 16)>
 hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
-  return io_dtype == 1 ? launch<D, DV, NW, uint16_t>(a, stream) : launch<D, DV, NW, float>(a, stream);
+  return io_dtype == 1 ? launch<D, DV, NW, uint16_t, SPLIT>(a, stream) : launch<D, DV, NW, float, SPLIT>(a, stream);
 }
 
 }  // namespace
 
 bool chunk_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }
 
-// Waves per head.  A wave that owns 16 columns instead of 32 has half the splits and products between two serial
-// sections but as much of everything else, so it pays while it runs on a SIMD that would be idle: as long as the
-// narrow workgroups are resident in one round.  T = 512, wide / narrow waves in ms, bf16 and float32 q, k, v:
+// Which kernel a call takes follows from the operand terms of k and q and not from the I/O type: one term for bf16
+// numbers, three for float32 ones and for ELU(x) + 1 of either.  Three terms of K^ and Q, double-buffered, decide how
+// many workgroups share a compute unit's LDS.  All times below: T = 512, ms.
+static int operand_terms(const ForwardArgs& a, int io_dtype) { return io_dtype == 1 && a.feature_map == 0 ? 1 : 3; }
+static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) / resident; }
+
+// Waves of 16 columns instead of 32?  Such a wave has half the splits and products between two serial sections but as
+// much of everything else, so it pays while it runs on a SIMD that would be idle: as long as the narrow workgroups are
+// resident in one round.  Wide / narrow waves, one term and three terms:
 //   d = 128 (4 / 8 waves): 256 heads 0.229 / 0.203 and 0.304 / 0.230, 512 heads 0.302 / 0.396 and 0.388 / 0.458
+//     d_v = 64: 256 heads 0.190 / 0.171 and 0.229 / 0.198, 512 heads 0.226 / 0.336 and 0.276 / 0.406
 //   d =  96 (3 / 6 waves): 256 heads 0.192 / 0.162 and 0.256 / 0.197, 512 heads 0.237 / 0.306 and 0.308 / 0.379
-//   d =  64 (2 / 4 waves): 768 heads 0.198 / 0.178 and 0.235 / 0.200, 1024 heads 0.212 / 0.307 and 0.422 / 0.361
-//   d =  32 (1 / 2 waves): 768 heads 0.138 / 0.133 and 0.156 / 0.138, 1024 heads 0.140 / 0.144 and 0.154 / 0.149
-//   d =  64, float32: 1536 heads 0.461 / 0.401, 2048: 0.656 / 0.554, 4096: 1.20 / 1.09 (three wide workgroups share a
-//                     compute unit's LDS, three narrow ones too)
-static bool narrow_waves(int d, int n_heads, int io_dtype) {
-  if (d == 64 && io_dtype == 0) return true;
-  return d >= 32 && n_heads <= (d >= 96 ? 256 : 768);
+//     d_v = 128: 512 heads 0.354 / 0.402 and 0.524 / 0.504, 2048 heads 1.42 / 1.60 and 2.07 / 2.01, mapped (one more
+//     pass over the staged rows, on two of three or three of six waves) 0.525 / 0.535 and, bf16, 0.462 / 0.551
+//   d =  64 (2 / 4 waves): 768 heads 0.198 / 0.178 and 0.235 / 0.206, 1024 heads 0.212 / 0.307 and 0.415 / 0.357,
+//                          2048 heads (three terms) 0.694 / 0.561
+//     d_v = 96: 768 heads 0.234 / 0.217 and 0.280 / 0.264, 1024 heads 0.249 / 0.372 and 0.504 / 0.432
+//   d =  32 (1 / 2 waves): 768 heads 0.138 / 0.133 and 0.151 / 0.134, 1024 heads 0.140 / 0.144 and 0.151 / 0.145,
+//                          1536 heads (three terms) 0.196 / 0.262
+//     d_v = 64: 1024 heads 0.162 / 0.153 and 0.183 / 0.165, 1280 heads (three terms) 0.240 / 0.217, 1536: 0.242 / 0.304,
+//               3072: 0.479 / 0.514, 2048 heads (one term) 0.223 / 0.318
+//     d_v = 128: 1024 heads 0.713 / 0.195 (the wide wave's slab of S does not fit its registers)
+static bool narrow_waves(int d_k, int d_v, int n_heads, int terms, bool mapped) {
+  switch (d_k) {
+    case 128: return n_heads <= 256;
+    case 96: return n_heads <= 256 || (d_v > 96 && terms == 3 && !mapped);
+    case 64: return n_heads <= 768 || terms == 3;
+    case 32:
+      if (d_v >= 96) return true;
+      if (d_v == 64) return terms == 3 ? rounds(n_heads, 1280) <= rounds(n_heads, 1536) : n_heads <= 1024;
+      return n_heads <= (terms == 3 ? 1024 : 768);
+    default: return false;
+  }
 }
 
-// Several heads per workgroup (vla_chunk_multihead.hip) or one?  With bf16 q, k, v one (the split products leave the
-// vector ALU free for the other heads' serial sections).  With float32 ones, T = 512, one head / several heads per workgroup in ms:
-//   d = 64: 1024 heads 0.361 / 0.283, 1536: 0.401 / 0.554, 2048: 0.576 / 0.562, 4096: 1.09 / 1.11
-//   d = 32: 1024 heads 0.149 / 0.161, 1536: 0.196 / 0.221, 2048: 0.321 / 0.226, 4096: 0.551 / 0.443
-bool prefer_multihead(int d, int n_heads) {
-  if (d == 32) return n_heads > 1536;
-  if (d == 64) return n_heads > 768 && n_heads <= 1024;
+// Three-term operands leave three workgroups of d = 64 and six of d = 32 (wide waves) a compute unit, FP32 products four
+// and eight: those win where they save a round.  Square heads then take several heads per workgroup
+// (vla_chunk_multihead.hip), others products on the FP32 instruction here.  float32, split / several heads:
+//   d = 64: 768 heads 0.206 / 0.278, 1024: 0.357 / 0.280, 1536: 0.398 / 0.552, 2048: 0.561 / 0.563, 3072: 0.790 / 0.837
+//           (with the feature map, bf16: 1024: 0.363 / 0.273, 2048: 0.589 / 0.547, 3072: 0.797 / 0.824)
+//   d = 32: 1024 heads 0.145 / 0.160, 1536: 0.196 / 0.219, 2048: 0.320 / 0.222, 3072: 0.385 / 0.431, 4096: 0.560 / 0.441
+// and, split / FP32 products here:
+//   64 x 16: 768 heads 0.166 / 0.198, 1024: 0.310 / 0.212, 2048: 0.475 / 0.524    64 x 32: 1024: 0.327 / 0.237, 2048: 0.510 / 0.576
+//   64 x 96: 769 heads 0.385 / 0.351, 1024: 0.432 / 0.366      64 x 128: 769 heads 0.384 / 0.413, 896: 0.426 / 0.430, 1024: 0.458 / 0.431
+//   32 x 16: 2048 heads 0.308 / 0.191    32 x 64: 1536 heads 0.242 / 0.276, 2048: 0.370 / 0.282, 3072: 0.479 / 0.542, 4096: 0.658 / 0.551
+static bool fewer_rounds_unsplit(int d_k, int n_heads) {
+  if (d_k == 32) return rounds(n_heads, 2048) < rounds(n_heads, 1536);
+  if (d_k == 64) return 11 * rounds(n_heads, 1024) < 8 * rounds(n_heads, 768);   // a round of each: 0.28 and 0.20 ms
   return false;
 }
+static bool fp32_products(int d_k, int d_v, int n_heads) {
+  if (d_v == d_k) return false;
+  if (d_k == 64) return n_heads > (d_v == 128 ? 896 : 768) && n_heads <= 1024;
+  return d_v <= 64 && fewer_rounds_unsplit(d_k, n_heads);
+}
 
-// The d_k / 32 waves of a head (one below d_k = 32) share out the d_v / 16 row tiles of S, evenly where the counts
-// divide and one by one in turn where they do not: every pair of head sizes runs.
+// The waves of a head share out the d_v / 16 row tiles of S, evenly where the counts divide and one by one in turn where
+// they do not: every pair of head sizes runs.
 bool chunk_supported(int d_k, int d_v) { return chunk_supported(d_k) && chunk_supported(d_v); }
 
 hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream) {
-  if (d_k == d_v && io_dtype == 0 && prefer_multihead(d_k, a.n_heads)) return launch_chunk_multihead(a, d_k, io_dtype, stream);
-  if (narrow_waves(d_k, a.n_heads, io_dtype)) {
+  const int terms = operand_terms(a, io_dtype);
+  if (terms == 3 && d_k == d_v && fewer_rounds_unsplit(d_k, a.n_heads)) return launch_chunk_multihead(a, d_k, io_dtype, stream);
+  if (terms == 3 && fp32_products(d_k, d_v, a.n_heads)) {
+    switch (d_k * 1000 + d_v) {
+      case 32016: return launch_io<32, 16, 1, false>(a, io_dtype, stream);
+      case 32064: return launch_io<32, 64, 1, false>(a, io_dtype, stream);
+      case 64016: return launch_io<64, 16, 2, false>(a, io_dtype, stream);
+      case 64032: return launch_io<64, 32, 2, false>(a, io_dtype, stream);
+      case 64096: return launch_io<64, 96, 2, false>(a, io_dtype, stream);
+      case 64128: return launch_io<64, 128, 2, false>(a, io_dtype, stream);
+      default: break;
+    }
+  }
+  if (narrow_waves(d_k, d_v, a.n_heads, terms, a.feature_map != 0)) {
     switch (d_k * 1000 + d_v) {
       case 32032: return launch_io<32, 32, 2>(a, io_dtype, stream);
+      case 32016: return launch_io<32, 16, 2>(a, io_dtype, stream);
       case 64016: return launch_io<64, 16, 4>(a, io_dtype, stream);
       case 64032: return launch_io<64, 32, 4>(a, io_dtype, stream);
       case 64064: return launch_io<64, 64, 4>(a, io_dtype, stream);
@@ -601,33 +675,41 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
       case 96032: return launch_io<96, 32, 6>(a, io_dtype, stream);
       case 96064: return launch_io<96, 64, 6>(a, io_dtype, stream);
       case 96096: return launch_io<96, 96, 6>(a, io_dtype, stream);
+      case 128016: return launch_io<128, 16, 8>(a, io_dtype, stream);
+      case 128032: return launch_io<128, 32, 8>(a, io_dtype, stream);
+      case 128064: return launch_io<128, 64, 8>(a, io_dtype, stream);
+      case 128096: return launch_io<128, 96, 8>(a, io_dtype, stream);
       case 128128: return launch_io<128, 128, 8>(a, io_dtype, stream);
-      default: break;   // d_v > d_k: narrow waves at every count, below
+      case 32064: return launch_io<32, 64, 2>(a, io_dtype, stream);
+      case 32096: return launch_io<32, 96, 2>(a, io_dtype, stream);
+      case 32128: return launch_io<32, 128, 2>(a, io_dtype, stream);
+      case 64096: return launch_io<64, 96, 4>(a, io_dtype, stream);
+      case 64128: return launch_io<64, 128, 4>(a, io_dtype, stream);
+      case 96128: return launch_io<96, 128, 6>(a, io_dtype, stream);
+      default: break;
     }
   }
-  switch (d_k * 1000 + d_v) {
+  switch (d_k * 1000 + d_v) {   // d_k = 64: one term only, see narrow_waves
     case 16016: return launch_io<16, 16, 1>(a, io_dtype, stream);
     case 32032: return launch_io<32, 32, 1>(a, io_dtype, stream);
-    case 64064: return launch_io<64, 64, 2>(a, io_dtype, stream);
+    case 64064: return launch_one_term<64, 64, 2>(a, stream);
     case 96096: return launch_io<96, 96, 3>(a, io_dtype, stream);
     case 128128: return launch_io<128, 128, 4>(a, io_dtype, stream);
     case 16032: return launch_io<16, 32, 1>(a, io_dtype, stream);
     case 32016: return launch_io<32, 16, 1>(a, io_dtype, stream);
-    case 32064: return launch_io<32, 64, 2>(a, io_dtype, stream);
-    case 64032: return launch_io<64, 32, 2>(a, io_dtype, stream);
-    case 64128: return launch_io<64, 128, 4>(a, io_dtype, stream);
+    case 32064: return launch_io<32, 64, 1>(a, io_dtype, stream);
+    case 64032: return launch_one_term<64, 32, 2>(a, stream);
+    case 64128: return launch_one_term<64, 128, 2>(a, stream);
     case 128064: return launch_io<128, 64, 4>(a, io_dtype, stream);
     case 16064: return launch_io<16, 64, 1>(a, io_dtype, stream);
     case 16096: return launch_io<16, 96, 1>(a, io_dtype, stream);
     case 16128: return launch_io<16, 128, 1>(a, io_dtype, stream);
-    case 32096: return launch_io<32, 96, 2>(a, io_dtype, stream);
-    case 32128: return launch_io<32, 128, 2>(a, io_dtype, stream);
-    case 64096: return launch_io<64, 96, 4>(a, io_dtype, stream);
-    case 64016: return launch_io<64, 16, 2>(a, io_dtype, stream);
+    case 64096: return launch_one_term<64, 96, 2>(a, stream);
+    case 64016: return launch_one_term<64, 16, 2>(a, stream);
     case 96016: return launch_io<96, 16, 3>(a, io_dtype, stream);
     case 96032: return launch_io<96, 32, 3>(a, io_dtype, stream);
     case 96064: return launch_io<96, 64, 3>(a, io_dtype, stream);
-    case 96128: return launch_io<96, 128, 6>(a, io_dtype, stream);
+    case 96128: return launch_io<96, 128, 3>(a, io_dtype, stream);
     case 128016: return launch_io<128, 16, 4>(a, io_dtype, stream);
     case 128032: return launch_io<128, 32, 4>(a, io_dtype, stream);
     case 128096: return launch_io<128, 96, 4>(a, io_dtype, stream);

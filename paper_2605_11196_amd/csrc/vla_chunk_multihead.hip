@@ -484,8 +484,10 @@ hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   constexpr int HPW = 128 / D;
   ForwardArgs args = a;
   void* params[] = {&args};
-  const void* fn = a.feature_map ? reinterpret_cast<const void*>(&chunk_multihead_kernel<D, IO, true>)
-                                 : reinterpret_cast<const void*>(&chunk_multihead_kernel<D, IO, false>);
+  const void* fn = reinterpret_cast<const void*>(&chunk_multihead_kernel<D, IO, true>);
+  if constexpr (sizeof(IO) == 4) {   // bf16 q and k come here mapped only
+    if (a.feature_map == 0) fn = reinterpret_cast<const void*>(&chunk_multihead_kernel<D, IO, false>);
+  }
   return hipLaunchKernel(fn, dim3((a.n_heads + HPW - 1) / HPW), dim3(256), params, 0, stream);
 }
 
@@ -493,6 +495,7 @@ hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
 
 hipError_t launch_chunk_multihead(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream) {
   const bool bf = io_dtype == 1;
+  if (bf && a.feature_map == 0) return hipErrorInvalidValue;
   switch (d) {
     case 32: return bf ? launch<32, uint16_t>(a, stream) : launch<32, float>(a, stream);
     case 64: return bf ? launch<64, uint16_t>(a, stream) : launch<64, float>(a, stream);

@@ -60,16 +60,14 @@ hipError_t launch_scan(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hip
 hipError_t launch_scan_general(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
 
 
-// Block form on FP32 MFMA, 16 tokens per block (vla_chunk.hip); head sizes 16, 32, 64, 96 and 128, and value
-// heads half or twice as wide as the key heads.
+// Block form on MFMA, 16 tokens per block (vla_chunk.hip); every pair of the head sizes 16, 32, 64, 96 and 128.
 bool chunk_supported(int d);
 bool chunk_supported(int d_k, int d_v);
 // Head sizes of the two-phase and time-parallel modes.
 inline bool block_family_supported(int d) { return d == 32 || d == 64 || d == 96 || d == 128; }
 hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
-// Same block form, several heads per workgroup (vla_chunk_multihead.hip); head sizes 32 and 64.
-// launch_chunk picks it by head size and head count (prefer_multihead).
-bool prefer_multihead(int d, int n_heads);
+// Same block form, several heads per workgroup (vla_chunk_multihead.hip); head sizes 32 and 64, float32 or mapped q and
+// k.  launch_chunk picks it by head size, head count and operand terms.
 hipError_t launch_chunk_multihead(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream);
 // Same block form with the optional lines of Algorithm 1 (vla_chunk_general.hip); every head size.
 inline bool general_block_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }

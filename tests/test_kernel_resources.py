@@ -1,68 +1,129 @@
-"""Build-time check of the registers the compiler gives the block kernels (CPU only: hipcc cross-compiles).
+"""Build-time check of the registers and the LDS the compiler gives the block and segment kernels (CPU only: hipcc
+cross-compiles).
 
 The headline kernel keeps 128 state registers per lane and runs two waves per SIMD, so it sits at the
 256-register limit: a change that pushes values into scratch memory inside the token loop would cost time on
 every block without failing any numerical test.  The compiler's own resource remarks are parsed here."""
 import os
 import re
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
 from paper_2605_11196_amd import build
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(build.__file__)), "csrc")
+LDS = 160 * 1024   # of a compute unit
+
+
+def _value(x):
+    x = x.strip()
+    return {"true": True, "false": False, "float": "f32", "unsigned short": "bf16"}.get(x) if not x.isdigit() else int(x)
 
 
 @pytest.fixture(scope="module")
-def chunk_usage():
-    use = build.resource_usage(os.path.join(CSRC, "vla_chunk.hip"))
+def usage():
+    """{kernel: {template arguments: resources}} of the sources with block and segment kernels"""
+    sources = ["vla_chunk.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
+    with ThreadPoolExecutor(len(sources)) as pool:
+        reports = list(pool.map(lambda f: build.resource_usage(os.path.join(CSRC, f)), sources))
     out = {}
-    for name, r in use.items():
-        m = re.search(r"chunk_kernel<(\d+), (\d+), (\d+), ([\w ]+), (true|false)>", name)
-        if m:
-            out[(int(m.group(1)), int(m.group(2)), "bf16" if "short" in m.group(4) else "f32",
-                 m.group(5) == "true")] = r
+    for report in reports:
+        for name, r in report.items():
+            m = re.search(r"(\w+)<([^>]*)>", name)
+            if m:
+                out.setdefault(m.group(1), {})[tuple(_value(x) for x in m.group(2).split(","))] = r
     return out
 
 
+@pytest.fixture(scope="module")
+def chunk_usage(usage):
+    """the block kernel by (d_k, d_v, waves, io, feature map, split products)"""
+    return usage["chunk_kernel"]
+
+
+SQUARE_WAVES = [(16, 1), (32, 1), (32, 2), (64, 2), (64, 4), (96, 3), (96, 6), (128, 4), (128, 8)]
+
+
 def test_every_block_kernel_instantiation_is_reported(chunk_usage):
-    for d in (16, 32, 64, 96, 128):
+    for d, nw in SQUARE_WAVES:
         for io in ("bf16", "f32"):
             for fmap in (False, True):
-                assert (d, d, io, fmap) in chunk_usage
+                if d != 64 or nw == 4 or (io == "bf16" and not fmap):   # two waves: one operand term only
+                    assert (d, d, nw, io, fmap, d > 16) in chunk_usage
 
 
-@pytest.mark.parametrize("d", [16, 32, 64, 96, 128])
-def test_bf16_block_kernels_use_no_scratch_and_keep_two_waves_per_simd(chunk_usage, d):
-    """bf16 I/O is what the large-batch and long-context workloads run."""
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("d,nw", SQUARE_WAVES)
+def test_block_kernels_use_no_scratch_and_keep_two_waves_per_simd(chunk_usage, d, nw, io):
+    """Square heads, with waves of 32 and of 16 columns."""
     for fmap in (False, True):
-        r = chunk_usage[(d, d, "bf16", fmap)]
+        if (d, d, nw, io, fmap, d > 16) not in chunk_usage:
+            continue
+        r = chunk_usage[(d, d, nw, io, fmap, d > 16)]
         assert r["ScratchSize"] == 0 and r["VGPRSpill"] == 0, r
         assert r["VGPRs"] + r.get("AGPRs", 0) <= 256 and r["Occupancy"] >= 2, r
 
 
-def test_float32_io_kernels_stay_within_their_known_spills(chunk_usage):
-    """With float32 I/O the staged rows take twice the registers: at d = 128 the compiler keeps two addresses in
-    scratch (reloaded, never stored, inside the loop); nothing else spills."""
-    for d in (16, 32, 64, 96):
-        for fmap in (False, True):
-            assert chunk_usage[(d, d, "f32", fmap)]["ScratchSize"] == 0
-    for fmap in (False, True):
-        r = chunk_usage[(128, 128, "f32", fmap)]
-        assert r["ScratchSize"] <= 12 and r["VGPRSpill"] <= 2 and r["Occupancy"] >= 2, r
-
-
 def test_headline_kernel_fits_two_workgroups_per_compute_unit(chunk_usage):
-    r = chunk_usage[(128, 128, "bf16", False)]
-    assert 2 * r["LDSSize"] <= 160 * 1024
+    r = chunk_usage[(128, 128, 4, "bf16", False, True)]
+    assert 2 * r["LDSSize"] <= LDS
 
 
-@pytest.mark.parametrize("io", ["short", "float"])
-def test_option_a_chain_leaves_room_for_the_workgroups_of_a_segment_plan(io):
+# Known scratch use, in bytes per lane and spilled registers; every other instantiation has none.
+#   chunk_kernel: (d_k, d_v, waves, io, feature map, split products)
+#   chunk_general_kernel: (d_k, d_v, columns of a wave, io, two sweeps, A chain alone, double buffers)
+#   s_rows_lds_kernel: (d_k, tile slots, other value head size, io, maps, terms, split products, waves per SIMD)
+KNOWN = {
+    "chunk_kernel": {
+        (128, 96, 4, "bf16", False, True): (8, 1),
+        (96, 128, 3, "f32", False, True): (108, 106), (96, 128, 3, "f32", True, True): (108, 106),
+        (96, 128, 3, "bf16", False, True): (48, 23), (96, 128, 3, "bf16", True, True): (48, 23),
+    },
+    "chunk_general_kernel": {
+        (128, 128, 32, "f32", True, False, False): (68, 40), (128, 128, 32, "bf16", True, False, False): (28, 6),
+        (128, 96, 32, "f32", True, False, False): (68, 40), (128, 96, 32, "bf16", True, False, False): (28, 6),
+        (32, 128, 16, "f32", True, False, False): (12, 2),
+        (64, 32, 16, "f32", True, False, False): (36, 8), (64, 64, 16, "f32", True, False, False): (36, 8),
+    },
+    "a_scan_kernel": {},
+    "s_rows_lds_kernel": {
+        (128, 1, False, "f32", False, 3, True, 4): (96, 35), (128, 1, False, "f32", True, 3, True, 4): (20, 8),
+        (128, 1, False, "bf16", False, 1, True, 4): (36, 20), (128, 1, False, "bf16", False, 3, True, 4): (60, 26),
+        (128, 1, False, "bf16", True, 3, True, 4): (20, 8),
+        (128, 1, True, "f32", False, 3, True, 4): (104, 37), (128, 1, True, "f32", True, 3, True, 4): (20, 8),
+        (128, 1, True, "bf16", False, 1, True, 4): (24, 9), (128, 1, True, "bf16", False, 3, True, 4): (56, 25),
+        (128, 1, True, "bf16", True, 1, True, 4): (20, 8), (128, 1, True, "bf16", True, 3, True, 4): (20, 8),
+        (32, 4, True, "f32", False, 3, True, 2): (64, 23), (32, 4, True, "bf16", False, 1, True, 2): (20, 8),
+        (32, 4, True, "bf16", False, 3, True, 2): (20, 8),
+        (96, 1, False, "bf16", False, 1, True, 4): (20, 8), (96, 1, True, "bf16", False, 1, True, 4): (20, 8),
+        (96, 2, True, "f32", False, 3, True, 2): (20, 8), (96, 2, True, "f32", True, 3, True, 2): (20, 8),
+        (96, 2, True, "bf16", True, 3, True, 2): (20, 8),
+    },
+}
+
+
+@pytest.mark.parametrize("kernel", sorted(KNOWN))
+def test_no_kernel_exceeds_its_known_scratch_use(usage, kernel):
+    assert usage[kernel], kernel
+    over = {args: (r["ScratchSize"], r["VGPRSpill"]) for args, r in usage[kernel].items()
+            if (r["ScratchSize"], r["VGPRSpill"]) > KNOWN[kernel].get(args, (0, 0))}
+    assert not over, over
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_option_a_chain_leaves_room_for_the_workgroups_of_a_segment_plan(usage, io):
     """Heads of 64 with options are planned as 768 (head, segment) pairs, one round of three workgroups per compute unit:
     single buffers with a separate u (two sweeps), double ones without."""
-    use = build.resource_usage(os.path.join(CSRC, "vla_chunk_general.hip"))
-    for full, double in (("true", "false"), ("false", "true")):
-        hits = [r for name, r in use.items() if re.search(
-            rf"chunk_general_kernel<64, 64, 16, [\w ]*{io}, {full}, true, {double}>", name)]
-        assert hits and 3 * hits[0]["LDSSize"] <= 160 * 1024 and hits[0]["Occupancy"] >= 3, (full, hits)
+    for full, double in ((True, False), (False, True)):
+        r = usage["chunk_general_kernel"][(64, 64, 16, io, full, True, double)]
+        assert 3 * r["LDSSize"] <= LDS and r["Occupancy"] >= 3, r
+
+
+@pytest.mark.parametrize("d,d_v,nw,workgroups", [(64, 16, 2, 4), (64, 32, 2, 4), (64, 96, 2, 4), (64, 128, 2, 4),
+                                                 (32, 16, 1, 8), (32, 64, 1, 8)])
+def test_unsplit_kernels_hold_the_workgroups_they_are_chosen_for(chunk_usage, d, d_v, nw, workgroups):
+    for io, fmap in (("f32", False), ("f32", True), ("bf16", True)):
+        r = chunk_usage[(d, d_v, nw, io, fmap, False)]
+        assert workgroups * r["LDSSize"] <= LDS, r
+        assert workgroups * nw <= 4 * r["Occupancy"], r

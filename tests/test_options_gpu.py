@@ -259,15 +259,31 @@ def test_block_kernel_with_options_is_deterministic_and_replays_in_a_hip_graph(d
     assert rel(S2, want[1]) < 1e-4 and rel(A2, want[2]) < 1e-4 and rel(z2, want[3]) < 1e-5
 
 
-@pytest.mark.parametrize("d,B,H", [(32, 5, 210), (64, 3, 100)])
-def test_feature_map_with_many_small_heads(d, B, H):
-    """The block kernel that shares a workgroup between several heads carries the feature map too."""
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,B,H", [(32, 5, 210), (64, 3, 100),
+                                   (32, 9, 183), (64, 3, 257)])   # several heads per workgroup, the last one partly filled
+def test_feature_map_with_many_small_heads(d, B, H, dtype):
+    """The block kernel that shares a workgroup between several heads carries the feature map too, for bf16 q and k as well
+    (mapped ones are float32 numbers)."""
     q, k, v = vla_inputs.gaussian_qkv(B, H, 27, d, seed=4000 + d)
-    got, ref = run_both(q, k, v, lambda0=0.1, feature_map=True, mode=BLOCK)
+    got, ref = run_both(q, k, v, dtype=dtype, lambda0=0.1, feature_map=True, mode=BLOCK)
     errs = dict(o=slab_rel_err(got["o"], ref["o"], 2), S=slab_rel_err(got["S_T"], ref["S_T"], 2),
                 A=slab_rel_err(got["A_T"], ref["A_T"], 2))
-    print(d, B * H, errs)
-    assert max(errs.values()) <= 1e-4, errs
+    print(d, B * H, dtype, errs)
+    assert errs["o"] <= TOL[dtype] and max(errs["S"], errs["A"]) <= 1e-4, errs
+
+
+@pytest.mark.parametrize("d_v", [16, 96])
+@pytest.mark.parametrize("d,heads", [(32, 1647), (64, 771)])
+def test_feature_map_with_value_heads_of_another_size(d, heads, d_v):
+    """Mapped bf16 calls at head counts where the products run on the FP32 instruction (d_v = 96 at d = 32: split ones)."""
+    q, k, _ = vla_inputs.gaussian_qkv(1, heads, 27, d, seed=4100 + d)
+    v = vla_inputs.gaussian_qkv(1, heads, 27, d_v, seed=4200 + d)[2]
+    got, ref = run_both(q, k, v, dtype="bf16", lambda0=0.1, feature_map=True, mode=BLOCK)
+    errs = dict(o=slab_rel_err(got["o"], ref["o"], 2), S=slab_rel_err(got["S_T"], ref["S_T"], 2),
+                A=slab_rel_err(got["A_T"], ref["A_T"], 2))
+    print(d, d_v, heads, errs)
+    assert errs["o"] <= TOL["bf16"] and max(errs["S"], errs["A"]) <= 1e-4, errs
 
 
 # ---------------------------------------------------------------- the options inside the segment modes

@@ -496,13 +496,17 @@ def test_shared_workgroup_kernel_holds_the_float32_tolerance_on_a_long_sequence(
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d,B,H,T", [(64, 7, 43, 40),      # 301 heads: two heads per workgroup, one spare wave pair
-                                     (64, 16, 64, 21),     # 1024 heads: whole rounds of two-head workgroups
-                                     (32, 11, 101, 35),    # 1111 heads: four heads per workgroup, one spare wave
-                                     (32, 8, 256, 17)])    # 2048 heads
+@pytest.mark.parametrize("d,B,H,T", [(64, 7, 43, 40),      # 301 heads
+                                     (64, 16, 64, 21),     # 1024 heads: float32: whole rounds of two-head workgroups
+                                     (64, 3, 257, 35),     # 771 heads: float32: two heads per workgroup, a spare wave pair
+                                     (64, 5, 205, 19),     # 1025 heads: one head per workgroup again
+                                     (32, 11, 101, 35),    # 1111 heads
+                                     (32, 8, 192, 17),     # 1536 heads: one head per workgroup
+                                     (32, 9, 183, 35),     # 1647 heads: float32: four heads per workgroup, a spare wave
+                                     (32, 8, 256, 17)])    # 2048 heads: float32: whole workgroups of four heads
 def test_many_small_heads_share_a_workgroup(d, B, H, T, dtype):
-    """Launches large enough for the block kernel that puts several heads on one workgroup (d = 32, 64):
-    ragged last block, head counts that do not fill the last workgroup, given initial state."""
+    """Head counts around the ones from which float32 calls take the block kernel that puts several heads on one workgroup
+    (d = 32, 64): ragged last block, head counts that do not fill the last workgroup, given initial state."""
     rng = np.random.default_rng(d + B)
     q, k, v = vla_inputs.gaussian_qkv(B, H, T, d, seed=3000 + d + B)
     k[:, :, 3] = 0.0
@@ -519,10 +523,14 @@ def test_many_small_heads_share_a_workgroup(d, B, H, T, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,d_v,heads", [(128, 128, 256), (128, 128, 257), (96, 96, 256), (96, 64, 256), (96, 96, 257),
                                          (64, 64, 768), (64, 16, 768), (64, 64, 769), (32, 32, 768), (32, 32, 769),
-                                         (32, 96, 3), (64, 128, 3), (96, 128, 3)])
+                                         (32, 96, 3), (64, 128, 3), (96, 128, 3),
+                                         (128, 16, 3), (128, 32, 3), (128, 64, 3), (128, 96, 3), (32, 16, 3), (96, 32, 257),
+                                         (96, 128, 257), (64, 96, 769), (64, 128, 1024), (64, 16, 1024), (64, 32, 769),
+                                         (64, 128, 1025), (32, 16, 2048), (32, 64, 1025), (32, 64, 1536), (32, 64, 1537)])
 def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
-    """The block kernel on both sides of the head counts where a wave owns 16 instead of 32 columns, and the pairs
-    that always run with 16: 33 tokens (two blocks and one token), values over eight orders of magnitude in the state."""
+    """The block kernel on both sides of the head counts where a wave owns 16 instead of 32 columns and where float32
+    calls with value heads of another size take products on the FP32 instruction, waves without a row tile of S among
+    them: 33 tokens (two blocks and one token), values over eight orders of magnitude in the state."""
     rng = np.random.default_rng(d + heads)
     B, T = 1, 33
     q, k = (rng.standard_normal((B, heads, T, d)).astype(np.float32) for _ in range(2))
