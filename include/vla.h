@@ -140,6 +140,9 @@ size_t vla_forward_workspace_bytes(int B, int H, int T, int d_k, int d_v, int io
  *   S0     [B, H, d_v, d_k] float32 row-major, or NULL for S_0 = 0     (Algorithm 1)
  *   A0     [B, H, d_k, d_k] float32 row-major, or NULL for I / lambda0 (Algorithm 1).
  *          Must be symmetric positive definite (precondition, not checked).
+ *          Values of all five are finite.  From an infinite or NaN one on, a head's results are NaN or infinite, without
+ *          a rule for which; so they may be where a product or sum of the recurrence leaves float32 or comes within
+ *          0.4 % of its largest value (3.39e38).  Other heads are not touched.
  *   o      [B, H, T, d_v]   io_dtype, written
  *   S_T    [B, H, d_v, d_k] float32, written; NULL if not wanted; may be S0 itself
  *   A_T    [B, H, d_k, d_k] float32, written; NULL if not wanted; may be A0 itself

@@ -126,13 +126,13 @@ int pick_mode(int B, int H, int T, int d, int d_v, const vla_opts& o) {
   const long long heads = static_cast<long long>(B) * H;
   // Measured crossovers against the fused block kernel (bf16, one MI355X; time-parallel against block kernel, ms).
   // The segment kernels gain on the block kernel as the sequence grows (their fixed passes amortise):
-  //   d = 128:  T = 2048: 64 heads 0.66 / 0.96, 80 heads 1.09 / 0.97;   T = 4096: 96 heads 1.67 / 1.93, 128: 1.99 / 1.93;
-  //             T = 8192: 128 heads 3.66 / 3.85, 160: 4.75 / 3.86;      T = 32768: 128 heads 14.2 / 15.4, 160: 18.9 / 15.4
-  //   d =  96:  T = 1024: 64 heads 0.33 / 0.41, 96: 0.55 / 0.41;        T = 2048: 64 heads 0.52 / 0.82, 80: 0.83 / 0.82;
-  //             T = 4096: 128 heads 1.52 / 1.64, 160: 1.91 / 1.64;      T = 32768: 128 heads 10.5 / 13.1, 160: 13.7 / 13.1
-  //   d =  64:  T = 2048: 192 heads 0.51 / 0.63, 256: 0.60 / 0.63, 320: 0.73 / 0.69;   T = 4096: 320 heads 1.33 / 1.38,
-  //             384: 1.78 / 1.38;                                       T = 16384: 320 heads 5.13 / 5.48, 384: 7.02 / 5.47
-  //   d =  32:  T = 2048: 512 heads 0.51 / 0.57, 640: 0.59 / 0.58;      T = 16384: 512 heads 3.71 / 4.54, 640: 4.59 / 4.56
+  //   d = 128:  T = 2048: 64 heads 0.46 / 0.74, 80 heads 0.57 / 0.74;  T = 4096: 96 heads 1.10 / 1.46, 128: 1.33 / 1.46;
+  //             T = 8192: 128 heads 2.47 / 2.93, 160: 3.16 / 2.93;     T = 32768: 128 heads 9.97 / 11.6, 160: 13.0 / 11.7
+  //   d =  96:  T = 1024: 64 heads 0.25 / 0.30, 96: 0.38 / 0.31;       T = 2048: 64 heads 0.39 / 0.61, 80: 0.48 / 0.61;
+  //             T = 4096: 128 heads 1.06 / 1.21, 160: 1.35 / 1.21;     T = 32768: 128 heads 7.79 / 9.58, 160: 10.2 / 9.60
+  //   d =  64:  T = 2048: 192 heads 0.39 / 0.48, 256: 0.46 / 0.47, 320: 0.56 / 0.55;   T = 4096: 320 heads 1.05 / 1.10,
+  //             384: 1.36 / 1.10;                                      T = 16384: 320 heads 3.98 / 4.37, 384: 5.38 / 4.39
+  //   d =  32:  T = 2048: 512 heads 0.47 / 0.49, 640: 0.55 / 0.50;     T = 16384: 512 heads 3.50 / 3.89, 640: 4.33 / 3.96
   const int t_128 = d == 96 ? 4096 : 8192;   // from here 128 heads still gain at d >= 96
   long long few = d >= 96 ? (T >= t_128 ? 128 : (T >= 4096 ? 96 : 64))
                           : (d >= 64 ? (T >= 4096 ? 320 : 192) : 512);
@@ -146,8 +146,8 @@ int pick_mode(int B, int H, int T, int d, int d_v, const vla_opts& o) {
     if (d == 128 && T >= 4096) few = 128;
     if (d == 32 && d_v == 128) few = 1280;
   }
-  // Short sequences (half the length): 64 heads at d = 64, T = 512: 0.11 against 0.16 ms, 128 heads 0.16 against
-  // 0.16; 256 heads at d = 32: 0.12 against 0.14, 512 heads 0.15 against 0.15.  Not at d = 96, whose Gram sums and boundary inverses run in the d = 128 layout (T = 512:
+  // Short sequences (half the length): 64 heads at d = 64, T = 512: 0.092 against 0.122 ms, 128 heads 0.140 against
+  // 0.122; 256 heads at d = 32: 0.114 against 0.104.  Not at d = 96, whose Gram sums and boundary inverses run in the d = 128 layout (T = 512:
   // 16 heads 0.26 against 0.21).
   const long long few_short = d >= 96 ? 32 : (d >= 64 ? 64 : 256);
   const int t_short = d == 96 ? 1024 : 512;

@@ -30,9 +30,9 @@
 // from bf16 terms (vla_mfma_util.h): the state is split into three terms as it is read (11 instructions per two
 // elements, once per block: S for both of its products), bf16 keys and queries are one term each, float32 ones
 // three; W and E are split once per block.  On FP32 matrix instructions the matrix unit alone took 78 % of the time
-// (large batch: 2048 heads of 128, 8192 tokens, bf16 q, k, v: 25.1 ms); with the split products 16.5 ms, 167
-// TFLOP/s, above the FP32 matrix peak of 157.  2048 heads of 64: 8.3 -> 6.2 ms; 256 heads of 64, float32, 2048
-// tokens: 0.63 -> 0.48 ms.  Error against float64 on the latter 4.3e-7 -> 3.8e-7 (2-norm, relative).
+// (large batch: 2048 heads of 128, 8192 tokens, bf16 q, k, v: 25.1 ms); with the split products 17.0 ms, 161
+// TFLOP/s, above the FP32 matrix peak of 157.  2048 heads of 64: 8.3 -> 6.4 ms; 256 heads of 64, float32, 2048
+// tokens: 0.63 -> 0.50 ms.  Error against float64 on the latter 4.3e-7 -> 3.3e-7 (2-norm, relative).
 #include "vla_mfma_util.h"
 
 namespace vla {

@@ -44,7 +44,7 @@
 // part.  The sweeps over A and S and the Gram matrices are FP32 products on split bf16 terms (vla_mfma_util.h); Y and X
 // share their LDS with W and Alpha and the next block is staged at the end of a block, so that two workgroups
 // of d = 128 fit a compute unit (80 KB each).  Every option on, 2048 heads of 128, 8192 tokens, bf16: 43.7 ms with FP32
-// matrix instructions and one workgroup per compute unit, 35.2 ms so.  T = 256: 2048 heads of 64 0.59 -> 0.43 ms,
+// matrix instructions and one workgroup per compute unit, 35.6 ms so.  T = 256: 2048 heads of 64 0.59 -> 0.43 ms,
 // of 32 0.33 -> 0.25, of 96 1.26 -> 1.17.
 #include "vla_mfma_util.h"
 

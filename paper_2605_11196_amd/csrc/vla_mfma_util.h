@@ -31,10 +31,13 @@ __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
 // ---- FP32 products on the bf16 matrix instruction.  A float32 value is the sum of three bf16 values (3 x 8
 // significant bits); a product of two bf16 values is exact in float32, which is what the instruction accumulates
 // in.  So a float32 matrix times a matrix of bf16 numbers is three products with nothing left out, and a float32
-// matrix times a float32 matrix is the six products of weight 2^-16 and more (what is left out is below 2^-25 of
-// the product).  Measured on one SIMD: 7.8 ns for 16x16x32 in bf16 against 14.2 ns for 16x16x4 in FP32, so three
-// products take 0.21 of the FP32 time and six 0.41; and the bf16 instruction leaves the vector ALU free for
-// other waves (32 MFMAs beside 64 FMAs of another wave 0.263 us, 0.249 and 0.116 us alone), which the FP32 one does not.
+// matrix times a float32 matrix is the six products of weight 2^-16 and more.  What is left out of a product x y is at
+// most 2^-24 |x y| where both factors are split by rounding and 3 x 2^-24 where one is cut off (the state); 0.1 and 0.3
+// of 2^-24 in the root mean square, with the sign of the rounded factor's low terms.  Factors are finite: an infinite
+// one gives NaN, and so does one that rounds to infinity in bf16 (3.39e38 and more).  Measured on one SIMD: 7.8 ns for
+// 16x16x32 in bf16 against 14.2 ns for 16x16x4 in FP32, so three products take 0.21 of the FP32 time and six 0.41; and
+// the bf16 instruction leaves the vector ALU free for other waves (32 MFMAs beside 64 FMAs of another wave 0.263 us,
+// 0.249 and 0.116 us alone), which the FP32 one does not.
 // v_dot2_f32_bf16 would form the residuals below in fewer instructions but excludes the matrix unit (0.428 us for
 // the same pair).
 //

@@ -1061,6 +1061,8 @@ hipError_t launch_s_rows_lds_n(const ForwardArgs& a, hipStream_t stream) {
     // is nearly empty costs float32 calls more than the FP32 products do (33 KB, four workgroups).  16 heads, T = 65536,
     // 1024 pairs: 1.12 to 1.13 ms against 1.17 with split products here and the maps apart; 24 heads, T = 4096, 384
     // pairs: 0.208 against 0.190.
+    // Not mapped bf16 calls, whose maps are apart in any case: 16 heads, T = 65536: 1.083 split, 1.107 FP32; 320 heads,
+    // T = 4096: 1.25 and 1.30.
     if constexpr (D == 64 && sizeof(IO) == 4 && !RECT && !MAP) {
       if (hs > 768) return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, false, kWps>);
     }
@@ -1122,7 +1124,7 @@ hipError_t launch_phases(const ForwardArgs& a, hipStream_t stream) {
   const bool fused_map = kFusedMap && !own_pass && !general && !rect && a.n_seg > 1 && hs >= 768;
   auto scan_of = [&](auto kt_tag) -> const void* {
     constexpr int kKt = decltype(kt_tag)::value;
-    if constexpr (kFusedMap) {
+    if constexpr (kFusedMap && !(D == 64 && sizeof(IO) == 2 && kKt == 3)) {
       if (fused_map) return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, true, kKt>);
     }
     return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, false, kKt>);
@@ -1200,9 +1202,10 @@ hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream
 // 2.52 with 24 (three quarters of a round take as long as a whole one); T = 8192 0.65 with 16 against 0.73 with
 // 32; 8 heads, T = 32768: 1.22 with 64 against 1.59 with 128; d = 96, 16 heads, T = 32768: 1.52 against 1.84.
 // With the options (`general`: the A chain runs on the option kernel, three workgroups per compute unit at
-// d = 64) a resident round is 768 pairs at d = 64, and the longer chain favours segments of 32 blocks there too:
-// 16 heads, T = 131072: 3.04 ms with 48 segments against 3.15 with 64; T = 16384: 0.49 with 32 against 0.55
-// with 64; 8 heads, T = 65536: 0.90 with 96 against 1.00 with 128.
+// d = 64) a resident round is 768 pairs at d = 64, and the longer chain favours segments of 32 blocks there too
+// (with u and the normalised read-out): 16 heads, T = 131072: 2.66 ms with 48 segments against 2.89 with 32 and 2.98
+// with 64; T = 16384: 0.42 with 32 against 0.52 with 24; 8 heads, T = 65536: 0.77 with 96 against 0.79 with 64 and 0.86
+// with 128.
 SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested) {
   const int nblk = (T + C - 1) / C;
   int ns = requested;
