@@ -26,6 +26,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector (and FP32 matrix) peak, TFLOP/s
+PEAK_BF16_TFLOPS = 2500.0  # dense bf16 matrix peak, TFLOP/s
 PEAK_HBM_GBS = 8000.0
 MODE_NAMES = {1: "scan", 2: "chunked", 3: "two_phase", 4: "time_parallel"}
 
@@ -181,6 +182,12 @@ def forward_case(c, *, mode=0, segments=None, options="none", steps=10, warmup=3
     n_streams = 5 if options != "none" else 4
     io_bytes = (2 if dtype == "bf16" else 4) * n_streams * d * head_tokens + B * H * 2 * d * d * 4
     tflops = flops / avg_s / 1e12
+    # The kernels of the block and segment modes form a float32 product from bf16 ones: three where k and q are bf16
+    # numbers, six where both factors are float32 (float32 or mapped k and q); d = 16 and the scan kernels use FP32 units.
+    if resolved in (2, 3, 4) and d > 16:
+        peak = PEAK_BF16_TFLOPS / (3 if dtype == "bf16" and options == "none" else 6)
+    else:
+        peak = PEAK_FP32_TFLOPS
     traffic, traffic_src = PROFILED_TRAFFIC_BYTES.get((B, H, T, d, dtype, resolved), (None, None))
     if options != "none":
         traffic, traffic_src = None, None
@@ -196,10 +203,10 @@ def forward_case(c, *, mode=0, segments=None, options="none", steps=10, warmup=3
         "wall_s": wall, "value": head_tokens * steps / wall, "ms_per_step": wall / steps * 1e3,
         "roofline": {
             "bound": "mfma" if resolved in (2, 3, 4) else "alu",
-            "achieved": tflops, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": tflops / PEAK_FP32_TFLOPS,
+            "achieved": tflops, "peak": peak, "unit": "TFLOP/s", "frac": tflops / peak,
             "traffic": traffic, "traffic_source": traffic_src,
             "kernel_ms": avg_s * 1e3, "kernel_ms_median": med_s * 1e3,
-            "frac_median": flops / med_s / 1e12 / PEAK_FP32_TFLOPS,
+            "frac_median": flops / med_s / 1e12 / peak,
             "algorithmic_flop_per_launch": flops, "algorithmic_bytes_per_launch": io_bytes,
             "hbm_GBps": io_bytes / avg_s / 1e9, "hbm_frac": io_bytes / avg_s / 1e9 / PEAK_HBM_GBS,
         },
