@@ -632,9 +632,9 @@ static bool narrow_waves(int d_k, int d_v, int n_heads, int terms, bool mapped) 
 //           (with the feature map, bf16: 1024: 0.363 / 0.273, 2048: 0.589 / 0.547, 3072: 0.797 / 0.824)
 //   d = 32: 1024 heads 0.145 / 0.160, 1536: 0.196 / 0.219, 2048: 0.320 / 0.222, 3072: 0.385 / 0.431, 4096: 0.560 / 0.441
 // and, split / FP32 products here:
-//   64 x 16: 768 heads 0.166 / 0.198, 1024: 0.310 / 0.212, 2048: 0.475 / 0.524    64 x 32: 1024: 0.327 / 0.237, 2048: 0.510 / 0.576
-//   64 x 96: 769 heads 0.385 / 0.351, 1024: 0.432 / 0.366      64 x 128: 769 heads 0.384 / 0.413, 896: 0.426 / 0.430, 1024: 0.458 / 0.431
-//   32 x 16: 2048 heads 0.308 / 0.191    32 x 64: 1536 heads 0.242 / 0.276, 2048: 0.370 / 0.282, 3072: 0.479 / 0.542, 4096: 0.658 / 0.551
+//   64 x 16: 1024 heads 0.310 / 0.222, 2048: 0.475 / 0.524     64 x 32: 1024 heads 0.327 / 0.247, 2048: 0.510 / 0.576
+//   64 x 96: 769 heads 0.385 / 0.358, 1024: 0.432 / 0.373      64 x 128: 769 heads 0.384 / 0.413, 896: 0.426 / 0.430, 1024: 0.458 / 0.437
+//   32 x 16: 2048 heads 0.308 / 0.195    32 x 64: 1536 heads 0.242 / 0.276, 2048: 0.370 / 0.288, 3072: 0.479 / 0.542, 4096: 0.658 / 0.559
 static bool fewer_rounds_unsplit(int d_k, int n_heads) {
   if (d_k == 32) return rounds(n_heads, 2048) < rounds(n_heads, 1536);
   if (d_k == 64) return 11 * rounds(n_heads, 1024) < 8 * rounds(n_heads, 768);   // a round of each: 0.28 and 0.20 ms

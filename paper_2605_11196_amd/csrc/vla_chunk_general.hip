@@ -77,7 +77,8 @@ constexpr int general_waves_per_simd(int d, int d_v, int sl, bool db) {
 // DV: head size of v and o (rows of S).  The DV / 16 row tiles of S go to the waves in turn (tile t to wave
 //     t % NW: exactly one each for square heads); a wave with fewer tiles than the others, or none, runs its spare
 //     slots on a copy of the last tile and stores nothing from them.
-template <int D, int DV, int SL, typename IO, bool FULL, bool SCAN, bool DB>
+// SPLIT: products on split bf16 terms, else on the FP32 matrix instruction.
+template <int D, int DV, int SL, typename IO, bool FULL, bool SCAN, bool DB, bool SPLIT>
 __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL, DB)) chunk_general_kernel(ForwardArgs a) {
   constexpr int NW = D / SL;       // waves; wave w owns columns SL w .. SL w + SL - 1 of A
   constexpr int NJ = SL / 16;      // 16-wide tiles in a slab of A
@@ -100,9 +101,10 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
 
   // Products over the head dimension and over the tokens on split bf16 terms (vla_mfma_util.h).  Keys are staged
   // normalised and mapped, directions scaled: float32 numbers, three terms each.
-  constexpr bool kSplit = D > 16;
-  constexpr int NKB = (NB + 1) / 2;   // 32-column steps of a contraction over the head dimension
-  using Ops = BlockOps<kSplit, kSplit ? 3 : 1, D>;
+  using Ops = BlockOps<SPLIT, SPLIT ? 3 : 1, D>;
+  constexpr int STEP = Ops::STEP;
+  constexpr int NKB = NB / STEP;      // steps of a contraction over the head dimension
+  static_assert(NB % STEP == 0, "whole steps");
   // Y^T and X^T live until the Gram matrices are formed, W and Alpha from then to the end of the block.  DB: regions of
   // their own, and K^ and Q double-buffered, so that the next block is staged beside the serial sections.  Otherwise
   // one region and single buffers, at the price of staging behind one more barrier.
@@ -353,7 +355,7 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
     for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
       for (int jn = 0; jn < NJ; ++jn) {
-        const auto ab = Ops::tiles(At[jn][2 * kb], At[jn][kSplit ? 2 * kb + 1 : 0]);
+        const auto ab = Ops::tiles(At[jn][STEP * kb], At[jn][STEP * kb + STEP - 1]);
         yt[jn] = Ops::sweep(Ops::operand(Us, kb, c, g), ab, yt[jn]);
         if constexpr (FULL) xt[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), ab, xt[jn]);
         if (NJ > 1) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
@@ -398,8 +400,8 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
           const auto av = Ops::operand(left, kb, c, g);
           if (i == kQZ) {
             const f4 zero{0, 0, 0, 0};
-            const f4 z0 = cc == 0 ? lds4(&zks[32 * kb + 4 * g]) : zero;
-            const f4 z1 = cc == 0 && kSplit ? lds4(&zks[kSplit ? 32 * kb + 16 + 4 * g : 0]) : zero;
+            const f4 z0 = cc == 0 ? lds4(&zks[16 * STEP * kb + 4 * g]) : zero;
+            const f4 z1 = cc == 0 && SPLIT ? lds4(&zks[SPLIT ? 32 * kb + 16 + 4 * g : 0]) : zero;
             acc[kb & 1] = Ops::sweep(av, Ops::tiles(z0, z1), acc[kb & 1]);
           } else {
             acc[kb & 1] = Ops::sweep(av, Ops::operand(right, kb, c, g), acc[kb & 1]);
@@ -429,7 +431,7 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
       for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJV; ++jn) {
-          const auto sb = Ops::tiles(St[jn][2 * kb], St[jn][kSplit ? 2 * kb + 1 : 0]);
+          const auto sb = Ops::tiles(St[jn][STEP * kb], St[jn][STEP * kb + STEP - 1]);
           ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
           ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
           if (NJ > 1) __builtin_amdgcn_sched_barrier(0);
@@ -698,31 +700,38 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
   }
 }
 
-template <int D, int DV, int SL, bool DB, typename IO>
+template <int D, int DV, int SL, bool DB, bool SPLIT, typename IO>
 hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
   const bool full = a.u != nullptr || a.refresh_period > 0;
-  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, true, false, DB>)
-                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, false, false, DB>);
+  const void* fn = full ? reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, true, false, DB, SPLIT>)
+                        : reinterpret_cast<const void*>(&chunk_general_kernel<D, DV, SL, IO, false, false, DB, SPLIT>);
   return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * D / SL), params, 0, stream);
+}
+template <int D, int DV, int SL, bool DB, bool SPLIT>
+hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
+  return io_dtype == 1 ? launch<D, DV, SL, DB, SPLIT, uint16_t>(a, stream) : launch<D, DV, SL, DB, SPLIT, float>(a, stream);
 }
 template <int D, int DV>
 hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
-  const bool bf = io_dtype == 1;
   // d = 128: waves of 32 columns (two workgroups of four waves per compute unit) from the count where a compute unit
   // gets two, waves of 16 (one of eight) below.  T = 256, every option, 16 / 32 columns: 256 heads 0.183 / 0.251 ms,
   // 512 heads 0.34 / 0.32, 2048 heads 1.27 / 1.15.
   if constexpr (D == 128) {
-    if (a.n_heads > 256) return bf ? launch<D, DV, 32, false, uint16_t>(a, stream) : launch<D, DV, 32, false, float>(a, stream);
+    if (a.n_heads > 256) return launch_as<D, DV, 32, false, true>(a, io_dtype, stream);
   }
-  // d <= 32: double buffers while a compute unit holds at most two workgroups (d = 32: 64 heads 0.095 ms, single
-  // buffers 0.103; 512 heads 0.114 / 0.118; 1024 heads 0.21 / 0.13).  d = 64: single ones at any count (256 heads
-  // 0.118 / 0.114, 2048 heads 0.55 / 0.43).
+  // Small heads on a compute unit of their own: the splits only lengthen the block.  T = 512, bf16, every option, split /
+  // FP32 products: d = 64, 256 heads 0.223 / 0.208 ms, 257 heads 0.256 / 0.274;  d = 32 (both double-buffered) 256
+  // heads 0.188 / 0.175, 512 heads 0.219 / 0.220, single-buffered 0.201 and 0.229.  d = 32, T = 256, 1024 heads: 0.21
+  // double-buffered and split, 0.13 single-buffered and split.
+  if constexpr (D == 64 && DV <= D) {
+    if (a.n_heads <= 256) return launch_as<D, DV, 16, false, false>(a, io_dtype, stream);
+  }
   if constexpr (D <= 32 && DV <= D) {
-    if (a.n_heads <= 512) return bf ? launch<D, DV, 16, true, uint16_t>(a, stream) : launch<D, DV, 16, true, float>(a, stream);
+    if (a.n_heads <= 512) return launch_as<D, DV, 16, true, false>(a, io_dtype, stream);
   }
-  return bf ? launch<D, DV, 16, false, uint16_t>(a, stream) : launch<D, DV, 16, false, float>(a, stream);
+  return launch_as<D, DV, 16, false, (D > 16)>(a, io_dtype, stream);
 }
 template <int D>
 hipError_t launch_dv(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t stream) {
@@ -741,19 +750,19 @@ hipError_t launch_scan_full(const ForwardArgs& a, hipStream_t stream) {
   constexpr int SL = 16;
   const long long wgs = static_cast<long long>(a.n_heads) * a.n_seg;
   if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-  // Double buffers shorten the block, single ones (31 KB, with u, at d = 32; 48 at 64) let more workgroups share a
-  // compute unit's LDS: double up to the (head, segment) pairs that are resident with them in one round (with u and
-  // without: d = 32 768 and 1024, d = 64 512 and 768; from d = 96 two workgroups without u, measured better single, and
-  // one either way with u).  Whole calls, 16 heads, bf16, single / double, ms:
-  //   d = 64, T = 131072, 768 pairs: u and normalised read-out 2.65 / 3.34, normalised read-out 2.46 / 2.33;
-  //           T = 16384, 512 pairs: 0.438 / 0.420 and 0.399 / 0.379
-  //   d = 32, T = 16384, 1024 pairs: 0.221 / 0.268 and 0.205 / 0.195;  T = 4096, 256 pairs: 0.147 / 0.136
-  //   d = 96, T = 32768, 512 pairs: 1.73 / 1.69 and 1.28 / 1.51;  d = 128: 2.08 / 2.02 and 1.65 / 1.86
-  constexpr bool kAlways = FULL && D >= 96;
-  constexpr int kMostDB = D >= 96 ? 256 : (D == 64 ? (FULL ? 512 : 768) : (FULL ? 768 : 1024));
-  const void* fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, true>);
-  if constexpr (!kAlways) {
-    if (wgs > kMostDB) fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, false>);
+  // Heads of 32 and 64: FP32 products, double-buffered, so that the 768 (d = 64) and 1024 pairs of a segment plan are
+  // resident in one round.  Three-term K^ and Q in two buffers would leave two workgroups of d = 64 with u (67 KB), in
+  // single ones three at the price of a longer block.  Whole calls, 16 heads, bf16, u and normalised read-out, split
+  // double / split single / FP32 double, ms:
+  //   d = 64, T = 4096 0.185 / 0.194 / 0.178, T = 16384 0.422 / 0.438 / 0.422, T = 131072 3.33 / 2.67 / 2.66
+  //   d = 32, T = 4096 0.136 / 0.149 / 0.134, T = 16384 0.267 / 0.221 / 0.214, T = 65536 0.899 / 0.716 / 0.673
+  // From d = 96 the products weigh more: split ones, double-buffered up to one pair per compute unit and, with u, beyond
+  // (one workgroup either way); without u two workgroups with single buffers beyond.  T = 32768, 512 pairs, single /
+  // double: d = 96 with u 1.73 / 1.69, without 1.28 / 1.51;  d = 128 2.08 / 2.02 and 1.65 / 1.86
+  constexpr bool kSplit = D >= 96;
+  const void* fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, true, kSplit>);
+  if constexpr (kSplit && !FULL) {
+    if (wgs > 256) fn = reinterpret_cast<const void*>(&chunk_general_kernel<D, D, SL, IO, FULL, true, false, true>);
   }
   ForwardArgs args = a;
   void* params[] = {&args};

@@ -322,7 +322,12 @@ struct BlockOps {
       for (int b = 0; b < N; ++b) {
         const f4 wa = __builtin_bit_cast(f4, hm[4 * (16 * b + c) + tok_chunk(c, g)]);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) a(b, j) = update(wa, y[j], a(b, j));
+        for (int j = 0; j < NJ; ++j) {
+          // summed apart as well: one rounding of A instead of four (heads of 64, mapped keys, T = 2500, error of S:
+          // 1.67e-6 accumulated); d = 16 is bound by this chain and has few columns to gather it
+          if constexpr (D > 16) a(b, j) += update(wa, y[j], f4{0, 0, 0, 0});
+          else a(b, j) = update(wa, y[j], a(b, j));
+        }
       }
     }
   }
