@@ -1203,8 +1203,8 @@ hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream
 // 32; 8 heads, T = 32768: 1.22 with 64 against 1.59 with 128; d = 96, 16 heads, T = 32768: 1.52 against 1.84.
 // With the options (`general`: the A chain runs on the option kernel, three workgroups per compute unit at
 // d = 64) a resident round is 768 pairs at d = 64, and the longer chain favours segments of 32 blocks there too
-// (with u and the normalised read-out): 16 heads, T = 131072: 2.66 ms with 48 segments against 2.89 with 32 and 2.98
-// with 64; T = 16384: 0.42 with 32 against 0.52 with 24; 8 heads, T = 65536: 0.77 with 96 against 0.79 with 64 and 0.86
+// (with u and the normalised read-out): 16 heads, T = 131072: 2.69 ms with 48 segments against 3.00 with 32 and 2.93
+// with 64; T = 16384: 0.43 with 32 against 0.53 with 24; 8 heads, T = 65536: 0.78 with 96 against 0.80 with 64 and 0.88
 // with 128.
 SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested) {
   const int nblk = (T + C - 1) / C;
