@@ -30,9 +30,9 @@
 // from bf16 terms (vla_mfma_util.h): the state is split into three terms as it is read (11 instructions per two
 // elements, once per block: S for both of its products), bf16 keys and queries are one term each, float32 ones
 // three; W and E are split once per block.  On FP32 matrix instructions the matrix unit alone took 78 % of the time
-// (large batch: 2048 heads of 128, 8192 tokens, bf16 q, k, v: 25.1 ms); with the split products 17.0 ms, 161
-// TFLOP/s, above the FP32 matrix peak of 157.  2048 heads of 64: 8.3 -> 6.4 ms; 256 heads of 64, float32, 2048
-// tokens: 0.63 -> 0.50 ms.  Error against float64 on the latter 4.3e-7 -> 3.3e-7 (2-norm, relative).
+// (2048 heads of 128, 512 tokens, float32 1.43 ms now).  Most calls run on the kernel of vla_chunk_pipe.hip; what is left
+// here are head sizes of 16, counts that would take that one another round of workgroups, and three-term operands of
+// large counts (see pipe_narrow and pipe_wide below).
 #include "vla_mfma_util.h"
 
 namespace vla {
@@ -573,6 +573,16 @@ hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   }
   return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * NW), params, 0, stream);
 }
+// float32 q and k, or the feature map
+template <int D, int DV, int NW>
+hipError_t launch_three_terms(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
+  ForwardArgs args = a;
+  void* params[] = {&args};
+  const void* fn = io_dtype == 1   ? reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, uint16_t, true, true>)
+                   : a.feature_map ? reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, float, true, true>)
+                                   : reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, float, false, true>);
+  return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * NW), params, 0, stream);
+}
 // bf16 q and k without the feature map
 template <int D, int DV, int NW>
 hipError_t launch_one_term(const ForwardArgs& a, hipStream_t stream) {
@@ -596,31 +606,59 @@ bool chunk_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 ||
 static int operand_terms(const ForwardArgs& a, int io_dtype) { return io_dtype == 1 && a.feature_map == 0 ? 1 : 3; }
 static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) / resident; }
 
-// Waves of 16 columns instead of 32?  Such a wave has half the splits and products between two serial sections but as
-// much of everything else, so it pays while it runs on a SIMD that would be idle: as long as the narrow workgroups are
-// resident in one round.  Wide / narrow waves, one term and three terms:
-//   d = 128 (4 / 8 waves): 256 heads 0.229 / 0.203 and 0.304 / 0.230, 512 heads 0.302 / 0.396 and 0.388 / 0.458
-//     d_v = 64: 256 heads 0.190 / 0.171 and 0.229 / 0.198, 512 heads 0.226 / 0.336 and 0.276 / 0.406
-//   d =  96 (3 / 6 waves): 256 heads 0.192 / 0.162 and 0.256 / 0.197, 512 heads 0.237 / 0.306 and 0.308 / 0.379
-//     d_v = 128: 512 heads 0.354 / 0.402 and 0.524 / 0.504, 2048 heads 1.42 / 1.60 and 2.07 / 2.01, mapped (one more
-//     pass over the staged rows, on two of three or three of six waves) 0.525 / 0.535 and, bf16, 0.462 / 0.551
-//   d =  64 (2 / 4 waves): 768 heads 0.198 / 0.178 and 0.235 / 0.206, 1024 heads 0.212 / 0.307 and 0.415 / 0.357,
-//                          2048 heads (three terms) 0.694 / 0.561
+// The kernel with the A chain and the S chain on waves of their own (vla_chunk_pipe.hip)?  It shortens the chain of a block
+// and holds twice the waves per head, so it wins as long as its workgroups are resident in one round, and beyond that
+// where the other kernel leaves a compute unit with fewer waves than SIMDs' worth of work.  Waves of 16 columns, one term
+// and three terms, this file's kernel / that one:
+//   d = 128: 16 heads 0.184 / 0.149 and 0.217 / 0.161, 256 heads 0.190 / 0.159 and 0.225 / 0.190, 512 heads 0.279 / 0.333
+//            and 0.365 / 0.371
+//     d_v = 16: 256 heads 0.153 / 0.151 and 0.176 / 0.205 (one wave stages every token); d_v = 64: 0.169 / 0.140 and
+//     0.197 / 0.153
+//   d =  96: 256 heads 0.157 / 0.127 and 0.189 / 0.144, 512 heads 0.236 / 0.245 and 0.300 / 0.296, 640 heads 0.423 / 0.381
+//            and 0.536 / 0.438, 2048 heads 0.934 / 1.023 and 1.188 / 1.161
+//     d_v = 128: 256 heads 0.200 / 0.139 and 0.254 / 0.157, 2048 heads 1.41 / 1.08 and 2.01 / 1.22
+//     d_v = 64: 2048 heads 0.968 / 0.990 and 1.21 / 1.12; d_v = 32: 0.776 / 0.594 and 0.954 / 1.017
+//   d =  64: 16 heads 0.120 / 0.087 and 0.124 / 0.090, 256 heads 0.121 / 0.097 and 0.126 / 0.096, 512 heads 0.147 / 0.128
+//            and 0.157 / 0.141, 640 heads 0.169 / 0.166 and 0.189 / 0.234
+//     d_v = 16: 512 heads 0.127 / 0.109 and 0.137 / 0.205; d_v = 128: 256 heads 0.130 / 0.114 and 0.158 / 0.128, 512 heads
+//     0.162 / 0.216 and 0.208 / 0.274
+//   d =  32: 256 heads 0.102 / 0.072 and 0.103 / 0.078, 1024 heads 0.135 / 0.127 and 0.142 / 0.137, 1536 heads 0.174 / 0.201
+//            and 0.194 / 0.251
+//     d_v = 64: 512 heads 0.140 / 0.112 and 0.152 / 0.128, 768 heads 0.142 / 0.211; d_v = 128: 256 heads 0.131 / 0.095 and
+//     0.158 / 0.109, 512 heads 0.179 / 0.184 and 0.200 / 0.228
+static bool pipe_narrow(int d_k, int d_v, int n_heads, int terms) {
+  switch (d_k) {
+    case 128: return n_heads <= 256 && d_v > 16;
+    case 96: return n_heads <= 256 || d_v == 128 || (terms == 1 ? d_v == 32 : d_v >= 64);
+    case 64: return n_heads <= 256 || (n_heads <= 512 && d_v <= 64 && (terms == 1 || d_v == 64));
+    case 32: return n_heads <= (d_v <= 32 ? 1024 : d_v <= 96 ? 512 : 256);
+    default: return false;
+  }
+}
+// Its waves of 32 columns, one term: 512 heads of 128 0.290 / 0.255, 768 0.531 / 0.394, 2048 1.092 / 0.985 (d_v = 64: 0.889 /
+// 1.150, not taken); 257 heads of 64 0.142 / 0.117, 1024 0.211 / 0.180, 1280 0.328 / 0.259, 2048 0.413 / 0.365.
+static bool pipe_wide(int d_k, int d_v, int n_heads, int terms) {
+  return terms == 1 && d_k == d_v && (d_k == 64 || d_k == 128) && n_heads > 256;
+}
+
+// What is left for the kernel here: waves of 16 columns instead of 32?  Such a wave has half the splits and products
+// between two serial sections but as much of everything else, so it pays while it runs on a SIMD that would be idle: as long
+// as the narrow workgroups are resident in one round.  Wide / narrow waves, one term and three terms:
+//   d = 128 (4 / 8 waves): d_v = 64: 256 heads 0.190 / 0.171 and 0.229 / 0.198, 512 heads 0.226 / 0.336 and 0.276 / 0.406
+//   d =  64 (2 / 4 waves), three terms: 768 heads 0.235 / 0.206, 1024 heads 0.415 / 0.357, 2048 heads 0.694 / 0.561
 //     d_v = 96: 768 heads 0.234 / 0.217 and 0.280 / 0.264, 1024 heads 0.249 / 0.372 and 0.504 / 0.432
-//   d =  32 (1 / 2 waves): 768 heads 0.138 / 0.133 and 0.151 / 0.134, 1024 heads 0.140 / 0.144 and 0.151 / 0.145,
-//                          1536 heads (three terms) 0.196 / 0.262
+//   d =  32 (1 / 2 waves):
 //     d_v = 64: 1024 heads 0.162 / 0.153 and 0.183 / 0.165, 1280 heads (three terms) 0.240 / 0.217, 1536: 0.242 / 0.304,
 //               3072: 0.479 / 0.514, 2048 heads (one term) 0.223 / 0.318
 //     d_v = 128: 1024 heads 0.713 / 0.195 (the wide wave's slab of S does not fit its registers)
-static bool narrow_waves(int d_k, int d_v, int n_heads, int terms, bool mapped) {
+static bool narrow_waves(int d_k, int d_v, int n_heads, int terms) {
   switch (d_k) {
     case 128: return n_heads <= 256;
-    case 96: return n_heads <= 256 || (d_v > 96 && terms == 3 && !mapped);
     case 64: return n_heads <= 768 || terms == 3;
     case 32:
       if (d_v >= 96) return true;
       if (d_v == 64) return terms == 3 ? rounds(n_heads, 1280) <= rounds(n_heads, 1536) : n_heads <= 1024;
-      return n_heads <= (terms == 3 ? 1024 : 768);
+      return false;
     default: return false;
   }
 }
@@ -664,37 +702,27 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
       default: break;
     }
   }
-  if (narrow_waves(d_k, d_v, a.n_heads, terms, a.feature_map != 0)) {
+  if (pipe_wide(d_k, d_v, a.n_heads, terms)) return launch_chunk_pipe_wide(a, d_k, stream);
+  if (pipe_narrow(d_k, d_v, a.n_heads, terms)) return launch_chunk_pipe_narrow(a, d_k, d_v, io_dtype, stream);
+  if (narrow_waves(d_k, d_v, a.n_heads, terms)) {
     switch (d_k * 1000 + d_v) {
-      case 32032: return launch_io<32, 32, 2>(a, io_dtype, stream);
-      case 32016: return launch_io<32, 16, 2>(a, io_dtype, stream);
       case 64016: return launch_io<64, 16, 4>(a, io_dtype, stream);
       case 64032: return launch_io<64, 32, 4>(a, io_dtype, stream);
-      case 64064: return launch_io<64, 64, 4>(a, io_dtype, stream);
-      case 96016: return launch_io<96, 16, 6>(a, io_dtype, stream);
-      case 96032: return launch_io<96, 32, 6>(a, io_dtype, stream);
-      case 96064: return launch_io<96, 64, 6>(a, io_dtype, stream);
-      case 96096: return launch_io<96, 96, 6>(a, io_dtype, stream);
+      case 64064: return launch_three_terms<64, 64, 4>(a, io_dtype, stream);
+      case 64096: return launch_io<64, 96, 4>(a, io_dtype, stream);
+      case 64128: return launch_io<64, 128, 4>(a, io_dtype, stream);
       case 128016: return launch_io<128, 16, 8>(a, io_dtype, stream);
-      case 128032: return launch_io<128, 32, 8>(a, io_dtype, stream);
-      case 128064: return launch_io<128, 64, 8>(a, io_dtype, stream);
-      case 128096: return launch_io<128, 96, 8>(a, io_dtype, stream);
-      case 128128: return launch_io<128, 128, 8>(a, io_dtype, stream);
       case 32064: return launch_io<32, 64, 2>(a, io_dtype, stream);
       case 32096: return launch_io<32, 96, 2>(a, io_dtype, stream);
       case 32128: return launch_io<32, 128, 2>(a, io_dtype, stream);
-      case 64096: return launch_io<64, 96, 4>(a, io_dtype, stream);
-      case 64128: return launch_io<64, 128, 4>(a, io_dtype, stream);
-      case 96128: return launch_io<96, 128, 6>(a, io_dtype, stream);
       default: break;
     }
   }
-  switch (d_k * 1000 + d_v) {   // d_k = 64: one term only, see narrow_waves
+  switch (d_k * 1000 + d_v) {   // what pipe_wide and pipe_narrow leave; d_k = 64: one term only, see narrow_waves
     case 16016: return launch_io<16, 16, 1>(a, io_dtype, stream);
     case 32032: return launch_io<32, 32, 1>(a, io_dtype, stream);
-    case 64064: return launch_one_term<64, 64, 2>(a, stream);
-    case 96096: return launch_io<96, 96, 3>(a, io_dtype, stream);
-    case 128128: return launch_io<128, 128, 4>(a, io_dtype, stream);
+    case 96096: return launch_one_term<96, 96, 3>(a, stream);
+    case 128128: return launch_three_terms<128, 128, 4>(a, io_dtype, stream);
     case 16032: return launch_io<16, 32, 1>(a, io_dtype, stream);
     case 32016: return launch_io<32, 16, 1>(a, io_dtype, stream);
     case 32064: return launch_io<32, 64, 1>(a, io_dtype, stream);
@@ -707,9 +735,8 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
     case 64096: return launch_one_term<64, 96, 2>(a, stream);
     case 64016: return launch_one_term<64, 16, 2>(a, stream);
     case 96016: return launch_io<96, 16, 3>(a, io_dtype, stream);
-    case 96032: return launch_io<96, 32, 3>(a, io_dtype, stream);
-    case 96064: return launch_io<96, 64, 3>(a, io_dtype, stream);
-    case 96128: return launch_io<96, 128, 3>(a, io_dtype, stream);
+    case 96032: return launch_three_terms<96, 32, 3>(a, io_dtype, stream);
+    case 96064: return launch_one_term<96, 64, 3>(a, stream);
     case 128016: return launch_io<128, 16, 4>(a, io_dtype, stream);
     case 128032: return launch_io<128, 32, 4>(a, io_dtype, stream);
     case 128096: return launch_io<128, 96, 4>(a, io_dtype, stream);

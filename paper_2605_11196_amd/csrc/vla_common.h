@@ -69,6 +69,9 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
 // Same block form, several heads per workgroup (vla_chunk_multihead.hip); head sizes 32 and 64, float32 or mapped q and
 // k.  launch_chunk picks it by head size, head count and operand terms.
 hipError_t launch_chunk_multihead(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream);
+// Same block form, A chain and S chain on waves of their own (vla_chunk_pipe.hip).  launch_chunk picks them.
+hipError_t launch_chunk_pipe_narrow(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
+hipError_t launch_chunk_pipe_wide(const ForwardArgs& a, int d, hipStream_t stream);
 // Same block form with the optional lines of Algorithm 1 (vla_chunk_general.hip); every head size.
 inline bool general_block_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }
 hipError_t launch_chunk_general(const ForwardArgs& a, int d, int d_v, int io_dtype, hipStream_t stream);

@@ -80,6 +80,29 @@ __device__ __forceinline__ void split3_cut(f4 x, u2& h, u2& m, u2& l) {
     l[p] = pack_tops(s0, s1);
   }
 }
+// The same split with the residuals formed by the matrix unit, which subtracts h times the identity from an accumulator
+// tile: operand slot i of a lane is the element in its accumulator register i, so h is used as packed, and x - h has no
+// bits below the last place of x, so that it comes out exactly (the same bits as above).  6 vector and 2 matrix instructions
+// where the above takes 22 vector ones, at twice the latency: for kernels whose waves cover it (vla_chunk_pipe.hip, 2048
+// heads of 128: 2.28 -> 2.00 ms); with two waves per SIMD it gains nothing (vla_chunk.hip: 17.35 and 17.36 ms, 2048 heads
+// of 64 6.69 -> 7.07).
+__device__ __forceinline__ u2 minus_identity() {
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int i = (lane & 15) - 4 * (lane >> 4);   // the slot on the diagonal, if 0..3
+  return u2{i == 0 ? 0x0000bf80u : i == 1 ? 0xbf800000u : 0u, i == 2 ? 0x0000bf80u : i == 3 ? 0xbf800000u : 0u};
+}
+__device__ __forceinline__ f4 residual(f4 x, u2 h, u2 minus_one) {
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, minus_one), __builtin_bit_cast(s4, h), x, 0, 0, 0);
+}
+__device__ __forceinline__ void split3_cut_matrix(f4 x, u2& h, u2& m, u2& l) {
+  const u2 minus_one = minus_identity();
+  h = u2{pack_tops(x[0], x[1]), pack_tops(x[2], x[3])};
+  const f4 r = residual(x, h, minus_one);
+  m = u2{pack_tops(r[0], r[1]), pack_tops(r[2], r[3])};
+  const f4 s = residual(r, m, minus_one);
+  l = u2{pack_tops(s[0], s[1]), pack_tops(s[2], s[3])};
+}
 // x = h + m + l with h and m rounded to nearest: the terms that a product of two split factors leaves out
 // (m l, l m, l l) are then unbiased.
 __device__ __forceinline__ void split3_rne(f4 x, u2& h, u2& m, u2& l) {
@@ -107,10 +130,16 @@ __device__ __forceinline__ u4 cat(u2 a, u2 b) { return u4{a[0], a[1], b[0], b[1]
 template <int NT> struct Terms { u4 t[NT]; };
 
 // Operand terms of two accumulator tiles (32 rows of the contraction).
+template <bool MATRIX = false>
 __device__ __forceinline__ Terms<3> split_tiles(f4 x0, f4 x1) {
   u2 h0, m0, l0, h1, m1, l1;
-  split3_cut(x0, h0, m0, l0);
-  split3_cut(x1, h1, m1, l1);
+  if constexpr (MATRIX) {
+    split3_cut_matrix(x0, h0, m0, l0);
+    split3_cut_matrix(x1, h1, m1, l1);
+  } else {
+    split3_cut(x0, h0, m0, l0);
+    split3_cut(x1, h1, m1, l1);
+  }
   return Terms<3>{{cat(h0, h1), cat(m0, m1), cat(l0, l1)}};
 }
 // acc += a b over 32 columns.  b holds three terms; a one or three.  Small products first.
@@ -283,7 +312,7 @@ struct BlockOps {
   // the sign of the product alternating from block to block, which cancels it: 0.9e-6.  S has no such small directions
   // and is accumulated into.  Rounding of an update: 0.29 units (root mean square); 0.82 accumulated, 1.15 in FP32.
   // Cost, large batch (2048 heads of 128, T = 8192, bf16): 16.4 -> 17.2 ms.
-  template <int N, int NJ, typename X>
+  template <int N, int NJ, bool TIGHT = false, typename X>
   static __device__ __forceinline__ void downdate(const u4* hm, const u2* l, int wrow0, int c, int g, bool odd_block,
                                                   X&& a) {
     if constexpr (SPLIT) {
@@ -293,7 +322,7 @@ struct BlockOps {
 #pragma unroll
       for (int j = 0; j < NJ; ++j) y[j] = tok_image_b(hm, l, wrow0 + 16 * j, c, g, flip);
       // row tiles at a time in registers; one where two column tiles and three-term operands leave no more
-      constexpr int GROUP = (D >= 128 && NT == 3 && NJ > 1) ? 1 : 2;
+      constexpr int GROUP = ((D >= 128 && NT == 3 && NJ > 1) || TIGHT) ? 1 : 2;
 #pragma unroll
       for (int b0 = 0; b0 < N; b0 += GROUP) {
         f4 sum[GROUP][NJ];

@@ -24,7 +24,7 @@ def _value(x):
 @pytest.fixture(scope="module")
 def usage():
     """{kernel: {template arguments: resources}} of the sources with block and segment kernels"""
-    sources = ["vla_chunk.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
+    sources = ["vla_chunk.hip", "vla_chunk_pipe.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
     with ThreadPoolExecutor(len(sources)) as pool:
         reports = list(pool.map(lambda f: build.resource_usage(os.path.join(CSRC, f)), sources))
     out = {}
@@ -42,14 +42,15 @@ def chunk_usage(usage):
     return usage["chunk_kernel"]
 
 
-SQUARE_WAVES = [(16, 1), (32, 1), (32, 2), (64, 2), (64, 4), (96, 3), (96, 6), (128, 4), (128, 8)]
+SQUARE_WAVES = [(16, 1), (32, 1), (64, 4), (96, 3), (128, 4)]   # d = 64, 128: three operand terms only, d = 96: one
 
 
 def test_every_block_kernel_instantiation_is_reported(chunk_usage):
     for d, nw in SQUARE_WAVES:
         for io in ("bf16", "f32"):
             for fmap in (False, True):
-                if d != 64 or nw == 4 or (io == "bf16" and not fmap):   # two waves: one operand term only
+                one_term = io == "bf16" and not fmap
+                if d <= 32 or one_term == (d == 96):
                     assert (d, d, nw, io, fmap, d > 16) in chunk_usage
 
 
@@ -65,20 +66,35 @@ def test_block_kernels_use_no_scratch_and_keep_two_waves_per_simd(chunk_usage, d
         assert r["VGPRs"] + r.get("AGPRs", 0) <= 256 and r["Occupancy"] >= 2, r
 
 
-def test_headline_kernel_fits_two_workgroups_per_compute_unit(chunk_usage):
-    r = chunk_usage[(128, 128, 4, "bf16", False, True)]
-    assert 2 * r["LDSSize"] <= LDS
+def test_headline_kernel_fits_two_workgroups_per_compute_unit(usage):
+    r = usage["chunk_pipe_kernel"][(128, 128, 4, 4, "bf16", False, 4)]
+    assert 2 * r["LDSSize"] <= LDS and r["Occupancy"] >= 4, r
+
+
+def test_two_chain_kernels_hold_the_workgroups_they_are_chosen_for(usage):
+    """(d_k, d_v, waves on A, waves on S): workgroups of a compute unit with one operand term and with three"""
+    for (d, d_v, na, ns), held in {(64, 64, 2, 2): (4, None), (64, 64, 4, 4): (2, 2), (64, 16, 4, 1): (2, 1),
+                                   (64, 128, 4, 8): (1, 1), (32, 32, 2, 2): (4, 4), (32, 96, 2, 6): (2, 2),
+                                   (32, 128, 2, 8): (1, 1), (96, 96, 6, 6): (1, 1), (128, 128, 8, 8): (1, 1)}.items():
+        for io, fmap, n in (("bf16", False, held[0]), ("bf16", True, held[1]), ("f32", False, held[1]), ("f32", True, held[1])):
+            if n:
+                r = next(r for k, r in usage["chunk_pipe_kernel"].items() if k[:6] == (d, d_v, na, ns, io, fmap))
+                assert n * r["LDSSize"] <= LDS and n * (na + ns) <= 4 * r["Occupancy"], r
 
 
 # Known scratch use, in bytes per lane and spilled registers; every other instantiation has none.
 #   chunk_kernel: (d_k, d_v, waves, io, feature map, split products)
+#   chunk_pipe_kernel: (d_k, d_v, waves on A, waves on S, io, feature map, waves per SIMD)
 #   chunk_general_kernel: (d_k, d_v, columns of a wave, io, two sweeps, A chain alone, double buffers, split products)
 #   s_rows_lds_kernel: (d_k, tile slots, other value head size, io, maps, terms, split products, waves per SIMD)
 KNOWN = {
     "chunk_kernel": {
         (128, 96, 4, "bf16", False, True): (8, 1),
-        (96, 128, 3, "f32", False, True): (108, 106), (96, 128, 3, "f32", True, True): (108, 106),
-        (96, 128, 3, "bf16", False, True): (48, 23), (96, 128, 3, "bf16", True, True): (48, 23),
+    },
+    "chunk_pipe_kernel": {
+        (128, 128, 4, 4, "bf16", False, 4): (28, 18),
+        (128, 96, 8, 6, "f32", False, 4): (40, 49), (128, 96, 8, 6, "f32", True, 4): (40, 49),
+        (128, 96, 8, 6, "bf16", True, 4): (40, 49),
     },
     "chunk_general_kernel": {
         (128, 128, 32, "f32", True, False, False, True): (68, 40), (128, 128, 32, "bf16", True, False, False, True): (28, 6),

@@ -541,6 +541,25 @@ def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
     print(d, d_v, heads, dtype, errs)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1, 16, 17, 49])
+@pytest.mark.parametrize("d,d_v,heads", [(128, 128, 257), (128, 32, 256), (96, 128, 300), (96, 32, 300), (64, 64, 257),
+                                         (64, 64, 512), (64, 64, 513), (64, 16, 512), (64, 96, 5), (32, 32, 1024),
+                                         (32, 32, 1025), (32, 96, 512), (32, 128, 256)])
+def test_a_and_s_chains_on_waves_of_their_own(d, d_v, heads, T, dtype):
+    """The block kernel whose S chain runs a block behind its A chain, on both sides of the head counts where it is
+    chosen: no block behind, one whole block, a block of one token, several."""
+    rng = np.random.default_rng(d + heads + T)
+    q, k = (rng.standard_normal((1, heads, T, d)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+    S0 = rng.standard_normal((1, heads, d_v, d)).astype(np.float32)
+    m = rng.standard_normal((1, heads, d, d)).astype(np.float32) / np.float32(np.sqrt(d))
+    A0 = 3 * np.eye(d, dtype=np.float32) + m @ m.transpose(0, 1, 3, 2)
+    A0 = 0.5 * (A0 + A0.transpose(0, 1, 3, 2))
+    errs, _, _ = check_parity(q, k, v, S0, A0, dtype=dtype, mode=2)
+    print(d, d_v, heads, T, dtype, errs)
+
+
 OPTION_SETS = {
     "every option": dict(with_u=True, refresh_period=7, refresh_eta=1e-2, step_offset=3, normalise_output=True,
                          feature_map=True),
