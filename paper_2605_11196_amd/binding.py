@@ -4,6 +4,7 @@ Every step of the recurrence runs in the HIP kernels behind the C ABI
 (include/vla.h); there is no Python or CPU fallback -- if the shared library is
 missing, loading raises.
 """
+import contextlib
 import ctypes
 import os
 
@@ -32,6 +33,8 @@ class VlaOpts(ctypes.Structure):
 
 
 _lib = None
+_default_opts = None      # the library's default options, as bytes
+_SAME_DEVICE = contextlib.nullcontext()
 
 
 def lib_path() -> str:
@@ -40,7 +43,7 @@ def lib_path() -> str:
 
 def load_library():
     """Load libvla.so (built in-tree by paper_2605_11196_amd/build.py). Raises if absent."""
-    global _lib
+    global _lib, _default_opts
     if _lib is not None:
         return _lib
     # PyTorch owns the device memory and the streams handed to the library, so libvla must bind
@@ -72,6 +75,9 @@ def load_library():
     lib.vla_version.restype = I
     lib.vla_resolve_mode.argtypes = [I] * 6 + [OP]
     lib.vla_resolve_mode.restype = I
+    defaults = VlaOpts()
+    lib.vla_default_opts(ctypes.byref(defaults))
+    _default_opts = bytes(defaults)
     _lib = lib
     return lib
 
@@ -85,18 +91,37 @@ def status_string(status: int) -> str:
 
 
 def _opts(lambda0, eps, mode, extra=None):
-    o = VlaOpts()
-    load_library().vla_default_opts(ctypes.byref(o))
+    load_library()
+    o = VlaOpts.from_buffer_copy(_default_opts)
     if lambda0 is not None:
         o.lambda0 = float(lambda0)
     if eps is not None:
         o.eps = float(eps)
     if mode is not None:
         o.mode = int(mode)
-    for key, val in (extra or {}).items():   # u, u_scale, refresh_period, ... (addresses as int)
-        if val is not None:
-            setattr(o, key, val)
+    if extra:
+        for key, val in extra.items():   # u, u_scale, refresh_period, ... (addresses as int)
+            if val is not None:
+                setattr(o, key, val)
     return o
+
+
+def _address(x):
+    return int(x) if x else None
+
+
+def _on_device(torch, dev):
+    """`dev` as the current device; entering it costs a microsecond, so only where another one is current."""
+    return _SAME_DEVICE if dev.index == torch.cuda.current_device() else torch.cuda.device(dev)
+
+
+def _stream_handle(torch, dev, stream):
+    """The handle of the caller's stream (torch's current one by default), and the torch stream that the tensors allocated
+    for the call have to be recorded on: none on the current stream, which they are allocated on."""
+    if stream is None:   # the handle alone: a torch.cuda.Stream object costs two microseconds
+        return torch._C._cuda_getCurrentRawStream(dev.index), None
+    handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    return handle, stream if isinstance(stream, torch.cuda.Stream) else None
 
 
 def vla_forward_workspace_bytes(B, H, T, d_k, d_v, io_dtype, *, lambda0=None, eps=None,
@@ -118,7 +143,7 @@ def vla_forward_raw(q, k, v, S0, A0, o, S_T, A_T, B, H, T, d_k, d_v, io_dtype, *
     """Direct call with integer device addresses (0 = NULL); returns the vla_status.
     `extra`: further vla_opts fields by name (u, zkey0, zkey_T as integer addresses)."""
     op = _opts(lambda0, eps, mode, extra)
-    n = lambda x: ctypes.c_void_p(int(x) if x else None)
+    n = _address
     return int(load_library().vla_forward(n(q), n(k), n(v), n(S0), n(A0), n(o), n(S_T), n(A_T),
                                           B, H, T, d_k, d_v, io_dtype, ctypes.byref(op),
                                           n(workspace), int(workspace_bytes), n(stream)))
@@ -128,7 +153,7 @@ def vla_forward_static_raw(q, k, v, S0, A0, o, S_T, A_T, B, H, T, d_k, d_v, io_d
                            eps=None, mode=None, stream=0, **extra) -> int:
     """vla_forward_raw without a workspace: the library's static array serves the modes that need one."""
     op = _opts(lambda0, eps, mode, extra)
-    n = lambda x: ctypes.c_void_p(int(x) if x else None)
+    n = _address
     return int(load_library().vla_forward_static(n(q), n(k), n(v), n(S0), n(A0), n(o), n(S_T), n(A_T),
                                                  B, H, T, d_k, d_v, io_dtype, ctypes.byref(op), n(stream)))
 
@@ -136,7 +161,7 @@ def vla_forward_static_raw(q, k, v, S0, A0, o, S_T, A_T, B, H, T, d_k, d_v, io_d
 def vla_decode_step_raw(q, k, v, S, A, o, B, H, d_k, d_v, io_dtype, *, eps=None, stream=0, **extra) -> int:
     """Direct call with integer device addresses; returns the vla_status."""
     op = _opts(None, eps, None, extra)
-    n = lambda x: ctypes.c_void_p(int(x) if x else None)
+    n = _address
     return int(load_library().vla_decode_step(n(q), n(k), n(v), n(S), n(A), n(o), B, H, d_k, d_v,
                                               io_dtype, ctypes.byref(op), n(stream)))
 
@@ -161,28 +186,39 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
         raise ValueError("expected q,k [B,H,d_k] and v [B,H,d_v] of one dtype")
     B, H, dk = q.shape
     dv = v.shape[-1]
+    dev = q.device
     for name, x, shape in (("S", S, (B, H, dv, dk)), ("A", A, (B, H, dk, dk)), ("zkey", zkey, (B, H, dk))):
-        if x is not None and (x.dtype != torch.float32 or tuple(x.shape) != shape or not x.is_contiguous()
-                              or x.device != q.device):
-            raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {q.device}")
+        if x is not None and (x.dtype != torch.float32 or x.shape != shape or not x.is_contiguous()
+                              or x.device != dev):
+            raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
     if u is not None and (u.dtype != q.dtype or tuple(u.shape) != tuple(q.shape) or u.device != q.device):
         raise ValueError("u must match q in dtype, shape and device")
     q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
     u = None if u is None else u.contiguous()
-    p = lambda x: None if x is None else x.data_ptr()
-    with torch.cuda.device(q.device):
-        o = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
-        st = stream if stream is not None else torch.cuda.current_stream(q.device)
-        handle = st.cuda_stream if hasattr(st, "cuda_stream") else int(st)
-        if isinstance(st, torch.cuda.Stream):
-            o.record_stream(st)
-        extra = dict(u=p(u), u_scale=u_scale, refresh_period=refresh_period, refresh_eta=refresh_eta,
-                     step_offset=step_offset,
-                     normalise_output=None if normalise_output is None else int(bool(normalise_output)),
-                     feature_map=None if feature_map is None else int(bool(feature_map)),
-                     zkey0=p(zkey), zkey_T=p(zkey))
-        rc = vla_decode_step_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), S.data_ptr(), A.data_ptr(),
-                                 o.data_ptr(), B, H, dk, dv, io, eps=eps, stream=handle, **extra)
+    op = _opts(None, eps, None)
+    if u is not None:
+        op.u = u.data_ptr()
+    if zkey is not None:
+        op.zkey0 = op.zkey_T = zkey.data_ptr()
+    if u_scale is not None:
+        op.u_scale = u_scale
+    if refresh_period is not None:
+        op.refresh_period = refresh_period
+    if refresh_eta is not None:
+        op.refresh_eta = refresh_eta
+    if step_offset is not None:
+        op.step_offset = step_offset
+    if normalise_output is not None:
+        op.normalise_output = bool(normalise_output)
+    if feature_map is not None:
+        op.feature_map = bool(feature_map)
+    with _on_device(torch, dev):
+        o = torch.empty((B, H, dv), dtype=q.dtype, device=dev)
+        handle, other = _stream_handle(torch, dev, stream)
+        if other is not None:
+            o.record_stream(other)
+        rc = _lib.vla_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), S.data_ptr(), A.data_ptr(), o.data_ptr(),
+                                  B, H, dk, dv, io, ctypes.byref(op), handle)
     if rc != 0:
         raise VlaError(rc, status_string(rc))
     return o
@@ -220,9 +256,7 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != shape
                               or not s.is_contiguous() or s.device != dev):
             raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
-    st = stream if stream is not None else torch.cuda.current_stream(dev)
-    handle = st.cuda_stream if hasattr(st, "cuda_stream") else int(st)
-    p = lambda x: 0 if x is None else x.data_ptr()
+    p = lambda x: None if x is None else x.data_ptr()
     if u is not None:
         if u.dtype != q.dtype or tuple(u.shape) != tuple(q.shape) or u.device != dev:
             raise ValueError("u must match q in dtype, shape and device")
@@ -230,29 +264,30 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
     if zkey0 is not None and (zkey0.dtype != torch.float32 or tuple(zkey0.shape) != (B, H, dk)
                               or not zkey0.is_contiguous() or zkey0.device != dev):
         raise ValueError(f"zkey0 must be a contiguous float32 tensor of shape {(B, H, dk)} on {dev}")
-    with torch.cuda.device(dev):
+    with _on_device(torch, dev):
+        handle, other = _stream_handle(torch, dev, stream)
         o = torch.empty((B, H, T, dv), dtype=q.dtype, device=dev)
         S_T = torch.empty((B, H, dv, dk), dtype=torch.float32, device=dev) if return_state else None
         A_T = torch.empty((B, H, dk, dk), dtype=torch.float32, device=dev) if return_state else None
         zkey_T = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if return_zkey else None
-        extra = dict(u=p(u) or None, u_scale=u_scale, refresh_period=refresh_period,
-                     refresh_eta=refresh_eta, step_offset=step_offset,
-                     normalise_output=None if normalise_output is None else int(bool(normalise_output)),
-                     feature_map=None if feature_map is None else int(bool(feature_map)),
-                     zkey0=p(zkey0) or None, zkey_T=p(zkey_T) or None, segments=segments)
+        op = _opts(lambda0, eps, mode,
+                   dict(u=p(u), u_scale=u_scale, refresh_period=refresh_period, refresh_eta=refresh_eta,
+                        step_offset=step_offset,
+                        normalise_output=None if normalise_output is None else int(bool(normalise_output)),
+                        feature_map=None if feature_map is None else int(bool(feature_map)),
+                        zkey0=p(zkey0), zkey_T=p(zkey_T), segments=segments))
         # the same options as the call, so that the query resolves AUTO to the mode the call will run
-        need = vla_forward_workspace_bytes(B, H, T, dk, dv, io, lambda0=lambda0, eps=eps, mode=mode, **extra)
+        need = _lib.vla_forward_workspace_bytes(B, H, T, dk, dv, io, ctypes.byref(op))
         ws = torch.empty((max(need, 16),), dtype=torch.uint8, device=dev) if need else None
-        # These tensors come from the allocator of torch's current stream while the kernels run on `st`: tell the
-        # allocator, so that memory dropped here (the workspace when this function returns) is not handed to
-        # other work before the kernels on `st` are done with it.
-        if isinstance(st, torch.cuda.Stream):
+        # These tensors come from the allocator of torch's current stream while the kernels run on the caller's: tell
+        # the allocator, so that memory dropped here (the workspace when this function returns) is not handed to
+        # other work before the kernels there are done with it.
+        if other is not None:
             for t in (o, S_T, A_T, zkey_T, ws):
                 if t is not None:
-                    t.record_stream(st)
-        rc = vla_forward_raw(p(q), p(k), p(v), p(S0), p(A0), p(o), p(S_T), p(A_T), B, H, T, dk, dv,
-                             io, lambda0=lambda0, eps=eps, mode=mode, workspace=p(ws),
-                             workspace_bytes=need, stream=handle, **extra)
+                    t.record_stream(other)
+        rc = _lib.vla_forward(p(q), p(k), p(v), p(S0), p(A0), p(o), p(S_T), p(A_T), B, H, T, dk, dv, io,
+                              ctypes.byref(op), p(ws), need, handle)
     if rc != 0:
         raise VlaError(rc, status_string(rc))
     if return_zkey:
