@@ -684,12 +684,23 @@ static bool fp32_products(int d_k, int d_v, int n_heads) {
   return d_v <= 64 && fewer_rounds_unsplit(d_k, n_heads);
 }
 
+// Key heads of 16: the blocks of 256 tokens at once (vla_chunk_d16.hip)?  A span costs a workgroup of 16 waves 14 us however
+// few of its blocks there are, a block 3 us here, where a compute unit holds eight heads: one head, 64 tokens 18 us here,
+// 80 tokens 17 / 14, 256 50 / 17; 2048 tokens, 256 heads 0.411 / 0.139 ms, 512 heads 0.419 / 0.278, 768 heads 0.42 either
+// way; d_v = 64, 1024 tokens, 256 heads 0.265 / 0.105.  That kernel starts from the inverse of A0, so a given A0 (which need
+// not have one) stays here, and so do value heads whose maps do not fit the LDS; from lambda0 = 1e-6 on the condition of
+// what it inverts, (lambda0 + tokens) / lambda0, leaves float64 the digits that float32 needs.
+static bool blocks_at_once(const ForwardArgs& a, int d_v) {
+  return d_v <= 64 && a.A0 == nullptr && a.lambda0 >= 1e-6f && a.n_heads <= 512 && a.T >= 64;
+}
+
 // The waves of a head share out the d_v / 16 row tiles of S, evenly where the counts divide and one by one in turn where
 // they do not: every pair of head sizes runs.
 bool chunk_supported(int d_k, int d_v) { return chunk_supported(d_k) && chunk_supported(d_v); }
 
 hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream) {
   const int terms = operand_terms(a, io_dtype);
+  if (d_k == 16 && blocks_at_once(a, d_v)) return launch_chunk_d16(a, d_v, io_dtype, stream);
   if (terms == 3 && d_k == d_v && fewer_rounds_unsplit(d_k, a.n_heads)) return launch_chunk_multihead(a, d_k, io_dtype, stream);
   if (terms == 3 && fp32_products(d_k, d_v, a.n_heads)) {
     switch (d_k * 1000 + d_v) {

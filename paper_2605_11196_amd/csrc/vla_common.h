@@ -72,6 +72,8 @@ hipError_t launch_chunk_multihead(const ForwardArgs& a, int d, int io_dtype, hip
 // Same block form, A chain and S chain on waves of their own (vla_chunk_pipe.hip).  launch_chunk picks them.
 hipError_t launch_chunk_pipe_narrow(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
 hipError_t launch_chunk_pipe_wide(const ForwardArgs& a, int d, hipStream_t stream);
+// Key heads of 16, no given A0, d_v <= 64: the blocks of 256 tokens at once (vla_chunk_d16.hip).  launch_chunk picks it.
+hipError_t launch_chunk_d16(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t stream);
 // Same block form with the optional lines of Algorithm 1 (vla_chunk_general.hip); every head size.
 inline bool general_block_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }
 hipError_t launch_chunk_general(const ForwardArgs& a, int d, int d_v, int io_dtype, hipStream_t stream);

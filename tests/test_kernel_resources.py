@@ -24,7 +24,7 @@ def _value(x):
 @pytest.fixture(scope="module")
 def usage():
     """{kernel: {template arguments: resources}} of the sources with block and segment kernels"""
-    sources = ["vla_chunk.hip", "vla_chunk_pipe.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
+    sources = ["vla_chunk.hip", "vla_chunk_pipe.hip", "vla_chunk_d16.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
     with ThreadPoolExecutor(len(sources)) as pool:
         reports = list(pool.map(lambda f: build.resource_usage(os.path.join(CSRC, f)), sources))
     out = {}
@@ -102,6 +102,7 @@ KNOWN = {
         (32, 128, 16, "f32", True, False, False, True): (12, 2),
         (64, 32, 16, "f32", True, False, False, True): (36, 8), (64, 64, 16, "f32", True, False, False, True): (36, 8),
     },
+    "chunk_d16_kernel": {},
     "a_scan_kernel": {},
     "s_rows_lds_kernel": {
         (128, 1, False, "f32", False, 3, True, 4): (96, 35), (128, 1, False, "f32", True, 3, True, 4): (20, 8),

@@ -560,6 +560,25 @@ def test_a_and_s_chains_on_waves_of_their_own(d, d_v, heads, T, dtype):
     print(d, d_v, heads, T, dtype, errs)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d_v,heads,T", [(16, 1, 63), (16, 1, 64), (16, 3, 255), (16, 3, 256), (16, 5, 257), (32, 3, 272),
+                                         (32, 2, 530), (64, 3, 300), (64, 1, 513), (96, 3, 300), (16, 512, 70),
+                                         (16, 513, 70)])
+def test_key_heads_of_16_take_the_blocks_of_a_span_at_once(d_v, heads, T, dtype):
+    """Spans that end inside a block, with one block and with none behind them, given S, keys of zero and one repeated."""
+    rng = np.random.default_rng(heads + T)
+    q, k = (rng.standard_normal((1, heads, T, 16)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+    k[:, :, 20:40] = 0
+    k[:, :, 41:50] = k[:, :, 40:41]
+    S0 = rng.standard_normal((1, heads, d_v, 16)).astype(np.float32)
+    # a float32 state is good to 6e-8 of its condition, (lambda0 + about 20 tokens in a direction) / lambda0: 1.2e-5 at the
+    # default 0.1 and below that at 1, inside the tolerance of 1e-4 (at 1e-3 it would be 1.2e-3)
+    for kwargs in ({}, {"lambda0": 1.0}):
+        errs, _, _ = check_parity(q, k, v, S0, dtype=dtype, mode=2, **kwargs)
+        print(d_v, heads, T, dtype, kwargs, errs)
+
+
 OPTION_SETS = {
     "every option": dict(with_u=True, refresh_period=7, refresh_eta=1e-2, step_offset=3, normalise_output=True,
                          feature_map=True),
