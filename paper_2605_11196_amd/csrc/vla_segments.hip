@@ -37,7 +37,7 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // runs in the d = 128 layout with the columns from 96 on held at zero (the loads, the staging and the final
 // stores skip them; three of the four waves then form the products).
 template <int D, int DL, typename IO>
-__global__ void __launch_bounds__(kThreads, D <= 64 ? 3 : 2) gram_kernel(ForwardArgs a, double* G) {
+__device__ __forceinline__ void gram_sum(const ForwardArgs& a, double* G) {
   static_assert(DL <= D && DL % 16 == 0, "padded layout");
   constexpr int NTI = D / 16;                                // tiles per side
   constexpr int TR = NTI * NTI <= 16 ? NTI : 16 / NTI;       // tile rows per wave
@@ -426,6 +426,50 @@ struct SpdInverse {
   }
 };
 
+template <int D, int DL, typename IO>
+__global__ void __launch_bounds__(kThreads, D <= 64 ? 3 : 2) gram_kernel(ForwardArgs a, double* G) {
+  gram_sum<D, DL, IO>(a, G);
+}
+
+// With a caller's A0 the workgroup of a head's last segment, which has no sum to form, inverts A0 into that segment's
+// place in G: beside the sums instead of once more in front of every boundary inverse (39 heads of 128, 6 segments, T = 1537,
+// float32: the two kernels 140 -> 111 us).  DL < D: bordered with an identity block, whose inverse is itself and which is
+// left out of the result.
+template <int D, int DL, typename IO>
+__global__ void __launch_bounds__(SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads, 2)
+gram_given_a0_kernel(ForwardArgs a, double* G) {
+  constexpr int NTL = SpdInverse<D>::NTL;
+  __shared__ __align__(16) double colp[SpdInverse<D>::LDS_DOUBLES];
+  const int head = blockIdx.x / a.n_seg;
+  if (static_cast<int>(blockIdx.x) - head * a.n_seg != a.n_seg - 1) {   // uniform over the workgroup
+    if (threadIdx.x < kThreads) gram_sum<D, DL, IO>(a, G);              // whole waves
+    return;
+  }
+  if (threadIdx.x >= SpdInverse<D>::NT) return;
+  const float* A0 = a.A0 + static_cast<size_t>(head) * DL * DL;
+  double* out = G + static_cast<size_t>(blockIdx.x) * DL * DL;
+  const int c = threadIdx.x & 15;
+  const int i0 = 16 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4);   // acc[tj][r] = M[i0 + 4 r][16 tj + c]
+  d4 acc[NTL];
+#pragma unroll
+  for (int tj = 0; tj < NTL; ++tj)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r, j = 16 * tj + c;
+      acc[tj][r] = D == DL || (i < DL && j < DL)
+                       ? 0.5 * (static_cast<double>(A0[i * DL + j]) + static_cast<double>(A0[j * DL + i]))
+                       : (i == j ? 1.0 : 0.0);
+    }
+  SpdInverse<D>{colp}.run(acc);
+#pragma unroll
+  for (int tj = 0; tj < NTL; ++tj)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r, j = 16 * tj + c;
+      if (D == DL || (i < DL && j < DL)) out[i * DL + j] = acc[tj][r];
+    }
+}
+
 // One workgroup per (head, segment): seg_A = inverse(inverse(A0) + sum of the Gram matrices before it),
 // G holding the prefix sums.
 // DL: the head size of the data; D >= DL: the size the inversion is laid out for (d = 96 runs in the d = 128
@@ -453,17 +497,15 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 64 ? 4 : 2) boundary_k
   auto data = [&](int i, int j) { return D == DL || (i < DL && j < DL); };   // inside the DL x DL matrix
   const SpdInverse<D> inv{colp};
   d4 acc[NTL];
-  if (A0) {
+  if (A0) {   // its inverse is in the last segment's place
+    const double* inv0 = G + (static_cast<size_t>(head) * a.n_seg + a.n_seg - 1) * DL * DL;
 #pragma unroll
     for (int tj = 0; tj < NTL; ++tj)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = i0 + 4 * r, j = 16 * tj + c;
-        acc[tj][r] = data(i, j) ? 0.5 * (static_cast<double>(A0[i * DL + j]) + static_cast<double>(A0[j * DL + i]))
-                                : (i == j ? 1.0 : 0.0);
+        acc[tj][r] = data(i, j) ? inv0[i * DL + j] : (i == j ? 1.0 : 0.0);
       }
-    inv.run(acc);
-    __syncthreads();   // the pivot buffers are reused by the second inversion
   } else {
 #pragma unroll
     for (int tj = 0; tj < NTL; ++tj)
@@ -589,8 +631,10 @@ template <int D, typename IO, int DL = D>
 hipError_t launch_gram_d(const ForwardArgs& a, double* G, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args, &G};
-  hipError_t err = hipLaunchKernel(reinterpret_cast<const void*>(&gram_kernel<D, DL, IO>),
-                                   dim3(a.n_heads * a.n_seg), dim3(kThreads), params, 0, stream);
+  const void* fn = a.A0 ? reinterpret_cast<const void*>(&gram_given_a0_kernel<D, DL, IO>)
+                        : reinterpret_cast<const void*>(&gram_kernel<D, DL, IO>);
+  const int threads = a.A0 && SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads;
+  hipError_t err = hipLaunchKernel(fn, dim3(a.n_heads * a.n_seg), dim3(threads), params, 0, stream);
   if (err != hipSuccess) return err;
   int nh = a.n_heads, ns = a.n_seg, dd = DL * DL;
   void* p2[] = {&G, &nh, &ns, &dd};
