@@ -262,8 +262,9 @@ struct BlockOps {
     return x;
   }
   // two accumulator tiles (one without the split) as the other operand
+  template <bool MATRIX = false>
   static __device__ __forceinline__ auto tiles(f4 x0, f4 x1) {
-    if constexpr (SPLIT) return split_tiles(x0, x1);
+    if constexpr (SPLIT) return split_tiles<MATRIX>(x0, x1);
     else return x0;
   }
   template <typename X>

@@ -342,7 +342,9 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       const auto ka = Prod::operand(Ks, kb, c, g);
 #pragma unroll
       for (int jn = 0; jn < NJ; ++jn)
-        yt[jn] = Prod::sweep(ka, Prod::tiles(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
+        // with the map runs beside it (MAPF) the residuals of the split go to the matrix unit: 16 heads of 64, T = 131072,
+        // 1.612 -> 1.592 ms; without them nothing (T = 4096: 0.150 -> 0.151), and nothing for the splits of the map runs
+        yt[jn] = Prod::sweep(ka, Prod::template tiles<MAPF>(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
       if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one step's splits at a time in registers
     }
     f4 rn4 = f4{1, 1, 1, 1};
