@@ -124,31 +124,33 @@ int pick_mode(int B, int H, int T, int d, int d_v, const vla_opts& o) {
     return needs_general_kernel(o) ? with_options : VLA_MODE_CHUNKED;
   }
   const long long heads = static_cast<long long>(B) * H;
-  // Measured crossovers against the fused block kernel (bf16, one MI355X; time-parallel against block kernel, ms).
-  // The segment kernels gain on the block kernel as the sequence grows (their fixed passes amortise):
-  //   d = 128:  T = 2048: 64 heads 0.46 / 0.74, 80 heads 0.57 / 0.74;  T = 4096: 96 heads 1.10 / 1.46, 128: 1.33 / 1.46;
-  //             T = 8192: 128 heads 2.47 / 2.93, 160: 3.16 / 2.93;     T = 32768: 128 heads 9.97 / 11.6, 160: 13.0 / 11.7
-  //   d =  96:  T = 1024: 64 heads 0.25 / 0.30, 96: 0.38 / 0.31;       T = 2048: 64 heads 0.39 / 0.61, 80: 0.48 / 0.61;
-  //             T = 4096: 128 heads 1.06 / 1.21, 160: 1.35 / 1.21;     T = 32768: 128 heads 7.79 / 9.58, 160: 10.2 / 9.60
-  //   d =  64:  T = 2048: 192 heads 0.39 / 0.48, 256: 0.46 / 0.47, 320: 0.56 / 0.55;   T = 4096: 320 heads 1.05 / 1.10,
-  //             384: 1.36 / 1.10;                                      T = 16384: 320 heads 3.98 / 4.37, 384: 5.38 / 4.39
-  //   d =  32:  T = 2048: 512 heads 0.47 / 0.49, 640: 0.55 / 0.50;     T = 16384: 512 heads 3.50 / 3.89, 640: 4.33 / 3.96
+  // Time-parallel mode or block kernel (bf16, one MI355X; time-parallel against block kernel, ms).  The segment kernels
+  // gain on the block kernel as the sequence grows (their fixed passes amortise):
+  //   d = 128:  T = 2048: 64 heads 0.48 / 0.60, 80 heads 0.59 / 0.60;  T = 4096: 96 heads 1.13 / 1.24, 128: 1.34 / 1.25;
+  //             T = 8192: 128 heads 2.49 / 2.50;                       T = 16384: 128 heads 4.90 / 4.99
+  //   d =  96:  T = 1024: 48 heads 0.23 / 0.24, 64: 0.26 / 0.24;       T = 2048: 64 heads 0.40 / 0.46, 96: 0.52 / 0.47;
+  //             T = 4096: 96 heads 0.88 / 0.98, 128: 1.07 / 0.99;      T = 16384: 128 heads 3.95 / 3.94
+  //   d =  64:  T = 2048: 128 heads 0.31 / 0.36, 192: 0.40 / 0.35;     T = 4096: 192 heads 0.72 / 0.77, 320: 1.05 / 0.90;
+  //             T = 16384: 192 heads 2.46 / 3.08, 320: 3.97 / 3.55
+  //   d =  32:  T = 2048: 320 heads 0.32 / 0.34, 512: 0.47 / 0.35;     T = 16384: 320 heads 2.31 / 2.81, 512: 3.49 / 2.84
+  // The thresholds lie above the present crossovers in places: they were measured when the block kernel took up to 1.4
+  // times as long, and they stay because every segment restarts from a float64 inverse, which calls that moved to the
+  // block kernel would lose (error of A at d = 64, T = 131072: 1e-6 against 2.6e-5).
   const int t_128 = d == 96 ? 4096 : 8192;   // from here 128 heads still gain at d >= 96
   long long few = d >= 96 ? (T >= t_128 ? 128 : (T >= 4096 ? 96 : 64))
                           : (d >= 64 ? (T >= 4096 ? 320 : 192) : 512);
   // Value heads of another size than the key heads: the same thresholds by the key head size, a notch higher
-  // where measured (the block kernel shares the row tiles of S out unevenly, the S rows kernel of the segment
-  // modes takes them in turn).  T = 4096: d_k = 64, d_v = 128: 384 heads 2.45 / 2.89, 448: 3.05 / 2.88; d_v = 16:
-  // 384 heads 1.56 / 1.68;  d_k = 128, d_v = 64: 128 heads 1.50 / 1.62, 160: 1.88 / 1.63; d_v = 16: 128 heads
-  // 1.36 / 1.59;  d_k = 32, d_v = 128: 1280 heads 3.25 / 3.58 (T = 1024: 0.83 / 0.90).
+  // where measured (the S rows kernel of the segment modes takes the row tiles of S in turn).  T = 4096, now: d_k = 64,
+  // d_v = 128: 160 heads 0.88 / 0.90, 384: 1.94 / 1.28; d_v = 16: 192 heads 0.69 / 0.74, 384: 1.36 / 0.89; d_k = 128, d_v = 64:
+  // 96 heads 1.01 / 1.11, 128: 1.22 / 1.11; d_v = 16: 128 heads 1.16 / 1.19; d_k = 32, d_v = 128: 192 heads 0.74 / 0.75.
   if (d != d_v) {
     if (d == 64 && T >= 4096) few = 384;
     if (d == 128 && T >= 4096) few = 128;
     if (d == 32 && d_v == 128) few = 1280;
   }
-  // Short sequences (half the length): 64 heads at d = 64, T = 512: 0.092 against 0.122 ms, 128 heads 0.140 against
-  // 0.122; 256 heads at d = 32: 0.114 against 0.104.  Not at d = 96, whose Gram sums and boundary inverses run in the d = 128 layout (T = 512:
-  // 16 heads 0.26 against 0.21).
+  // Short sequences (half the length), T = 512: 48 heads at d = 64 0.087 against 0.089 ms, 64: 0.093 against 0.088; 64 heads
+  // at d = 32 0.061 against 0.071, 128: 0.098 against 0.073; 2 heads at d = 128 0.127 against 0.149, 16: 0.163 against 0.149.
+  // Not at d = 96, whose Gram sums and boundary inverses run in the d = 128 layout.
   const long long few_short = d >= 96 ? 32 : (d >= 64 ? 64 : 256);
   const int t_short = d == 96 ? 1024 : 512;
   const bool take = T >= 1024 ? heads <= few : (T >= t_short && heads <= few_short);

@@ -1,8 +1,8 @@
 """Build-time check of the registers and the LDS the compiler gives the block and segment kernels (CPU only: hipcc
 cross-compiles).
 
-The headline kernel keeps 128 state registers per lane and runs two waves per SIMD, so it sits at the
-256-register limit: a change that pushes values into scratch memory inside the token loop would cost time on
+The headline kernel keeps 64 state registers per lane and runs four waves per SIMD, so it sits at the
+128-register limit: a change that pushes values into scratch memory inside the token loop would cost time on
 every block without failing any numerical test.  The compiler's own resource remarks are parsed here."""
 import os
 import re
