@@ -39,8 +39,9 @@ __device__ __forceinline__ double readlane(double x, int lane) {
 }
 
 // In-place inverse of a symmetric positive definite 16 x 16 matrix, m[r] = M[g + 4r][c] (the result layout of the float64
-// matrix instruction), by Gauss-Jordan.  With the pivot d taken as d - 1 in its column and as 1 + 1/d in its scaled row,
-// every element takes the same update m -= column * row.
+// matrix instruction), by Gauss-Jordan.  With 1 + 1/d in the place of the pivot d in its scaled row, every element off that
+// row takes the same update m -= column * row; the pivot row is then the scaled row with 1/d itself, which the update could
+// not form for a large d (as d - (d - 1)(1 + 1/d) it carries a relative error of 1e-16 d^2).
 template <int P>
 __device__ __forceinline__ void invert_from(d4& m, int c, int g) {
   if constexpr (P < 16) {
@@ -51,11 +52,8 @@ __device__ __forceinline__ void invert_from(d4& m, int c, int g) {
     ri = fma(fma(-d, ri, 1.0), ri, ri);
     x = c == P ? 1.0 + ri : x * ri;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double y = row_bcast<P>(m[r]);                  // M[g + 4r][P]
-      if (r == P / 4 && g == P % 4) y -= 1.0;
-      m[r] = fma(-y, x, m[r]);
-    }
+    for (int r = 0; r < 4; ++r) m[r] = fma(-row_bcast<P>(m[r]), x, m[r]);   // M[g + 4r][P]
+    if (g == P % 4) m[P / 4] = c == P ? ri : x;
     invert_from<P + 1>(m, c, g);
   }
 }
