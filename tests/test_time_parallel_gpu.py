@@ -81,6 +81,29 @@ def test_given_initial_state_enters_the_boundary_inverse(d):
     assert max(errs.values()) <= TOL["f32"], errs
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("lambda0", [1e3, 1e6, 1e9, 1e30])
+def test_boundary_inverse_of_large_elements(lambda0, d):
+    """The block kernel is at 4e-7 and below over this range."""
+    q, k, v = vla_inputs.gaussian_qkv(1, 3, 200, d, seed=80 + d)
+    errs, _, _ = check_parity(q, k, v, lambda0=lambda0, mode=TP, segments=4, tol=1e-5)
+    print(lambda0, d, errs)
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("grades", [(-9, -9), (-8, 0)])
+def test_given_initial_state_of_small_or_graded_elements(grades, d):
+    """A0 with diagonal elements from 10^grades[0] to 10^grades[1], whose inverse has their reciprocals.  It is inverted twice,
+    and A0 as small as 1e-9 passes both inverses all but unchanged."""
+    q, k, v = vla_inputs.gaussian_qkv(1, 3, 200, d, seed=90 + d)
+    R = np.random.default_rng(d).standard_normal((1, 3, d, d)) / np.sqrt(d)
+    scale = 10.0 ** (0.5 * np.linspace(*grades, d))
+    A0 = (scale[:, None] * (np.eye(d) + R @ np.swapaxes(R, -1, -2)) * scale).astype(np.float32)
+    A0 = 0.5 * (A0 + np.swapaxes(A0, -1, -2))
+    errs, _, _ = check_parity(q, k, v, None, A0, mode=TP, segments=4, tol=1e-5)
+    print(grades, d, errs)
+
+
 def test_recall_workload_with_zero_and_repeated_directions():
     """Mostly all-zero tokens and few distinct keys: the Gram sums are low-rank, so the boundary matrix
     lambda0 I + G has many eigenvalues equal to lambda0."""
