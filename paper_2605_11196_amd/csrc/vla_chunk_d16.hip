@@ -3,9 +3,12 @@
 //
 // Without the identity refresh A at the start of a block is an explicit inverse, (A_0^{-1} + sum k^ k^T)^{-1} (Section 3.2,
 // eq. (penalty); eq. (sm) is its Sherman-Morrison form), and at d = 16 that is one tile: every wave sums the Gram tiles of
-// the blocks before its own and inverts the sum, both in float64 (the k^ are the float32 numbers the recurrence uses, and
-// their products are exact in float64).  From there each wave does the C x C work of its block (the algebra is at the head
-// of vla_chunk.hip) and forms what its block does to S, which is affine:
+// the blocks before its own, inverts the sum and forms K^ A, all in float64 (the k^ are the float32 numbers the recurrence
+// uses, and their products are exact in float64).  K^ A has to come from the unrounded inverse: along keys seen often A k^
+// is far below the elements of A, and where the recurrence keeps the two consistent step by step, an inverse rounded to
+// float32 does not (8192 tokens of four keys, lambda0 = 0.1: error of o 1e-2; lambda0 = 1e-6, 500 tokens: beyond 1e20).
+// From there each wave does the C x C work of its block (the algebra is at the head of vla_chunk.hip) and forms what its
+// block does to S, which is affine:
 //
 //   S1^T = S0^T + W diag(c) E^T,  E^T = Z (V - K^ S0^T)    =>    S1^T = S0^T + P' S0^T + Q,
 //   P' = -(W diag(c)) (Z K^),  Q = (W diag(c)) (Z V)
@@ -123,7 +126,7 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
     const int t0 = C * blk;
     const bool live = t0 < T;   // uniform in a wave
     const int here = nblk - b0 < NW ? nblk - b0 : NW;   // blocks of this span
-    f4 ka = f4{0, 0, 0, 0}, qa = f4{0, 0, 0, 0}, kt, vt[TV];
+    f4 ka = f4{0, 0, 0, 0}, qa = f4{0, 0, 0, 0}, kt, kc, vt[TV];
     if (live) {
       float kx[4], qx[4];
       kr.unpack(kx);
@@ -153,7 +156,10 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
       *reinterpret_cast<f4*>(&T0[c * LT + 4 * g]) = ka;
       // same-wave write -> read: LDS operations of one wave are ordered
 #pragma unroll
-      for (int r = 0; r < 4; ++r) kt[r] = T0[(4 * g + r) * LT + c];   // K^[4g + r][c]
+      for (int r = 0; r < 4; ++r) {
+        kt[r] = T0[(4 * g + r) * LT + c];   // K^[4g + r][c]
+        kc[r] = T0[c * LT + 4 * r + g];     // K^[c][g + 4r]
+      }
       d4 gram = d4{0, 0, 0, 0};
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -178,13 +184,15 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
       for (int r = 0; r < 4; ++r) total[r] += Gs[w][(g + 4 * r) * D + c];
     }
     if (live) {
-      // ================= A at the start of the block: At[r] = A[4g + r][c], exactly symmetric
-      f4 At;
+      // ================= A at the start of the block, m[r] = A[g + 4r][c]
       if (blk == 0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) At[r] = 4 * g + r == c ? diag : 0.0f;
+        for (int r = 0; r < 4; ++r) m[r] = g + 4 * r == c ? static_cast<double>(diag) : 0.0;
       } else {
         invert_from<0>(m, c, g);
+      }
+      f4 At = f4{0, 0, 0, 0};   // A[4g + r][c], exactly symmetric, for A after the last block
+      if (blk == nblk - 1 && a.A_T) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) T0[(g + 4 * r) * LT + c] = static_cast<float>(m[r]);
         const f4 across = lds4(&T0[c * LT + 4 * g]);
@@ -193,11 +201,19 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
       }
       fresh();
       // ================= Y^T = K^ A, Gram matrices
-      f4 yt = f4{0, 0, 0, 0}, gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
+      f4 yt, gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
+      {
+        d4 y0 = d4{0, 0, 0, 0}, y1 = d4{0, 0, 0, 0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) yt = mfma16(ka[r], At[r], yt);
+        for (int r = 0; r < 4; r += 2) {
+          y0 = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(kc[r]), m[r], y0, 0, 0, 0);
+          y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(kc[r + 1]), m[r + 1], y1, 0, 0, 0);
+        }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) T0[(4 * g + r) * LT + c] = yt[r];
+        for (int r = 0; r < 4; ++r) T0[(g + 4 * r) * LT + c] = static_cast<float>(y0[r] + y1[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) yt[r] = T0[(4 * g + r) * LT + c];
+      }
       const f4 y = lds4(&T0[c * LT + 4 * g]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {

@@ -592,6 +592,18 @@ def test_key_heads_of_16_from_a_large_lambda0(lambda0, d_v):
     print(lambda0, d_v, errs)
 
 
+@pytest.mark.parametrize("distinct,lambda0,T,tol", [(1, 0.1, 4096, 2e-4), (4, 0.1, 4096, 2e-4), (1, 1e-5, 1000, 1.0),
+                                                    (4, 1e-5, 1000, 1.0), (4, 1e-6, 500, 1.0)])
+def test_key_heads_of_16_keep_the_digits_of_keys_seen_often(distinct, lambda0, T, tol):
+    """A k^ falls with every repetition of a key and the elements of A off the keys do not.  Only the first block works in
+    float32 on that: 6e-8 of 1 + 16 / lambda0, 1e-5 at 0.1, and at 1e-5 and below no digit, but nothing may grow from it."""
+    rng = np.random.default_rng(distinct)
+    q, v = (rng.standard_normal((1, 3, T, 16)).astype(np.float32) for _ in range(2))
+    k = rng.standard_normal((1, 3, distinct, 16)).astype(np.float32)[:, :, rng.integers(0, distinct, T)]
+    errs, _, _ = check_parity(q, k, v, mode=2, lambda0=lambda0, tol=tol)
+    print(lambda0, T, distinct, errs)
+
+
 OPTION_SETS = {
     "every option": dict(with_u=True, refresh_period=7, refresh_eta=1e-2, step_offset=3, normalise_output=True,
                          feature_map=True),
