@@ -688,13 +688,13 @@ static bool fp32_products(int d_k, int d_v, int n_heads) {
 // few of its blocks there are, a block 3 us here, where a compute unit holds eight heads: one head, 64 tokens 18 us here,
 // 80 tokens 17 / 14, 256 50 / 17; 2048 tokens, 256 heads 0.411 / 0.139 ms, 512 heads 0.419 / 0.278, 768 heads 0.42 either
 // way; d_v = 64, 1024 tokens, 256 heads 0.265 / 0.105.  That kernel starts from the inverse of A0, so a given A0 (which need
-// not have one) stays here, and so do value heads whose maps do not fit the LDS, and lambda0 below 1e-6, where nothing
-// was measured.  The condition of what it inverts, up to (lambda0 + tokens) / lambda0, costs it 1e-16 of it in A k^; block
-// after block loses 6e-8 of it.  Error of o, here / there: one key 4096 times, lambda0 = 0.04 6e-2 / 5e-5; four keys, lambda0
-// = 1e-6, 524288 tokens 38 / 0.3; keys of rank 4, lambda0 = 0.1, 16384 tokens 0.17 / 0.02; Gaussian keys, lambda0 = 1e-6, 300
-// tokens 0.09 / 4e-6.
+// not have one) stays here, and so do value heads whose maps do not fit the LDS, lambda0 below 1e-6, where nothing
+// was measured, and lambda0 whose reciprocal is zero or subnormal (an infinite one is A0 = 0).  The condition of what it
+// inverts, up to (lambda0 + tokens) / lambda0, costs it 1e-16 of it in A k^; block after block loses 6e-8 of it.  Error of o,
+// here / there: one key 4096 times, lambda0 = 0.04 6e-2 / 5e-5; four keys, lambda0 = 1e-6, 524288 tokens 38 / 0.3; keys of
+// rank 4, lambda0 = 0.1, 16384 tokens 0.17 / 0.02; Gaussian keys, lambda0 = 1e-6, 300 tokens 0.09 / 4e-6.
 static bool blocks_at_once(const ForwardArgs& a, int d_v) {
-  return d_v <= 64 && a.A0 == nullptr && a.lambda0 >= 1e-6f && a.n_heads <= 512 && a.T >= 64;
+  return d_v <= 64 && a.A0 == nullptr && a.lambda0 >= 1e-6f && a.lambda0 <= 8e37f && a.n_heads <= 512 && a.T >= 64;
 }
 
 // The waves of a head share out the d_v / 16 row tiles of S, evenly where the counts divide and one by one in turn where

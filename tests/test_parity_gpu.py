@@ -580,10 +580,11 @@ def test_key_heads_of_16_take_the_blocks_of_a_span_at_once(d_v, heads, T, dtype)
 
 
 @pytest.mark.parametrize("d_v", [16, 64])
-@pytest.mark.parametrize("lambda0", [1e3, 1e6, 1e9, 1e37])
+@pytest.mark.parametrize("lambda0", [1e3, 1e6, 1e9, 1e37, 2e38, float("inf")])
 def test_key_heads_of_16_from_a_large_lambda0(lambda0, d_v):
     """A starts far below one and the matrix whose inverse every block starts from far above it.  The float32 kernels are at
-    2e-6 and below over this range; two spans, so that inverses of sums are among the blocks."""
+    2e-6 and below over this range; two spans, so that inverses of sums are among the blocks.  The last two have no normal
+    float32 reciprocal."""
     rng = np.random.default_rng(d_v)
     q, k = (rng.standard_normal((1, 3, 300, 16)).astype(np.float32) for _ in range(2))
     v = rng.standard_normal((1, 3, 300, d_v)).astype(np.float32)
