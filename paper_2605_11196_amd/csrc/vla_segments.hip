@@ -509,7 +509,8 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, (D <= 64 || DL < D) ? 4 : 2
   float* out = seg_A + static_cast<size_t>(blockIdx.x) * DL * DL;
   const float diag = 1.0f / a.lambda0;   // the same float32 value the first segment starts from
 
-  if (seg == 0) {   // the first segment starts from the caller's A0, bit for bit
+  // the first segment starts from the caller's A0, bit for bit; an A0 = 0 (infinite lambda0) stays zero
+  if (seg == 0 || (!A0 && diag == 0.0f)) {
     for (int e = threadIdx.x; e < DL * DL; e += NT) out[e] = A0 ? A0[e] : (e / DL == e % DL ? diag : 0.0f);
     return;
   }

@@ -82,7 +82,7 @@ def test_given_initial_state_enters_the_boundary_inverse(d):
 
 
 @pytest.mark.parametrize("d", [32, 64, 96, 128])
-@pytest.mark.parametrize("lambda0", [1e3, 1e6, 1e9, 1e30])
+@pytest.mark.parametrize("lambda0", [1e3, 1e6, 1e9, 1e30, float("inf")])
 def test_boundary_inverse_of_large_elements(lambda0, d):
     """The block kernel is at 4e-7 and below over this range."""
     q, k, v = vla_inputs.gaussian_qkv(1, 3, 200, d, seed=80 + d)
