@@ -684,17 +684,20 @@ static bool fp32_products(int d_k, int d_v, int n_heads) {
   return d_v <= 64 && fewer_rounds_unsplit(d_k, n_heads);
 }
 
-// Key heads of 16: the blocks of 256 tokens at once (vla_chunk_d16.hip)?  A span costs a workgroup of 16 waves 14 us however
-// few of its blocks there are, a block 3 us here, where a compute unit holds eight heads: one head, 64 tokens 18 us here,
-// 80 tokens 17 / 14, 256 50 / 17; 2048 tokens, 256 heads 0.411 / 0.139 ms, 512 heads 0.419 / 0.278, 768 heads 0.42 either
-// way; d_v = 64, 1024 tokens, 256 heads 0.265 / 0.105.  That kernel starts from the inverse of A0, so a given A0 (which need
+// Key heads of 16: the blocks of 256 tokens at once (vla_chunk_d16.hip)?  A span costs a workgroup of 16 waves 8 us with
+// four of its blocks there and 16 us with all, a block 3.2 us here; a compute unit holds one such workgroup, here eight
+// heads.  Time here / there in us: 64 tokens, 1 head 14.9 / 7.9, 256 heads 15.6 / 8.7; 256 tokens 52.6 / 17.5 and 53.3 / 19.5;
+// 2048 tokens 409 / 127 and 414 / 142 (d_v = 64: 534 / 197).  Two rounds, 512 heads: 64 tokens 15.6 / 15.8, 80 tokens 19.0 / 19.4
+// (d_v = 64: 24.3 / 26.1), 96 tokens 22.4 / 21.5 (28.7 / 28.2), 272 tokens 57.6 / 47.3 (74.9 / 65.6), 2048 tokens 420 / 276;
+// 257 heads are within 0.03 of these ratios.  Three rounds, 768 heads: 0.42 ms either way.  That kernel starts from the inverse of A0, so a given A0 (which need
 // not have one) stays here, and so do value heads whose maps do not fit the LDS, lambda0 below 1e-6, where nothing
 // was measured, and lambda0 whose reciprocal is zero or subnormal (an infinite one is A0 = 0).  The condition of what it
 // inverts, up to (lambda0 + tokens) / lambda0, costs it 1e-16 of it in A k^; block after block loses 6e-8 of it.  Error of o,
 // here / there: one key 4096 times, lambda0 = 0.04 6e-2 / 5e-5; four keys, lambda0 = 1e-6, 524288 tokens 38 / 0.3; keys of
 // rank 4, lambda0 = 0.1, 16384 tokens 0.17 / 0.02; Gaussian keys, lambda0 = 1e-6, 300 tokens 0.09 / 4e-6.
 static bool blocks_at_once(const ForwardArgs& a, int d_v) {
-  return d_v <= 64 && a.A0 == nullptr && a.lambda0 >= 1e-6f && a.lambda0 <= 8e37f && a.n_heads <= 512 && a.T >= 64;
+  return d_v <= 64 && a.A0 == nullptr && a.lambda0 >= 1e-6f && a.lambda0 <= 8e37f && a.T >= 64 &&
+         (a.n_heads <= 256 || (a.n_heads <= 512 && a.T > 80));
 }
 
 // The waves of a head share out the d_v / 16 row tiles of S, evenly where the counts divide and one by one in turn where

@@ -563,7 +563,7 @@ def test_a_and_s_chains_on_waves_of_their_own(d, d_v, heads, T, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d_v,heads,T", [(16, 1, 63), (16, 1, 64), (16, 3, 255), (16, 3, 256), (16, 5, 257), (32, 3, 272),
                                          (32, 2, 530), (64, 3, 300), (64, 1, 513), (96, 3, 300), (16, 512, 70),
-                                         (16, 513, 70)])
+                                         (16, 513, 70), (16, 256, 70), (16, 257, 80), (16, 257, 81), (64, 512, 100)])
 def test_key_heads_of_16_take_the_blocks_of_a_span_at_once(d_v, heads, T, dtype):
     """Spans that end inside a block, with one block and with none behind them, given S, keys of zero and one repeated."""
     rng = np.random.default_rng(heads + T)
