@@ -30,6 +30,8 @@
 namespace vla {
 namespace {
 
+constexpr int group(int n) { return n <= 1 ? 1 : 2 * group((n + 1) / 2); }   // the power of two from n on
+
 // NWA waves own SL = D / NWA columns of A each, NWS waves DV / NWS rows of S each.  WPE: waves per SIMD to compile for.
 template <int D, int DV, int NWA, int NWS, typename IO, bool FMAP, int WPE>
 __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(ForwardArgs a) {
@@ -43,12 +45,21 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
   constexpr int NKB = NB / 2;
   constexpr int LDY = SL + 4;
   // Staging (by the S waves): a token row is split over TPR threads of EPT elements each.  Where the threads do not
-  // divide into rows of a power of two, or into pieces of four elements, a row takes D / 16 threads in a group of 8.
+  // divide into rows of a power of two, or into pieces of four elements, a row takes D / EPT threads of a group of TPR, a
+  // power of two up to 16 (whose sum needs no shuffles through LDS), in the smallest pieces of 4, 8 or 16 elements that there
+  // are threads for; rows of 96 with one operand term, quick to stage, in pieces of 16.  2048 tokens, pieces of 16 and the
+  // smallest, ms: 32 x 64, 16 heads, bf16 with the feature map 0.507 / 0.319, 256 heads, float32 0.414 / 0.341; 64 x 96, 256
+  // heads, float32 0.518 / 0.436, bf16 0.451 / 0.409; 128 x 96 0.770 / 0.666 and 0.612 / 0.583; 96 x 96 0.576 / 0.567 and 0.506 /
+  // 0.515; 96 x 64 0.552 / 0.552 and 0.493 / 0.524.
   constexpr int NT = 64 * NWS;
   constexpr int TPR0 = NT / C;
   constexpr bool PADDED = (TPR0 & (TPR0 - 1)) != 0 || (C * D / NT) % 4 != 0;
-  constexpr int EPT = PADDED ? 16 : C * D / NT;
-  constexpr int TPR = PADDED ? 8 : D / EPT;
+  constexpr int PIECE = D == 96 && KT == 1                                 ? 16
+                        : group(D / 4) <= 16 && C * group(D / 4) <= NT ? 4
+                        : C * group(D / 8) <= NT                           ? 8
+                                                                           : 16;
+  constexpr int EPT = PADDED ? PIECE : C * D / NT;
+  constexpr int TPR = group(D / EPT);
   static_assert(EPT % 4 == 0 && TPR <= 32 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
