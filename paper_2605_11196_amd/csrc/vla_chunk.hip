@@ -614,10 +614,13 @@ static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) /
 //            and 0.365 / 0.371
 //     d_v = 16: 256 heads 0.153 / 0.151 and 0.176 / 0.205 (one wave stages every token); d_v = 64: 0.169 / 0.140 and
 //     0.197 / 0.153
-//   d =  96: 256 heads 0.157 / 0.127 and 0.189 / 0.144, 512 heads 0.236 / 0.245 and 0.300 / 0.296, 640 heads 0.423 / 0.381
-//            and 0.536 / 0.438, 2048 heads 0.934 / 1.023 and 1.188 / 1.161
-//     d_v = 128: 256 heads 0.200 / 0.139 and 0.254 / 0.157, 2048 heads 1.41 / 1.08 and 2.01 / 1.22
-//     d_v = 64: 2048 heads 0.968 / 0.990 and 1.21 / 1.12; d_v = 32: 0.776 / 0.594 and 0.954 / 1.017
+//   d =  96: 256 heads 0.157 / 0.127 and 0.189 / 0.142, 512 heads 0.236 / 0.245 and 0.302 / 0.296, 640 heads 0.423 / 0.381
+//            and 0.536 / 0.432, 2048 heads 0.934 / 1.023 and 1.192 / 1.146
+//     d_v = 128: 256 heads 0.206 / 0.143 and 0.256 / 0.154, 2048 heads 1.41 / 1.09 and 2.01 / 1.28
+//     d_v = 64: 2048 heads 0.968 / 0.990 and 1.21 / 1.11; d_v = 32: 0.774 / 0.611 and 0.954 / 1.017
+//     The first block of each chain stands alone, so where this one has half the rounds of workgroups, two of its heads
+//     beside each other win on the shortest sequences.  257 heads, 16 and 32 tokens, in us: 96 x 96, three terms 16 / 19 and
+//     26 / 28 (48 tokens: 35 / 36); 96 x 64, three terms 16 / 18 and 27 / 27; 96 x 128, one term 17 / 19 and 28 / 29.
 //   d =  64: 16 heads 0.120 / 0.087 and 0.124 / 0.090, 256 heads 0.121 / 0.097 and 0.126 / 0.096, 512 heads 0.147 / 0.128
 //            and 0.157 / 0.141, 640 heads 0.169 / 0.166 and 0.189 / 0.234
 //     d_v = 16: 512 heads 0.127 / 0.109 and 0.137 / 0.205; d_v = 128: 256 heads 0.130 / 0.114 and 0.158 / 0.128, 512 heads
@@ -626,10 +629,15 @@ static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) /
 //            and 0.194 / 0.251
 //     d_v = 64: 512 heads 0.140 / 0.112 and 0.152 / 0.128, 768 heads 0.142 / 0.211; d_v = 128: 256 heads 0.131 / 0.095 and
 //     0.158 / 0.109, 512 heads 0.179 / 0.184 and 0.200 / 0.228
-static bool pipe_narrow(int d_k, int d_v, int n_heads, int terms) {
+static bool pipe_narrow(int d_k, int d_v, int n_heads, int T, int terms) {
   switch (d_k) {
     case 128: return n_heads <= 256 && d_v > 16;
-    case 96: return n_heads <= 256 || d_v == 128 || (terms == 1 ? d_v == 32 : d_v >= 64);
+    case 96: {
+      const bool any_length = terms == 1 ? d_v == 32 : d_v == 128;
+      const bool blocks = terms == 1 ? d_v == 128 : d_v == 64 || d_v == 96;   // from a few blocks on
+      return n_heads <= 256 || any_length ||
+             (blocks && (T > (d_v == 96 ? 32 : 16) || rounds(n_heads, 256) < 2 * rounds(n_heads, 512)));
+    }
     case 64: return n_heads <= 256 || (n_heads <= 512 && d_v <= 64 && (terms == 1 || d_v == 64));
     case 32: return n_heads <= (d_v <= 32 ? 1024 : d_v <= 96 ? 512 : 256);
     default: return false;
@@ -720,7 +728,7 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
     }
   }
   if (pipe_wide(d_k, d_v, a.n_heads, terms)) return launch_chunk_pipe_wide(a, d_k, stream);
-  if (pipe_narrow(d_k, d_v, a.n_heads, terms)) return launch_chunk_pipe_narrow(a, d_k, d_v, io_dtype, stream);
+  if (pipe_narrow(d_k, d_v, a.n_heads, a.T, terms)) return launch_chunk_pipe_narrow(a, d_k, d_v, io_dtype, stream);
   if (narrow_waves(d_k, d_v, a.n_heads, terms)) {
     switch (d_k * 1000 + d_v) {
       case 64016: return launch_io<64, 16, 4>(a, io_dtype, stream);
@@ -738,7 +746,7 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
   switch (d_k * 1000 + d_v) {   // what pipe_wide and pipe_narrow leave; d_k = 64: one term only, see narrow_waves
     case 16016: return launch_io<16, 16, 1>(a, io_dtype, stream);
     case 32032: return launch_io<32, 32, 1>(a, io_dtype, stream);
-    case 96096: return launch_one_term<96, 96, 3>(a, stream);
+    case 96096: return launch_io<96, 96, 3>(a, io_dtype, stream);
     case 128128: return launch_three_terms<128, 128, 4>(a, io_dtype, stream);
     case 16032: return launch_io<16, 32, 1>(a, io_dtype, stream);
     case 32016: return launch_io<32, 16, 1>(a, io_dtype, stream);
@@ -753,7 +761,8 @@ hipError_t launch_chunk(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hi
     case 64016: return launch_one_term<64, 16, 2>(a, stream);
     case 96016: return launch_io<96, 16, 3>(a, io_dtype, stream);
     case 96032: return launch_three_terms<96, 32, 3>(a, io_dtype, stream);
-    case 96064: return launch_one_term<96, 64, 3>(a, stream);
+    case 96064: return launch_io<96, 64, 3>(a, io_dtype, stream);
+    case 96128: return launch_one_term<96, 128, 3>(a, stream);
     case 128016: return launch_io<128, 16, 4>(a, io_dtype, stream);
     case 128032: return launch_io<128, 32, 4>(a, io_dtype, stream);
     case 128096: return launch_io<128, 96, 4>(a, io_dtype, stream);

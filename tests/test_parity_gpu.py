@@ -543,7 +543,8 @@ def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [1, 16, 17, 49])
-@pytest.mark.parametrize("d,d_v,heads", [(128, 128, 257), (128, 32, 256), (96, 128, 300), (96, 32, 300), (64, 64, 257),
+@pytest.mark.parametrize("d,d_v,heads", [(128, 128, 257), (128, 32, 256), (96, 128, 300), (96, 32, 300), (96, 64, 300),
+                                         (96, 96, 300), (96, 96, 513), (64, 64, 257),
                                          (64, 64, 512), (64, 64, 513), (64, 16, 512), (64, 96, 5), (32, 32, 1024),
                                          (32, 32, 1025), (32, 96, 512), (32, 128, 256)])
 def test_a_and_s_chains_on_waves_of_their_own(d, d_v, heads, T, dtype):
