@@ -118,8 +118,9 @@ def _on_device(torch, dev):
 def _stream_handle(torch, dev, stream):
     """The handle of the caller's stream (torch's current one by default), and the torch stream that the tensors allocated
     for the call have to be recorded on: none on the current stream, which they are allocated on."""
-    if stream is None:   # the handle alone: a torch.cuda.Stream object costs two microseconds
-        return torch._C._cuda_getCurrentRawStream(dev.index), None
+    if stream is None:   # the handle alone, where torch has this undocumented call: a Stream object costs two microseconds
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return (raw(dev.index) if raw else torch.cuda.current_stream(dev).cuda_stream), None
     handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     return handle, stream if isinstance(stream, torch.cuda.Stream) else None
 

@@ -254,6 +254,17 @@ def test_torch_front_end_refuses_cpu_tensors():
         vla.vla_forward(x, x, x)
 
 
+def test_current_stream_without_the_undocumented_torch_call():
+    from types import SimpleNamespace as NS
+
+    from paper_2605_11196_amd import binding
+
+    dev = NS(index=2)
+    cuda = NS(current_stream=lambda d: NS(cuda_stream=7 + d.index))
+    assert binding._stream_handle(NS(_C=NS(), cuda=cuda), dev, None) == (9, None)
+    assert binding._stream_handle(NS(_C=NS(_cuda_getCurrentRawStream=lambda i: 5 + i), cuda=cuda), dev, None) == (7, None)
+
+
 def test_device_image_exports_the_static_workspace_symbol():
     """vla_forward_static finds its array through hipGetSymbolAddress, which looks the name up in the device
     code object: the array has to be a global, defined symbol of 64 MiB there (a file-scope static that the
