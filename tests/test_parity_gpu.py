@@ -606,6 +606,23 @@ def test_key_heads_of_16_keep_the_digits_of_keys_seen_often(distinct, lambda0, T
     print(lambda0, T, distinct, errs)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,d_v,heads,T", [(16, 16, 3, 300), (16, 32, 3, 272), (16, 64, 2, 530), (16, 64, 300, 100),
+                                           (32, 32, 5, 49), (32, 64, 5, 49), (32, 96, 512, 33), (64, 64, 5, 49),
+                                           (64, 64, 512, 17), (64, 16, 5, 49), (64, 128, 256, 33), (96, 96, 5, 49),
+                                           (96, 96, 300, 33), (96, 64, 300, 16), (96, 128, 257, 33), (128, 128, 5, 49),
+                                           (128, 96, 256, 33), (128, 32, 5, 49)])
+def test_feature_map_on_the_two_chain_kernel_and_key_heads_of_16(d, d_v, heads, T, dtype):
+    """Keys and queries mapped as they are staged: a second span of key heads of 16, every staging layout of the two-chain
+    kernel, rows past the end of the sequence (the map of a zero is one)."""
+    rng = np.random.default_rng(d + d_v + T)
+    q, k = (rng.standard_normal((1, heads, T, d)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+    S0 = rng.standard_normal((1, heads, d_v, d)).astype(np.float32)
+    errs, _, _ = check_parity(q, k, v, S0, dtype=dtype, mode=2, feature_map=True)
+    print(d, d_v, heads, T, dtype, errs)
+
+
 OPTION_SETS = {
     "every option": dict(with_u=True, refresh_period=7, refresh_eta=1e-2, step_offset=3, normalise_output=True,
                          feature_map=True),

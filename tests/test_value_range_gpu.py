@@ -25,3 +25,17 @@ def test_large_keys_against_a_large_state(d, heads, mode, dtype):
     errs, _, _ = check_parity(q * np.float32(1e-20), k * scale, v * np.float32(1e28), S0 * np.float32(1e28), dtype=dtype,
                               mode=mode)
     print(d, heads, mode, dtype, errs)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d_v,T", [(16, 64), (16, 300), (64, 300)])
+def test_large_keys_against_a_large_state_in_spans_of_256_tokens(d_v, T, dtype):
+    """Key heads of 16 from 64 tokens on: the state passes through the affine maps of the blocks of a span."""
+    rng = np.random.default_rng(T)
+    q, k = (rng.standard_normal((1, 3, T, 16)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, 3, T, d_v)).astype(np.float32)
+    S0 = rng.standard_normal((1, 3, d_v, 16)).astype(np.float32)
+    scale = np.float32(10.0) ** rng.integers(8, 15, size=(1, 3, T, 1)).astype(np.float32)
+    errs, _, _ = check_parity(q * np.float32(1e-20), k * scale, v * np.float32(1e28), S0 * np.float32(1e28), dtype=dtype,
+                              mode=2)
+    print(d_v, T, dtype, errs)
