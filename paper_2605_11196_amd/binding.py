@@ -115,14 +115,17 @@ def _on_device(torch, dev):
     return _SAME_DEVICE if dev.index == torch.cuda.current_device() else torch.cuda.device(dev)
 
 
-def _stream_handle(torch, dev, stream):
-    """The handle of the caller's stream (torch's current one by default), and the torch stream that the tensors allocated
-    for the call have to be recorded on: none on the current stream, which they are allocated on."""
+def _on_stream(torch, dev, stream):
+    """Where a call puts its work: the handle of the caller's stream (torch's current one by default), a context in which
+    the tensors of the call are allocated and copied on that stream, and the stream that is current outside, on which the
+    outputs may be read as well (None where it is the same)."""
     if stream is None:   # the handle alone, where torch has this undocumented call: a Stream object costs two microseconds
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        return (raw(dev.index) if raw else torch.cuda.current_stream(dev).cuda_stream), None
+        return (raw(dev.index) if raw else torch.cuda.current_stream(dev).cuda_stream), _on_device(torch, dev), None
     handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-    return handle, stream if isinstance(stream, torch.cuda.Stream) else None
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(handle, device=dev) if handle else torch.cuda.default_stream(dev)
+    return handle, torch.cuda.stream(stream), torch.cuda.current_stream(dev)
 
 
 def vla_forward_workspace_bytes(B, H, T, d_k, d_v, io_dtype, *, lambda0=None, eps=None,
@@ -194,11 +197,7 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
             raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
     if u is not None and (u.dtype != q.dtype or tuple(u.shape) != tuple(q.shape) or u.device != q.device):
         raise ValueError("u must match q in dtype, shape and device")
-    q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
-    u = None if u is None else u.contiguous()
     op = _opts(None, eps, None)
-    if u is not None:
-        op.u = u.data_ptr()
     if zkey is not None:
         op.zkey0 = op.zkey_T = zkey.data_ptr()
     if u_scale is not None:
@@ -213,11 +212,15 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
         op.normalise_output = bool(normalise_output)
     if feature_map is not None:
         op.feature_map = bool(feature_map)
-    with _on_device(torch, dev):
+    handle, context, outside = _on_stream(torch, dev, stream)
+    with context:
+        q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
+        if u is not None:
+            u = u.contiguous()
+            op.u = u.data_ptr()
         o = torch.empty((B, H, dv), dtype=q.dtype, device=dev)
-        handle, other = _stream_handle(torch, dev, stream)
-        if other is not None:
-            o.record_stream(other)
+        if outside is not None:
+            o.record_stream(outside)
         rc = _lib.vla_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), S.data_ptr(), A.data_ptr(), o.data_ptr(),
                                   B, H, dk, dv, io, ctypes.byref(op), handle)
     if rc != 0:
@@ -249,7 +252,6 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
         raise ValueError("q, k, v must share a dtype")
     if q.dim() != 4 or k.shape != q.shape or v.shape[:3] != q.shape[:3]:
         raise ValueError("expected q,k [B,H,T,d_k] and v [B,H,T,d_v]")
-    q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
     B, H, T, dk = q.shape
     dv = v.shape[-1]
     dev = q.device
@@ -261,12 +263,13 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
     if u is not None:
         if u.dtype != q.dtype or tuple(u.shape) != tuple(q.shape) or u.device != dev:
             raise ValueError("u must match q in dtype, shape and device")
-        u = u.contiguous()
     if zkey0 is not None and (zkey0.dtype != torch.float32 or tuple(zkey0.shape) != (B, H, dk)
                               or not zkey0.is_contiguous() or zkey0.device != dev):
         raise ValueError(f"zkey0 must be a contiguous float32 tensor of shape {(B, H, dk)} on {dev}")
-    with _on_device(torch, dev):
-        handle, other = _stream_handle(torch, dev, stream)
+    handle, context, outside = _on_stream(torch, dev, stream)
+    with context:
+        q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
+        u = None if u is None else u.contiguous()
         o = torch.empty((B, H, T, dv), dtype=q.dtype, device=dev)
         S_T = torch.empty((B, H, dv, dk), dtype=torch.float32, device=dev) if return_state else None
         A_T = torch.empty((B, H, dk, dk), dtype=torch.float32, device=dev) if return_state else None
@@ -280,13 +283,13 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
         # the same options as the call, so that the query resolves AUTO to the mode the call will run
         need = _lib.vla_forward_workspace_bytes(B, H, T, dk, dv, io, ctypes.byref(op))
         ws = torch.empty((max(need, 16),), dtype=torch.uint8, device=dev) if need else None
-        # These tensors come from the allocator of torch's current stream while the kernels run on the caller's: tell
-        # the allocator, so that memory dropped here (the workspace when this function returns) is not handed to
-        # other work before the kernels there are done with it.
-        if other is not None:
-            for t in (o, S_T, A_T, zkey_T, ws):
+        # Copies, outputs and workspace belong to the stream that the kernels run on: none of them is memory that other work
+        # still uses, and what is dropped here is not handed on before the kernels are done with it.  The outputs are
+        # kept for reads on the stream that is current outside too.
+        if outside is not None:
+            for t in (o, S_T, A_T, zkey_T):
                 if t is not None:
-                    t.record_stream(other)
+                    t.record_stream(outside)
         rc = _lib.vla_forward(p(q), p(k), p(v), p(S0), p(A0), p(o), p(S_T), p(A_T), B, H, T, dk, dv, io,
                               ctypes.byref(op), p(ws), need, handle)
     if rc != 0:

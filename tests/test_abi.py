@@ -260,9 +260,9 @@ def test_current_stream_without_the_undocumented_torch_call():
     from paper_2605_11196_amd import binding
 
     dev = NS(index=2)
-    cuda = NS(current_stream=lambda d: NS(cuda_stream=7 + d.index))
-    assert binding._stream_handle(NS(_C=NS(), cuda=cuda), dev, None) == (9, None)
-    assert binding._stream_handle(NS(_C=NS(_cuda_getCurrentRawStream=lambda i: 5 + i), cuda=cuda), dev, None) == (7, None)
+    cuda = NS(current_stream=lambda d: NS(cuda_stream=7 + d.index), current_device=lambda: 2)
+    assert binding._on_stream(NS(_C=NS(), cuda=cuda), dev, None)[0] == 9
+    assert binding._on_stream(NS(_C=NS(_cuda_getCurrentRawStream=lambda i: 5 + i), cuda=cuda), dev, None)[0] == 7
 
 
 def test_device_image_exports_the_static_workspace_symbol():

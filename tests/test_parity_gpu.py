@@ -324,6 +324,37 @@ def test_state_outputs_may_alias_inputs_or_be_null(mode):
     assert torch.equal(o2, o_ref)
 
 
+@pytest.mark.parametrize("as_handle", [False, True])
+def test_inputs_that_are_copied_and_outputs_on_another_stream(as_handle):
+    """`stream` given while the current stream is busy: the contiguous copies of the inputs are made on `stream`, and neither
+    they nor the outputs are memory that work on the current stream still writes."""
+    import torch
+
+    import paper_2605_11196_amd as vla
+
+    dev = torch.device("cuda:0")
+    B, H, T, d = 2, 3, 2048, 64   # time-parallel: a workspace as well
+    q, k, v = (torch.from_numpy(x).to(dev) for x in vla_inputs.gaussian_qkv(B, H, T, d, seed=5))
+    want = vla.vla_forward(q, k, v)
+    step = tuple(x[:, :, 0].contiguous() for x in (q, k, v))
+    S, A = want[1].clone(), want[2].clone()
+    want_o = vla.vla_decode_step(*step, S, A)
+    q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
+    S1, A1 = want[1].clone(), want[2].clone()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)   # some 50 ms on the current stream, and behind it writes to memory that is free by then
+    for x in (want[0], want[1], want[2], q):
+        torch.full_like(x, 7.0)
+    stream = side.cuda_stream if as_handle else side
+    got = vla.vla_forward(q, k, v, stream=stream)
+    got_o = vla.vla_decode_step(q[:, :, 0], k[:, :, 0], v[:, :, 0], S1, A1, stream=stream)
+    side.synchronize()
+    torch.cuda.synchronize()
+    for x, y in zip((*got, got_o, S1, A1), (*want, want_o, S, A)):
+        assert torch.equal(x, y)
+
+
 def test_runs_on_a_side_stream_and_is_deterministic():
     import torch
 
