@@ -133,16 +133,19 @@ int pick_mode(int B, int H, int T, int d, int d_v, const vla_opts& o) {
   //   d =  64:  T = 2048: 128 heads 0.31 / 0.36, 192: 0.40 / 0.35;     T = 4096: 192 heads 0.72 / 0.77, 320: 1.05 / 0.90;
   //             T = 16384: 192 heads 2.46 / 3.08, 320: 3.97 / 3.55
   //   d =  32:  T = 2048: 320 heads 0.32 / 0.34, 512: 0.47 / 0.35;     T = 16384: 320 heads 2.31 / 2.81, 512: 3.49 / 2.84
-  // The thresholds lie above the present crossovers in places: they were measured when the block kernel took up to 1.4
-  // times as long, and they stay because every segment restarts from a float64 inverse, which calls that moved to the
-  // block kernel would lose (error of A at d = 64, T = 131072: 1e-6 against 2.6e-5).
+  // The thresholds lie above the present crossovers in places, by up to 1.5 times in the time of a call: they were measured
+  // when the block kernel took longer, and they stay because every segment restarts from a float64 inverse, which calls that
+  // moved to the block kernel would lose.  Error of A, time-parallel / block kernel, lambda0 = 0.1, Gaussian keys: d = 64, 512
+  // tokens 7e-8 / 3e-7, 4096 7e-8 / 2.9e-7, 16384 1.2e-7 / 5.2e-7, 131072 1e-6 / 2.6e-5; o and S differ from 16384 tokens on
+  // (3.3e-7 / 6.0e-7).
   const int t_128 = d == 96 ? 4096 : 8192;   // from here 128 heads still gain at d >= 96
   long long few = d >= 96 ? (T >= t_128 ? 128 : (T >= 4096 ? 96 : 64))
                           : (d >= 64 ? (T >= 4096 ? 320 : 192) : 512);
   // Value heads of another size than the key heads: the same thresholds by the key head size, a notch higher
   // where measured (the S rows kernel of the segment modes takes the row tiles of S in turn).  T = 4096, now: d_k = 64,
-  // d_v = 128: 160 heads 0.88 / 0.90, 384: 1.94 / 1.28; d_v = 16: 192 heads 0.69 / 0.74, 384: 1.36 / 0.89; d_k = 128, d_v = 64:
-  // 96 heads 1.01 / 1.11, 128: 1.22 / 1.11; d_v = 16: 128 heads 1.16 / 1.19; d_k = 32, d_v = 128: 192 heads 0.74 / 0.75.
+  // d_v = 128: 128 heads 0.75 / 0.84, 160: 0.93 / 0.82, 384: 1.94 / 1.24; d_v = 16: 192 heads 0.70 / 0.76, 384: 1.35 / 0.89; d_k =
+  // 128, d_v = 64: 96 heads 1.07 / 1.10, 128: 1.27 / 1.12; d_v = 16: 128 heads 1.20 / 1.19; d_k = 32, d_v = 128: 128 heads 0.52 /
+  // 0.68, 192: 0.76 / 0.68, 1280: 3.07 / 2.37.
   if (d != d_v) {
     if (d == 64 && T >= 4096) few = 384;
     if (d == 128 && T >= 4096) few = 128;

@@ -610,25 +610,31 @@ static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) /
 // and holds twice the waves per head, so it wins as long as its workgroups are resident in one round, and beyond that
 // where the other kernel leaves a compute unit with fewer waves than SIMDs' worth of work.  Waves of 16 columns, one term
 // and three terms, this file's kernel / that one:
-//   d = 128: 16 heads 0.184 / 0.149 and 0.217 / 0.161, 256 heads 0.190 / 0.159 and 0.225 / 0.190, 512 heads 0.279 / 0.333
-//            and 0.365 / 0.371
-//     d_v = 16: 256 heads 0.153 / 0.151 and 0.176 / 0.205 (one wave stages every token); d_v = 64: 0.169 / 0.140 and
-//     0.197 / 0.153
-//   d =  96: 256 heads 0.157 / 0.127 and 0.189 / 0.142, 512 heads 0.236 / 0.245 and 0.302 / 0.296, 640 heads 0.423 / 0.381
-//            and 0.536 / 0.432, 2048 heads 0.934 / 1.023 and 1.192 / 1.146
-//     d_v = 128: 256 heads 0.206 / 0.143 and 0.256 / 0.154, 2048 heads 1.41 / 1.09 and 2.01 / 1.28
-//     d_v = 64: 2048 heads 0.968 / 0.990 and 1.21 / 1.11; d_v = 32: 0.774 / 0.611 and 0.954 / 1.017
+//   d = 128: 16 heads 0.189 / 0.152 and 0.221 / 0.164, 256 heads 0.198 / 0.166 and 0.229 / 0.185, 512 heads 0.282 / 0.331
+//            and 0.364 / 0.368, 768 heads (three terms) 0.705 / 0.561
+//     d_v = 96: 256 heads 0.186 / 0.147 and 0.226 / 0.166, 512 heads 0.296 / 0.297 and 0.370 / 0.340, 768 heads 0.522 / 0.452
+//     and 0.659 / 0.512; d_v = 64: 256 heads 0.171 / 0.142 and 0.198 / 0.155, 512 heads 0.228 / 0.276 and 0.275 / 0.320, 768
+//     heads 0.406 / 0.434 and 0.539 / 0.477; d_v = 16: 256 heads 0.153 / 0.151 and 0.176 / 0.205 (one wave stages every token)
+//   d =  96: 256 heads 0.157 / 0.126 and 0.189 / 0.141, 512 heads 0.239 / 0.248 and 0.302 / 0.294, 768 heads 0.461 / 0.391
+//            and 0.559 / 0.443, 2048 heads 0.938 / 1.026 and 1.191 / 1.147
+//     d_v = 128: 256 heads 0.201 / 0.140 and 0.253 / 0.152, 2048 heads 1.41 / 1.09 and 2.01 / 1.25
+//     d_v = 64: 768 heads 0.466 / 0.375 and 0.572 / 0.425, 2048 heads 0.967 / 0.991 and 1.21 / 1.12; d_v = 32: 768 heads
+//     0.359 / 0.256 and 0.472 / 0.385, 2048 heads 0.771 / 0.622 and 0.957 / 1.018
 //     The first block of each chain stands alone, so where this one has half the rounds of workgroups, two of its heads
 //     beside each other win on the shortest sequences.  257 heads, 16 and 32 tokens, in us: 96 x 96, three terms 16 / 19 and
 //     26 / 28 (48 tokens: 35 / 36); 96 x 64, three terms 16 / 18 and 27 / 27; 96 x 128, one term 17 / 19 and 28 / 29.
-//   d =  64: 16 heads 0.120 / 0.087 and 0.124 / 0.090, 256 heads 0.121 / 0.097 and 0.126 / 0.096, 512 heads 0.147 / 0.128
-//            and 0.157 / 0.141, 640 heads 0.169 / 0.166 and 0.189 / 0.234
-//     d_v = 16: 512 heads 0.127 / 0.109 and 0.137 / 0.205; d_v = 128: 256 heads 0.130 / 0.114 and 0.158 / 0.128, 512 heads
-//     0.162 / 0.216 and 0.208 / 0.274
-//   d =  32: 256 heads 0.102 / 0.072 and 0.103 / 0.078, 1024 heads 0.135 / 0.127 and 0.142 / 0.137, 1536 heads 0.174 / 0.201
-//            and 0.194 / 0.251
-//     d_v = 64: 512 heads 0.140 / 0.112 and 0.152 / 0.128, 768 heads 0.142 / 0.211; d_v = 128: 256 heads 0.131 / 0.095 and
-//     0.158 / 0.109, 512 heads 0.179 / 0.184 and 0.200 / 0.228
+//   d =  64: 16 heads 0.123 / 0.089 and 0.126 / 0.092, 256 heads 0.123 / 0.095 and 0.128 / 0.097, 512 heads 0.146 / 0.130
+//            and 0.161 / 0.144, 640 heads 0.169 / 0.168 and 0.192 / 0.241
+//     d_v = 16: 512 heads 0.125 / 0.109 and 0.137 / 0.206; d_v = 96: 256 heads 0.140 / 0.101 and 0.162 / 0.106, 512 heads
+//     0.174 / 0.147 and 0.208 / 0.222; d_v = 128: 256 heads 0.131 / 0.104 and 0.163 / 0.115, 512 heads 0.163 / 0.160 and
+//     0.202 / 0.235
+//   d =  32: 256 heads 0.104 / 0.074 and 0.105 / 0.078, 1024 heads 0.136 / 0.127 and 0.148 / 0.138, 1536 heads 0.175 / 0.203
+//            and 0.197 / 0.253
+//     d_v = 64: 512 heads 0.139 / 0.105 and 0.150 / 0.108, 768 heads 0.143 / 0.131 and 0.155 / 0.142, 1024 heads 0.155 / 0.156
+//     and 0.174 / 0.235; d_v = 96: 512 heads 0.164 / 0.110 and 0.176 / 0.113, 768 heads 0.167 / 0.146 and 0.189 / 0.161;
+//     d_v = 128: 256 heads 0.133 / 0.087 and 0.160 / 0.091, 512 heads 0.180 / 0.130 and 0.201 / 0.140, 768 heads 0.185 / 0.200
+// The lines below do not reach every count at which that kernel is ahead: 513 to 768 heads of 96 and, with three terms, of
+// 128 x 64 to 128 x 128 stay here by 9 to 27 %, 512 heads of 32 x 128 and 64 x 96 and 768 of 32 x 64 and 32 x 96 by 8 to 30 %.
 static bool pipe_narrow(int d_k, int d_v, int n_heads, int T, int terms) {
   switch (d_k) {
     case 128: return n_heads <= 256 && d_v > 16;

@@ -6,7 +6,7 @@
 // the blocks before its own, inverts the sum and forms K^ A, all in float64 (the k^ are the float32 numbers the recurrence
 // uses, and their products are exact in float64).  K^ A has to come from the unrounded inverse: along keys seen often A k^
 // is far below the elements of A, and where the recurrence keeps the two consistent step by step, an inverse rounded to
-// float32 does not (8192 tokens of four keys, lambda0 = 0.1: error of o 1e-2; lambda0 = 1e-6, 500 tokens: beyond 1e20).
+// float32 does not (four keys, 16384 tokens, lambda0 = 0.1: error of o 1.3e-2, now 5e-6; lambda0 = 1e-6, 500 tokens: 6e24, 0.2).
 // From there each wave does the C x C work of its block (the algebra is at the head of vla_chunk.hip) and forms what its
 // block does to S, which is affine:
 //
@@ -18,8 +18,8 @@
 //
 // What bounds it: latency.  Block after block on one wave (vla_chunk.hip with one tile, which larger counts of heads keep)
 // takes 3.1 us a block, all of it dependent instructions of one wave: one head of 256 tokens 50 us, 16384 tokens 3.25 ms.
-// Here a span of 16 blocks takes 15 us, four waves on every SIMD: 17 us and 0.99 ms.  Error against float64 of the first
-// 3.9e-7 -> 3.0e-7 (o), 2.8e-7 -> 1.6e-7 (A): every block starts from a float64 inverse.
+// Here a span of 16 blocks takes 16 us, four waves on every SIMD: 17.2 us and 1.0 ms.  Error against float64 of the first
+// 3.9e-7 -> 2.8e-7 (o), 2.8e-7 -> 1.6e-7 (A): every block starts from a float64 inverse.
 #include "vla_mfma_util.h"
 
 namespace vla {

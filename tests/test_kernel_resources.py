@@ -2,8 +2,9 @@
 cross-compiles).
 
 The headline kernel keeps 64 state registers per lane and runs four waves per SIMD, so it sits at the
-128-register limit: a change that pushes values into scratch memory inside the token loop would cost time on
-every block without failing any numerical test.  The compiler's own resource remarks are parsed here."""
+128-register limit: a change that pushes more values into scratch memory inside the token loop would cost time on
+every block without failing any numerical test.  (18 registers of a lane spill there now, 28 bytes, which caches
+hold: traffic is 1.013 times the algorithmic one.)  The compiler's own resource remarks are parsed here."""
 import os
 import re
 from concurrent.futures import ThreadPoolExecutor
@@ -94,8 +95,6 @@ KNOWN = {
     },
     "chunk_pipe_kernel": {
         (128, 128, 4, 4, "bf16", False, 4): (28, 18),
-        (128, 96, 8, 6, "f32", False, 4): (40, 49), (128, 96, 8, 6, "f32", True, 4): (40, 49),
-        (128, 96, 8, 6, "bf16", True, 4): (40, 49),
     },
     "chunk_general_kernel": {
         (128, 128, 32, "f32", True, False, False, True): (68, 40), (128, 128, 32, "bf16", True, False, False, True): (28, 6),
