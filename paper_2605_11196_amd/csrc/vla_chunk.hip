@@ -23,7 +23,7 @@
 // Work split: NW waves per (batch, head); wave w owns columns [SL*w, SL*w+SL) of A and the same rows of
 // S, as 16x16 float32 accumulator tiles that stay in VGPRs for the whole sequence (A is symmetric, so an
 // accumulator tile of A can be fed straight back as the B operand).  The C x C factorisations run on
-// one wave (rotating with the block index) with lanes = rows and v_readlane broadcasts.
+// one wave (rotating with the block index) four columns at a time (cholesky16).
 //
 // What bounds it: instruction issue -- the matrix unit, the vector instructions that split the state, and the two
 // serial sections, of which one head hides the other's.  The five sweeps over A and S are FP32 products formed
@@ -327,8 +327,6 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // Lanes 0-31 hold rows of I + G (-> rows of L), lanes 32-63 hold columns of the identity
     // (-> columns of L^{-1}); both halves are updated by the same instruction stream: one broadcast of
     // L[j][t] serves the Cholesky trailing update and the forward substitution for L^{-1}.
-    int cc = c;  // opaque copy: keeps the (c == t) masks from being hoisted into 16 registers
-    asm volatile("" : "+v"(cc));
     // ================= -F^T = K^ S0^T - V^T and R^T = Q S0^T: one pass over S, whose split serves both; needed only
     // after barrier (5), so it fills the serial windows
     f4 ft[NJV], ot[NJV];
@@ -369,35 +367,11 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     }
     if (w == sw) {
       prio<kLevels, 3, 3>();   // the dependent chain is what the other waves wait for: issue it first
-      float m[C];  // lanes <32, lane c: row c of L;  lanes >=32, lane c: m[t] = L^{-1}[t][c]
-      const bool lower = lane < 32;
+      f4 gram = lds4(&Gp[0][0][c * LT + 4 * g]);
 #pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        f4 acc = lds4(&Gp[0][0][c * LT + s4]);
-#pragma unroll
-        for (int ww = 1; ww < NW; ++ww) acc += lds4(&Gp[ww][0][c * LT + s4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          m[s4 + e] = (lower ? acc[e] : 0.0f) + ((s4 + e) == cc ? 1.0f : 0.0f);
-      }
-#pragma unroll
-      for (int t = 0; t < C; ++t) {
-        const float p = readlane(m[t], t);  // pivot = delta_t >= 1
-        const float ri = __builtin_amdgcn_rsqf(p);  // 1 ulp; L only has to satisfy L L^T = I + G to rounding
-        const float li = m[t] * ri;  // lanes <32: column t of L;  lanes >=32: row t of L^{-1}, final
-        m[t] = li;
-#pragma unroll
-        for (int j = t + 1; j < C; ++j) m[j] = fmaf(-li, readlane(li, j), m[j]);
-      }
-      if (g == 2) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Lis[t * LT + c] = m[t];
-      }
-      if (g == 0) {
-#pragma unroll
-        for (int s4 = 0; s4 < C; s4 += 4)
-          *reinterpret_cast<f4*>(&Lrs[c * LT + s4]) = f4{m[s4], m[s4 + 1], m[s4 + 2], m[s4 + 3]};
-      }
+      for (int ww = 1; ww < NW; ++ww) gram += lds4(&Gp[ww][0][c * LT + 4 * g]);
+      const Lane at = fresh_lane(c, g);
+      cholesky16(gram, Lrs, Lis, at.c, at.g);
       prio<kLevels, 1, 0>();
     }
     __syncthreads();  // (3) L^{-1} visible
@@ -438,13 +412,6 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     }
     if (w == sw2) {
       prio<kLevels, 3, 3>();
-      float m[C];  // lane c: row c of L
-#pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        const f4 lr = lds4(&Lrs[c * LT + s4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m[s4 + e] = lr[e];
-      }
       const float dl = Lrs[c * LT + c];  // L_cc
       float wn2 = 0.0f;
 #pragma unroll
@@ -454,17 +421,9 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       const float an = __builtin_amdgcn_sqrtf(wn2) * rdl;                // ||A_t k^_t|| = ||w_t|| / L_tt
       const float cs = rdl * __builtin_amdgcn_rcpf(fmaxf(an, eps));      // alpha^_t = c_t w_t
       if (g == 0) cvec[c] = -cs;  // the residual tiles carry -E, see below
-      // Z = (I + strict_lower(L) diag(c))^{-1}: lane c holds column c (rows of L live in lanes 0-31)
-      float nm[C], Zr[C];
-      float ncs = -cs;
-      asm volatile("s_nop 1" : "+v"(ncs));   // a DPP read of a VGPR needs 2 wait states after its write
-      scale_cols<0>(m, nm, ncs);             // lane t: -L[t][s] c_s
-      asm volatile("s_nop 1" : "+v"(nm[0]));
-      z_rows<0>(nm, Zr, cc);
-      if (g == 0) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Zs[t * LT + c] = Zr[t];
-      }
+      // Z = (I + strict_lower(L) diag(c))^{-1}
+      const Lane at = fresh_lane(c, g);
+      lower_inverse16(Lrs, cs, at.c, at.g, [&](int t, int s, float z) { Zs[t * LT + s] = z; });
       // H = L^{-1} GQ (one MFMA tile), NQ[s][t] = c_s H[s][t] for s <= t
       f4 hq = f4{0, 0, 0, 0};
 #pragma unroll

@@ -220,39 +220,12 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
         gg = mfma16(ka[r], y[r], gg);   // G[s][t], GQ[s][t] with t on the rows of the accumulator
         gq = mfma16(qa[r], y[r], gq);
       }
-      *reinterpret_cast<f4*>(&T0[c * LT + 4 * g]) = gg;
       *reinterpret_cast<f4*>(&T1[c * LT + 4 * g]) = gq;
 #pragma unroll
       for (int r = 0; r < 4; ++r) gq[r] = T1[(4 * g + r) * LT + c];   // GQ[4g + r][c]
-      // ================= Cholesky of I + G and L^{-1}: lanes 0-31 hold rows of I + G, lanes 32-63 columns of the identity
+      // ================= Cholesky of I + G and L^{-1}
       fresh();
-      float l[C];
-      {
-        const bool lower = lane < 32;
-#pragma unroll
-        for (int s4 = 0; s4 < C; s4 += 4) {
-          const f4 acc = lds4(&T0[c * LT + s4]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) l[s4 + e] = (lower ? acc[e] : 0.0f) + ((s4 + e) == c ? 1.0f : 0.0f);
-        }
-#pragma unroll
-        for (int t = 0; t < C; ++t) {
-          const float p = vla::readlane(l[t], t);  // pivot = delta_t >= 1
-          const float li = l[t] * __builtin_amdgcn_rsqf(p);
-          l[t] = li;
-#pragma unroll
-          for (int j = t + 1; j < C; ++j) l[j] = fmaf(-li, vla::readlane(li, j), l[j]);
-        }
-        if (g == 2) {
-#pragma unroll
-          for (int t = 0; t < C; ++t) T1[t * LT + c] = l[t];
-        }
-        if (g == 0) {
-#pragma unroll
-          for (int s4 = 0; s4 < C; s4 += 4)
-            *reinterpret_cast<f4*>(&T0[c * LT + s4]) = f4{l[s4], l[s4 + 1], l[s4 + 2], l[s4 + 3]};
-        }
-      }
+      cholesky16(gg, T0, T1, c, g);
       fresh();
       // ================= W^T = L^{-1} Y^T, ||w_t||^2, H = L^{-1} GQ
       const f4 la = lds4(&T1[c * LT + 4 * g]);
@@ -267,25 +240,10 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
       for (int r = 0; r < 4; ++r) n2[r] = row_sum16(n2[r]);
       if (c == 0) *reinterpret_cast<f4*>(&wns[w][4 * g]) = n2;
       // ================= c_t, Z = (I + strict_lower(L) diag(c))^{-1}, NQ
-#pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        const f4 lr = lds4(&T0[c * LT + s4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) l[s4 + e] = lr[e];
-      }
       const float rdl = __builtin_amdgcn_rcpf(T0[c * LT + c]);
       const float an = __builtin_amdgcn_sqrtf(wns[w][c]) * rdl;          // ||A_t k^_t|| = ||w_t|| / L_tt
       const float cs = rdl * __builtin_amdgcn_rcpf(fmaxf(an, eps));      // alpha^_t = c_t w_t
-      float nm[C], Zr[C];
-      float ncs = -cs;
-      asm volatile("s_nop 1" : "+v"(ncs));   // a DPP read of a VGPR needs 2 wait states after its write
-      scale_cols<0>(l, nm, ncs);             // lane t: -L[t][s] c_s
-      asm volatile("s_nop 1" : "+v"(nm[0]));
-      z_rows<0>(nm, Zr, c);
-      if (g == 0) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) T1[t * LT + c] = Zr[t];
-      }
+      lower_inverse16(T0, cs, c, g, [&](int t, int s, float z) { T1[t * LT + s] = z; });
       f4 cg;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {

@@ -458,37 +458,16 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
       key_sum_pass();
       if (DB && tn + C < T) load_kqu(tn + C);
     } else {
-      // Lanes 0-31 hold rows of I + G (-> rows of L), lanes 32-63 columns of the identity (-> columns of
-      // L^{-1}); one broadcast of L[j][t] serves the trailing update and the forward substitution.
       __builtin_amdgcn_s_setprio(3);   // the dependent chain is what the other waves wait for: issue it first
-      float m[C];
-      const bool lower = lane < 32;
+      f4 gram;
+      if (FULL && period > 0) {  // entry (c, s) with s < c from its mirror image (s, c): see the header
 #pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        f4 acc = lds4(&Gs[kG][c * LT + s4]);
-        if (FULL && period > 0) {  // entry (c, s) with s < c from its mirror image (s, c): see the header
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float mir = Gs[kG][(s4 + e) * LT + c];
-            acc[e] = (s4 + e < cc) ? mir : acc[e];
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m[s4 + e] = (lower ? acc[e] : 0.0f) + ((s4 + e) == cc ? 1.0f : 0.0f);
+        for (int r = 0; r < 4; ++r) gram[r] = Gs[kG][(4 * g + r) * LT + c];
+      } else {
+        gram = lds4(&Gs[kG][c * LT + 4 * g]);
       }
-#pragma unroll
-      for (int t = 0; t < C; ++t) {
-        const float p = readlane(m[t], t);  // pivot = delta_t >= 1
-        const float ri = __builtin_amdgcn_rsqf(p);
-        const float li = m[t] * ri;  // lanes <32: column t of L;  lanes >=32: row t of L^{-1}, final
-        m[t] = li;
-#pragma unroll
-        for (int j = t + 1; j < C; ++j) m[j] = fmaf(-li, readlane(li, j), m[j]);
-      }
-      if (g == 2) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Lis[t * LT + c] = m[t];
-      }
+      const Lane at = fresh_lane(c, g);
+      cholesky16<false>(gram, nullptr, Lis, at.c, at.g);
       __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();  // (3) L^{-1} visible
@@ -576,28 +555,13 @@ __global__ void __launch_bounds__(64 * D / SL, general_waves_per_simd(D, DV, SL,
         pt = mfma16(mop[r], nhm[r], pt);
         aq = mfma16(mop[r], nhq[r], aq);
       }
-      // rows of P^T on lanes: lane t reads alpha_s . k^_t for all s
+      // same wave writes and reads: LDS operations of one wave are ordered
       *reinterpret_cast<f4*>(&Ps[c * LT + 4 * g]) = pt;
-      float m[C];
-#pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        const f4 pr = lds4(&Ps[c * LT + s4]);  // same wave wrote it: LDS operations of one wave are ordered
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m[s4 + e] = pr[e];
-      }
-      float nm[C], Zr[C];
-      float ncs = -cs;
-      asm volatile("s_nop 1" : "+v"(ncs));   // a DPP read of a VGPR needs 2 wait states after its write
-      scale_cols<0>(m, nm, ncs);             // lane t: -P[s][t] c_s = -N[t][s]
-      asm volatile("s_nop 1" : "+v"(nm[0]));
-      z_rows<0>(nm, Zr, cc);
-      if (g == 0) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) {
-          if constexpr (SCAN) smb[t * C + c] = Zr[t];
-          else Zs[t * LT + c] = Zr[t];
-        }
-      }
+      const Lane at = fresh_lane(c, g);
+      lower_inverse16(Ps, cs, at.c, at.g, [&](int t, int s, float z) {   // N[t][s] = c_s P[s][t]
+        if constexpr (SCAN) smb[static_cast<unsigned>(t * C + s)] = z;
+        else Zs[t * LT + s] = z;
+      });
       f4 nq;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {

@@ -145,36 +145,12 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
 #pragma unroll
       for (int r = 0; r < 4; ++r) GQp[blk & 1][w][(4 * g + r) * LT + c] = gq[r];
     };
-    // Cholesky of I + G and L^{-1}: lanes 0-31 hold rows of I + G, lanes 32-63 columns of the identity
+    // Cholesky of I + G and L^{-1}; G is stored with its rows on the columns of the tile
     auto factorise = [&](int blk) __attribute__((always_inline)) {
-      float m[C];
-      const bool lower = lane < 32;
+      f4 gram = lds4(&Yg[0][c * LT + 4 * g]);
 #pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        f4 acc = lds4(&Yg[0][c * LT + s4]);
-#pragma unroll
-        for (int ww = 1; ww < NWA; ++ww) acc += lds4(&Yg[ww][c * LT + s4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m[s4 + e] = (lower ? acc[e] : 0.0f) + ((s4 + e) == c ? 1.0f : 0.0f);
-      }
-#pragma unroll
-      for (int t = 0; t < C; ++t) {
-        const float p = readlane(m[t], t);  // pivot = delta_t >= 1
-        const float ri = __builtin_amdgcn_rsqf(p);
-        const float li = m[t] * ri;  // lanes < 32: column t of L;  lanes >= 32: row t of L^{-1}, final
-        m[t] = li;
-#pragma unroll
-        for (int j = t + 1; j < C; ++j) m[j] = fmaf(-li, readlane(li, j), m[j]);
-      }
-      if (g == 2) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Lis[blk & 1][t * LT + c] = m[t];
-      }
-      if (g == 0) {
-#pragma unroll
-        for (int s4 = 0; s4 < C; s4 += 4)
-          *reinterpret_cast<f4*>(&Lrs[blk & 1][c * LT + s4]) = f4{m[s4], m[s4 + 1], m[s4 + 2], m[s4 + 3]};
-      }
+      for (int ww = 1; ww < NWA; ++ww) gram += lds4(&Yg[ww][c * LT + 4 * g]);
+      cholesky16(gram, Lrs[blk & 1], Lis[blk & 1], c, g);
     };
     // c_t on lane t of every row of 16
     auto strength = [&](int blk) __attribute__((always_inline)) -> float {
@@ -203,27 +179,11 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
         NQs[c * LT + s] = (s <= c) ? -(csr * hq[r]) : 0.0f;
       }
     };
+    // Z = (I + strict_lower(L) diag(c))^{-1}
     auto form_z = [&](int blk) __attribute__((always_inline)) {
-      float m[C];  // lane c: row c of L
-#pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        const f4 lr = lds4(&Lrs[blk & 1][c * LT + s4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m[s4 + e] = lr[e];
-      }
       const float cs = strength(blk);
       if (g == 0) cvec[c] = -cs;  // the residual tiles carry -E
-      // Z = (I + strict_lower(L) diag(c))^{-1}: lane c holds column c
-      float nm[C], Zr[C];
-      float ncs = -cs;
-      asm volatile("s_nop 1" : "+v"(ncs));   // a DPP read of a VGPR needs 2 wait states after its write
-      scale_cols<0>(m, nm, ncs);             // lane t: -L[t][s] c_s
-      asm volatile("s_nop 1" : "+v"(nm[0]));
-      z_rows<0>(nm, Zr, c);
-      if (g == 0) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Zs[t * LT + c] = Zr[t];
-      }
+      lower_inverse16(Lrs[blk & 1], cs, c, g, [&](int t, int s, float z) { Zs[t * LT + s] = z; });
     };
     // W^T = L^{-1} Y^T, partial ||w_t||^2, W to LDS
     auto form_w = [&](int blk) __attribute__((always_inline)) {

@@ -363,9 +363,6 @@ struct BlockOps {
   }
 };
 
-__device__ __forceinline__ float readlane(float x, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
-}
 __device__ __forceinline__ f4 lds4(const float* p) { return *reinterpret_cast<const f4*>(p); }
 
 // Sum over the 16 lanes of a DPP row; every lane of the row gets the total.
@@ -422,6 +419,119 @@ __device__ __forceinline__ void scale_cols(const float (&m)[C], float (&nm)[C], 
     nm[S_] = mul_row_bcast<S_>(ncs, m[S_]);
     scale_cols<S_ + 1>(m, nm, ncs);
   }
+}
+
+// ---- Triangular work on a 16 x 16 tile by one wave, four columns at a time.  The tile sits in the accumulator layout
+// (lane l = 16g + c, register r: element [4g + r][c]), so that the rows 4P .. 4P + 3 of a panel are the four registers of the
+// 16 lanes g = P: inside the panel every coefficient is a DPP broadcast within those lanes (the other lanes compute values
+// that nothing reads), and the rows after it take their rank-4 update from one v_mfma_f32_16x16x4_f32.
+//
+// Bound by one wave's issue (a vector instruction about every 6 cycles, 8 where it waits for the one before) and the chain
+// of 16 pivots.  The factorisation takes some 190 instructions and 1460 cycles; with a column of L and L^{-1} per register
+// and v_readlane broadcasts it took 430 and 2220, and scaled only at the end (rcp in the chain) 1630.  Z: 70 instructions
+// against 300 with DPP multiply-adds.  Same bits.  256 heads of 64, float32, 2048 tokens 0.402 -> 0.353 ms; 16 heads of 64,
+// 4096 tokens 0.147 -> 0.139; 2048 heads of 64, 8192 tokens, bf16 5.78 -> 5.60, of 128 15.72 -> 15.55.
+// x[lane L of this row of 16 lanes]
+template <int L>
+__device__ __forceinline__ float row_bcast(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, true));
+}
+// x[g] of the lanes 16P + c, on lane 16g + c: the four rows of a panel as one operand register
+template <int P>
+__device__ __forceinline__ float panel_operand(float x0, float x1, float x2, float x3) {
+  auto swap16 = [](float& a, float& b) __attribute__((always_inline)) {   // odd rows of lanes of a, even ones of b
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  };
+  swap16(x0, x1);
+  swap16(x2, x3);
+  const auto r = P % 2 == 0 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x2), false, false)
+                            : __builtin_amdgcn_permlane32_swap(__float_as_uint(x1), __float_as_uint(x3), false, false);
+  return __uint_as_float(r[P / 2]);
+}
+// One panel of cholesky16: m is what the earlier panels left of the matrix, n of the identity.  The panel's rows of L^T
+// and L^{-1} go to LDS; m and n take the update (rows up to the panel's last are not read again).
+template <int P, bool WITH_L>
+__device__ __forceinline__ void cholesky_panel(f4& m, f4& n, float* L, float* Linv, int c, int g) {
+  const float r0 = __builtin_amdgcn_rsqf(row_bcast<4 * P>(m[0]));   // 1 ulp; the pivots are delta_t >= 1
+  const float l10 = row_bcast<4 * P + 1>(m[0]) * r0, u0 = m[0] * r0;
+  float u1 = fmaf(-l10, u0, m[1]);
+  const float l20 = row_bcast<4 * P + 2>(m[0]) * r0, l30 = row_bcast<4 * P + 3>(m[0]) * r0;
+  const float r1 = __builtin_amdgcn_rsqf(row_bcast<4 * P + 1>(u1));
+  const float l21 = row_bcast<4 * P + 2>(u1) * r1, l31 = row_bcast<4 * P + 3>(u1) * r1;
+  float u2 = fmaf(-l20, u0, m[2]);
+  u1 *= r1;
+  u2 = fmaf(-l21, u1, u2);
+  const float r2 = __builtin_amdgcn_rsqf(row_bcast<4 * P + 2>(u2));
+  const float l32 = row_bcast<4 * P + 3>(u2) * r2;
+  float u3 = fmaf(-l31, u1, fmaf(-l30, u0, m[3]));
+  u2 *= r2;
+  u3 = fmaf(-l32, u2, u3);
+  const float r3 = __builtin_amdgcn_rsqf(row_bcast<4 * P + 3>(u3));
+  u3 *= r3;
+  const float u = panel_operand<P>(u0, u1, u2, u3);   // L[c][4P + g]
+  if constexpr (P < 3) m = mfma16(-u, u, m);
+  const float v0 = n[0] * r0;
+  const float v1 = fmaf(-l10, v0, n[1]) * r1;
+  const float v2 = fmaf(-l21, v1, fmaf(-l20, v0, n[2])) * r2;
+  const float v3 = fmaf(-l32, v2, fmaf(-l31, v1, fmaf(-l30, v0, n[3]))) * r3;
+  const float v = panel_operand<P>(v0, v1, v2, v3);   // L^{-1}[4P + g][c]
+  if constexpr (P < 3) n = mfma16(-u, v, n);
+  if constexpr (WITH_L) L[c * LT + 4 * P + g] = u;
+  Linv[(4 * P + g) * LT + c] = v;
+}
+// m = I + G -> L [t][s] (row stride LT; only s <= t is meaningful) and L^{-1} [t][s] (zero above the diagonal).  Reads the
+// elements [t][s], s <= t, of m's transpose.
+template <bool WITH_L = true>
+__device__ __forceinline__ void cholesky16(f4 gram, float* L, float* Linv, int c, int g) {
+  f4 n;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) n[r] = 4 * g + r == c ? 1.0f : 0.0f;
+  f4 m = gram + n;
+  cholesky_panel<0, WITH_L>(m, n, L, Linv, c, g);
+  cholesky_panel<1, WITH_L>(m, n, L, Linv, c, g);
+  cholesky_panel<2, WITH_L>(m, n, L, Linv, c, g);
+  cholesky_panel<3, WITH_L>(m, n, L, Linv, c, g);
+}
+// Z = (I + N)^{-1}, N = strict_lower(X) diag(c), X [t][s] in LDS (row stride LT), cs: c_t on lane t of every 16 lanes;
+// put(t, s, z): z = Z[t][s].  row[r] = -N[c][4g + r], col[p] = -N[c][4p + g]; what they hold on and above the diagonal is not used.
+template <int P, typename F>
+__device__ __forceinline__ void lower_inverse_panel(f4& x, f4 row, float col, int c, int g, F&& put) {
+  const float x0 = x[0];
+  const float x1 = fmaf(row_bcast<4 * P + 1>(row[0]), x0, x[1]);
+  const float x2 = fmaf(row_bcast<4 * P + 2>(row[1]), x1, fmaf(row_bcast<4 * P + 2>(row[0]), x0, x[2]));
+  const float x3 = fmaf(row_bcast<4 * P + 3>(row[2]), x2,
+                        fmaf(row_bcast<4 * P + 3>(row[1]), x1, fmaf(row_bcast<4 * P + 3>(row[0]), x0, x[3])));
+  const float z = panel_operand<P>(x0, x1, x2, x3);
+  if constexpr (P < 3) x = mfma16(col, z, x);
+  put(4 * P + g, c, z);
+}
+template <typename F>
+__device__ __forceinline__ void lower_inverse16(const float* X, float cs, int c, int g, F&& put) {
+  f4 row = lds4(&X[c * LT + 4 * g]);
+  float col[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) col[p] = X[c * LT + 4 * p + g];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) row[r] *= -__shfl(cs, 4 * g + r);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) col[p] *= -__shfl(cs, 4 * p + g);
+  f4 x;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) x[r] = 4 * g + r == c ? 1.0f : 0.0f;
+  lower_inverse_panel<0>(x, row, col[0], c, g, put);
+  lower_inverse_panel<1>(x, row, col[1], c, g, put);
+  lower_inverse_panel<2>(x, row, col[2], c, g, put);
+  lower_inverse_panel<3>(x, row, 0.0f, c, g, put);
+}
+
+// For kernels without registers to spare: the masks and offsets of the two functions above are formed where they are called,
+// not kept over the block loop.
+struct Lane { int c, g; };
+__device__ __forceinline__ Lane fresh_lane(int c, int g) {
+  asm volatile("" : "+v"(c), "+v"(g));
+  return Lane{c, g};
 }
 
 __device__ __forceinline__ void io_store(float* p, float x) { *p = x; }

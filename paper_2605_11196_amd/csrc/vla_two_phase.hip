@@ -153,19 +153,9 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   };
   if (tb < T) prefetch(tb);
 
-  int cc = c;  // opaque copy: keeps the (c == t) masks from being hoisted into 16 registers
-  asm volatile("" : "+v"(cc));
-
   // c_t, Z = (I + strict_lower(L) diag(c))^{-1} and -NQ^T of one block from what its factorisation left in LDS
   // copy `pb`; one wave.  Results go to the block's record in the workspace.
   auto cz_pass = [&](int pb, float* smb) {
-    float m[C];  // lane c: row c of L
-#pragma unroll
-    for (int s4 = 0; s4 < C; s4 += 4) {
-      const f4 lr = lds4(&Lrs[pb][c * LT + s4]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m[s4 + e] = lr[e];
-    }
     const float dl = Lrs[pb][c * LT + c];  // L_cc
     float wn2 = 0.0f;
 #pragma unroll
@@ -174,12 +164,10 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     const float rdl = __builtin_amdgcn_rcpf(dl);
     const float an = __builtin_amdgcn_sqrtf(wn2) * rdl;                // ||A_t k^_t|| = ||w_t|| / L_tt
     const float cs = rdl * __builtin_amdgcn_rcpf(fmaxf(an, eps));      // alpha^_t = c_t w_t
-    float nm[C], Zr[C];
-    float ncs = -cs;
-    asm volatile("s_nop 1" : "+v"(ncs));   // a DPP read of a VGPR needs 2 wait states after its write
-    scale_cols<0>(m, nm, ncs);             // lane t: -L[t][s] c_s
-    asm volatile("s_nop 1" : "+v"(nm[0]));
-    z_rows<0>(nm, Zr, cc);
+    lower_inverse16(Lrs[pb], cs, c, g, [&](int t, int s, float z) {
+      smb[static_cast<unsigned>(t * C + s)] = z;
+      if constexpr (MAPF) Zs[t * LT + s] = z;
+    });
     const f4 la = lds4(&Lis[pb][c * LT + 4 * g]);
     f4 hq = f4{0, 0, 0, 0};   // H = L^{-1} GQ
 #pragma unroll
@@ -192,14 +180,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       nq[r] = (sidx <= c) ? -(csr * hq[r]) : 0.0f;
     }
     if (g == 0) {
-#pragma unroll
-      for (int t = 0; t < C; ++t) smb[t * C + c] = Zr[t];
       smb[2 * C * C + c] = -cs;
-      if constexpr (MAPF) {
-#pragma unroll
-        for (int t = 0; t < C; ++t) Zs[t * LT + c] = Zr[t];
-        cvs[c] = -cs;
-      }
+      if constexpr (MAPF) cvs[c] = -cs;
     }
     *reinterpret_cast<f4*>(smb + C * C + c * C + 4 * g) = nq;  // -NQ^T[t = c][s = 4g + r]
   };
@@ -381,46 +363,21 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     }
     __syncthreads();  // (2)
 
-    // ---- one wave: Cholesky of I + G and L^{-1} (lanes <32 rows of L, lanes >=32 columns of L^{-1});
+    // ---- one wave: Cholesky of I + G and L^{-1};
     //      another wave meanwhile: c, Z, NQ of the previous block
     const int sw = it % NW;
     const int sw2 = (it + 1) % NW;
     if (w == sw) {
       __builtin_amdgcn_s_setprio(3);   // the dependent chain is what the other wave waits for: issue it first
-      const bool lower = lane < 32;
-      float m[C];
+      f4 gram = lds4(&Gp[0][0][c * LT + 4 * g]);
+      f4 gq = lds4(&Gp[0][1][c * LT + 4 * g]);
 #pragma unroll
-      for (int s4 = 0; s4 < C; s4 += 4) {
-        f4 acc = lds4(&Gp[0][0][c * LT + s4]);
-        f4 acq = lds4(&Gp[0][1][c * LT + s4]);
-#pragma unroll
-        for (int ww = 1; ww < NW; ++ww) {
-          acc += lds4(&Gp[ww][0][c * LT + s4]);
-          acq += lds4(&Gp[ww][1][c * LT + s4]);
-        }
-        if (g == 1) *reinterpret_cast<f4*>(&GQs[pb][c * LT + s4]) = acq;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          m[s4 + e] = (lower ? acc[e] : 0.0f) + ((s4 + e) == cc ? 1.0f : 0.0f);
+      for (int ww = 1; ww < NW; ++ww) {
+        gram += lds4(&Gp[ww][0][c * LT + 4 * g]);
+        gq += lds4(&Gp[ww][1][c * LT + 4 * g]);
       }
-#pragma unroll
-      for (int t = 0; t < C; ++t) {
-        const float p = readlane(m[t], t);
-        const float ri = __builtin_amdgcn_rsqf(p);  // 1 ulp; L only has to satisfy L L^T = I + G to rounding
-        const float li = m[t] * ri;
-        m[t] = li;
-#pragma unroll
-        for (int j = t + 1; j < C; ++j) m[j] = fmaf(-li, readlane(li, j), m[j]);
-      }
-      if (g == 0) {  // rows of L
-#pragma unroll
-        for (int s4 = 0; s4 < C; s4 += 4)
-          *reinterpret_cast<f4*>(&Lrs[pb][c * LT + s4]) = f4{m[s4], m[s4 + 1], m[s4 + 2], m[s4 + 3]};
-      }
-      if (g == 2) {  // columns of L^{-1}
-#pragma unroll
-        for (int t = 0; t < C; ++t) Lis[pb][t * LT + c] = m[t];
-      }
+      *reinterpret_cast<f4*>(&GQs[pb][c * LT + 4 * g]) = gq;
+      cholesky16(gram, Lrs[pb], Lis[pb], c, g);
       __builtin_amdgcn_s_setprio(1);
     } else if (w == sw2 && it > 0) {
       __builtin_amdgcn_s_setprio(3);
