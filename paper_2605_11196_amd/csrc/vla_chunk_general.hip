@@ -44,8 +44,8 @@
 // part.  The sweeps over A and S and the Gram matrices are FP32 products on split bf16 terms (vla_mfma_util.h); Y and X
 // share their LDS with W and Alpha and the next block is staged at the end of a block, so that two workgroups
 // of d = 128 fit a compute unit (80 KB each).  Every option on, 2048 heads of 128, 8192 tokens, bf16: 43.7 ms with FP32
-// matrix instructions and one workgroup per compute unit, 35.6 ms so.  T = 256: 2048 heads of 64 0.59 -> 0.43 ms,
-// of 32 0.33 -> 0.25, of 96 1.26 -> 1.17.
+// matrix instructions and one workgroup per compute unit, 35.6 ms so, and 25.2 with the two chains on waves of their own
+// (vla_chunk_general_pipe.hip), which takes most calls; pipe_narrow() and pipe_wide() below say which.
 #include "vla_mfma_util.h"
 
 namespace vla {
@@ -677,36 +677,48 @@ template <int D, int DV, int SL, bool DB, bool SPLIT>
 hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
   return io_dtype == 1 ? launch<D, DV, SL, DB, SPLIT, uint16_t>(a, stream) : launch<D, DV, SL, DB, SPLIT, float>(a, stream);
 }
+// Which calls the kernel with the A chain and the S chain on waves of their own (vla_chunk_general_pipe.hip) takes.  T = 256,
+// this file's kernel / that one with waves of 16 columns (/ of 32), ms; bf16, every option on, unless said otherwise:
+//   d = 128: 64 heads 0.164 / 0.114, 256 heads 0.179 / 0.128, 512 heads 0.307 / 0.238 / 0.201, 2048 heads 1.160 / 0.918 /
+//            0.792; float32 256 heads 0.172 / 0.132, 2048 heads 1.253 / 0.993 / 1.006 (three-term u leaves one workgroup of
+//            wide waves a compute unit); no u, 2048 heads 0.951 / 0.799 / 0.845 (registers spill)
+//     d_v = 96: 2048 heads 1.149 / 0.882;  d_v = 64: 256 heads 0.178 / 0.116, 2048 heads 0.922 / 0.815, 16 tokens 0.080 / 0.084;
+//     d_v = 32: 256 heads 0.178 / 0.120, 512 heads, float32 0.246 / 0.244, 2048 heads, float32 0.907 / 0.950;
+//     d_v = 16: 256 heads 0.168 / 0.139, 512 heads 0.243 / 0.270
+//   d =  96: 256 heads 0.147 / 0.105, 2048 heads 1.146 / 0.768, 2048 heads, 16 tokens 0.102 / 0.076; every d_v alike
+//   d =  64: 256 heads 0.100 / 0.079, 512 heads 0.132 / 0.109 / 0.114, 768 heads 0.160 / 0.164 / 0.138, 2048 heads 0.408 / 0.388 /
+//            0.312; float32 256 heads 0.096 / 0.080, 768 heads 0.161 / 0.174 / 0.159, 2048 heads 0.407 / 0.407 / 0.406
+//     d_v = 96: 256 heads 0.118 / 0.082, 512 heads 0.154 / 0.156 / 0.128, 768 heads 0.251 / 0.233 / 0.207, 1024 heads 0.297 /
+//     0.304 / 0.324;  d_v = 128 the same within 5 %;  d_v = 32: 512 heads 0.131 / 0.109, 768 heads 0.159 / 0.167 / 0.215
+//   d =  32: 512 heads 0.107 / 0.078, 1024 heads 0.112 / 0.106, 2048 heads 0.217 / 0.191, 4096 heads 0.445 / 0.351
+//     d_v = 64: 768 heads 0.126 / 0.104, 1024 heads, float32 0.127 / 0.152;  d_v = 128: 256 heads 0.126 / 0.070, 640 heads,
+//     float32 0.152 / 0.153, 1024 heads 0.168 / 0.235
+bool pipe_narrow(const ForwardArgs& a, int d, int d_v) {
+  switch (d) {
+    case 128: return a.n_heads <= 256 || d_v >= 96 || (d_v == 64 && a.T > 16);
+    case 96: return true;
+    case 64: return a.n_heads <= 256 || (a.n_heads <= 512 && d_v <= 64);
+    case 32: return a.n_heads <= 768 || d_v <= 32;
+    default: return false;
+  }
+}
+// Waves of 32 columns: half the waves per head, so twice the heads of a compute unit.
+bool pipe_wide(const ForwardArgs& a, int d, int d_v, int io_dtype) {
+  if (d == 128) return d_v == 128 && a.n_heads > 256 && io_dtype == 1 && a.u != nullptr;
+  if (d == 64) return d_v == 64 ? a.n_heads > 512 : d_v > 64 && a.n_heads > 256 && a.n_heads <= 768;
+  return false;
+}
+
+// What those leave: d = 128 with narrow value heads beyond one head per compute unit (waves of 32 columns, two workgroups per
+// compute unit), small heads beyond the counts above, and d = 16 (T = 512, bf16, every option, heads of 32 on their own
+// compute unit: FP32 products, double-buffered 0.175, split 0.188 ms; d = 16 keeps them).
 template <int D, int DV>
 hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
-  // d = 128: waves of 32 columns (two workgroups of four waves per compute unit) from the count where a compute unit
-  // gets two, waves of 16 (one of eight) below.  T = 256, every option, 16 / 32 columns: 256 heads 0.183 / 0.251 ms,
-  // 512 heads 0.34 / 0.32, 2048 heads 1.27 / 1.15.
-  if constexpr (D == 128) {
-    if (a.n_heads > 256) return launch_as<D, DV, 32, false, true>(a, io_dtype, stream);
-  }
-  // Small heads on a compute unit of their own: the splits only lengthen the block.  T = 512, bf16, every option, split /
-  // FP32 products: d = 64, 256 heads 0.223 / 0.208 ms, 257 heads 0.256 / 0.274;  d = 32 (both double-buffered) 256
-  // heads 0.188 / 0.175, 512 heads 0.219 / 0.220, single-buffered 0.201 and 0.229.  d = 32, T = 256, 1024 heads: 0.21
-  // double-buffered and split, 0.13 single-buffered and split.
-  if constexpr (D == 64 && DV <= D) {
-    if (a.n_heads <= 256) return launch_as<D, DV, 16, false, false>(a, io_dtype, stream);
-  }
-  if constexpr (D <= 32 && DV <= D) {
+  if constexpr (D == 128) return launch_as<D, DV, 32, false, true>(a, io_dtype, stream);
+  if constexpr (D == 16 && DV == 16) {
     if (a.n_heads <= 512) return launch_as<D, DV, 16, true, false>(a, io_dtype, stream);
   }
   return launch_as<D, DV, 16, false, (D > 16)>(a, io_dtype, stream);
-}
-template <int D>
-hipError_t launch_dv(const ForwardArgs& a, int d_v, int io_dtype, hipStream_t stream) {
-  switch (d_v) {
-    case 16: return launch_io<D, 16>(a, io_dtype, stream);
-    case 32: return launch_io<D, 32>(a, io_dtype, stream);
-    case 64: return launch_io<D, 64>(a, io_dtype, stream);
-    case 96: return launch_io<D, 96>(a, io_dtype, stream);
-    case 128: return launch_io<D, 128>(a, io_dtype, stream);
-    default: return hipErrorInvalidValue;
-  }
 }
 // phase 1 of the two-phase and time-parallel modes with options: one workgroup per (head, segment)
 template <int D, typename IO, bool FULL>
@@ -741,12 +753,24 @@ hipError_t launch_scan(const ForwardArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_chunk_general(const ForwardArgs& a, int d, int d_v, int io_dtype, hipStream_t stream) {
-  switch (d) {
-    case 16: return launch_dv<16>(a, d_v, io_dtype, stream);
-    case 32: return launch_dv<32>(a, d_v, io_dtype, stream);
-    case 64: return launch_dv<64>(a, d_v, io_dtype, stream);
-    case 96: return launch_dv<96>(a, d_v, io_dtype, stream);
-    case 128: return launch_dv<128>(a, d_v, io_dtype, stream);
+  if (pipe_wide(a, d, d_v, io_dtype)) return launch_chunk_general_pipe_wide(a, d, d_v, io_dtype, stream);
+  if (pipe_narrow(a, d, d_v)) return launch_chunk_general_pipe_narrow(a, d, d_v, io_dtype, stream);
+  switch (d * 1000 + d_v) {
+    case 16016: return launch_io<16, 16>(a, io_dtype, stream);
+    case 16032: return launch_io<16, 32>(a, io_dtype, stream);
+    case 16064: return launch_io<16, 64>(a, io_dtype, stream);
+    case 16096: return launch_io<16, 96>(a, io_dtype, stream);
+    case 16128: return launch_io<16, 128>(a, io_dtype, stream);
+    case 32064: return launch_io<32, 64>(a, io_dtype, stream);
+    case 32096: return launch_io<32, 96>(a, io_dtype, stream);
+    case 32128: return launch_io<32, 128>(a, io_dtype, stream);
+    case 64016: return launch_io<64, 16>(a, io_dtype, stream);
+    case 64032: return launch_io<64, 32>(a, io_dtype, stream);
+    case 64096: return launch_io<64, 96>(a, io_dtype, stream);
+    case 64128: return launch_io<64, 128>(a, io_dtype, stream);
+    case 128016: return launch_io<128, 16>(a, io_dtype, stream);
+    case 128032: return launch_io<128, 32>(a, io_dtype, stream);
+    case 128064: return launch_io<128, 64>(a, io_dtype, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -77,6 +77,9 @@ hipError_t launch_chunk_d16(const ForwardArgs& a, int d_v, int io_dtype, hipStre
 // Same block form with the optional lines of Algorithm 1 (vla_chunk_general.hip); every head size.
 inline bool general_block_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 96 || d == 128; }
 hipError_t launch_chunk_general(const ForwardArgs& a, int d, int d_v, int io_dtype, hipStream_t stream);
+// A chain and S chain on waves of their own (vla_chunk_general_pipe.hip), d_k >= 32.  launch_chunk_general picks them.
+hipError_t launch_chunk_general_pipe_narrow(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
+hipError_t launch_chunk_general_pipe_wide(const ForwardArgs& a, int d_k, int d_v, int io_dtype, hipStream_t stream);
 // Its A chain alone, one workgroup per (head, time segment), writing the workspace records of the two-phase and
 // time-parallel modes (head sizes 32, 64, 96, 128).
 hipError_t launch_a_scan_general(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream);

@@ -374,3 +374,25 @@ def test_option_block_kernel_on_both_sides_of_its_head_counts(d, heads, dtype):
     got, ref = run_both(q, k, v, dtype=dtype, u=u, S0=S0, A0=A0, zkey0=z0, lambda0=0.1, u_scale=0.25, refresh_period=5,
                         refresh_eta=1e-2, step_offset=3, normalise_output=True, feature_map=True, mode=BLOCK)
     print(d, heads, dtype, assert_close(got, ref, TOL[dtype]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,d_v,heads", [(32, 16, 3), (32, 128, 3), (32, 64, 769), (64, 32, 3), (64, 64, 513), (64, 96, 257), (96, 64, 3),
+                                         (128, 16, 3), (128, 96, 3), (128, 128, 257)])
+def test_option_chains_on_waves_of_their_own(d, d_v, heads, dtype):
+    """Every staging layout and both wave widths, from one token to ragged third blocks, state and phase carried in; the
+    first and the last heads against the oracle (relative error bound of the I/O type, as everywhere)."""
+    rng = np.random.default_rng(d + d_v)
+    S0 = rng.standard_normal((1, heads, d_v, d)).astype(np.float32)
+    A0 = 0.1 * rng.standard_normal((1, heads, d, d)).astype(np.float32)
+    A0 = (A0 @ A0.transpose(0, 1, 3, 2) + np.eye(d, dtype=np.float32)).astype(np.float32)
+    A0 = 0.5 * (A0 + A0.transpose(0, 1, 3, 2))
+    z0 = np.abs(rng.standard_normal((1, heads, d))).astype(np.float32)
+    for T in (1, 16, 35):
+        q, k, _ = vla_inputs.gaussian_qkv(1, heads, T, d, seed=T + d)
+        v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+        u = rng.standard_normal(q.shape).astype(np.float32)
+        for opt, du in ((dict(u_scale=-0.3, refresh_period=9, step_offset=4, normalise_output=True, feature_map=True), u),
+                        (dict(refresh_period=5, refresh_eta=1e-2), None), (dict(normalise_output=True, feature_map=True), None)):
+            got, ref = run_both(q, k, v, u=du, S0=S0, A0=A0, zkey0=z0, dtype=dtype, mode=BLOCK, **opt)
+            assert_close(got, ref, TOL[dtype])
