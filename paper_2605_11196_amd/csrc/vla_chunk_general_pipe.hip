@@ -104,7 +104,15 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
   int c = lane & 15;
   int g = lane >> 4;
   // Once per block: what is derived from the lane (LDS and global offsets) is formed anew, not kept in registers.
-  auto fresh = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(c), "+v"(g)); };
+  auto fresh = [&]() __attribute__((always_inline)) { renew(c, g); };
+  // -1 on the diagonal for the splits: two registers where the waves have them, else formed where it is used
+  constexpr bool kKeepIdentity = NB * NJ < 16 && NB * NJV < 16;
+  u2 minus_one = minus_identity(c, g);
+  asm volatile("" : "+v"(minus_one));
+  auto identity = [&]() __attribute__((always_inline)) -> u2 {
+    if constexpr (kKeepIdentity) return minus_one;
+    else return minus_identity(c, g);
+  };
   const int T = a.T;
   const int nblk = (T + C - 1) / C;
   const float eps = a.eps;
@@ -169,7 +177,7 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
       for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJ; ++jn) {
-          const auto ab = split_tiles<true>(At[2 * kb][jn], At[2 * kb + 1][jn]);
+          const auto ab = split_tiles(At[2 * kb][jn], At[2 * kb + 1][jn], identity());
           xt[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), ab, xt[jn]);
           if constexpr (UK == kUSeparate) yt[jn] = UOps::sweep(UOps::operand(Us, kb, c, g), ab, yt[jn]);
           if (NJ > 1) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
@@ -205,48 +213,44 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
       }
       // token rows to operand rows: through LDS, where the partial matrices go afterwards (LDS operations of one wave are ordered)
       float* Yw = &region[w * kOwn];
-      auto operand_of = [&](const f4 (&x)[NJ], float* slab) __attribute__((always_inline)) -> Terms<3> {
+      auto operand_of = [&](const f4 (&x)[NJ], float* slab) __attribute__((always_inline)) {
 #pragma unroll
         for (int jn = 0; jn < NJ; ++jn)
 #pragma unroll
           for (int r = 0; r < 4; ++r) slab[(4 * g + r) * LDY + 16 * jn + c] = x[jn][r];
-        // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
-        const f4 zero{0, 0, 0, 0};
         const f4 x0 = lds4(&slab[c * LDY + 4 * g]);
-        const f4 x1 = NJ > 1 ? lds4(&slab[c * LDY + (NJ > 1 ? 16 : 0) + 4 * g]) : (w & 1) ? x0 : zero;
-        return split_tiles<true>(NJ == 1 && (w & 1) ? zero : x0, x1);
+        if constexpr (NJ > 1) return split_tiles(x0, lds4(&slab[c * LDY + 16 + 4 * g]), identity());
+        else return split_tile(x0, identity());
+      };
+      // this wave's columns of a staged operand
+      auto own_columns = [&](auto ops, const uint16_t* src) __attribute__((always_inline)) {
+        if constexpr (NJ > 1) return decltype(ops)::operand(src, w, c, g);
+        else return decltype(ops)::half_operand(src, w, c, g);
       };
       const f4 zero{0, 0, 0, 0};
-      const int kb = col0 / 32;
       {
-        const Terms<3> y = operand_of(yt, Yw);
+        const auto y = operand_of(yt, Yw);
         [[maybe_unused]] f4 gg;
         if constexpr (UK == kUSeparate) {
-          const Terms<UT> u = UOps::operand(Us, kb, c, g);
-          if constexpr (UT == 1) {
-            gg = mfma_bf16(y.t[2], u.t[0], zero);
-            gg = mfma_bf16(y.t[1], u.t[0], gg);
-            gg = mfma_bf16(y.t[0], u.t[0], gg);
-            gg *= urest[c];
-          } else {
-            gg = mfma_terms(y, u, zero);
-          }
+          const auto u = own_columns(UOps{}, Us);
+          if constexpr (UT == 1) gg = mfma_terms_left(y, u, zero) * urest[c];
+          else gg = mfma_terms(y, u, zero);
         }
         if constexpr (UK == kUSeparate) part(kG, w) = gg;
         __builtin_amdgcn_sched_barrier(0);
-        const f4 gk = Ops::sweep(y, Ops::operand(Ks, kb, c, g), zero);
+        const f4 gk = mfma_terms(y, own_columns(Ops{}, Ks), zero);
         part(kGK, w) = gk;
         if constexpr (UK == kUKeyRefresh) part(kG, w) = gk;
         __builtin_amdgcn_sched_barrier(0);
-        part(kGQ, w) = Ops::sweep(y, Ops::operand(Qs, kb, c, g), zero);
+        part(kGQ, w) = mfma_terms(y, own_columns(Ops{}, Qs), zero);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (FULL) {
-        const Terms<3> x = operand_of(xt, Yw + kXSlab);
+        const auto x = operand_of(xt, Yw + kXSlab);
         __builtin_amdgcn_sched_barrier(0);
-        part(kGX, w) = Ops::sweep(x, Ops::operand(Ks, kb, c, g), zero);
+        part(kGX, w) = mfma_terms(x, own_columns(Ops{}, Ks), zero);
         __builtin_amdgcn_sched_barrier(0);
-        part(kXQ, w) = Ops::sweep(x, Ops::operand(Qs, kb, c, g), zero);
+        part(kXQ, w) = mfma_terms(x, own_columns(Ops{}, Qs), zero);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -559,7 +563,7 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
       for (int kb = kb0; kb < kb1; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJV; ++jn) {
-          const auto sb = split_tiles<true>(St[2 * kb][jn], St[2 * kb + 1][jn]);
+          const auto sb = split_tiles(St[2 * kb][jn], St[2 * kb + 1][jn], identity());
           ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
           __builtin_amdgcn_sched_barrier(0);
           ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
@@ -632,7 +636,10 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
     constexpr int kHalf = (NKB + 1) / 2;
     for (int blk = 0; blk < nblk; ++blk) {
       fresh();
-      if (blk > 0) s_update(blk - 1);
+      // opaque: the compiler would peel the first block and keep twice the values over the loop (118 spilled registers for 61)
+      int done = blk;
+      asm volatile("" : "+s"(done));
+      if (done > 0) s_update(blk - 1);
       __syncthreads();  // (1)
 #pragma unroll
       for (int jn = 0; jn < NJV; ++jn) ft[jn] = ot[jn] = f4{0, 0, 0, 0};

@@ -20,6 +20,14 @@
 // 2.00 ms; vla_chunk.hip 2.20).  T = 512, bf16, vla_chunk.hip / here: 16 heads of 64 0.120 / 0.087 ms, 256 heads of 64
 // 0.121 / 0.097, 2048 heads of 64 0.413 / 0.365, 256 heads of 128 0.190 / 0.159, 512 heads 0.290 / 0.255.
 //
+// Vector instructions are what a SIMD has most of: one takes 4.9 cycles, a bf16 matrix instruction 17.7 by itself and 7.7 of
+// the vector unit's beside vector work, an FP32 one 32.5 of both.  So rows are addressed as a uniform base with an offset of the
+// lane (only the ragged last block clamps and masks), lane indices carry their range (24-bit products), and the partial Gram
+// matrices of a wave of 16 columns are formed from half operands: the S waves of d = 64 357 -> 290 vector instructions a block.
+// 256 heads of 64, float32, 2048 tokens 0.352 -> 0.318 ms; 2048 heads of 64, 8192 tokens, bf16 5.54 -> 5.33, of 128 15.4 ->
+// 15.1.  W kept as l, h, m in 24 bytes (two overlapping reads without moves) was 3 % faster with one head per compute unit
+// and 3 % slower with four: twice the LDS reads.
+//
 // Waves of 32 columns (two heads of 128 or four of 64 per compute unit) have to stay within 128 registers: offsets derived
 // from the lane are formed anew in each block (the compiler keeps some 60 of them otherwise: 1.27 -> 1.12 ms for 2048 heads
 // of 128, 512 tokens), v is fetched beside the pass over S and not a block ahead.  Measured and not kept: staging on the A
@@ -83,7 +91,15 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
   int c = lane & 15;
   int g = lane >> 4;
   // Once per block: what is derived from the lane (LDS and global offsets) is formed anew, not kept in registers.
-  auto fresh = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(c), "+v"(g)); };
+  auto fresh = [&]() __attribute__((always_inline)) { renew(c, g); };
+  // -1 on the diagonal for the splits: two registers where the waves have them, else formed where it is used
+  constexpr bool kKeepIdentity = NB * NJ < 16 && NB * NJV < 16;
+  u2 minus_one = minus_identity(c, g);
+  asm volatile("" : "+v"(minus_one));
+  auto identity = [&]() __attribute__((always_inline)) -> u2 {
+    if constexpr (kKeepIdentity) return minus_one;
+    else return minus_identity(c, g);
+  };
   const int T = a.T;
   const int nblk = (T + C - 1) / C;
   const float eps = a.eps;
@@ -117,7 +133,7 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
       for (int kb = 0; kb < NKB; ++kb) {
         const Terms<KT> ka = Ops::operand(Ks, kb, c, g);
 #pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) yt[jn] = Ops::sweep(ka, split_tiles<true>(At[2 * kb][jn], At[2 * kb + 1][jn]), yt[jn]);
+        for (int jn = 0; jn < NJ; ++jn) yt[jn] = Ops::sweep(ka, split_tiles(At[2 * kb][jn], At[2 * kb + 1][jn], identity()), yt[jn]);
         if (KT > 1 || NB * NJ >= 16) __builtin_amdgcn_sched_barrier(0);
       }
       const f4 rn4 = lds4(&rns[blk & 1][4 * g]);
@@ -131,14 +147,15 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
       // same-wave write -> read: LDS operations of one wave are ordered
       f4 gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
 #pragma unroll
-      for (int j2 = 0; j2 < (NJ + 1) / 2; ++j2) {
-        // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
-        const f4 zero{0, 0, 0, 0};
-        const f4 y0 = lds4(&Yw[c * LDY + 32 * j2 + 4 * g]);
-        const f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + (NJ > 1 ? 32 * j2 + 16 : 0) + 4 * g]) : (w & 1) ? y0 : zero;
-        const auto ya = split_tiles<true>(NJ == 1 && (w & 1) ? zero : y0, y1);
+      for (int j2 = 0; j2 < NJ / 2; ++j2) {
+        const auto ya = split_tiles(lds4(&Yw[c * LDY + 32 * j2 + 4 * g]), lds4(&Yw[c * LDY + 32 * j2 + 16 + 4 * g]), identity());
         gg = Ops::sweep(Ops::operand(Ks, col0 / 32 + j2, c, g), ya, gg);
         gq = Ops::sweep(Ops::operand(Qs, col0 / 32 + j2, c, g), ya, gq);
+      }
+      if constexpr (NJ == 1) {
+        const HalfTerms<3> ya = split_tile(lds4(&Yw[c * LDY + 4 * g]), identity());
+        gg = mfma_terms(Ops::half_operand(Ks, w, c, g), ya, gg);
+        gq = mfma_terms(Ops::half_operand(Qs, w, c, g), ya, gq);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) Yw[c * LT + 4 * g + r] = gg[r] * rn4[r];
@@ -276,10 +293,12 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
     // registers are consumed.
     auto load_kq = [&](int t0) __attribute__((always_inline)) {
       if (stager()) {
-        const int tr = t0 + srow();
-        const unsigned koff = static_cast<unsigned>((tr < T ? tr : T - 1) * D + sseg());
-        kpre.load(kh + koff);
-        qpre.load(qh + koff);
+        // uniform base and an offset of the lane; only the ragged last block clamps its rows
+        const size_t tok = static_cast<size_t>(t0) * D;
+        const int row = t0 + C <= T ? srow() : min(srow(), T - 1 - t0);
+        const unsigned koff = static_cast<unsigned>(row * D + sseg());
+        kpre.load(kh + tok + koff);
+        qpre.load(qh + tok + koff);
       }
     };
     auto stage = [&](int t0, int buf) __attribute__((always_inline)) {
@@ -340,12 +359,20 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
     auto vcol = [&]() { return row0 + c; };
     IO vpre[NJV][4];   // V[t0 + 4g + r][row0 + 16jn + c]
     auto load_v = [&](int t0) __attribute__((always_inline)) {
+      const IO* vb = vh + static_cast<size_t>(t0) * DV;
+      if (t0 + C <= T) {   // uniform
+        const IO* vl = vb + static_cast<unsigned>(4 * g * DV + vcol());
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = t0 + 4 * g + r;
-        const unsigned voff = static_cast<unsigned>((t < T ? t : T - 1) * DV + vcol());
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int jn = 0; jn < NJV; ++jn) vpre[jn][r] = vh[voff + 16 * jn];
+          for (int jn = 0; jn < NJV; ++jn) vpre[jn][r] = vl[r * DV + 16 * jn];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const IO* vl = vb + static_cast<unsigned>(min(4 * g + r, T - 1 - t0) * DV + vcol());
+#pragma unroll
+          for (int jn = 0; jn < NJV; ++jn) vpre[jn][r] = vl[16 * jn];
+        }
       }
     };
     f4 ft[NJV], ot[NJV];
@@ -359,7 +386,7 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
       for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
         for (int jn = 0; jn < NJV; ++jn) {
-          const auto sb = split_tiles<true>(St[2 * kb][jn], St[2 * kb + 1][jn]);
+          const auto sb = split_tiles(St[2 * kb][jn], St[2 * kb + 1][jn], identity());
           ft[jn] = Ops::sweep(Ops::operand(Ks, kb, c, g), sb, ft[jn]);
           if constexpr (KT > 1) __builtin_amdgcn_sched_barrier(0);
           ot[jn] = Ops::sweep(Ops::operand(Qs, kb, c, g), sb, ot[jn]);
@@ -397,16 +424,20 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_pipe_kernel(Forwa
       for (int jn = 0; jn < NJV; ++jn)
 #pragma unroll
         for (int r = 0; r < 4; ++r) ot[jn] = mfma16(nqa[r], ft[jn][r], ot[jn]);
+      IO* ol = oh + static_cast<size_t>(t0) * DV + static_cast<unsigned>(4 * g * DV + vcol());
+      auto store_row = [&](int r) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = t0 + 4 * g + r;
-        if (t < T) {
-          const unsigned ooff = static_cast<unsigned>(t * DV + vcol());
+        for (int jn = 0; jn + 1 < NJV; jn += 2)
+          io_store2(ol + r * DV + 16 * jn, ol + r * DV + 16 * jn + 16, ot[jn][r], ot[jn + 1][r]);
+        if (NJV % 2 == 1) io_store(ol + r * DV + 16 * (NJV - 1), ot[NJV - 1][r]);
+      };
+      if (t0 + C <= T) {   // uniform
 #pragma unroll
-          for (int jn = 0; jn + 1 < NJV; jn += 2)
-            io_store2(oh + ooff + 16 * jn, oh + ooff + 16 * jn + 16, ot[jn][r], ot[jn + 1][r]);
-          if (NJV % 2 == 1) io_store(oh + ooff + 16 * (NJV - 1), ot[NJV - 1][r]);
-        }
+        for (int r = 0; r < 4; ++r) store_row(r);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t0 + 4 * g + r < T) store_row(r);
       }
       __builtin_amdgcn_sched_barrier(0);
       decltype(Ops::tokens_b(f4{})) ce[NJV];

@@ -86,17 +86,17 @@ __device__ __forceinline__ void split3_cut(f4 x, u2& h, u2& m, u2& l) {
 // where the above takes 22 vector ones, at twice the latency: for kernels whose waves cover it (vla_chunk_pipe.hip, 2048
 // heads of 128: 2.28 -> 2.00 ms); with two waves per SIMD it gains nothing (vla_chunk.hip: 17.35 and 17.36 ms, 2048 heads
 // of 64 6.69 -> 7.07).
-__device__ __forceinline__ u2 minus_identity() {
-  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int i = (lane & 15) - 4 * (lane >> 4);   // the slot on the diagonal, if 0..3
+__device__ __forceinline__ u2 minus_identity(int c, int g) {
+  const int i = c - 4 * g;   // the slot on the diagonal, if 0..3
   return u2{i == 0 ? 0x0000bf80u : i == 1 ? 0xbf800000u : 0u, i == 2 ? 0x0000bf80u : i == 3 ? 0xbf800000u : 0u};
 }
-__device__ __forceinline__ f4 residual(f4 x, u2 h, u2 minus_one) {
+// a b over 16 columns, four slots of a lane group
+__device__ __forceinline__ f4 mfma_bf16_half(u2 a, u2 b, f4 acc) {
   typedef short s4 __attribute__((ext_vector_type(4)));
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, minus_one), __builtin_bit_cast(s4, h), x, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), acc, 0, 0, 0);
 }
-__device__ __forceinline__ void split3_cut_matrix(f4 x, u2& h, u2& m, u2& l) {
-  const u2 minus_one = minus_identity();
+__device__ __forceinline__ f4 residual(f4 x, u2 h, u2 minus_one) { return mfma_bf16_half(minus_one, h, x); }
+__device__ __forceinline__ void split3_cut_matrix(f4 x, u2 minus_one, u2& h, u2& m, u2& l) {
   h = u2{pack_tops(x[0], x[1]), pack_tops(x[2], x[3])};
   const f4 r = residual(x, h, minus_one);
   m = u2{pack_tops(r[0], r[1]), pack_tops(r[2], r[3])};
@@ -130,16 +130,17 @@ __device__ __forceinline__ u4 cat(u2 a, u2 b) { return u4{a[0], a[1], b[0], b[1]
 template <int NT> struct Terms { u4 t[NT]; };
 
 // Operand terms of two accumulator tiles (32 rows of the contraction).
-template <bool MATRIX = false>
 __device__ __forceinline__ Terms<3> split_tiles(f4 x0, f4 x1) {
   u2 h0, m0, l0, h1, m1, l1;
-  if constexpr (MATRIX) {
-    split3_cut_matrix(x0, h0, m0, l0);
-    split3_cut_matrix(x1, h1, m1, l1);
-  } else {
-    split3_cut(x0, h0, m0, l0);
-    split3_cut(x1, h1, m1, l1);
-  }
+  split3_cut(x0, h0, m0, l0);
+  split3_cut(x1, h1, m1, l1);
+  return Terms<3>{{cat(h0, h1), cat(m0, m1), cat(l0, l1)}};
+}
+// with the residuals from the matrix unit (minus_one: minus_identity() of the lane)
+__device__ __forceinline__ Terms<3> split_tiles(f4 x0, f4 x1, u2 minus_one) {
+  u2 h0, m0, l0, h1, m1, l1;
+  split3_cut_matrix(x0, minus_one, h0, m0, l0);
+  split3_cut_matrix(x1, minus_one, h1, m1, l1);
   return Terms<3>{{cat(h0, h1), cat(m0, m1), cat(l0, l1)}};
 }
 // acc += a b over 32 columns.  b holds three terms; a one or three.  Small products first.
@@ -157,6 +158,38 @@ __device__ __forceinline__ f4 mfma_terms(const Terms<NT>& a, const Terms<3>& b, 
     acc = mfma_bf16(a.t[1], b.t[0], acc);
     return mfma_bf16(a.t[0], b.t[0], acc);
   }
+}
+
+// The same over 16 columns (a wave's slab of one tile): half an operand, half the terms to split.
+template <int NT> struct HalfTerms { u2 t[NT]; };
+__device__ __forceinline__ HalfTerms<3> split_tile(f4 x, u2 minus_one) {
+  HalfTerms<3> s;
+  split3_cut_matrix(x, minus_one, s.t[0], s.t[1], s.t[2]);
+  return s;
+}
+template <int NT>
+__device__ __forceinline__ f4 mfma_terms(const HalfTerms<NT>& a, const HalfTerms<3>& b, f4 acc) {
+  if constexpr (NT == 3) {
+    acc = mfma_bf16_half(a.t[0], b.t[2], acc);
+    acc = mfma_bf16_half(a.t[2], b.t[0], acc);
+    acc = mfma_bf16_half(a.t[1], b.t[1], acc);
+    acc = mfma_bf16_half(a.t[0], b.t[1], acc);
+    acc = mfma_bf16_half(a.t[1], b.t[0], acc);
+  } else {
+    acc = mfma_bf16_half(a.t[0], b.t[2], acc);
+    acc = mfma_bf16_half(a.t[0], b.t[1], acc);
+  }
+  return mfma_bf16_half(a.t[0], b.t[0], acc);
+}
+// three terms on the left, one on the right
+template <typename T3, typename T1>
+__device__ __forceinline__ f4 mfma_terms_left(const T3& a, const T1& b, f4 acc) {
+#pragma unroll
+  for (int i = 2; i >= 0; --i) {
+    if constexpr (sizeof(a.t[0]) == sizeof(u4)) acc = mfma_bf16(a.t[i], b.t[0], acc);
+    else acc = mfma_bf16_half(a.t[i], b.t[0], acc);
+  }
+  return acc;
 }
 
 // A contraction over the 16 tokens of a block fills only half of the 32 slots, so one instruction takes two of the
@@ -261,10 +294,17 @@ struct BlockOps {
     for (int i = 0; i < NT; ++i) x.t[i] = *reinterpret_cast<const u4*>(&src[i * TERM + c * LDK + 32 * kb + 8 * g]);
     return x;
   }
+  // its columns 16 b .. 16 b + 15
+  static __device__ __forceinline__ HalfTerms<NT> half_operand(const uint16_t* src, int b, int c, int g) {
+    HalfTerms<NT> x;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+      x.t[i] = *reinterpret_cast<const u2*>(&src[i * TERM + c * LDK + 32 * (b >> 1) + 8 * g + 4 * (b & 1)]);
+    return x;
+  }
   // two accumulator tiles (one without the split) as the other operand
-  template <bool MATRIX = false>
   static __device__ __forceinline__ auto tiles(f4 x0, f4 x1) {
-    if constexpr (SPLIT) return split_tiles<MATRIX>(x0, x1);
+    if constexpr (SPLIT) return split_tiles(x0, x1);
     else return x0;
   }
   template <typename X>
@@ -529,8 +569,14 @@ __device__ __forceinline__ void lower_inverse16(const float* X, float cs, int c,
 // For kernels without registers to spare: the masks and offsets of the two functions above are formed where they are called,
 // not kept over the block loop.
 struct Lane { int c, g; };
-__device__ __forceinline__ Lane fresh_lane(int c, int g) {
+// (With their ranges, so that products with them are shifts and 24-bit ones: v_mul_lo_u32 takes four times as long.)
+__device__ __forceinline__ void renew(int& c, int& g) {
   asm volatile("" : "+v"(c), "+v"(g));
+  __builtin_assume(c >= 0 && c < 16);
+  __builtin_assume(g >= 0 && g < 4);
+}
+__device__ __forceinline__ Lane fresh_lane(int c, int g) {
+  renew(c, g);
   return Lane{c, g};
 }
 

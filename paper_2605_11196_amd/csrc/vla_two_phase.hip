@@ -316,6 +316,10 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     if (do_map) load_map_v(t0, vnext);   // consumed one block later
 
     // ---- Y^T = K^ A0 and the partial Gram matrices
+    auto split = [&](f4 x0, f4 x1) {
+      if constexpr (MAPF && kSplit) return split_tiles(x0, x1, minus_identity(c, g));
+      else return Prod::tiles(x0, x1);
+    };
     f4 yt[NJ];
 #pragma unroll
     for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
@@ -326,7 +330,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       for (int jn = 0; jn < NJ; ++jn)
         // with the map runs beside it (MAPF) the residuals of the split go to the matrix unit: 16 heads of 64, T = 131072,
         // 1.612 -> 1.592 ms; without them nothing (T = 4096: 0.150 -> 0.151), and nothing for the splits of the map runs
-        yt[jn] = Prod::sweep(ka, Prod::template tiles<MAPF>(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
+        yt[jn] = Prod::sweep(ka, split(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
       if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one step's splits at a time in registers
     }
     f4 rn4 = f4{1, 1, 1, 1};
