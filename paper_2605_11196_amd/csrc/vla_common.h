@@ -90,6 +90,9 @@ hipError_t launch_a_scan_general(const ForwardArgs& a, int d, int io_dtype, hipS
 size_t two_phase_workspace_bytes(int n_heads, int T, int d);
 hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream);
 
+// The A chain and the affine map of S of every (head, time segment), into the workspace (vla_a_map.hip).
+hipError_t launch_a_map(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream);
+
 // Time-parallel mode: the sequence is cut into segments that run concurrently (vla_two_phase.hip drives it,
 // vla_segments.hip holds the kernels that compute the state at the segment boundaries).
 struct SegmentPlan {

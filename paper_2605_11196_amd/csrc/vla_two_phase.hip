@@ -10,7 +10,8 @@
 //   SM  [544]        Z | -NQ^T | -c_t | 1 / max(q_t . zkey_t, eps)  (two 16x16 row-major matrices and two vectors of
 //                    16; the last one only with the normalised read-out)
 //
-//   phase 1 (a_scan_kernel):  one workgroup per head, the A chain of the block form; the C x C work the S
+//   phase 1 (a_scan_kernel; with segments a_map_kernel in vla_a_map.hip):  one workgroup per head, the A chain of the block
+//                             form; the C x C work the S
 //                             recurrence needs (c_t, Z, NQ) is done one block behind by a wave that would
 //                             otherwise wait for the factorisation of the next block
 //   phase 2 (s_rows_kernel):  one wave per (head, 16-row slab of S); operands come straight from
@@ -21,6 +22,8 @@
 // (driver at the end of this file, boundary states in vla_segments.hip) runs the segments concurrently.
 #include "vla_mfma_util.h"
 
+#include <math.h>
+
 #include <type_traits>
 
 namespace vla {
@@ -29,34 +32,17 @@ namespace {
 // ------------------------------------------------------------------------------------------ phase 1
 // Two-wave workgroups (d <= 64) are compiled for three waves per SIMD.
 //
-// MAPF (time-parallel mode, d <= 64): the workgroup also forms the affine map S_end = S_start P + Q of its
-// segment, which the composition of the segment-start states needs.  Rows of S are independent, so P is what the
-// rows of the identity evolve into with v = 0 and Q what a zero state evolves into with the real v; both run here
-// one block behind the A chain, on the operands that are still in LDS (K^ and W of the previous block in a second
-// copy, Z and c from the C x C pass), instead of in a pass of their own that reads them back from the workspace.
-// The 2 d/16 row slabs of 16 rows are dealt out over the waves.
-//
-// Products with A, S and W: split bf16 terms (vla_mfma_util.h); W is split once, as it is formed.  KT = 1: bf16 keys
+// Products with A and W: split bf16 terms (vla_mfma_util.h); W is split once, as it is formed.  KT = 1: bf16 keys
 // and queries without a feature map are staged as they are (keys times a power of two, key_scale), and the rest of
-// 1 / ||k|| goes on the rows and columns of the results; KT = 3 otherwise (terms of k^ and q).  With MAPF and KT = 3 the
-// products stay on the FP32 instruction: two copies of three-term keys would leave three instead of four workgroups per
-// compute unit, and without MAPF the maps cost a pass.
-// Bound by the block's serial chain and, with the maps, the matrix pipes.  16 heads of 64, bf16, T = 131072, whole call,
-// with the S rows below already on split products: 1.89 ms with FP32 products here, 1.63 split; heads of 128,
-// T = 32768: 1.49 and 1.38.
-template <int D, int NW, typename IO, bool MAPF, int KT>
-__global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_kernel(ForwardArgs a) {
+// 1 / ||k|| goes on the rows and columns of the results; KT = 3 otherwise (terms of k^ and q).
+// Bound by the block's serial chain.  Segments of a sequence take vla_a_map.hip.
+template <int D, int NW, typename IO, int KT>
+__global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(ForwardArgs a) {
   static_assert(NW >= 2, "the C x C pass of the previous block runs on a second wave");
-  constexpr int NKB = MAPF ? 2 : 1;            // copies of K^ and W in LDS
-  constexpr int NSLAB = D / 16;                // 16-row slabs of a d x d state
-  constexpr int SPW = 2 * NSLAB / NW;          // slabs of the map (Q run, then P run) per wave
-  static_assert(!MAPF || NSLAB % NW == 0, "whole slabs per wave, the Q run in its first slots");
-  constexpr int QSL = NSLAB / NW;              // slots i < QSL of a wave are Q-run slabs, the others P-run slabs
   constexpr int SL = D / NW;
   constexpr int NJ = SL / 16;
   constexpr int NB = D / 16;
-  constexpr bool kSplit = KT == 1 || !MAPF;
-  using Prod = BlockOps<kSplit, kSplit ? KT : 1, D>;
+  using Prod = BlockOps<true, KT, D>;
   constexpr int STEP = Prod::STEP;
   constexpr bool kRawKeys = KT == 1;
   static_assert(!kRawKeys || sizeof(IO) == 2, "one term: bf16 numbers");
@@ -73,19 +59,13 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   static_assert(EPT % 4 == 0 && TPR <= 16 && (TPR & (TPR - 1)) == 0 && C * TPR <= NT && D % EPT == 0 &&
                 D / EPT <= TPR, "staging layout");
 
-  __shared__ __align__(16) uint16_t Ksb[NKB][Prod::SIZE];   // terms of K^ (of k times a power of two: kRawKeys)
+  __shared__ __align__(16) uint16_t Ks[Prod::SIZE];          // terms of K^ (of k times a power of two: kRawKeys)
   __shared__ __align__(16) uint16_t Qs[Prod::SIZE];
   __shared__ __align__(16) float Ysb[NW][C * LDY];           // Y^T [t][j], a slab per wave, which no other wave reads
-  __shared__ __align__(16) u4 Whm[NKB][4 * D];               // W [j][t], split
-  __shared__ __align__(16) u2 Wl[NKB][kSplit ? 4 * D : 1];
+  __shared__ __align__(16) u4 Whm[4 * D];                    // W [j][t], split
+  __shared__ __align__(16) u2 Wl[4 * D];
   __shared__ __align__(16) float rns[2][C];                  // 1 / max(||k_t||, eps) over its power of two (kRawKeys)
   __shared__ __align__(16) float Gp[NW][2][C * LT];
-  // MAPF: Z [t][s] and -c of the previous block live in Y^T's array, which is dead between barrier (2) of a block
-  // and the first barrier of the next one: exactly the window in which they are written and read (four
-  // workgroups of 40 KB share a compute unit; separate arrays would make it three)
-  static_assert(NW * C * LDY >= C * LT + C, "Z and c fit the Y^T array");
-  float* const Zs = &Ysb[0][0];
-  float* const cvs = Zs + C * LT;
   // kept for one more block (two copies, by block parity): the wave that turns them into c, Z, NQ reads the
   // previous block's while the factorisation of the current block writes its own
   __shared__ __align__(16) float Lis[2][C * LT];   // L^{-1} [t][s]
@@ -166,7 +146,6 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     const float cs = rdl * __builtin_amdgcn_rcpf(fmaxf(an, eps));      // alpha^_t = c_t w_t
     lower_inverse16(Lrs[pb], cs, c, g, [&](int t, int s, float z) {
       smb[static_cast<unsigned>(t * C + s)] = z;
-      if constexpr (MAPF) Zs[t * LT + s] = z;
     });
     const f4 la = lds4(&Lis[pb][c * LT + 4 * g]);
     f4 hq = f4{0, 0, 0, 0};   // H = L^{-1} GQ
@@ -179,79 +158,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       const float csr = __shfl(cs, sidx);
       nq[r] = (sidx <= c) ? -(csr * hq[r]) : 0.0f;
     }
-    if (g == 0) {
-      smb[2 * C * C + c] = -cs;
-      if constexpr (MAPF) cvs[c] = -cs;
-    }
+    if (g == 0) smb[2 * C * C + c] = -cs;
     *reinterpret_cast<f4*>(smb + C * C + c * C + 4 * g) = nq;  // -NQ^T[t = c][s = 4g + r]
-  };
-
-  // ---- the segment's affine map (MAPF): mst[i][b][r] = X[row0_i + c][16b + 4g + r] for this wave's slabs
-  const bool do_map = MAPF && seg != a.n_seg - 1;   // nothing follows the last segment
-  const IO* vh = static_cast<const IO*>(a.v) + static_cast<size_t>(head) * static_cast<size_t>(a.T) * D;
-  f4 mst[MAPF ? SPW : 1][NB];
-  IO vcur[MAPF ? SPW : 1][4] = {}, vnext[MAPF ? SPW : 1][4] = {};
-  if constexpr (MAPF) {
-#pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-      const int sl = w + NW * i;                       // slab: Q run for sl < NSLAB, then P run
-      const bool p_run = sl >= NSLAB;
-      const int row0 = (sl % NSLAB) * 16;
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mst[i][b][r] = (p_run && row0 + c == 16 * b + 4 * g + r) ? 1.0f : 0.0f;
-    }
-  }
-  // v of the block starting at t0 in accumulator layout, for the Q-run slabs (rows past the end: the last row)
-  auto load_map_v = [&](int t0, IO (&vv)[MAPF ? SPW : 1][4]) {
-    if constexpr (MAPF) {
-#pragma unroll
-      for (int i = 0; i < QSL; ++i) {
-        const int sl = w + NW * i;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = t0 + 4 * g + r;
-          vv[i][r] = vh[static_cast<size_t>(t < T ? t : T - 1) * D + sl * 16 + c];
-        }
-      }
-    }
-  };
-  // one block of the S recurrence on this wave's slabs: operands of the block in LDS copy `kb`
-  auto map_step = [&](int t0, int cp, const IO (&vv)[MAPF ? SPW : 1][4]) {
-    if constexpr (MAPF) {
-      const f4 za = lds4(&Zs[c * LT + 4 * g]);
-      const f4 cg = lds4(&cvs[4 * g]);
-      const f4 rn4 = lds4(&rns[cp][4 * g]);
-#pragma unroll
-      for (int i = 0; i < SPW; ++i) {
-        f4 ft = f4{0, 0, 0, 0};
-#pragma unroll
-        for (int kb = 0; kb < NB / STEP; ++kb) {
-          ft = Prod::sweep(Prod::operand(Ksb[cp], kb, c, g),
-                           Prod::tiles(mst[i][STEP * kb], mst[i][STEP * kb + STEP - 1]), ft);
-          if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one split at a time in registers
-        }
-        if constexpr (kRawKeys) ft *= rn4;
-        if (i < QSL) {   // known at compile time: the P run starts from v = 0
-          if (t0 + C <= T) {   // uniform: only the ragged last block masks rows past the end
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ft[r] += neg_widen(vv[i][r]);
-          } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ft[r] += (t0 + 4 * g + r < T) ? neg_widen(vv[i][r]) : 0.0f;
-          }
-        }
-        f4 et = f4{0, 0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) et = mfma16(za[r], ft[r], et);
-        const f4 ce = et * cg;
-        const auto cb = Prod::tokens_b(ce);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          mst[i][b] = Prod::update(Prod::w_load(Whm[cp], Wl[cp], 16 * b + c, c, g), cb, mst[i][b]);
-      }
-    }
   };
 
   int blk = seg * a.seg_blocks;
@@ -259,8 +167,6 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
   __builtin_amdgcn_s_setprio(1);
   for (int t0 = tb; t0 < T; t0 += C, ++blk, ++it) {
     const int pb = it & 1;
-    const int cp = MAPF ? pb : 0;
-    uint16_t* Ks = Ksb[cp];
     // ---- stage K^ and Q (LDS); 1 / max(||k||, eps) per token goes to the workspace
     if (stage_wave) {
       float kx[EPT];
@@ -313,13 +219,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
     }
     __syncthreads();  // (1)
     if (t0 + C < T) prefetch(t0 + C);
-    if (do_map) load_map_v(t0, vnext);   // consumed one block later
 
     // ---- Y^T = K^ A0 and the partial Gram matrices
-    auto split = [&](f4 x0, f4 x1) {
-      if constexpr (MAPF && kSplit) return split_tiles(x0, x1, minus_identity(c, g));
-      else return Prod::tiles(x0, x1);
-    };
     f4 yt[NJ];
 #pragma unroll
     for (int jn = 0; jn < NJ; ++jn) yt[jn] = f4{0, 0, 0, 0};
@@ -328,10 +229,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       const auto ka = Prod::operand(Ks, kb, c, g);
 #pragma unroll
       for (int jn = 0; jn < NJ; ++jn)
-        // with the map runs beside it (MAPF) the residuals of the split go to the matrix unit: 16 heads of 64, T = 131072,
-        // 1.612 -> 1.592 ms; without them nothing (T = 4096: 0.150 -> 0.151), and nothing for the splits of the map runs
-        yt[jn] = Prod::sweep(ka, split(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
-      if constexpr (kSplit) __builtin_amdgcn_sched_barrier(0);   // one step's splits at a time in registers
+        yt[jn] = Prod::sweep(ka, Prod::tiles(At[STEP * kb][jn], At[STEP * kb + STEP - 1][jn]), yt[jn]);
+      __builtin_amdgcn_sched_barrier(0);   // one step's splits at a time in registers
     }
     f4 rn4 = f4{1, 1, 1, 1};
     if constexpr (kRawKeys) rn4 = lds4(&rns[pb][4 * g]);
@@ -346,22 +245,13 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
       // same-wave write -> read: LDS operations of one wave are ordered
       // G[s][t] and GQ[s][t] come out with t on the rows of the accumulator
       f4 gg = f4{0, 0, 0, 0}, gq = f4{0, 0, 0, 0};
-      if constexpr (kSplit) {
-        // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
-        const f4 zero{0, 0, 0, 0};
-        const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
-        const f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + (NJ > 1 ? 16 : 0) + 4 * g]) : (w & 1) ? y0 : zero;
-        const auto ya = Prod::tiles(NJ == 1 && (w & 1) ? zero : y0, y1);
-        gg = Prod::sweep(Prod::operand(Ks, col0 / 32, c, g), ya, gg);
-        gq = Prod::sweep(Prod::operand(Qs, col0 / 32, c, g), ya, gq);
-      } else {
-#pragma unroll
-        for (int jn = 0; jn < NJ; ++jn) {
-          const f4 y = lds4(&Yw[c * LDY + 16 * jn + 4 * g]);
-          gg = Prod::sweep(Prod::operand(Ks, col0 / 16 + jn, c, g), y, gg);
-          gq = Prod::sweep(Prod::operand(Qs, col0 / 16 + jn, c, g), y, gq);
-        }
-      }
+      // slots 0-3 hold the first 16 of 32 columns, slots 4-7 the second ones: a slab of 16 columns fills one half
+      const f4 zero{0, 0, 0, 0};
+      const f4 y0 = lds4(&Yw[c * LDY + 4 * g]);
+      const f4 y1 = NJ > 1 ? lds4(&Yw[c * LDY + (NJ > 1 ? 16 : 0) + 4 * g]) : (w & 1) ? y0 : zero;
+      const auto ya = Prod::tiles(NJ == 1 && (w & 1) ? zero : y0, y1);
+      gg = Prod::sweep(Prod::operand(Ks, col0 / 32, c, g), ya, gg);
+      gq = Prod::sweep(Prod::operand(Qs, col0 / 32, c, g), ya, gq);
       *reinterpret_cast<f4*>(&Gp[w][0][c * LT + 4 * g]) = gg * rn4;
       *reinterpret_cast<f4*>(&Gp[w][1][c * LT + 4 * g]) = gq;
     }
@@ -401,49 +291,20 @@ __global__ void __launch_bounds__(64 * NW, (NW == 2 && !MAPF) ? 3 : 2) a_scan_ke
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc = mfma16(la[r], yt[jn][r], acc);
         n2 += acc * acc;
-        Prod::w_store(Whm[cp], Wl[cp], col0 + 16 * jn + c, c, g, acc);
+        Prod::w_store(Whm, Wl, col0 + 16 * jn + c, c, g, acc);
         *reinterpret_cast<f4*>(wg + (col0 + 16 * jn + c) * C + 4 * g) = acc;
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) n2[r] = row_sum16(n2[r]);
       if (c == 0) *reinterpret_cast<f4*>(&wn2p[w][4 * g]) = n2;
     }
-    // ---- the map, one block behind: Z and c of block it - 1 were formed before barrier (3), its K^ and W sit in
-    //      the other LDS copy, which is not written again before barrier (4)
-    if constexpr (MAPF) {
-      if (do_map) {
-        __builtin_amdgcn_s_setprio(0);   // off the A chain's path: behind the other workgroups' work
-        if (it > 0) map_step(t0 - C, pb ^ 1, vcur);
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int i = 0; i < QSL; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) vcur[i][r] = vnext[i][r];
-      }
-    }
     __syncthreads();  // (4)
 
     // ---- A -= W W^T
-    Prod::template downdate<NB, NJ>(Whm[cp], Wl[cp], col0 + c, c, g, pb, [&](int b, int jn) -> f4& { return At[b][jn]; });
+    Prod::template downdate<NB, NJ>(Whm, Wl, col0 + c, c, g, pb, [&](int b, int jn) -> f4& { return At[b][jn]; });
   }
   // c, Z, NQ of the last block: everything it needs was written before the last barrier
   if (it > 0 && w == it % NW) cz_pass((it - 1) & 1, SMp + static_cast<size_t>(blk - 1) * SMB);
-  if constexpr (MAPF) {
-    if (do_map && it > 0) {   // uniform over the workgroup
-      __syncthreads();        // Z and c of the last block
-      map_step((blk - 1) * C, (it - 1) & 1, vcur);
-#pragma unroll
-      for (int i = 0; i < SPW; ++i) {
-        const int sl = w + NW * i;
-        float* out = a.seg_PQ + (static_cast<size_t>(blockIdx.x) * 2 + (sl >= NSLAB ? 0 : 1)) * D * D;
-        const int row0 = (sl % NSLAB) * 16;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          *reinterpret_cast<f4*>(out + (row0 + c) * D + 16 * b + 4 * g) = mst[i][b];
-      }
-    }
-  }
-
   if (a.A_T && seg == a.n_seg - 1) {
     float* AT = a.A_T + static_cast<size_t>(head) * D * D;
     int g2 = g, c2 = c;
@@ -1070,49 +931,40 @@ template <int D, int NW, typename IO>
 hipError_t launch_phases(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
+  const int io_dtype = std::is_same<IO, uint16_t>::value ? 1 : 0;
   const long long hs = static_cast<long long>(a.n_heads) * a.n_seg;
   if (hs * (D / 8) > 0x7fffffffLL) return hipErrorInvalidValue;   // the largest grid below: 2 D/16 waves per pair
-  // A separate penalty direction or the normalised read-out: the A chain of the block kernel that carries
-  // them; its records have the layout the S-row kernels below read.
-  const bool general = runs_on_option_kernel(a);
-  // Up to d = 64 the plain A scan also forms the per-segment affine maps of S (its registers hold them beside A).
-  constexpr bool kFusedMap = D <= 64;
-  // Worth it once the (head, segment) pairs fill the chip (measured at 16 heads, d = 64: 3 % faster at 1024
-  // pairs, 5 % slower at 512 and below, where a block's latency counts and the maps lengthen it).
   const bool rect = a.d_v > 0 && a.d_v != D;   // value heads of another size: the A scan is the same, S has d_v rows
-  const bool raw_keys = sizeof(IO) == 2 && a.feature_map == 0;   // operands of one term
-  // Mapped bf16 heads of 64: not (16 heads, T = 65536: 1.10 ms with the maps in a pass of their own on split products,
-  // 1.12 ms with the FP32 ones that fit here; float32 input 1.17 and 1.12, d = 32 0.59 and 0.54).
-  const bool own_pass = D == 64 && sizeof(IO) == 2 && !raw_keys;
-  const bool fused_map = kFusedMap && !own_pass && !general && !rect && a.n_seg > 1 && hs >= 768;
-  auto scan_of = [&](auto kt_tag) -> const void* {
-    constexpr int kKt = decltype(kt_tag)::value;
-    if constexpr (kFusedMap && !(D == 64 && sizeof(IO) == 2 && kKt == 3)) {
-      if (fused_map) return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, true, kKt>);
+  // A separate penalty direction or the normalised read-out: the A chain of the block kernel that carries
+  // them; its records have the layout the S-row kernels below read, and the maps of segments take a pass of their own.
+  // Else segments take the A chain with the maps beside it, a whole sequence the A chain alone.
+  const bool general = runs_on_option_kernel(a);
+  hipError_t err;
+  if (general) {
+    err = launch_a_scan_general(a, D, io_dtype, stream);
+  } else if (a.n_seg > 1) {
+    err = launch_a_map(a, D, io_dtype, stream);
+  } else {
+    const void* fn = reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, 3>);
+    if constexpr (sizeof(IO) == 2) {   // operands of one term
+      if (a.feature_map == 0) fn = reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, 1>);
     }
-    return reinterpret_cast<const void*>(&a_scan_kernel<D, NW, IO, false, kKt>);
-  };
-  const void* scan_fn = scan_of(std::integral_constant<int, 3>{});
-  if constexpr (sizeof(IO) == 2) {
-    if (raw_keys) scan_fn = scan_of(std::integral_constant<int, 1>{});
+    err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(hs)), dim3(64 * NW), params, 0, stream);
   }
-  hipError_t err = general ? launch_a_scan_general(a, D, std::is_same<IO, uint16_t>::value ? 1 : 0, stream)
-                           : hipLaunchKernel(scan_fn, dim3(static_cast<unsigned>(hs)), dim3(64 * NW), params, 0,
-                                             stream);
   if (err != hipSuccess) return err;
-  // From half a chip of (head, segment) pairs the block operands are shared through LDS by a workgroup per
-  // pair; with fewer, one wave per slab of S and deep register prefetch (measured, whole call, LDS kernel
-  // against the other: 240 to 255 pairs -7 to -13 % at d = 64, -8 to -25 % at d = 128; 128 pairs -3.5 and
-  // -0.4 %; 9 to 32 pairs +2 to +8 %).
+  // The block operands are shared through LDS by a workgroup per pair, but with up to 32 pairs, one wave per slab of S and deep
+  // register prefetch: one head, T = 1024 (20 pairs), per wave / shared: d = 32 0.0399 / 0.0425 ms, d = 64 0.0586 / 0.0591; 40
+  // pairs, T = 4096: d = 32 0.0607 / 0.0603, d = 64 0.0887 / 0.0863; 90 pairs, T = 8192, d = 128 0.294 / 0.281.  The shared one is
+  // also the more accurate (split products against FP32 ones; error of o, d = 32: 2.7e-7 / 3.3e-7).
   // (value heads of another size: the LDS kernel at any count)
-  const bool shared = rect || hs >= 128;
+  const bool shared = rect || hs > 32;
   auto rows = [&](auto map_tag) -> hipError_t {
     constexpr bool kMap = decltype(map_tag)::value;
     return shared ? launch_s_rows_lds<D, IO, kMap>(a, stream) : launch_s_rows<D, IO, kMap>(a, stream);
   };
   if (a.n_seg > 1) {
     // the state of S at the segment boundaries: per-segment affine maps, then their composition
-    if (!fused_map) {
+    if (general) {
       err = rows(std::true_type{});
       if (err != hipSuccess) return err;
     }
@@ -1154,21 +1006,23 @@ hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream
 }
 
 // ---------------------------------------------------------------------------------- time-parallel mode
-// Segments are sized so that heads x segments gives every compute unit about four workgroups on long
-// sequences (segments of at least 16 blocks: the map pass costs two extra sweeps of S whatever the segment
-// count) and one workgroup on short ones (segments of at least 2 blocks).  Measured at d = 64: 16 heads are
-// fastest with 16 segments from T = 512 (0.10 ms, fused block kernel 0.16 ms) to T = 4096 (0.20 ms), 64 heads
-// with 4 segments up to T = 1024 and 8 at T = 2048, 128 heads with 2-4.
-// From d = 96 the A scan holds two workgroups per compute unit and the d^3 work per segment (boundary inverse,
-// composition of the maps) weighs four to eight times more: 512 pairs (one resident round) and segments of at
-// least 32 blocks.  Measured at d = 128, 16 heads: T = 32768 2.00 ms with 32 segments against 2.28 with 64 and
-// 2.52 with 24 (three quarters of a round take as long as a whole one); T = 8192 0.65 with 16 against 0.73 with
-// 32; 8 heads, T = 32768: 1.22 with 64 against 1.59 with 128; d = 96, 16 heads, T = 32768: 1.52 against 1.84.
+// Segments are sized so that the (head, segment) pairs are one resident round of workgroups of the A chain (vla_a_map.hip:
+// 256 pairs from d = 96, 512 at d = 64, 1024 at d = 32), in segments of at least 2 blocks up to one pair per compute unit and of
+// 16 blocks beyond.  The boundary inverses and the composition of the maps cost time per segment.  16 heads, bf16, ms:
+// d = 128, T = 32768: 16 segments 1.22, 32 1.30, 64 1.55;  d = 64, T = 32768: 16 0.56, 32 0.45, 48 0.50, 64 0.50, T = 131072: 32
+// 1.58, 48 1.75, 64 1.62;  d = 32, T = 131072: 32 1.02, 64 0.78.
+// Few heads: the composition walks the segments of a head one after another, so their count stops at about the square
+// root of the blocks times 2.5 (2 from d = 96).  One head, d = 64: T = 4096 16 segments 0.104, 32 0.084, 64 0.090, 128 0.129;
+// T = 32768 64 0.205, 128 0.181, 256 0.233;  d = 128, T = 4096: 16 0.246, 32 0.218, 64 0.257;  T = 32768 64 0.515, 96 0.506, 256 0.741.
+// Head counts that leave more than an eighth of a round empty take up to two.  T = 4096: 192 heads of 64 2 segments 0.79, 3 0.75,
+// 4 0.64, 5 0.68;  320 heads 2 1.17, 3 1.02;  90 heads of 128 2 1.19, 5 1.06;  96 heads of 96, T = 8192 2 1.84, 5 1.44.
+//
 // With the options (`general`: the A chain runs on the option kernel, three workgroups per compute unit at
 // d = 64) a resident round is 768 pairs at d = 64, and the longer chain favours segments of 32 blocks there too
 // (with u and the normalised read-out): 16 heads, T = 131072: 2.69 ms with 48 segments against 3.00 with 32 and 2.93
 // with 64; T = 16384: 0.43 with 32 against 0.53 with 24; 8 heads, T = 65536: 0.78 with 96 against 0.80 with 64 and 0.88
-// with 128.
+// with 128.  d = 32: 1024 pairs.  From d = 96: 512 pairs and segments of at least 32 blocks (16 heads, d = 128, without options
+// on the kernels before vla_a_map.hip: T = 32768 2.00 ms with 32 segments against 2.28 with 64 and 2.52 with 24).
 SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested) {
   const int nblk = (T + C - 1) / C;
   int ns = requested;
@@ -1176,17 +1030,22 @@ SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested
     const int heads = n_heads < 1 ? 1 : n_heads;
     const bool wide = d >= 96;
     const bool long_chain = wide || (general && d == 64);
-    const int most_pairs = wide ? 512 : (long_chain ? 768 : 1024);
+    const int round = general ? (wide ? 512 : (long_chain ? 768 : 1024)) : (wide ? 256 : (d == 64 ? 512 : 1024));
+    int most_pairs = round;
+    if (!general && d >= 64 && heads * (round / heads) < round / 8 * 7) most_pairs = 2 * round;
     const int by_chip = most_pairs / heads;
     const int by_length = nblk / (long_chain ? 32 : 16);
     int one_per_cu = 256 / heads;
     if (one_per_cu > nblk / 2) one_per_cu = nblk / 2;
     ns = by_length > one_per_cu ? by_length : one_per_cu;
     if (ns > by_chip) ns = by_chip;
+    if (!general) {
+      const int by_chain = static_cast<int>((wide ? 2.0f : 2.5f) * sqrtf(static_cast<float>(nblk)));
+      if (ns > by_chain) ns = by_chain;
+    }
     // Whole rounds of 256 pairs: a compute unit that gets a second workgroup of the S-row kernels while others
-    // have one takes twice as long over it.  24 heads, d = 64, T = 16384: 21 segments (504 pairs) 0.57 ms, 22
-    // segments 0.68; T = 4096: 16 segments (384 pairs) 0.23, 21 segments 0.22, 10 segments 0.23, 11 segments 0.30;
-    // d = 128, T = 8192: 16 segments 1.05, 21 segments 0.92.
+    // have one takes twice as long over it.  24 heads, d = 64, T = 4096: 10 segments 0.158, 16 segments (384 pairs) 0.162,
+    // 21 segments 0.151.
     if (heads <= 128 && ns * heads > 256) {
       int rounds = (ns * heads + 128) / 256;
       if (rounds > most_pairs / 256) rounds = most_pairs / 256;

@@ -297,3 +297,19 @@ def test_split_and_fp32_products_on_both_sides_of_their_pair_counts(d, d_v, head
         err = slab_rel_err(x.float().cpu().numpy(), ref[name], 2)
         print(d, d_v, heads, segments, dtype, feature_map, name, err)
         assert err <= TOL[dtype], (name, err)
+
+
+@pytest.mark.parametrize("dtype,feature_map", [("f32", False), ("bf16", False), ("bf16", True)])
+@pytest.mark.parametrize("d,d_v", [(32, 16), (32, 64), (32, 96), (32, 128), (64, 64), (64, 96), (96, 96), (96, 128), (128, 16), (128, 128)])
+def test_maps_beside_the_a_chain_in_every_slot_layout(d, d_v, dtype, feature_map):
+    """Segments of one block, of one token more and of several blocks; every number of row slabs per map wave and both
+    numbers of operand terms; given states."""
+    rng = np.random.default_rng(d * d_v)
+    for T, segments in ((33, 3), (17, 2), (150, 3)):
+        q, k, _ = vla_inputs.gaussian_qkv(2, 2, T, d, seed=T)
+        v = rng.standard_normal((2, 2, T, d_v)).astype(np.float32)
+        S0 = rng.standard_normal((2, 2, d_v, d)).astype(np.float32)
+        m = rng.standard_normal((2, 2, d, d)).astype(np.float32) / np.sqrt(d)
+        A0 = np.eye(d, dtype=np.float32) + m @ m.transpose(0, 1, 3, 2)
+        A0 = (0.5 * (A0 + A0.transpose(0, 1, 3, 2))).astype(np.float32)
+        check_parity(q, k, v, S0, A0, dtype=dtype, mode=TP, segments=segments, feature_map=feature_map)
