@@ -324,71 +324,107 @@ __global__ void __launch_bounds__(kThreads) keysum_prefix_kernel(const double* p
 
 // ------------------------------------------------------------------------------------------ boundary
 // Gauss-Jordan inverse, in place, of a symmetric positive definite D x D matrix spread over the workgroup's
-// registers (no pivoting needed for such a matrix) in the result layout of the float64 matrix instruction:
-// wave w holds the tile row w, lane (g, c) of it acc[tj][r] = M[16 w + g + 4 r][16 tj + c].
+// registers (no pivoting needed for such a matrix) in the result layout of the float64 matrix instruction, the tiles on and
+// below the diagonal only: wave w holds the tile rows w and NTL - 1 - w, NTL + 1 tiles whatever w; lane (g, c) of it
+// M[16 ti + g + 4 r][16 tj + c] of tile (ti, tj), tj <= ti, in element r.
 //
 // The sweep eliminates KB = 4 pivots at a time.  With P the pivot indices of a step, B = M[P][P], C = M[:, P]
 // and R = M[P, :], the in-place step is  M <- M - C' R'  with
 //   C'[i] = C[i] (i not in P),  C'[P] = B - I;     R'[:, j] = B^{-1} R[:, j] (j not in P),  R'[:, P] = I + B^{-1}
 // which is the usual block sweep (Schur complement off the pivot rows and columns, -C B^{-1} in the pivot
 // columns, B^{-1} R in the pivot rows, B^{-1} in the pivot block) written so that every element takes the same
-// rank-4 update: one v_mfma_f64_16x16x4_f64 per 16 x 16 tile and step.  The pivot rows are not fetched at
-// all: after the earlier steps the not yet eliminated part of M is a Schur complement (symmetric) and the
-// eliminated part of a pivot row is minus the transposed column, so R[a][j] = C[j][a] for j after P and -C[j][a]
-// for j before it.  Only the four pivot columns go through LDS (the lanes that hold them copy their registers
-// out, with the identity already subtracted from the pivot block), double-buffered: one barrier per step.
+// rank-4 update: one v_mfma_f64_16x16x4_f64 per 16 x 16 tile and step.  After the earlier steps the not yet eliminated part
+// of M is a Schur complement (symmetric), the eliminated part is symmetric too, and an eliminated row is minus the transposed
+// column: R[a][j] = C[j][a] for j after P and -C[j][a] for j before it, and likewise C[i][a] = -M[P_a][i] for i before P, which is
+// where the upper triangle would be read.  The four pivot columns go through LDS: rows from the pivots' tile on out of that
+// tile column, the rows before it out of the pivots' tile row (with the sign turned), the identity already subtracted from the
+// pivot block; double-buffered, one barrier per step.
 // Every lane factors the 4 x 4 block B = L diag(dd) L^T for itself in registers and solves for the one row of
-// B^{-1} it needs (row g: a lane supplies R'[g][16 tj + c] as the B operand of tile tj and C'[16 w + c][g] as
-// the A operand); the pivot columns get theirs from the identity x = e_e - B^{-1} e_e that the stored B - I gives
-// them.  A lane reads 4 tj + 15 doubles from LDS per step; with the matrix spread as a quarter of a column per
-// thread and the update on the vector units it read D + 14, and the LDS pipe was what the sweep waited for
-// (d = 128, 496 matrices: 0.18 ms).
+// B^{-1} it needs (row g: a lane supplies R'[g][16 tj + c] as the B operand of column tile tj and C'[16 ti + c][g] as
+// the A operand of row tile ti); the pivot columns get theirs from the identity x = e_e - B^{-1} e_e that the stored B - I gives
+// them.
+// Bound by the issue of a step's float64 instructions (2 x 2 blocks of B with half the reciprocals in the chain but more
+// of the others: 41 -> 44 us).  One wave per SIMD and matrix of 128 (two, with the whole
+// matrix on a wave per tile row, formed the factor and every x twice as often and twice the products): 234
+// matrices of 128 57.6 -> 41.0 us, 39 given ones 54.9 -> 41.7; 256 of 64 14.7 -> 15.2.
 // B - I and I + B^{-1} lose the small one of B and B^{-1} against the identity (an element d comes out as 1/d with a
 // relative error of 1e-16 d^2), so the sweep runs on the matrix scaled by powers of two, row and column i by the one that
 // brings the diagonal element i to [0.5, 2): 0.5 us of 51 (4 heads, 1024 tokens, d = 128).
 template <int D>
 struct SpdInverse {
-  static constexpr int NTL = D / 16;        // tile rows (one wave each) and tile columns
-  static constexpr int NT = 64 * NTL;       // 4 D threads
+  static constexpr int NTL = D / 16;        // tile rows and columns
+  static constexpr int NW = NTL / 2;        // waves, two tile rows each
+  static constexpr int NT = 64 * NW;        // threads
+  static constexpr int NPT = NTL + 1;       // tiles of a wave
   static constexpr int KB = 4;              // pivots per step: the contraction length of the matrix instruction
   static constexpr int STRIDE = D;          // doubles per pivot column
   static constexpr int LDS_DOUBLES = 2 * KB * STRIDE + D / 2;
+  static_assert(NTL % 2 == 0, "tile rows in pairs");
   double* colp;                             // LDS [2][KB][STRIDE], then the exponents of the scaling, int [D]
   static __device__ __forceinline__ double recip(double d) {   // hardware estimate refined twice: full precision
     const double y = __builtin_amdgcn_rcp(d);
     const double y1 = y * fma(-d, y, 2.0);
     return y1 * fma(-d, y1, 2.0);
   }
-  // M <- S M S with the powers of two S that the exponents hold; on the inverse of that it leaves the inverse of M
-  static __device__ __forceinline__ void scale(const int* ex, int w, int c, int g, d4 (&acc)[NTL]) {
+  // f(tile, row tile, column tile) for the tiles of wave W: row NTL - 1 - W first (from its column 0 on), then row W
+  template <int W, typename F>
+  static __device__ __forceinline__ void tiles(F&& f) {
 #pragma unroll
-    for (int tj = 0; tj < NTL; ++tj)
+    for (int tj = 0; tj < NTL - W; ++tj) f(tj, NTL - 1 - W, tj);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[tj][r] = __builtin_amdgcn_ldexp(acc[tj][r], ex[16 * tj + c] + ex[16 * w + g + 4 * r]);
+    for (int tj = 0; tj <= W; ++tj) f(NTL - W + tj, W, tj);
   }
-  __device__ __forceinline__ void run(d4 (&acc)[NTL]) const {
-    const int lane = threadIdx.x & 63;
+  // the wave's own copy of body<W>() (w is uniform over the wave)
+  template <typename F>
+  static __device__ __forceinline__ void for_my_wave(F&& f) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w == 0) f(std::integral_constant<int, 0>{});
+    if (NW > 1 && w == 1) f(std::integral_constant<int, (NW > 1 ? 1 : 0)>{});
+    if (NW > 2 && w == 2) f(std::integral_constant<int, (NW > 2 ? 2 : 0)>{});
+    if (NW > 3 && w == 3) f(std::integral_constant<int, (NW > 3 ? 3 : 0)>{});
+  }
+  template <int W>
+  __device__ __forceinline__ void run(d4 (&acc)[NPT]) const {
+    constexpr int TI[2] = {NTL - 1 - W, W};   // the wave's tile rows
+    const int lane = threadIdx.x & 63;
     const int c = lane & 15;
     const int g = lane >> 4;
     int* ex = reinterpret_cast<int*>(colp + 2 * KB * STRIDE);
-#pragma unroll
-    for (int tj = 0; tj < NTL; ++tj)
+    tiles<W>([&](int i, int ti, int tj) {
+      if (ti != tj) return;
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (w == tj && c == g + 4 * r) ex[16 * tj + c] = -(__builtin_amdgcn_frexp_exp(acc[tj][r]) >> 1);
+        if (c == g + 4 * r) ex[16 * tj + c] = -(__builtin_amdgcn_frexp_exp(acc[i][r]) >> 1);
+    });
     __syncthreads();
-    scale(ex, w, c, g, acc);
+    // M <- E M E with the powers of two E; on the inverse of that it leaves the inverse of M
+    auto scale = [&]() {
+      tiles<W>([&](int i, int ti, int tj) {
 #pragma unroll
-    for (int tp = 0; tp < NTL; ++tp) {       // the tile column that holds the pivots
+        for (int r = 0; r < 4; ++r) acc[i][r] = __builtin_amdgcn_ldexp(acc[i][r], ex[16 * tj + c] + ex[16 * ti + g + 4 * r]);
+      });
+    };
+    scale();
+#pragma unroll
+    for (int tp = 0; tp < NTL; ++tp) {       // the tile row and column that hold the pivots
       for (int ps = 0; ps < 4; ++ps) {       // its columns 4 ps .. 4 ps + 3
         const int p0 = 16 * tp + KB * ps;
         double* cp = colp + (ps & 1) * (KB * STRIDE);
-        if ((c >> 2) == ps) {                // this lane's column of tile tp is pivot e of the step
-          double* mine = cp + (c & 3) * STRIDE + 16 * w + g;
+        // rows of tile tp and after it: this lane's column of tile (ti, tp) is pivot c & 3 of the step
+        if ((c >> 2) == ps) {
+          double* mine = cp + (c & 3) * STRIDE + g;
+          tiles<W>([&](int i, int ti, int tj) {
+            if (tj != tp) return;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) mine[4 * r] = acc[tp][r] - ((w == tp && g + 4 * r == c) ? 1.0 : 0.0);
+            for (int r = 0; r < 4; ++r) mine[16 * ti + 4 * r] = acc[i][r] - ((ti == tp && g + 4 * r == c) ? 1.0 : 0.0);
+          });
         }
+        // rows before it, from the pivots' rows of the tiles (tp, tj): register ps of lane group g is pivot g of the step
+        tiles<W>([&](int i, int ti, int tj) {
+          if (ti != tp || tj >= tp) return;
+          const d4 t = acc[i];
+          cp[g * STRIDE + 16 * tj + c] = -(ps == 0 ? t[0] : ps == 1 ? t[1] : ps == 2 ? t[2] : t[3]);
+        });
         __syncthreads();
         // B = L diag(dd) L^T (unit lower triangular L, no pivoting: B is symmetric positive definite), every
         // lane for itself in registers; lo[a][c] holds B's lower triangle, then t = L diag(dd) below the diagonal
@@ -425,23 +461,25 @@ struct SpdInverse {
         for (int a = KB - 2; a >= 0; --a)
 #pragma unroll
           for (int k = a + 1; k < KB; ++k) y[a] = fma(-l[k][a], y[k], y[a]);
-        const double cv = cp[g * STRIDE + 16 * w + c];   // C'[16 w + c][g]
-        // x = (B^{-1} (M[j][P])^T)[g] for the lane's column j of every tile; then R'[g][j]:
+        // C'[16 ti + c][g]
+        const double cv[2] = {cp[g * STRIDE + 16 * TI[0] + c], cp[g * STRIDE + 16 * TI[1] + c]};
+        // x = (B^{-1} (M[j][P])^T)[g] for the lane's column j of every column tile; then R'[g][j]:
         //   j after the pivots:   R[:, j] = +M[j][P]^T            -> x
         //   j before the pivots:  R[:, j] = -M[j][P]^T            -> -x
         //   j = pivot e:          the column holds (B - I)[:, e]  -> x = (e_e - B^{-1} e_e)[g],  R' = 2 [e = g] - x
 #pragma unroll
-        for (int tj = 0; tj < NTL; ++tj) {
+        for (int tj = 0; tj < NTL - W; ++tj) {
           const int j = 16 * tj + c;
           double x = y[0] * cp[j];
 #pragma unroll
           for (int k = 1; k < KB; ++k) x = fma(y[k], cp[k * STRIDE + j], x);
           const double rr = (j >= p0 + KB) ? x : ((j - p0 == g) ? 2.0 - x : -x);
-          acc[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(cv, -rr, acc[tj], 0, 0, 0);
+          acc[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(cv[0], -rr, acc[tj], 0, 0, 0);
+          if (tj <= W) acc[NTL - W + tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(cv[1], -rr, acc[NTL - W + tj], 0, 0, 0);
         }
       }
     }
-    scale(ex, w, c, g, acc);
+    scale();
   }
 };
 
@@ -457,7 +495,6 @@ __global__ void __launch_bounds__(kThreads, D <= 64 ? 3 : 2) gram_kernel(Forward
 template <int D, int DL, typename IO>
 __global__ void __launch_bounds__(SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads, 2)
 gram_given_a0_kernel(ForwardArgs a, double* G) {
-  constexpr int NTL = SpdInverse<D>::NTL;
   __shared__ __align__(16) double colp[SpdInverse<D>::LDS_DOUBLES];
   const int head = blockIdx.x / a.n_seg;
   if (static_cast<int>(blockIdx.x) - head * a.n_seg != a.n_seg - 1) {   // uniform over the workgroup
@@ -468,25 +505,31 @@ gram_given_a0_kernel(ForwardArgs a, double* G) {
   const float* A0 = a.A0 + static_cast<size_t>(head) * DL * DL;
   double* out = G + static_cast<size_t>(blockIdx.x) * DL * DL;
   const int c = threadIdx.x & 15;
-  const int i0 = 16 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4);   // acc[tj][r] = M[i0 + 4 r][16 tj + c]
-  d4 acc[NTL];
+  const int g = (threadIdx.x & 63) >> 4;
+  using Inverse = SpdInverse<D>;
+  Inverse::for_my_wave([&](auto wtag) {
+    constexpr int W = decltype(wtag)::value;
+    d4 acc[Inverse::NPT];
+    Inverse::template tiles<W>([&](int n, int ti, int tj) {
 #pragma unroll
-  for (int tj = 0; tj < NTL; ++tj)
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
+        acc[n][r] = D == DL || (i < DL && j < DL)
+                        ? 0.5 * (static_cast<double>(A0[i * DL + j]) + static_cast<double>(A0[j * DL + i]))
+                        : (i == j ? 1.0 : 0.0);
+      }
+    });
+    Inverse{colp}.template run<W>(acc);
+    Inverse::template tiles<W>([&](int n, int ti, int tj) {   // both triangles from the lower one's tiles
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + 4 * r, j = 16 * tj + c;
-      acc[tj][r] = D == DL || (i < DL && j < DL)
-                       ? 0.5 * (static_cast<double>(A0[i * DL + j]) + static_cast<double>(A0[j * DL + i]))
-                       : (i == j ? 1.0 : 0.0);
-    }
-  SpdInverse<D>{colp}.run(acc);
-#pragma unroll
-  for (int tj = 0; tj < NTL; ++tj)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + 4 * r, j = 16 * tj + c;
-      if (D == DL || (i < DL && j < DL)) out[i * DL + j] = acc[tj][r];
-    }
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
+        if (D != DL && (i >= DL || j >= DL)) continue;
+        out[i * DL + j] = acc[n][r];
+        if (ti != tj) out[j * DL + i] = acc[n][r];
+      }
+    });
+  });
 }
 
 // One workgroup per (head, segment): seg_A = inverse(inverse(A0) + sum of the Gram matrices before it),
@@ -494,9 +537,8 @@ gram_given_a0_kernel(ForwardArgs a, double* G) {
 // DL: the head size of the data; D >= DL: the size the inversion is laid out for (d = 96 runs in the d = 128
 // layout: the matrix is bordered with an identity block, whose inverse is itself).
 template <int D, int DL>
-__global__ void __launch_bounds__(SpdInverse<D>::NT, (D <= 64 || DL < D) ? 4 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A) {
+__global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A) {
   static_assert(DL <= D, "padded layout");
-  constexpr int NTL = SpdInverse<D>::NTL;
   constexpr int NT = SpdInverse<D>::NT;
   __shared__ __align__(16) double colp[SpdInverse<D>::LDS_DOUBLES];
 
@@ -504,7 +546,7 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, (D <= 64 || DL < D) ? 4 : 2
   const int seg = blockIdx.x - head * a.n_seg;
   const int lane = threadIdx.x & 63;
   const int c = lane & 15;
-  const int i0 = 16 * (threadIdx.x >> 6) + (lane >> 4);   // acc[tj][r] = M[i0 + 4 r][16 tj + c]
+  const int g = lane >> 4;
   const float* A0 = a.A0 ? a.A0 + static_cast<size_t>(head) * DL * DL : nullptr;
   float* out = seg_A + static_cast<size_t>(blockIdx.x) * DL * DL;
   const float diag = 1.0f / a.lambda0;   // the same float32 value the first segment starts from
@@ -514,50 +556,39 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, (D <= 64 || DL < D) ? 4 : 2
     for (int e = threadIdx.x; e < DL * DL; e += NT) out[e] = A0 ? A0[e] : (e / DL == e % DL ? diag : 0.0f);
     return;
   }
-  auto data = [&](int i, int j) { return D == DL || (i < DL && j < DL); };   // inside the DL x DL matrix
-  const SpdInverse<D> inv{colp};
-  d4 acc[NTL];
-  if (A0) {   // its inverse is in the last segment's place
-    const double* inv0 = G + (static_cast<size_t>(head) * a.n_seg + a.n_seg - 1) * DL * DL;
-#pragma unroll
-    for (int tj = 0; tj < NTL; ++tj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * r, j = 16 * tj + c;
-        acc[tj][r] = data(i, j) ? inv0[i * DL + j] : (i == j ? 1.0 : 0.0);
-      }
-  } else {
-#pragma unroll
-    for (int tj = 0; tj < NTL; ++tj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * r, j = 16 * tj + c;
-        acc[tj][r] = (i == j) ? (data(i, j) ? 1.0 / static_cast<double>(diag) : 1.0) : 0.0;
-      }
-  }
-  // G holds inclusive prefix sums: G[head][seg - 1] covers every token before this segment
+  // its inverse is in the last segment's place;  G holds inclusive prefix sums: G[head][seg - 1] covers every token before
+  // this segment
+  const double* inv0 = A0 ? G + (static_cast<size_t>(head) * a.n_seg + a.n_seg - 1) * DL * DL : nullptr;
   const double* Gh = G + (static_cast<size_t>(blockIdx.x) - 1) * DL * DL;
+  const double diag0 = 1.0 / static_cast<double>(diag);
+  using Inverse = SpdInverse<D>;
+  Inverse::for_my_wave([&](auto wtag) {
+    constexpr int W = decltype(wtag)::value;
+    d4 acc[Inverse::NPT];
+    Inverse::template tiles<W>([&](int n, int ti, int tj) {
 #pragma unroll
-  for (int tj = 0; tj < NTL; ++tj)
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
+        if (D == DL || (i < DL && j < DL))   // inside the DL x DL matrix
+          acc[n][r] = (inv0 ? inv0[i * DL + j] : i == j ? diag0 : 0.0) + Gh[i * DL + j];
+        else
+          acc[n][r] = i == j ? 1.0 : 0.0;
+      }
+    });
+    Inverse{colp}.template run<W>(acc);
+    // The inverse of a symmetric matrix is symmetric up to rounding; the lower triangle's values go to both
+    // sides so that the float32 matrix the recurrence starts from is exactly symmetric.
+    Inverse::template tiles<W>([&](int n, int ti, int tj) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + 4 * r, j = 16 * tj + c;
-      if (data(i, j)) acc[tj][r] += Gh[i * DL + j];
-    }
-  inv.run(acc);
-  // The inverse of a symmetric matrix is symmetric up to rounding; store the lower triangle's values on both
-  // sides so that the float32 matrix the recurrence starts from is exactly symmetric.
-#pragma unroll
-  for (int tj = 0; tj < NTL; ++tj)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + 4 * r, j = 16 * tj + c;
-      const float v = static_cast<float>(acc[tj][r]);
-      if (i >= j && data(i, j)) {
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
+        if (i < j || (D != DL && (i >= DL || j >= DL))) continue;
+        const float v = static_cast<float>(acc[n][r]);
         out[i * DL + j] = v;
         out[j * DL + i] = v;
       }
-    }
+    });
+  });
 }
 
 // ------------------------------------------------------------------------------------------ combine
