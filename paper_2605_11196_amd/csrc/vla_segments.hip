@@ -13,6 +13,8 @@
 // The S recurrence is affine in S (eq. (s-update)): S_end = S_start P + Q per segment.  P and Q come from the
 // map pass of the S-rows kernel; combine_kernel composes them from left to right.
 #include "vla_mfma_util.h"
+#include <math.h>
+
 #include <type_traits>
 
 namespace vla {
@@ -234,6 +236,267 @@ __device__ __forceinline__ void gram_sum(const ForwardArgs& a, double* G) {
     }
   }
 }
+
+// ---- The same sums in fixed point on the 8-bit integer matrix instruction.
+//
+// A direction of length at most 2^E (1 for keys) is rounded to a multiple of 2^(E - 30), an error of at most 2^(E - 31) in an
+// element (float32 keeps elements from 2^(E - 7) on exactly so), and written as four signed base-256 digits, X = sum a_i 256^i.  The
+// products of digits and their sums over the tokens are exact in 32-bit integers; those of weight 256^2 and more are formed (13 of
+// 16), one sum per weight, and put together in float64 every kChunk tokens, before a sum can overflow.  What is left out is at most 2^-36
+// of a token's product of two units.
+//
+// One workgroup per (head, segment).  A thread stages four tokens x four columns: the digits of a column's four
+// tokens are transposed in its registers (8 byte permutations) into LDS planes [digit][column][token], from which a lane
+// reads the 16 tokens of an operand as 16 bytes.  A plane's rows and their 16-byte pieces are permuted by the column (row()
+// and piece()), so that neither the writes nor the reads hit a bank twice.  Tiles on and above the diagonal only, shared out by
+// tile rows.
+//
+// Bound by the staging's vector instructions (about 10 an element) beside 13 matrix ones per tile and 64 tokens.  16 heads of 64,
+// 131072 tokens, bf16: 195 us in float64 (v_mfma_f64_16x16x4_f64, 64 cycles each), 101 here; 16 heads of
+// 128, 32768 tokens 188 and 80; 16 of 64, 4096 tokens 13.6 and 10.5.
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+constexpr int fixed_threads(int d) { return d >= 96 ? 512 : 256; }
+
+template <int D, typename IO>
+__global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_kernel(ForwardArgs a, double* G, int shift) {
+  constexpr int NS = D / 16;                        // column strips
+  constexpr int KG = D == 32 ? 2 : 1;               // waves across the tokens of a tile
+  constexpr int TT = 64 * KG;                       // tokens of a tile
+  constexpr int LPR = D == 32 ? 8 : D == 64 ? 16 : 32;   // threads across a token's row
+  constexpr int W32 = TT / 4;                       // words of a plane's row
+  constexpr int kChunk = 16384;                     // tokens whose sums (at most four products of 2^14 each) fit 31 bits
+  static_assert(fixed_threads(D) / LPR * 4 == TT && D / 4 <= LPR, "one cell of 4 x 4 per thread");
+  __shared__ __align__(16) uint32_t planes[2][4][D * W32];
+
+  const int head = blockIdx.x / a.n_seg;
+  const int seg = blockIdx.x - head * a.n_seg;
+  if (seg == a.n_seg - 1) return;                   // the last segment's matrix is never needed
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int c = lane & 15;
+  const int g = lane >> 4;
+  const int tb = seg * a.seg_blocks * C;
+  const int te = min(a.T, tb + a.seg_blocks * C);
+  const bool has_u = a.u != nullptr;
+  const IO* kh = static_cast<const IO*>(has_u ? a.u : a.k) + static_cast<size_t>(head) * static_cast<size_t>(a.T) * D;
+  const bool fmap = a.feature_map != 0 && !has_u;
+  const float eps = a.eps;
+  const float scale = has_u ? a.u_scale : 1.0f;
+  const int cg = tid % LPR, tg = tid / LPR;         // column group and token group of this thread
+  const bool in_row = D / 4 == LPR || cg < D / 4;
+  auto row = [](int col) { return (col & ~3) | ((col ^ (col >> 2)) & 3); };
+  auto piece = [](int col, int tq) { return tq ^ ((col >> 2) & 3) ^ ((col >> 4) & 3); };   // tq: 16 tokens
+
+  constexpr int PF = 2;   // tiles in flight
+  RawRow<IO, 4> raw[PF][4];
+  auto fetch = [&](int t0, RawRow<IO, 4> (&o)[4]) {
+    if (!in_row) return;
+    const IO* base = kh + static_cast<size_t>(t0) * D + 4 * cg;
+    const int lim = te - 1 - t0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i].load(base + static_cast<unsigned>((lim >= TT - 1 ? 4 * tg + i : min(4 * tg + i, lim)) * D));
+  };
+  bool bad = false;   // a direction that is not finite: the matrix is none
+  auto stage = [&](int t0, const RawRow<IO, 4> (&o)[4], uint32_t (&pl)[4][D * W32]) {
+    uint32_t word[4][4];   // [column][token]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x[4];
+      if (in_row) {
+        o[i].unpack(x);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = 0.0f;
+      }
+      if (fmap && in_row) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = elu_plus_one(x[j]);
+      }
+      if (t0 + TT > te) {   // uniform: rows past the end are zero
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = t0 + 4 * tg + i < te ? x[j] : 0.0f;
+      }
+      float ss = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ss = fmaf(x[j], x[j], ss);
+      if constexpr (LPR >= 16) ss = row_sum16(ss);
+      if constexpr (LPR == 32) ss += __shfl_xor(ss, 16);
+      if constexpr (LPR == 8) {
+#pragma unroll
+        for (int off = 4; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
+      }
+      // 1 / max(||k||, eps): hardware reciprocal square root, one Newton step, as the recurrence kernels form it
+      const float sm = fmaxf(ss, eps * eps);
+      float rn = __builtin_amdgcn_rsqf(sm);
+      rn = rn * fmaf(-0.5f * sm * rn, rn, 1.5f) * scale;
+      bad = bad || !(ss < __builtin_inff()) || !(fabsf(rn) < __builtin_inff());
+      const float fixed = __builtin_ldexpf(rn, shift);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        int X;   // to the nearest integer
+        asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(X) : "v"(x[j] * fixed));
+        word[j][i] = static_cast<uint32_t>(X) + 0x00808080u;   // the digits but the highest one plus 128
+      }
+    }
+    if (!in_row) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t (&w)[4] = word[j];
+      const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+      const uint32_t lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+      const int col = 4 * cg + j;
+      const int at = row(col) * W32 + 16 * (tg >> 4) + 4 * piece(col, (tg >> 2) & 3) + (tg & 3);
+      pl[0][at] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+      pl[1][at] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+      pl[2][at] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
+      pl[3][at] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+    }
+  };
+
+  auto body = [&](auto wtag) {
+    constexpr int W = decltype(wtag)::value;
+    // the tiles (i, j), i <= j, of wave W: D = 64: first row but its last tile; last column; (1, 1), (1, 2); (2, 2), (3, 3).  From
+    // d = 96 the even or the odd columns of the rows W % 4 and NS - 1 - W % 4.  d = 32: the diagonal or (0, 1), for one half of the
+    // tokens.
+    auto mine = [](int i, int j) constexpr -> bool {
+      if (i > j) return false;
+      if (D == 32) return (i == j) == (W / 2 == 0);
+      if (D == 64) return W == 0 ? i == 0 && j < 3 : W == 1 ? j == 3 && i < 3 : W == 2 ? i == 1 && j < 3 : i == j && i >= 2;
+      return W % 4 < NS / 2 && (i == W % 4 || i == NS - 1 - W % 4) && j % 2 == W / 4;
+    };
+    constexpr int NT = D == 32 ? 2 : D == 64 ? 3 : NS / 2 + 1;   // at most
+    i4 acc[NT][5];
+    auto clear = [&]() {
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) acc[n][k] = i4{0, 0, 0, 0};
+    };
+    struct Strip { i4 a[4]; };
+    auto strip = [&](const uint32_t (&pl)[4][D * W32], int s) {
+      const int col = 16 * s + c;
+      const int at = row(col) * W32 + 16 * (KG > 1 ? W % KG : 0) + 4 * piece(col, g);
+      Strip x;
+#pragma unroll
+      for (int l = 0; l < 4; ++l) x.a[l] = *reinterpret_cast<const i4*>(&pl[l][at]);
+      return x;
+    };
+    auto products = [&](const uint32_t (&pl)[4][D * W32]) {
+      Strip left[NS];
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        bool used = false;
+#pragma unroll
+        for (int j = i + 1; j < NS; ++j) used = used || mine(i, j);
+        if (used) left[i] = strip(pl, i);
+      }
+      int n = 0;
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        bool used = false;
+#pragma unroll
+        for (int i = 0; i <= j; ++i) used = used || mine(i, j);
+        if (!used) continue;
+        const Strip right = strip(pl, j);
+#pragma unroll
+        for (int i = 0; i <= j; ++i) {
+          if (!mine(i, j)) continue;
+          const Strip& x = i == j ? right : left[i];
+#pragma unroll
+          for (int la = 0; la < 4; ++la)
+#pragma unroll
+            for (int lb = 0; lb < 4; ++lb)
+              if (la + lb >= 2) acc[n][la + lb - 2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.a[la], right.a[lb], acc[n][la + lb - 2], 0, 0, 0);
+          ++n;
+        }
+        __builtin_amdgcn_sched_barrier(0);   // one strip on the right at a time in registers
+      }
+    };
+    double* Gh = G + static_cast<size_t>(blockIdx.x) * D * D;
+    // the sums so far into G (added where an earlier chunk left its own)
+    auto flush = [&](bool first, bool none) {
+      double* half = reinterpret_cast<double*>(&planes[0][0][0]);   // d = 32: the other half of the tokens
+      const double unit = __builtin_ldexp(1.0, 16 - 2 * shift);
+      int n = 0;
+      if constexpr (KG > 1) __syncthreads();   // every wave is done with the planes
+#pragma unroll
+      for (int pass = 0; pass < KG; ++pass) {
+        n = 0;
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+          for (int i = 0; i <= j; ++i) {
+            if (!mine(i, j)) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              double v = static_cast<double>(acc[n][4][r]);
+#pragma unroll
+              for (int k = 3; k >= 0; --k) v = fma(v, 256.0, static_cast<double>(acc[n][k][r]));
+              v *= unit;
+              const int ri = 16 * i + 4 * g + r, cj = 16 * j + c;
+              if constexpr (KG > 1) {
+                if (pass == 0 && W % KG == 1) half[ri * D + cj] = v;
+                if (pass == 0 || W % KG == 1) continue;
+                v += half[ri * D + cj];
+              }
+              if (!first) v += Gh[ri * D + cj];
+              if (none) v = __builtin_nan("");
+              Gh[ri * D + cj] = v;
+              if (i != j) Gh[cj * D + ri] = v;
+            }
+            ++n;
+          }
+        if constexpr (KG > 1) __syncthreads();
+      }
+    };
+
+    clear();
+    bool first = true;
+    int since = 0;   // tokens in the sums
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (tb + u * TT < te) fetch(tb + u * TT, raw[u]);
+    for (int t0 = tb; t0 < te; t0 += PF * TT) {
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        const int tu = t0 + u * TT;
+        if (tu < te) {   // uniform over the workgroup
+          stage(tu, raw[u], planes[u & 1]);
+          // the planes written here were last read two tiles ago, and every wave has passed the barrier of the tile in between
+          __syncthreads();
+          if (tu + PF * TT < te) fetch(tu + PF * TT, raw[u]);
+          products(planes[u & 1]);
+        }
+      }
+      since += PF * TT;
+      if (since >= kChunk && t0 + PF * TT < te) {
+        flush(first, false);
+        clear();
+        first = false;
+        since = 0;
+      }
+    }
+    flush(first, __syncthreads_or(bad) != 0);
+  };
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (w == 0) body(std::integral_constant<int, 0>{});
+  if (w == 1) body(std::integral_constant<int, 1>{});
+  if (w == 2) body(std::integral_constant<int, 2>{});
+  if (w == 3) body(std::integral_constant<int, 3>{});
+  if constexpr (D >= 96) {
+    if (w == 4) body(std::integral_constant<int, 4>{});
+    if (w == 5) body(std::integral_constant<int, 5>{});
+    if (w == 6) body(std::integral_constant<int, 6>{});
+    if (w == 7) body(std::integral_constant<int, 7>{});
+  }
+}
+
+// Calls that take it.  Its rounding matters where A is far less certain than float32 can say: relative to the smallest eigenvalue
+// of the penalty matrix, sqrt(tokens / lambda0) 2^-32 at worst (one direction of length sqrt(lambda0 / tokens), rounded alike
+// every time: only keys far below eps have it).  From lambda0 = 0.01 on that stays below 1e-6 for 131072 tokens; a given A0,
+// whose inverse has eigenvalues that nobody has looked at, keeps float64.
+bool fixed_point_gram(const ForwardArgs& a) { return a.A0 == nullptr && a.lambda0 >= 0.01f; }
 
 // In-place inclusive prefix sum of the Gram matrices over the segments of a head, one thread per element:
 // afterwards G[h][s] = sum over segments 0..s.
@@ -681,10 +944,15 @@ hipError_t launch_boundary_d(const ForwardArgs& a, const double* G, float* seg_A
 template <int D, typename IO, int DL = D>
 hipError_t launch_gram_d(const ForwardArgs& a, double* G, hipStream_t stream) {
   ForwardArgs args = a;
-  void* params[] = {&args, &G};
-  const void* fn = a.A0 ? reinterpret_cast<const void*>(&gram_given_a0_kernel<D, DL, IO>)
+  int exponent = 0;   // directions are shorter than 2^exponent
+  if (a.u != nullptr && a.u_scale != 0.0f && isfinite(a.u_scale)) frexpf(a.u_scale, &exponent);
+  int shift = 30 - exponent;
+  void* params[] = {&args, &G, &shift};
+  const bool fixed = fixed_point_gram(a);
+  const void* fn = fixed  ? reinterpret_cast<const void*>(&gram_fixed_kernel<DL, IO>)
+                   : a.A0 ? reinterpret_cast<const void*>(&gram_given_a0_kernel<D, DL, IO>)
                         : reinterpret_cast<const void*>(&gram_kernel<D, DL, IO>);
-  const int threads = a.A0 && SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads;
+  const int threads = fixed ? fixed_threads(DL) : a.A0 && SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads;
   hipError_t err = hipLaunchKernel(fn, dim3(a.n_heads * a.n_seg), dim3(threads), params, 0, stream);
   if (err != hipSuccess) return err;
   int nh = a.n_heads, ns = a.n_seg, dd = DL * DL;

@@ -313,3 +313,51 @@ def test_maps_beside_the_a_chain_in_every_slot_layout(d, d_v, dtype, feature_map
         A0 = np.eye(d, dtype=np.float32) + m @ m.transpose(0, 1, 3, 2)
         A0 = (0.5 * (A0 + A0.transpose(0, 1, 3, 2))).astype(np.float32)
         check_parity(q, k, v, S0, A0, dtype=dtype, mode=TP, segments=segments, feature_map=feature_map)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,T,segments,lambda0", [
+    (32, 16 * 9 + 5, 3, 0.1), (64, 16 * 12 + 1, 3, 0.1), (96, 16 * 8 + 15, 2, 0.1), (128, 16 * 9, 3, 0.1),   # ragged tiles of 64 and 128 tokens
+    (32, 40000, 2, 0.1),            # more tokens in a segment than one set of integer sums takes
+    (64, 900, 4, 0.01), (64, 900, 4, 0.009),   # both sides of the smallest lambda0 in fixed point
+])
+# (no larger scale: A goes from 10 to lambda0 / u_scale^2 within d tokens, and the first segment's float32 recurrence loses as much,
+# in float64 sums and in these alike: heads of 32, 30: 8e-4 of o, 300: 3e-2)
+@pytest.mark.parametrize("u_scale", [None, 0.3, 3.0, 1e-3])
+def test_fixed_point_gram_sums(d, T, segments, lambda0, u_scale, dtype):
+    """A after the last segment starts from the inverse of the summed directions: against the oracle, with and without given
+    directions whose scale is no power of two, large or small.  Bound: that of the I/O type, as everywhere (a rounding of the
+    directions to 2^-31 moves A by less than 1e-6 of itself)."""
+    import torch
+
+    import paper_2605_11196_amd as vla
+
+    rng = np.random.default_rng(T)
+    heads = 1 if T > 10000 else 3
+    q, k, v = vla_inputs.gaussian_qkv(1, heads, T, d, seed=T + d)
+    u = rng.standard_normal(k.shape).astype(np.float32) if u_scale is not None else None
+    if dtype == "bf16":
+        q, k, v = (vla_inputs.round_to_bf16(x) for x in (q, k, v))
+        u = None if u is None else vla_inputs.round_to_bf16(u)
+    opt = dict(lambda0=lambda0) if u is None else dict(lambda0=lambda0, u_scale=u_scale)
+    ref = oracle.forward(q, k, v, u=u, **opt)
+    t = lambda x: None if x is None else torch.from_numpy(x).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    _, S_T, A_T = vla.vla_forward(t(q), t(k), t(v), u=t(u), mode=TP, segments=segments, **opt)
+    torch.cuda.synchronize()
+    assert slab_rel_err(A_T.cpu().numpy(), ref["A_T"], 2) <= 1e-4
+    assert slab_rel_err(S_T.cpu().numpy(), ref["S_T"], 2) <= 1e-4
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+def test_a_key_that_is_not_finite_reaches_every_later_segment_of_its_head_only(d, value):
+    import torch
+
+    import paper_2605_11196_amd as vla
+
+    q, k, v = (torch.from_numpy(x).cuda() for x in vla_inputs.gaussian_qkv(1, 2, 200, d, seed=d))
+    k[0, 1, 20, 3] = value
+    o, S_T, A_T = vla.vla_forward(q, k, v, lambda0=0.1, mode=TP, segments=4)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o[0, 0]).all() and torch.isfinite(A_T[0, 0]).all()
+    assert torch.isnan(A_T[0, 1]).any() and torch.isnan(o[0, 1, 64:]).any(dim=-1).all()
