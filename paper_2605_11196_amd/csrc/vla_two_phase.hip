@@ -1023,35 +1023,27 @@ hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream
 // with 64; T = 16384: 0.43 with 32 against 0.53 with 24; 8 heads, T = 65536: 0.78 with 96 against 0.80 with 64 and 0.88
 // with 128.  d = 32: 1024 pairs.  From d = 96: 512 pairs and segments of at least 32 blocks (16 heads, d = 128, without options
 // on the kernels before vla_a_map.hip: T = 32768 2.00 ms with 32 segments against 2.28 with 64 and 2.52 with 24).
-SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested) {
-  const int nblk = (T + C - 1) / C;
-  int ns = requested;
-  if (ns <= 0) {
-    const int heads = n_heads < 1 ? 1 : n_heads;
-    const bool wide = d >= 96;
-    const bool long_chain = wide || (general && d == 64);
-    const int round = general ? (wide ? 512 : (long_chain ? 768 : 1024)) : (wide ? 256 : (d == 64 ? 512 : 1024));
-    int most_pairs = round;
-    if (!general && d >= 64 && heads * (round / heads) < round / 8 * 7) most_pairs = 2 * round;
-    const int by_chip = most_pairs / heads;
-    const int by_length = nblk / (long_chain ? 32 : 16);
-    int one_per_cu = 256 / heads;
-    if (one_per_cu > nblk / 2) one_per_cu = nblk / 2;
-    ns = by_length > one_per_cu ? by_length : one_per_cu;
-    if (ns > by_chip) ns = by_chip;
-    if (!general) {
-      const int by_chain = static_cast<int>((wide ? 2.0f : 2.5f) * sqrtf(static_cast<float>(nblk)));
-      if (ns > by_chain) ns = by_chain;
-    }
-    // Whole rounds of 256 pairs: a compute unit that gets a second workgroup of the S-row kernels while others
-    // have one takes twice as long over it.  24 heads, d = 64, T = 4096: 10 segments 0.158, 16 segments (384 pairs) 0.162,
-    // 21 segments 0.151.
-    if (heads <= 128 && ns * heads > 256) {
-      int rounds = (ns * heads + 128) / 256;
-      if (rounds > most_pairs / 256) rounds = most_pairs / 256;
-      ns = 256 * rounds / heads;
-    }
+namespace {
+// heads x segments up to most_pairs, in segments of at least 2 blocks up to one pair per compute unit and of min_blocks beyond
+int segments_for(int heads, int nblk, int most_pairs, int min_blocks, int at_most) {
+  const int by_chip = most_pairs / heads;
+  const int by_length = nblk / min_blocks;
+  int one_per_cu = 256 / heads;
+  if (one_per_cu > nblk / 2) one_per_cu = nblk / 2;
+  int ns = by_length > one_per_cu ? by_length : one_per_cu;
+  if (ns > by_chip) ns = by_chip;
+  if (ns > at_most) ns = at_most;
+  // Whole rounds of 256 pairs: a compute unit that gets a second workgroup of the S-row kernels while others
+  // have one takes twice as long over it.  24 heads, d = 64, T = 4096: 10 segments 0.158, 16 segments (384 pairs) 0.162,
+  // 21 segments 0.151.
+  if (heads <= 128 && ns * heads > 256) {
+    int rounds = (ns * heads + 128) / 256;
+    if (rounds > most_pairs / 256) rounds = most_pairs / 256;
+    ns = 256 * rounds / heads;
   }
+  return ns;
+}
+SegmentPlan whole_blocks(int nblk, int ns) {
   if (ns > 256) ns = 256;
   if (ns > nblk) ns = nblk;
   if (ns < 1) ns = 1;
@@ -1059,6 +1051,27 @@ SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested
   p.seg_blocks = nblk > 0 ? (nblk + ns - 1) / ns : 0;
   p.n_seg = nblk > 0 ? (nblk + p.seg_blocks - 1) / p.seg_blocks : 1;  // no empty segment
   return p;
+}
+// The segments that the workspace has room for: the option kernel's plan, and what calls without options took before theirs
+// became fewer, so that a workspace or a static array that held a call still does, and the same calls exceed it.
+SegmentPlan widest_plan(int n_heads, int T, int d, bool general, int requested) {
+  const int nblk = (T + C - 1) / C;
+  if (requested > 0) return whole_blocks(nblk, requested);
+  const bool long_chain = d >= 96 || (general && d == 64);
+  return whole_blocks(nblk, segments_for(n_heads < 1 ? 1 : n_heads, nblk, d >= 96 ? 512 : (long_chain ? 768 : 1024),
+                                         long_chain ? 32 : 16, 256));
+}
+}  // namespace
+
+SegmentPlan plan_segments(int n_heads, int T, int d, bool general, int requested) {
+  if (general || requested > 0) return widest_plan(n_heads, T, d, general, requested);
+  const int nblk = (T + C - 1) / C;
+  const int heads = n_heads < 1 ? 1 : n_heads;
+  const bool wide = d >= 96;
+  const int round = wide ? 256 : (d == 64 ? 512 : 1024);
+  const bool emptier = d >= 64 && heads * (round / heads) < round / 8 * 7;
+  const int by_chain = static_cast<int>((wide ? 2.0f : 2.5f) * sqrtf(static_cast<float>(nblk)));
+  return whole_blocks(nblk, segments_for(heads, nblk, emptier ? 2 * round : round, wide ? 32 : 16, by_chain));
 }
 
 namespace {
@@ -1087,7 +1100,7 @@ TpLayout tp_layout(int n_heads, int T, int d, int d_v, int n_seg) {
 }  // namespace
 
 size_t time_parallel_workspace_bytes(int n_heads, int T, int d, int d_v, bool general, int requested_segments) {
-  const SegmentPlan p = plan_segments(n_heads, T, d, general, requested_segments);
+  const SegmentPlan p = widest_plan(n_heads, T, d, general, requested_segments);
   if (p.n_seg <= 1) return two_phase_workspace_bytes(n_heads, T, d);
   return tp_layout(n_heads, T, d, d_v, p.n_seg).total * sizeof(float);
 }
