@@ -110,6 +110,18 @@ def _address(x):
     return int(x) if x else None
 
 
+def _refuse_state(name, shape, dev):
+    raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
+
+
+def _like_v(torch, v, shape):
+    """The output tensor: v's shape, type and device (empty_like: 1.4 us, empty with all three spelled out 2.3), unless v came with
+    further dimensions of one element."""
+    if v.dim() == len(shape):
+        return torch.empty_like(v, memory_format=torch.contiguous_format)
+    return torch.empty(shape, dtype=v.dtype, device=v.device)
+
+
 def _on_device(torch, dev):
     """`dev` as the current device; entering it costs a microsecond, so only where another one is current."""
     return _SAME_DEVICE if dev.index == torch.cuda.current_device() else torch.cuda.device(dev)
@@ -191,10 +203,13 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
     B, H, dk = q.shape
     dv = v.shape[-1]
     dev = q.device
-    for name, x, shape in (("S", S, (B, H, dv, dk)), ("A", A, (B, H, dk, dk)), ("zkey", zkey, (B, H, dk))):
-        if x is not None and (x.dtype != torch.float32 or x.shape != shape or not x.is_contiguous()
-                              or x.device != dev):
-            raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
+    f32 = torch.float32
+    if S.dtype != f32 or S.shape != (B, H, dv, dk) or not S.is_contiguous() or S.device != dev:
+        _refuse_state("S", (B, H, dv, dk), dev)
+    if A.dtype != f32 or A.shape != (B, H, dk, dk) or not A.is_contiguous() or A.device != dev:
+        _refuse_state("A", (B, H, dk, dk), dev)
+    if zkey is not None and (zkey.dtype != f32 or zkey.shape != (B, H, dk) or not zkey.is_contiguous() or zkey.device != dev):
+        _refuse_state("zkey", (B, H, dk), dev)
     if u is not None and (u.dtype != q.dtype or tuple(u.shape) != tuple(q.shape) or u.device != q.device):
         raise ValueError("u must match q in dtype, shape and device")
     op = _opts(None, eps, None)
@@ -218,7 +233,7 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
         if u is not None:
             u = u.contiguous()
             op.u = u.data_ptr()
-        o = torch.empty((B, H, dv), dtype=q.dtype, device=dev)
+        o = _like_v(torch, v, (B, H, dv))
         if outside is not None:
             o.record_stream(outside)
         rc = _lib.vla_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), S.data_ptr(), A.data_ptr(), o.data_ptr(),
@@ -270,7 +285,7 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
     with context:
         q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
         u = None if u is None else u.contiguous()
-        o = torch.empty((B, H, T, dv), dtype=q.dtype, device=dev)
+        o = _like_v(torch, v, (B, H, T, dv))
         S_T = torch.empty((B, H, dv, dk), dtype=torch.float32, device=dev) if return_state else None
         A_T = torch.empty((B, H, dk, dk), dtype=torch.float32, device=dev) if return_state else None
         zkey_T = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if return_zkey else None
