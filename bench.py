@@ -35,8 +35,8 @@ MODE_NAMES = {1: "scan", 2: "chunked", 3: "two_phase", 4: "time_parallel"}
 # summary, valid for that shape and mode only; every other case reports null.
 PROFILED_TRAFFIC_BYTES = {
     # (B, H, T, d_h, io dtype, resolved mode): (bytes per launch, summary)
-    (64, 32, 8192, 128, "bf16", 2): (17264737 * 1024, "profiles/chunk_pipe_kernel_large_batch.txt"),
-    (1, 16, 131072, 64, "bf16", 4): (4013682 * 1024, "profiles/time_parallel_long_context_hbm_traffic.txt"),
+    (64, 32, 8192, 128, "bf16", 2): (17259845 * 1024, "profiles/chunk_pipe_kernel_large_batch.txt"),
+    (1, 16, 131072, 64, "bf16", 4): (3842784 * 1024, "profiles/time_parallel_long_context_hbm_traffic.txt"),
 }
 
 

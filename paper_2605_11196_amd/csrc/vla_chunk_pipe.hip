@@ -23,7 +23,7 @@
 // Vector instructions are what a SIMD has most of: one takes 4.9 cycles, a bf16 matrix instruction 17.7 by itself and 7.7 of
 // the vector unit's beside vector work, an FP32 one 32.5 of both.  So rows are addressed as a uniform base with an offset of the
 // lane (only the ragged last block clamps and masks), lane indices carry their range (24-bit products), and the partial Gram
-// matrices of a wave of 16 columns are formed from half operands: the S waves of d = 64 357 -> 290 vector instructions a block.
+// matrices of a wave of 16 columns are formed from half operands: the S waves of d = 64 about 320 -> 270 vector instructions a block.
 // 256 heads of 64, float32, 2048 tokens 0.352 -> 0.318 ms; 2048 heads of 64, 8192 tokens, bf16 5.54 -> 5.33, of 128 15.4 ->
 // 15.1.  W kept as l, h, m in 24 bytes (two overlapping reads without moves) was 3 % faster with one head per compute unit
 // and 3 % slower with four: twice the LDS reads.

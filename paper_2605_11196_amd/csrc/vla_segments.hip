@@ -7,7 +7,8 @@
 // independent of each other; the segments then run the exact rank-1 recurrence concurrently.  The paper
 // treats the A loop as sequential (Section 3.4); this goes beyond it and is not valid with the identity
 // refresh.  The directions are the float32 numbers the recurrence kernels work with; their outer products (exact
-// in float64), the sums and the inversions are float64, so that the boundary matrices are at least as accurate
+// in float64) and the sums are float64, or, where no A0 is given and lambda0 is not tiny (fixed_point_gram), fixed point with an
+// error that float32 cannot show; the inversions are float64.  So the boundary matrices are at least as accurate
 // as the float32 chain they replace.
 //
 // The S recurrence is affine in S (eq. (s-update)): S_end = S_start P + Q per segment.  P and Q come from the
