@@ -797,11 +797,11 @@ gram_given_a0_kernel(ForwardArgs a, double* G) {
 }
 
 // One workgroup per (head, segment): seg_A = inverse(inverse(A0) + sum of the Gram matrices before it),
-// G holding the prefix sums.
+// G holding the prefix sums (prefixed) or the segments' own, added up here in the same order.
 // DL: the head size of the data; D >= DL: the size the inversion is laid out for (d = 96 runs in the d = 128
 // layout: the matrix is bordered with an identity block, whose inverse is itself).
 template <int D, int DL>
-__global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A) {
+__global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A, int prefixed) {
   static_assert(DL <= D, "padded layout");
   constexpr int NT = SpdInverse<D>::NT;
   __shared__ __align__(16) double colp[SpdInverse<D>::LDS_DOUBLES];
@@ -820,21 +820,43 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 :
     for (int e = threadIdx.x; e < DL * DL; e += NT) out[e] = A0 ? A0[e] : (e / DL == e % DL ? diag : 0.0f);
     return;
   }
-  // its inverse is in the last segment's place;  G holds inclusive prefix sums: G[head][seg - 1] covers every token before
-  // this segment
+  // its inverse is in the last segment's place;  as inclusive prefix sums G[head][seg - 1] covers every token before this
+  // segment, else G[head][0 .. seg - 1] do
   const double* inv0 = A0 ? G + (static_cast<size_t>(head) * a.n_seg + a.n_seg - 1) * DL * DL : nullptr;
-  const double* Gh = G + (static_cast<size_t>(blockIdx.x) - 1) * DL * DL;
+  const int terms = prefixed ? 1 : seg;
+  const double* Gh = G + (static_cast<size_t>(blockIdx.x) - terms) * DL * DL;
   const double diag0 = 1.0 / static_cast<double>(diag);
   using Inverse = SpdInverse<D>;
   Inverse::for_my_wave([&](auto wtag) {
     constexpr int W = decltype(wtag)::value;
     d4 acc[Inverse::NPT];
+    constexpr int AHEAD = 2;   // segments in flight
+    for (int s = 0; s < terms; s += AHEAD) {
+      d4 x[AHEAD][Inverse::NPT];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const double* Gs = Gh + static_cast<size_t>(min(s + u, terms - 1)) * DL * DL;
+        Inverse::template tiles<W>([&](int n, int ti, int tj) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
+            x[u][n][r] = D == DL || (i < DL && j < DL) ? Gs[i * DL + j] : 0.0;   // inside the DL x DL matrix
+          }
+        });
+      }
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (s + u < terms) {   // uniform over the workgroup
+#pragma unroll
+          for (int n = 0; n < Inverse::NPT; ++n) acc[n] = s + u == 0 ? x[u][n] : acc[n] + x[u][n];
+        }
+    }
     Inverse::template tiles<W>([&](int n, int ti, int tj) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = 16 * ti + g + 4 * r, j = 16 * tj + c;
-        if (D == DL || (i < DL && j < DL))   // inside the DL x DL matrix
-          acc[n][r] = (inv0 ? inv0[i * DL + j] : i == j ? diag0 : 0.0) + Gh[i * DL + j];
+        if (D == DL || (i < DL && j < DL))
+          acc[n][r] = (inv0 ? inv0[i * DL + j] : i == j ? diag0 : 0.0) + acc[n][r];
         else
           acc[n][r] = i == j ? 1.0 : 0.0;
       }
@@ -935,10 +957,19 @@ __global__ void __launch_bounds__(64 * (D / 16)) combine_kernel(ForwardArgs a, f
   }
 }
 
+// Up to six segments boundary_kernel adds up the Gram matrices before its own by itself (the same sums in the same order), in place
+// of a launch of gram_prefix_kernel, which takes 5 us at d = 64 and 10 at 128 and the gap after it; each further two
+// cost the last segment a trip to memory, 1 us or more.  Whole calls, prefix kernel / added up, us: 8 heads of 64 in 2, 4, 6, 8, 16
+// segments of 4 blocks 44.6 / 42.5, 45.7 / 44.7, 48.4 / 48.0, 50.2 / 51.8, 59.2 / 64.0; 8 heads of 128 90.5 / 88.0, 100.6 /
+// 99.5, 110.9 / 109.4, 116.0 / 118.9, 137 / 145; 39 heads of 128 x 64, A0 given, 6 segments 258.0 / 251.3; 96 heads of 128, 5
+// segments, T = 4096 934 / 921.
+bool boundary_adds_up(int n_seg) { return n_seg <= 6; }
+
 template <int D, int DL = D>
 hipError_t launch_boundary_d(const ForwardArgs& a, const double* G, float* seg_A, hipStream_t stream) {
   ForwardArgs args = a;
-  void* params[] = {&args, &G, &seg_A};
+  int prefixed = boundary_adds_up(a.n_seg) ? 0 : 1;
+  void* params[] = {&args, &G, &seg_A, &prefixed};
   return hipLaunchKernel(reinterpret_cast<const void*>(&boundary_kernel<D, DL>), dim3(a.n_heads * a.n_seg),
                          dim3(SpdInverse<D>::NT), params, 0, stream);
 }
@@ -955,7 +986,7 @@ hipError_t launch_gram_d(const ForwardArgs& a, double* G, hipStream_t stream) {
                         : reinterpret_cast<const void*>(&gram_kernel<D, DL, IO>);
   const int threads = fixed ? fixed_threads(DL) : a.A0 && SpdInverse<D>::NT > kThreads ? SpdInverse<D>::NT : kThreads;
   hipError_t err = hipLaunchKernel(fn, dim3(a.n_heads * a.n_seg), dim3(threads), params, 0, stream);
-  if (err != hipSuccess) return err;
+  if (err != hipSuccess || boundary_adds_up(a.n_seg)) return err;
   int nh = a.n_heads, ns = a.n_seg, dd = DL * DL;
   void* p2[] = {&G, &nh, &ns, &dd};
   const long long elems = static_cast<long long>(nh) * dd;

@@ -299,6 +299,21 @@ def test_split_and_fp32_products_on_both_sides_of_their_pair_counts(d, d_v, head
         assert err <= TOL[dtype], (name, err)
 
 
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("segments", [2, 5, 6, 7])
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+def test_gram_matrices_added_up_in_front_of_the_inverse_or_by_a_kernel(d, segments, given):
+    """Six segments are the last whose sums the boundary inverse forms itself, two at a time: odd and even counts and the first
+    count that has them summed before, from an identity and from a given A0."""
+    q, k, v = vla_inputs.gaussian_qkv(2, 2, 32 * segments - 3, d, seed=1900 + segments)
+    A0 = None
+    if given:
+        m = np.random.default_rng(d).standard_normal((2, 2, d, d)).astype(np.float32) / np.sqrt(d)
+        A0 = np.eye(d, dtype=np.float32) + m @ m.transpose(0, 1, 3, 2)
+        A0 = (0.5 * (A0 + A0.transpose(0, 1, 3, 2))).astype(np.float32)
+    check_parity(q, k, v, None, A0, dtype="f32", lambda0=0.1, mode=TP, segments=segments)
+
+
 @pytest.mark.parametrize("dtype,feature_map", [("f32", False), ("bf16", False), ("bf16", True)])
 @pytest.mark.parametrize("d,d_v", [(32, 16), (32, 64), (32, 96), (32, 128), (64, 64), (64, 96), (96, 96), (96, 128), (128, 16), (128, 128)])
 def test_maps_beside_the_a_chain_in_every_slot_layout(d, d_v, dtype, feature_map):
