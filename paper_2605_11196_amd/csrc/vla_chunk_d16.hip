@@ -16,9 +16,11 @@
 // One wave per 16 rows of S runs through these maps from left to right (four dependent products a block), and every wave
 // reads out its own block from the S it is handed.
 //
-// What bounds it: latency.  Block after block on one wave (vla_chunk.hip with one tile, which larger counts of heads keep)
+// What bounds it: the vector instructions of four waves on every SIMD (about 1300 a wave and span).  Block after block on one wave (vla_chunk.hip with one tile, which larger counts of heads keep)
 // takes 3.1 us a block, all of it dependent instructions of one wave: one head of 256 tokens 50 us, 16384 tokens 3.25 ms.
-// Here a span of 16 blocks takes 16 us, four waves on every SIMD: 17.2 us and 1.0 ms.  Error against float64 of the first
+// Here a span of 16 blocks takes 14 us: 16.3 us and 0.905 ms (0.925 with each half of a double broadcast by itself and
+// lane indices of unknown range; 0.96 with the inverse by four pivots a step on the float64 matrix instruction, 0.94 with the Gram
+// tiles read four at a time).  Error against float64 of the first
 // 3.9e-7 -> 2.8e-7 (o), 2.8e-7 -> 1.6e-7 (A): every block starts from a float64 inverse.
 #include "vla_mfma_util.h"
 
@@ -29,10 +31,7 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <int LANE>
 __device__ __forceinline__ double row_bcast(double x) {   // x of lane LANE of this 16-lane row
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), 0x150 + LANE, 0xf, 0xf, true);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), 0x150 + LANE, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+  return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + LANE, 0xf, 0xf, true);
 }
 __device__ __forceinline__ double readlane(double x, int lane) {
   const uint64_t u = __builtin_bit_cast(uint64_t, x);
@@ -81,7 +80,7 @@ __global__ void __launch_bounds__(64 * NW, 4) chunk_d16_kernel(ForwardArgs a) {
   int c = lane & 15;
   int g = lane >> 4;
   // offsets derived from the lane are formed anew in each part, not kept in registers
-  auto fresh = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(c), "+v"(g)); };
+  auto fresh = [&]() __attribute__((always_inline)) { renew(c, g); };
   const int T = a.T;
   const float eps = a.eps;
   const int nblk = (T + C - 1) / C;
