@@ -884,7 +884,9 @@ __global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 :
 // its start state in; the contraction index is taken in the order k = 16b + 4g + r so that a tile feeds
 // straight back as the MFMA B operand), computes its own slice of x P + Q and hands it to the other waves
 // through LDS.  The chain is sequential in s and short per step, so the operands of the next three
-// segments are kept in flight in rotating register sets.
+// segments are kept in flight in rotating register sets: every load on a path of its own without a condition, because where a
+// path with and one without it meet the compiler cannot count what is in flight and waits for all of it.  One head of 128,
+// T = 32768 (90 segments) 443 -> 375 us the whole call, of 64, float32 184 -> 173; 8 heads of 128 in 16 segments 137 -> 128.
 // S has a.d_v rows (value heads of another size than the key heads: more or fewer slabs per head, P stays D x D).
 template <int D>
 __global__ void __launch_bounds__(64 * (D / 16)) combine_kernel(ForwardArgs a, float* seg_S) {
@@ -910,13 +912,15 @@ __global__ void __launch_bounds__(64 * (D / 16)) combine_kernel(ForwardArgs a, f
     float pa[NB][4];   // P[16b + 4g + r][16 jb + c]
     f4 q;              // Q[row0 + c][16 jb + 4g ..]
   };
-  auto load = [&](int s, Seg& o) {
-    const float* P = a.seg_PQ + (hbase + s) * pqsz;
+  const unsigned po = 4 * g * D + c;
+  const unsigned qo = static_cast<unsigned>(c * D + 4 * g);
+  auto load = [&](int s, Seg& o) {   // s past the last step: that one's again
+    const float* P = a.seg_PQ + (hbase + min(s, n - 1)) * pqsz;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o.pa[b][r] = P[(16 * b + 4 * g + r) * D + 16 * jb + c];
-    o.q = *reinterpret_cast<const f4*>(P + D * D + ro + 16 * jb);
+      for (int r = 0; r < 4; ++r) o.pa[b][r] = (P + 16 * b * D + 16 * jb)[po + r * D];
+    o.q = *reinterpret_cast<const f4*>(P + D * D + row0 * D + 16 * jb + qo);
   };
 
   f4 xt[NB];
@@ -943,16 +947,26 @@ __global__ void __launch_bounds__(64 * (D / 16)) combine_kernel(ForwardArgs a, f
   };
 
   Seg buf[LA + 1];
+  if (n <= LA) {   // all at once, none twice: 1 us of 94 in three segments of 128
 #pragma unroll
-  for (int u = 0; u < LA; ++u)
-    if (u < n) load(u, buf[u]);
-  for (int s = 0; s < n; s += LA + 1) {
+    for (int u = 0; u < LA; ++u)
+      if (u < n) load(u, buf[u]);
+#pragma unroll
+    for (int u = 0; u < LA; ++u)
+      if (u < n) step(u, buf[u]);
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < LA; ++u) {
+    load(u, buf[u]);
+    __builtin_amdgcn_sched_barrier(0);   // requested in the order of their use, as in the loop
+  }
+  for (int s = 0;; s += LA + 1) {
 #pragma unroll
     for (int u = 0; u <= LA; ++u) {
-      if (s + u < n) {   // uniform over the workgroup
-        if (s + u + LA < n) load(s + u + LA, buf[(u + LA) % (LA + 1)]);
-        step(s + u, buf[u]);
-      }
+      if (s + u >= n) return;   // uniform over the workgroup
+      load(s + u + LA, buf[(u + LA) % (LA + 1)]);
+      step(s + u, buf[u]);
     }
   }
 }
