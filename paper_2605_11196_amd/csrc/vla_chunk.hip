@@ -51,7 +51,8 @@ __device__ __forceinline__ void prio() {
 // FMAP: q and k are replaced by ELU(x) + 1 while they are staged (the feature map of Section 3.3).
 // DV: head size of v and o (rows of S); the wave that owns columns [SL w, SL w + SL) of A owns rows
 // [SLV w, SLV w + SLV) of S.
-template <int D, int DV, int NW, typename IO, bool FMAP, bool SPLIT>
+// LOOP: the workgroups of a launch go through the heads in turn (takes_turns below), else one workgroup per head.
+template <int D, int DV, int NW, typename IO, bool FMAP, bool SPLIT, bool LOOP>
 __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   // Measured at 2048 heads, T = 8192: the full scheme gains 5 % with four waves (d = 128), 1 % with three (d = 96),
   // 1-5 % with one (d = 16, 32); two-wave workgroups (d = 64), four of which share a compute unit, lose up to
@@ -100,8 +101,12 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
   __shared__ __align__(16) float rns[2][C];           // 1 / max(||k_t||, eps) over its power of two (key_scale)
   static_assert(C * LDY <= 2 * C * LT, "a slab of Y^T fits the wave's Gram tiles");
 
-  const int head = blockIdx.x;
-  const int tid = threadIdx.x;
+  // A head begins with LDS that nothing reads any more: after barrier (5) of its last block a wave reads W, Z, NQ and c, and
+  // those are written again only behind the barriers of the next head's first block.
+  int head = blockIdx.x;
+  do {
+  int tid = threadIdx.x;
+  if constexpr (LOOP) asm volatile("" : "+v"(tid));   // what is derived from it is formed per head, not kept in registers over all
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, known to be uniform
   const int lane = tid & 63;
   const int c = lane & 15;
@@ -324,9 +329,6 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
     // ================= C x C factorisation, phase 1 (one wave): Cholesky of I + G and L^{-1}
     const int sw = (blk + head) % NW;   // wave factorising I + G this block (rotates over waves/SIMDs)
     const int sw2 = (sw + NW / 2) % NW;  // a different wave forms c, Z, NQ
-    // Lanes 0-31 hold rows of I + G (-> rows of L), lanes 32-63 hold columns of the identity
-    // (-> columns of L^{-1}); both halves are updated by the same instruction stream: one broadcast of
-    // L[j][t] serves the Cholesky trailing update and the forward substitution for L^{-1}.
     // ================= -F^T = K^ S0^T - V^T and R^T = Q S0^T: one pass over S, whose split serves both; needed only
     // after barrier (5), so it fills the serial windows
     f4 ft[NJV], ot[NJV];
@@ -519,36 +521,72 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
       }
     }
   }
+  head += gridDim.x;
+  } while (LOOP && head < a.n_heads);
 }
 
-template <int D, int DV, int NW, typename IO, bool SPLIT>
-hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
+// Which calls go through the heads in turn (LOOP), as many workgroups as the compute units hold together?  A workgroup that
+// the hardware starts in another's place comes where room is, and two kinds of last round suffer for it; a workgroup that
+// goes on with another head stays where it was.  T = 512, one workgroup per head / in turn, us:
+//   A round of workgroups of two waves that is all but full: the free places of some compute units lie on one SIMD, and the
+//   last heads wait.  64 x 96, one term: 2000 heads 480 / 480, 2040 538 / 480, 2048 549 / 480, 3000 712 / 717, 3072 772 / 724;
+//   64 x 128: 2000 545 / 548, 2048 619 / 548, 3072 897 / 822;  32 x 128, one term 2048 388 / 371, three 517 / 445.  32 x 96 of
+//   float32 numbers lets three waves on a SIMD, so that this begins where two rounds of four workgroups would do: 1700 heads 355 / 352,
+//   1800 391 / 365, 2048 424 / 370, but 1200 (five together, one round) 240 / 305, 2500 463 / 517.
+//   A second round of between a quarter and half of the places: two of its workgroups go where two end together, and none to the
+//   next.  128 x 96, one term: 640 heads 532 / 507, 768 555 / 508, 900 564 / 563;  16 x 128, 256 tokens: 2500 heads 232 / 232,
+//   3072 280 / 242, 3500 292 / 293.
+// One block does not pay for it: 64 x 128, 3072 heads, 16 tokens 43.8 / 45.8.
+enum LastRound { kAny, kFull, kThreeQuarters, kHalf };
+constexpr LastRound loop_rule(int d, int d_v, int nw, bool f32, bool one_term) {
+  if (d == 16) return d_v == 128 ? kHalf : kAny;
+  if (nw == 2 && d == 32) return d_v == 128 ? kFull : d_v == 96 && f32 ? kThreeQuarters : kAny;
+  if (nw == 2 && d == 64) return one_term && d_v > d ? kFull : kAny;
+  return d == 128 && d_v == 96 && one_term ? kHalf : kAny;
+}
+// workgroups that the compute units hold together, by registers (two waves per SIMD; 32 x 96 of float32 numbers: as if two)
+constexpr int loop_resident(int nw) { return 256 * 8 / nw; }
+inline bool takes_turns(LastRound rule, int n_heads, int T, int resident) {
+  if (rule == kAny || n_heads <= resident || T < 64) return false;
+  const int last = (n_heads - 1) % resident + 1;
+  const bool second = n_heads <= 2 * resident;
+  if (rule == kFull) return 32 * last >= 31 * resident;
+  if (rule == kThreeQuarters) return second && 4 * last > 3 * resident;
+  return second && 4 * last >= resident && 2 * last <= resident;
+}
+
+template <int D, int DV, int NW, typename IO, bool FMAP, bool SPLIT>
+hipError_t launch_kernel(const ForwardArgs& a, hipStream_t stream) {
   ForwardArgs args = a;
   void* params[] = {&args};
-  const void* fn = reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, true, SPLIT>);
+  constexpr LastRound kRule = loop_rule(D, DV, NW, sizeof(IO) == 4, sizeof(IO) == 2 && !FMAP);
+  if constexpr (kRule != kAny) {
+    if (takes_turns(kRule, a.n_heads, a.T, loop_resident(NW)))
+      return hipLaunchKernel(reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, FMAP, SPLIT, true>),
+                             dim3(loop_resident(NW)), dim3(64 * NW), params, 0, stream);
+  }
+  return hipLaunchKernel(reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, FMAP, SPLIT, false>), dim3(a.n_heads),
+                         dim3(64 * NW), params, 0, stream);
+}
+template <int D, int DV, int NW, typename IO, bool SPLIT>
+hipError_t launch(const ForwardArgs& a, hipStream_t stream) {
   // products on the FP32 instruction are for three-term operands only (d = 16 has no others)
   if constexpr (SPLIT || D == 16 || sizeof(IO) == 4) {
-    if (a.feature_map == 0) fn = reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, IO, false, SPLIT>);
+    if (a.feature_map == 0) return launch_kernel<D, DV, NW, IO, false, SPLIT>(a, stream);
   }
-  return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * NW), params, 0, stream);
+  return launch_kernel<D, DV, NW, IO, true, SPLIT>(a, stream);
 }
 // float32 q and k, or the feature map
 template <int D, int DV, int NW>
 hipError_t launch_three_terms(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
-  ForwardArgs args = a;
-  void* params[] = {&args};
-  const void* fn = io_dtype == 1   ? reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, uint16_t, true, true>)
-                   : a.feature_map ? reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, float, true, true>)
-                                   : reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, float, false, true>);
-  return hipLaunchKernel(fn, dim3(a.n_heads), dim3(64 * NW), params, 0, stream);
+  return io_dtype == 1        ? launch_kernel<D, DV, NW, uint16_t, true, true>(a, stream)
+         : a.feature_map != 0 ? launch_kernel<D, DV, NW, float, true, true>(a, stream)
+                              : launch_kernel<D, DV, NW, float, false, true>(a, stream);
 }
 // bf16 q and k without the feature map
 template <int D, int DV, int NW>
 hipError_t launch_one_term(const ForwardArgs& a, hipStream_t stream) {
-  ForwardArgs args = a;
-  void* params[] = {&args};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&chunk_kernel<D, DV, NW, uint16_t, false, true>), dim3(a.n_heads),
-                         dim3(64 * NW), params, 0, stream);
+  return launch_kernel<D, DV, NW, uint16_t, false, true>(a, stream);
 }
 template <int D, int DV, int NW, bool SPLIT = (D > 16)>
 hipError_t launch_io(const ForwardArgs& a, int io_dtype, hipStream_t stream) {

@@ -39,8 +39,8 @@ def usage():
 
 @pytest.fixture(scope="module")
 def chunk_usage(usage):
-    """the block kernel by (d_k, d_v, waves, io, feature map, split products)"""
-    return usage["chunk_kernel"]
+    """the block kernel with one workgroup per head by (d_k, d_v, waves, io, feature map, split products)"""
+    return {k[:6]: r for k, r in usage["chunk_kernel"].items() if not k[6]}
 
 
 SQUARE_WAVES = [(16, 1), (32, 1), (64, 4), (96, 3), (128, 4)]   # d = 64, 128: three operand terms only
@@ -84,14 +84,13 @@ def test_two_chain_kernels_hold_the_workgroups_they_are_chosen_for(usage):
 
 
 # Known scratch use, in bytes per lane and spilled registers; every other instantiation has none.
-#   chunk_kernel: (d_k, d_v, waves, io, feature map, split products)
+#   chunk_kernel: (d_k, d_v, waves, io, feature map, split products, heads in turn)
 #   chunk_pipe_kernel: (d_k, d_v, waves on A, waves on S, io, feature map, waves per SIMD)
 #   chunk_general_kernel: (d_k, d_v, columns of a wave, io, two sweeps, A chain alone, double buffers, split products)
 #   s_rows_lds_kernel: (d_k, tile slots, other value head size, io, maps, terms, split products, waves per SIMD)
 KNOWN = {
     "chunk_kernel": {
-        (128, 96, 4, "bf16", False, True): (8, 1),
-        (96, 128, 3, "bf16", False, True): (48, 23),
+        (96, 128, 3, "bf16", False, True, False): (20, 4),
     },
     "chunk_pipe_kernel": {
         (128, 128, 4, 4, "bf16", False, 4): (28, 18),

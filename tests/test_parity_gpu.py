@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import vla_inputs
-from parity_utils import TOL, check_parity, gpu_forward, slab_rel_err, to_np
+from parity_utils import TOL, check_parity, gpu_forward, oracle_inputs, slab_rel_err, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -570,6 +570,48 @@ def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
     S0 = rng.standard_normal((B, heads, d_v, d)).astype(np.float32) * np.abs(v).max(axis=(2, 3), keepdims=True)
     errs, _, _ = check_parity(q, k, v, S0, dtype=dtype, mode=2)
     print(d, d_v, heads, dtype, errs)
+
+
+@pytest.mark.parametrize("d,d_v,heads,resident,dtype", [
+    (64, 96, 2047, 1024, "bf16"), (64, 96, 3072, 1024, "bf16"), (64, 128, 2040, 1024, "bf16"), (32, 128, 2048, 1024, "bf16"),
+    (32, 128, 2040, 1024, "f32"), (32, 96, 1793, 1024, "f32"), (128, 96, 640, 512, "bf16"), (128, 96, 768, 512, "bf16"),
+    (16, 128, 2560, 2048, "f32"), (16, 128, 3072, 2048, "bf16")])
+def test_workgroups_that_go_through_the_heads_in_turn(d, d_v, heads, resident, dtype):
+    """The block kernel where a workgroup takes the heads h, h + resident, ...: odd and even numbers of blocks before the next
+    head, a state carried in and written over itself.  The oracle on the heads on both sides of each round; the same head in
+    another round gives the same bits."""
+    import torch
+
+    import paper_2605_11196_amd as vla
+
+    rng = np.random.default_rng(d + heads)
+    some = sorted({0, 1, resident - 1, resident, resident + 1, heads - 1, (heads - 1) // resident * resident})
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dev = torch.device("cuda:0")
+    for T in (64, 83):
+        q, k = (rng.standard_normal((1, heads, T, d)).astype(np.float32) for _ in range(2))
+        v = rng.standard_normal((1, heads, T, d_v)).astype(np.float32)
+        S0 = rng.standard_normal((1, heads, d_v, d)).astype(np.float32)
+        for x in (q, k, v, S0):
+            x[:, resident + 1] = x[:, 1]
+        q, k, v = oracle_inputs(q, k, v, dtype)
+        ref = oracle.forward(*(x[:, some] for x in (q, k, v, S0)), None, lambda0=0.1)
+        A0 = np.broadcast_to(np.eye(d, dtype=np.float32) / np.float32(0.1), (1, heads, d, d)).copy()
+        t = lambda x, dt=torch.float32: torch.from_numpy(x).to(dev).to(dt)
+        tq, tk, tv, S, A = t(q, tdt), t(k, tdt), t(v, tdt), t(S0), t(A0)
+        o = torch.full_like(tv, float("nan"))
+        io = vla.VLA_F32 if dtype == "f32" else vla.VLA_BF16
+        rc = vla.vla_forward_raw(tq.data_ptr(), tk.data_ptr(), tv.data_ptr(), S.data_ptr(), A.data_ptr(), o.data_ptr(), S.data_ptr(),
+                                 A.data_ptr(), 1, heads, T, d, d_v, io, mode=2, stream=torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert all(torch.isfinite(x).all() for x in (o, S, A))
+        errs = dict(o=slab_rel_err(to_np(o)[:, some], ref["o"], 2), S=slab_rel_err(to_np(S)[:, some], ref["S_T"], 2),
+                    A=slab_rel_err(to_np(A)[:, some], ref["A_T"], 2))
+        print(d, d_v, heads, T, dtype, errs)
+        assert max(errs.values()) <= TOL[dtype], errs
+        for x in (o, S, A):
+            assert torch.equal(x[:, 1], x[:, resident + 1])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
