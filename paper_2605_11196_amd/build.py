@@ -74,14 +74,18 @@ def build(verbose: bool = False, extra=(), incremental: bool = False, jobs: int 
 def resource_usage(src, extra=()):
     """The compiler's own resource report for every kernel of one source (device pass only, nothing is
     written next to the library): {demangled kernel name: {"VGPRs": n, "AGPRs": n, "ScratchSize": bytes per
-    lane, "VGPRSpill": n, "SGPRSpill": n, "Occupancy": waves per SIMD, "LDSSize": bytes, ...}}."""
+    lane, "VGPRSpill": n, "SGPRSpill": n, "Occupancy": waves per SIMD, "LDSSize": bytes, "Threads": most of a
+    workgroup, ...}}."""
     import re
     import tempfile
 
     with tempfile.TemporaryDirectory() as tmp:
-        cmd = [HIPCC] + FLAGS + list(extra) + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
-                                               "-c", src, "-o", os.path.join(tmp, "dev.o")]
+        obj = os.path.join(tmp, "dev.o")
+        cmd = [HIPCC] + FLAGS + list(extra) + ["--cuda-device-only", "--no-gpu-bundle-output",
+                                               "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
+        readelf = os.path.join(os.path.dirname(HIPCC), "..", "llvm", "bin", "llvm-readelf")
+        notes = subprocess.run([readelf, "--notes", obj], capture_output=True, text=True).stdout
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise subprocess.CalledProcessError(r.returncode, cmd)
@@ -97,6 +101,13 @@ def resource_usage(src, extra=()):
         m = re.search(r"remark: (?:\S+: )?\s*([A-Za-z][A-Za-z /\[\]]*?): (\d+)", line)
         if m and cur is not None and m.group(1).strip() in keys:
             cur[keys[m.group(1).strip()]] = int(m.group(2))
+    threads = 0   # in the notes a kernel's largest workgroup stands before its name
+    for line in notes.splitlines():
+        key, _, val = line.strip().partition(":")
+        if key == ".max_flat_workgroup_size":
+            threads = int(val)
+        elif key == ".name" and val.strip() in out:
+            out[val.strip()]["Threads"] = threads
     names = list(out)
     if names:
         dem = subprocess.run(["c++filt"] + names, capture_output=True, text=True).stdout.split("\n")

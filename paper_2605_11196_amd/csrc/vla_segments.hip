@@ -796,16 +796,22 @@ gram_given_a0_kernel(ForwardArgs a, double* G) {
   });
 }
 
+// Never a workgroup of one wave, a second one without work if need be: an odd number of waves leaves the waves of the next kernel's
+// workgroups on other SIMDs than those they would share two and two, and the option kernel's A chain, two waves a workgroup, took
+// 1670 instead of 1380 us for it (128 heads of 32, 30000 tokens, bf16, u and normalised read-out; whole call 2590 -> 2286).
+constexpr int boundary_threads(int d) { return d <= 64 ? 128 : 2 * d; }
+
 // One workgroup per (head, segment): seg_A = inverse(inverse(A0) + sum of the Gram matrices before it),
 // G holding the prefix sums (prefixed) or the segments' own, added up here in the same order.
 // DL: the head size of the data; D >= DL: the size the inversion is laid out for (d = 96 runs in the d = 128
 // layout: the matrix is bordered with an identity block, whose inverse is itself).
 template <int D, int DL>
-__global__ void __launch_bounds__(SpdInverse<D>::NT, D <= 32 ? 4 : D <= 64 ? 3 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A, int prefixed) {
+__global__ void __launch_bounds__(boundary_threads(D), D <= 32 ? 4 : D <= 64 ? 3 : 2) boundary_kernel(ForwardArgs a, const double* G, float* seg_A, int prefixed) {
   static_assert(DL <= D, "padded layout");
   constexpr int NT = SpdInverse<D>::NT;
   __shared__ __align__(16) double colp[SpdInverse<D>::LDS_DOUBLES];
 
+  if (NT < boundary_threads(D) && threadIdx.x >= NT) return;   // a whole wave; a barrier counts those that are left
   const int head = blockIdx.x / a.n_seg;
   const int seg = blockIdx.x - head * a.n_seg;
   const int lane = threadIdx.x & 63;
@@ -985,7 +991,7 @@ hipError_t launch_boundary_d(const ForwardArgs& a, const double* G, float* seg_A
   int prefixed = boundary_adds_up(a.n_seg) ? 0 : 1;
   void* params[] = {&args, &G, &seg_A, &prefixed};
   return hipLaunchKernel(reinterpret_cast<const void*>(&boundary_kernel<D, DL>), dim3(a.n_heads * a.n_seg),
-                         dim3(SpdInverse<D>::NT), params, 0, stream);
+                         dim3(boundary_threads(D)), params, 0, stream);
 }
 template <int D, typename IO, int DL = D>
 hipError_t launch_gram_d(const ForwardArgs& a, double* G, hipStream_t stream) {

@@ -25,7 +25,8 @@ def _value(x):
 @pytest.fixture(scope="module")
 def usage():
     """{kernel: {template arguments: resources}} of the sources with block and segment kernels"""
-    sources = ["vla_chunk.hip", "vla_chunk_pipe.hip", "vla_chunk_d16.hip", "vla_chunk_general.hip", "vla_two_phase.hip"]
+    sources = ["vla_chunk.hip", "vla_chunk_pipe.hip", "vla_chunk_d16.hip", "vla_chunk_general.hip", "vla_two_phase.hip",
+               "vla_segments.hip"]
     with ThreadPoolExecutor(len(sources)) as pool:
         reports = list(pool.map(lambda f: build.resource_usage(os.path.join(CSRC, f)), sources))
     out = {}
@@ -125,6 +126,13 @@ def test_no_kernel_exceeds_its_known_scratch_use(usage, kernel):
     over = {args: (r["ScratchSize"], r["VGPRSpill"]) for args, r in usage[kernel].items()
             if (r["ScratchSize"], r["VGPRSpill"]) > KNOWN[kernel].get(args, (0, 0))}
     assert not over, over
+
+
+def test_no_boundary_workgroup_has_an_odd_number_of_waves(usage):
+    """They would put the two waves of the workgroups that follow, those of the option kernel's A chain of heads of 32, on
+    other SIMDs than those they share two and two, which costs that kernel a fifth of its time."""
+    for args, r in usage["boundary_kernel"].items():
+        assert r["Threads"] % 128 == 0, (args, r)
 
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
