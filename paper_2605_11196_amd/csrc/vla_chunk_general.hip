@@ -692,13 +692,17 @@ hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
 //     0.304 / 0.324;  d_v = 128 the same within 5 %;  d_v = 32: 512 heads 0.131 / 0.109, 768 heads 0.159 / 0.167 / 0.215
 //   d =  32: 512 heads 0.107 / 0.078, 1024 heads 0.112 / 0.106, 2048 heads 0.217 / 0.191, 4096 heads 0.445 / 0.351
 //     d_v = 64: 768 heads 0.126 / 0.104, 1024 heads, float32 0.127 / 0.152;  d_v = 128: 256 heads 0.126 / 0.070, 640 heads,
-//     float32 0.152 / 0.153, 1024 heads 0.168 / 0.235
-bool pipe_narrow(const ForwardArgs& a, int d, int d_v) {
+//     float32 0.152 / 0.153, 1024 heads 0.168 / 0.235;  one block, float32, u, 513 heads 0.0132 / 0.0139, 768 heads 0.0143 / 0.0149
+//     (with the normalised read-out 0.0148 / 0.0159; two blocks 0.0223 / 0.0225, without u, 513 heads 0.0132 / 0.0127)
+bool pipe_narrow(const ForwardArgs& a, int d, int d_v, int io_dtype) {
   switch (d) {
     case 128: return a.n_heads <= 256 || d_v >= 96 || (d_v == 64 && a.T > 16);
     case 96: return true;
     case 64: return a.n_heads <= 256 || (a.n_heads <= 512 && d_v <= 64);
-    case 32: return a.n_heads <= 768 || d_v <= 32;
+    case 32: {
+      const bool one_block = d_v == 128 && io_dtype == 0 && a.u != nullptr && a.T <= 16;
+      return a.n_heads <= (one_block ? 512 : 768) || d_v <= 32;
+    }
     default: return false;
   }
 }
@@ -754,7 +758,7 @@ hipError_t launch_scan(const ForwardArgs& a, hipStream_t stream) {
 
 hipError_t launch_chunk_general(const ForwardArgs& a, int d, int d_v, int io_dtype, hipStream_t stream) {
   if (pipe_wide(a, d, d_v, io_dtype)) return launch_chunk_general_pipe_wide(a, d, d_v, io_dtype, stream);
-  if (pipe_narrow(a, d, d_v)) return launch_chunk_general_pipe_narrow(a, d, d_v, io_dtype, stream);
+  if (pipe_narrow(a, d, d_v, io_dtype)) return launch_chunk_general_pipe_narrow(a, d, d_v, io_dtype, stream);
   switch (d * 1000 + d_v) {
     case 16016: return launch_io<16, 16>(a, io_dtype, stream);
     case 16032: return launch_io<16, 32>(a, io_dtype, stream);
