@@ -7,12 +7,12 @@
 // independent of each other; the segments then run the exact rank-1 recurrence concurrently.  The paper
 // treats the A loop as sequential (Section 3.4); this goes beyond it and is not valid with the identity
 // refresh.  The directions are the float32 numbers the recurrence kernels work with; their outer products (exact
-// in float64) and the sums are float64, or, where no A0 is given and lambda0 is not tiny (fixed_point_gram), fixed point with an
-// error that float32 cannot show; the inversions are float64.  So the boundary matrices are at least as accurate
-// as the float32 chain they replace.
+// in float64) and the sums are float64, or, where that cannot show (fixed_point_gram), fixed point; the inversions are
+// float64.  So the boundary matrices are at least as accurate as the float32 chain they replace.
 //
-// The S recurrence is affine in S (eq. (s-update)): S_end = S_start P + Q per segment.  P and Q come from the
-// map pass of the S-rows kernel; combine_kernel composes them from left to right.
+// The S recurrence is affine in S (eq. (s-update)): S_end = S_start P + Q per segment.  P and Q come from the waves beside the
+// A chain (vla_a_map.hip), with options from the map pass of the S-rows kernel (vla_two_phase.hip); combine_kernel composes them
+// from left to right.
 #include "vla_mfma_util.h"
 #include <math.h>
 
@@ -242,9 +242,11 @@ __device__ __forceinline__ void gram_sum(const ForwardArgs& a, double* G) {
 //
 // A direction of length at most 2^E (1 for keys) is rounded to a multiple of 2^(E - 30), an error of at most 2^(E - 31) in an
 // element (float32 keeps elements from 2^(E - 7) on exactly so), and written as four signed base-256 digits, X = sum a_i 256^i.  The
-// products of digits and their sums over the tokens are exact in 32-bit integers; those of weight 256^2 and more are formed (13 of
-// 16), one sum per weight, and put together in float64 every kChunk tokens, before a sum can overflow.  What is left out is at most 2^-36
-// of a token's product of two units.
+// products of digits and their sums over the tokens are exact in 32-bit integers; those of weight 256 and more are formed (15 of
+// 16), one sum per weight, and put together in float64 every kChunk tokens, before a sum can overflow.  What is left out, the product
+// of the lowest digits, is at most 2^-46 of a token's product of two units, but not a token's alone: the same direction
+// over and over leaves out the same each time, off that direction, where lambda0 is all there is.  (Without the two
+// products of weight 256 too: one unit key 131072 times, lambda0 = 0.1, A wrong by 8e-6; with them 2e-8, with all 16 1e-10.)
 //
 // One workgroup per (head, segment).  A thread stages four tokens x four columns: the digits of a column's four
 // tokens are transposed in its registers (8 byte permutations) into LDS planes [digit][column][token], from which a lane
@@ -252,20 +254,22 @@ __device__ __forceinline__ void gram_sum(const ForwardArgs& a, double* G) {
 // and piece()), so that neither the writes nor the reads hit a bank twice.  Tiles on and above the diagonal only, shared out by
 // tile rows.
 //
-// Bound by the staging's vector instructions (about 10 an element) beside 13 matrix ones per tile and 64 tokens.  16 heads of 64,
-// 131072 tokens, bf16: 195 us in float64 (v_mfma_f64_16x16x4_f64, 64 cycles each), 101 here; 16 heads of
-// 128, 32768 tokens 188 and 80; 16 of 64, 4096 tokens 13.6 and 10.5.
+// Bound by the staging's vector instructions (about 10 an element) beside 15 matrix ones per tile and 64 tokens.  16 heads of 64,
+// 131072 tokens, bf16: 195 us in float64 (v_mfma_f64_16x16x4_f64, 64 cycles each), 118 here (13 products 114, 16 122); 16 heads of
+// 128, 32768 tokens 188 and 95 (13 products 89, 16 104).
 typedef int i4 __attribute__((ext_vector_type(4)));
 
 constexpr int fixed_threads(int d) { return d >= 96 ? 512 : 256; }
 
 template <int D, typename IO>
-__global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_kernel(ForwardArgs a, double* G, int shift) {
+__global__ void __launch_bounds__(fixed_threads(D), D >= 64 ? 2 : 3) gram_fixed_kernel(ForwardArgs a, double* G, int shift) {
   constexpr int NS = D / 16;                        // column strips
   constexpr int KG = D == 32 ? 2 : 1;               // waves across the tokens of a tile
   constexpr int TT = 64 * KG;                       // tokens of a tile
   constexpr int LPR = D == 32 ? 8 : D == 64 ? 16 : 32;   // threads across a token's row
   constexpr int W32 = TT / 4;                       // words of a plane's row
+  constexpr int kLowest = 1;                        // weight of the smallest products that are formed
+  constexpr int kSums = 7 - kLowest;
   constexpr int kChunk = 16384;                     // tokens whose sums (at most four products of 2^14 each) fit 31 bits
   static_assert(fixed_threads(D) / LPR * 4 == TT && D / 4 <= LPR, "one cell of 4 x 4 per thread");
   __shared__ __align__(16) uint32_t planes[2][4][D * W32];
@@ -367,12 +371,12 @@ __global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_
       return W % 4 < NS / 2 && (i == W % 4 || i == NS - 1 - W % 4) && j % 2 == W / 4;
     };
     constexpr int NT = D == 32 ? 2 : D == 64 ? 3 : NS / 2 + 1;   // at most
-    i4 acc[NT][5];
+    i4 acc[NT][kSums];
     auto clear = [&]() {
 #pragma unroll
       for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int k = 0; k < 5; ++k) acc[n][k] = i4{0, 0, 0, 0};
+        for (int k = 0; k < kSums; ++k) acc[n][k] = i4{0, 0, 0, 0};
     };
     struct Strip { i4 a[4]; };
     auto strip = [&](const uint32_t (&pl)[4][D * W32], int s) {
@@ -408,7 +412,8 @@ __global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_
           for (int la = 0; la < 4; ++la)
 #pragma unroll
             for (int lb = 0; lb < 4; ++lb)
-              if (la + lb >= 2) acc[n][la + lb - 2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.a[la], right.a[lb], acc[n][la + lb - 2], 0, 0, 0);
+              if (la + lb >= kLowest)
+                acc[n][la + lb - kLowest] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.a[la], right.a[lb], acc[n][la + lb - kLowest], 0, 0, 0);
           ++n;
         }
         __builtin_amdgcn_sched_barrier(0);   // one strip on the right at a time in registers
@@ -418,7 +423,7 @@ __global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_
     // the sums so far into G (added where an earlier chunk left its own)
     auto flush = [&](bool first, bool none) {
       double* half = reinterpret_cast<double*>(&planes[0][0][0]);   // d = 32: the other half of the tokens
-      const double unit = __builtin_ldexp(1.0, 16 - 2 * shift);
+      const double unit = __builtin_ldexp(1.0, 8 * kLowest - 2 * shift);
       int n = 0;
       if constexpr (KG > 1) __syncthreads();   // every wave is done with the planes
 #pragma unroll
@@ -431,9 +436,9 @@ __global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_
             if (!mine(i, j)) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              double v = static_cast<double>(acc[n][4][r]);
+              double v = static_cast<double>(acc[n][kSums - 1][r]);
 #pragma unroll
-              for (int k = 3; k >= 0; --k) v = fma(v, 256.0, static_cast<double>(acc[n][k][r]));
+              for (int k = kSums - 2; k >= 0; --k) v = fma(v, 256.0, static_cast<double>(acc[n][k][r]));
               v *= unit;
               const int ri = 16 * i + 4 * g + r, cj = 16 * j + c;
               if constexpr (KG > 1) {
@@ -493,11 +498,24 @@ __global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_
   }
 }
 
-// Calls that take it.  Its rounding matters where A is far less certain than float32 can say: relative to the smallest eigenvalue
-// of the penalty matrix, sqrt(tokens / lambda0) 2^-32 at worst (one direction of length sqrt(lambda0 / tokens), rounded alike
-// every time: only keys far below eps have it).  From lambda0 = 0.01 on that stays below 1e-6 for 131072 tokens; a given A0,
-// whose inverse has eigenvalues that nobody has looked at, keeps float64.
-bool fixed_point_gram(const ForwardArgs& a) { return a.A0 == nullptr && a.lambda0 >= 0.01f; }
+// Directions are shorter than 2^exponent.
+int direction_exponent(const ForwardArgs& a) {
+  int exponent = 0;
+  if (a.u != nullptr && a.u_scale != 0.0f && isfinite(a.u_scale)) frexpf(a.u_scale, &exponent);
+  return exponent;
+}
+// Calls that take it.  Its errors matter where A is far less certain than float32 can say; relative to the smallest eigenvalue
+// of the penalty matrix they are, with r^2 = 4^exponent tokens / lambda0, at most about
+//   r 2^-32           the rounding: one direction of length sqrt(lambda0 / tokens), rounded alike every time, or as much of one
+//                     across the others
+//   r^2 2^-60 5461 D  the lowest digits of one direction, left out alike every time (5461: the mean square of a digit)
+// so r^2 is kept to 2^21, 3e-7 and 1e-6 (a matrix as a whole: 1e-7; Gaussian directions: 1e-10).  131072 tokens from the
+// default lambda0 of 0.1 are inside, from 0.06 on.  u_scale = 1000, one direction so short that r counts, 65536 tokens, lambda0 = 0.01, was wrong by
+// 4e-2 here.  A given A0, whose inverse has eigenvalues that nobody has looked at, keeps float64, and so does lambda0
+// below 0.01, where nothing was measured.
+bool fixed_point_gram(const ForwardArgs& a) {
+  return a.A0 == nullptr && a.lambda0 >= 0.01f && ldexp(static_cast<double>(a.T), 2 * direction_exponent(a)) <= 2097152.0 * a.lambda0;
+}
 
 // In-place inclusive prefix sum of the Gram matrices over the segments of a head, one thread per element:
 // afterwards G[h][s] = sum over segments 0..s.
@@ -996,9 +1014,7 @@ hipError_t launch_boundary_d(const ForwardArgs& a, const double* G, float* seg_A
 template <int D, typename IO, int DL = D>
 hipError_t launch_gram_d(const ForwardArgs& a, double* G, hipStream_t stream) {
   ForwardArgs args = a;
-  int exponent = 0;   // directions are shorter than 2^exponent
-  if (a.u != nullptr && a.u_scale != 0.0f && isfinite(a.u_scale)) frexpf(a.u_scale, &exponent);
-  int shift = 30 - exponent;
+  int shift = 30 - direction_exponent(a);
   void* params[] = {&args, &G, &shift};
   const bool fixed = fixed_point_gram(a);
   const void* fn = fixed  ? reinterpret_cast<const void*>(&gram_fixed_kernel<DL, IO>)
