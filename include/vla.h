@@ -64,9 +64,11 @@ typedef enum { VLA_F32 = 0, VLA_BF16 = 1 } vla_dtype;
  *   TIME_PARALLEL: TWO_PHASE with the sequence cut into segments that run concurrently (for small
  *              B*H and long T).  Without the refresh, A at a segment boundary is the explicit
  *              inverse (A_0^{-1} + sum of u u^T up to there)^{-1} of Section 3.2 / eq. (penalty) (u = k^
- *              unless opts->u is given), computed in float64 from one Gram matrix per segment; S at a
- *              boundary follows by composing the per-segment affine maps S -> S P + Q of
- *              eq. (s-update); the key sum of the normalised read-out at a boundary is a prefix sum.
+ *              unless opts->u is given): one Gram matrix per segment, summed in float64 or, where no A_0
+ *              is given and (tokens / lambda0) u_scale^2 is at most about 2e6, in fixed point with an error
+ *              of about 1e-6 of A in the worst case, and inverted in float64; S at a boundary follows by
+ *              composing the per-segment affine maps S -> S P + Q of eq. (s-update); the key sum of the
+ *              normalised read-out at a boundary is a prefix sum.
  *              Inside a segment the recurrence is the same exact block form.  Same result up to float32
  *              rounding.
  */

@@ -105,9 +105,10 @@ size_t time_parallel_workspace_bytes(int n_heads, int T, int d, int d_v, bool ge
 hipError_t launch_time_parallel(const ForwardArgs& a, int d, int io_dtype, int requested_segments,
                                 hipStream_t stream);
 // Boundary kernels (vla_segments.hip).  All buffers are device memory inside the caller's workspace.
-//   gram:      G[h][s] = sum over the tokens of segments 0..s of u u^T (u = k^ unless the caller supplies
-//              penalty directions), float64 [d][d]
-//   boundary:  seg_A[h][s] = inverse(inverse(A0[h]) + G[h][s-1]) rounded to float32
+//   gram:      G[h][s] = sum of u u^T (u = k^ unless the caller supplies penalty directions) over the tokens of segments 0..s,
+//              or of segment s alone where boundary adds them up (boundary_adds_up); float64 numbers [d][d], summed in float64 or in
+//              fixed point (fixed_point_gram).  Of the last segment: inverse(A0[h]) where A0 is given
+//   boundary:  seg_A[h][s] = inverse(inverse(A0[h]) + sum over segments 0..s-1), inverted in float64, rounded to float32
 //   combine:   seg_S[h][0] = S0[h];  seg_S[h][s+1] = seg_S[h][s] P[h][s] + Q[h][s]  (a.d_v rows)
 hipError_t launch_gram(const ForwardArgs& a, int d, int io_dtype, double* G, hipStream_t stream);
 hipError_t launch_boundary(const ForwardArgs& a, int d, const double* G, float* seg_A, hipStream_t stream);
