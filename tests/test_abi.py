@@ -295,3 +295,31 @@ def test_device_image_exports_the_static_workspace_symbol():
             found += [l.split() for l in syms.splitlines() if l.strip().endswith("scratch") or "7scratch" in l]
     assert found, "no scratch symbol in any device code object"
     assert any(f[2] == str(64 << 20) and f[3] == "OBJECT" and f[4] == "GLOBAL" and f[6] != "UND" for f in found), found
+
+
+@pytest.mark.parametrize("extra", [False, True])
+def test_outputs_are_on_the_device_of_q(monkeypatch, extra):
+    """Values may live on another device than queries (a peer's memory that the kernels reach); the outputs are q's neighbours.
+    The library's calls are replaced, so that host tensors can stand in."""
+    import contextlib
+
+    import torch
+
+    vla.load_library()
+
+    class OnGpu(torch.Tensor):
+        is_cuda = property(lambda self: True)
+
+    class Calls:
+        vla_forward_workspace_bytes = staticmethod(lambda *a: 0)
+        vla_forward = vla_decode_step = staticmethod(lambda *a: 0)
+
+    monkeypatch.setattr(binding, "_lib", Calls)
+    monkeypatch.setattr(binding, "_on_stream", lambda *a: (0, contextlib.nullcontext(), None))
+    t = lambda *shape, **kw: torch.empty(shape, **kw).as_subclass(OnGpu)
+    q, k, S, A = t(2, 3, 5, 32), t(2, 3, 5, 32), t(2, 3, 16, 32), t(2, 3, 32, 32)
+    v = t(*((2, 3, 5, 1, 16) if extra else (2, 3, 5, 16)), device="meta")
+    o = vla.vla_forward(q, k, v, S, A)[0]
+    assert o.device == q.device and o.shape == (2, 3, 5, 16) and o.dtype == v.dtype
+    o = vla.vla_decode_step(q[:, :, 0], k[:, :, 0], v[:, :, 0], S, A)
+    assert o.device == q.device and o.shape == (2, 3, 16) and o.dtype == v.dtype
