@@ -73,20 +73,17 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
   __shared__ __align__(16) float GQs[2][C * LT];   // GQ [s][t]
   __shared__ __align__(16) float wn2p[NW][C];
 
-  // One workgroup per (head, time segment); with a single segment it walks the whole sequence.
-  const int head = blockIdx.x / a.n_seg;
-  const int seg = blockIdx.x - head * a.n_seg;
+  const int head = blockIdx.x;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int c = lane & 15;
   const int g = lane >> 4;
-  const int tb = seg * a.seg_blocks * C;                                   // first token of the segment
-  const int T = min(a.T, tb + a.seg_blocks * C);                           // one past its last token
+  const int T = a.T;
   const float eps = a.eps;
   const bool fmap = a.feature_map != 0;   // q and k are replaced by ELU(x) + 1 as they are staged
   const int col0 = SL * w;
-  const int nblk = (a.T + C - 1) / C;                                      // blocks of the whole sequence
+  const int nblk = (T + C - 1) / C;
 
   float* wsh = a.ws + static_cast<size_t>(head) * head_stride(nblk, D);
   float* RN = wsh + off_rn(nblk, D);
@@ -95,8 +92,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
 
   f4 At[NB][NJ];
   {
-    const float* A0 = a.seg_A ? a.seg_A + static_cast<size_t>(blockIdx.x) * D * D
-                              : (a.A0 ? a.A0 + static_cast<size_t>(head) * D * D : nullptr);
+    const float* A0 = a.A0 ? a.A0 + static_cast<size_t>(head) * D * D : nullptr;
     const float diag = 1.0f / a.lambda0;
     const int arc = (4 * g) * D + col0 + c;
 #pragma unroll
@@ -114,7 +110,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
       }
   }
 
-  const size_t slab = static_cast<size_t>(head) * static_cast<size_t>(a.T) * D;
+  const size_t slab = static_cast<size_t>(head) * static_cast<size_t>(T) * D;
   const IO* qh = static_cast<const IO*>(a.q) + slab;
   const IO* kh = static_cast<const IO*>(a.k) + slab;
   const int srow = tid / TPR;
@@ -131,7 +127,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
       qpre.load(qh + koff);
     }
   };
-  if (tb < T) prefetch(tb);
+  if (T > 0) prefetch(0);
 
   // c_t, Z = (I + strict_lower(L) diag(c))^{-1} and -NQ^T of one block from what its factorisation left in LDS
   // copy `pb`; one wave.  Results go to the block's record in the workspace.
@@ -162,11 +158,10 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
     *reinterpret_cast<f4*>(smb + C * C + c * C + 4 * g) = nq;  // -NQ^T[t = c][s = 4g + r]
   };
 
-  int blk = seg * a.seg_blocks;
-  int it = 0;   // blocks done by this workgroup
+  int blk = 0;
   __builtin_amdgcn_s_setprio(1);
-  for (int t0 = tb; t0 < T; t0 += C, ++blk, ++it) {
-    const int pb = it & 1;
+  for (int t0 = 0; t0 < T; t0 += C, ++blk) {
+    const int pb = blk & 1;
     // ---- stage K^ and Q (LDS); 1 / max(||k||, eps) per token goes to the workspace
     if (stage_wave) {
       float kx[EPT];
@@ -259,8 +254,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
 
     // ---- one wave: Cholesky of I + G and L^{-1};
     //      another wave meanwhile: c, Z, NQ of the previous block
-    const int sw = it % NW;
-    const int sw2 = (it + 1) % NW;
+    const int sw = blk % NW;
+    const int sw2 = (blk + 1) % NW;
     if (w == sw) {
       __builtin_amdgcn_s_setprio(3);   // the dependent chain is what the other wave waits for: issue it first
       f4 gram = lds4(&Gp[0][0][c * LT + 4 * g]);
@@ -273,7 +268,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
       *reinterpret_cast<f4*>(&GQs[pb][c * LT + 4 * g]) = gq;
       cholesky16(gram, Lrs[pb], Lis[pb], c, g);
       __builtin_amdgcn_s_setprio(1);
-    } else if (w == sw2 && it > 0) {
+    } else if (w == sw2 && blk > 0) {
       __builtin_amdgcn_s_setprio(3);
       cz_pass(pb ^ 1, SMp + static_cast<size_t>(blk - 1) * SMB);
       __builtin_amdgcn_s_setprio(1);
@@ -304,8 +299,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) a_scan_kernel(Forwar
     Prod::template downdate<NB, NJ>(Whm, Wl, col0 + c, c, g, pb, [&](int b, int jn) -> f4& { return At[b][jn]; });
   }
   // c, Z, NQ of the last block: everything it needs was written before the last barrier
-  if (it > 0 && w == it % NW) cz_pass((it - 1) & 1, SMp + static_cast<size_t>(blk - 1) * SMB);
-  if (a.A_T && seg == a.n_seg - 1) {
+  if (blk > 0 && w == blk % NW) cz_pass((blk - 1) & 1, SMp + static_cast<size_t>(blk - 1) * SMB);
+  if (a.A_T) {
     float* AT = a.A_T + static_cast<size_t>(head) * D * D;
     int g2 = g, c2 = c;
     asm volatile("" : "+v"(g2), "+v"(c2));
