@@ -126,33 +126,43 @@ int pick_mode(int B, int H, int T, int d, int d_v, const vla_opts& o) {
   const long long heads = static_cast<long long>(B) * H;
   // Time-parallel mode or block kernel (bf16, one MI355X; time-parallel against block kernel, ms).  The segment kernels
   // gain on the block kernel as the sequence grows (their fixed passes amortise):
-  //   d = 128:  T = 2048: 64 heads 0.48 / 0.60, 80 heads 0.59 / 0.60;  T = 4096: 96 heads 1.13 / 1.24, 128: 1.34 / 1.25;
-  //             T = 8192: 128 heads 2.49 / 2.50;                       T = 16384: 128 heads 4.90 / 4.99
-  //   d =  96:  T = 1024: 48 heads 0.23 / 0.24, 64: 0.26 / 0.24;       T = 2048: 64 heads 0.40 / 0.46, 96: 0.52 / 0.47;
-  //             T = 4096: 96 heads 0.88 / 0.98, 128: 1.07 / 0.99;      T = 16384: 128 heads 3.95 / 3.94
-  //   d =  64:  T = 2048: 128 heads 0.31 / 0.36, 192: 0.40 / 0.35;     T = 4096: 192 heads 0.72 / 0.77, 320: 1.05 / 0.90;
-  //             T = 16384: 192 heads 2.46 / 3.08, 320: 3.97 / 3.55
-  //   d =  32:  T = 2048: 320 heads 0.32 / 0.34, 512: 0.47 / 0.35;     T = 16384: 320 heads 2.31 / 2.81, 512: 3.49 / 2.84
-  // The thresholds lie above the present crossovers in places, by up to 1.5 times in the time of a call: they were measured
+  //   d = 128:  T = 2048: 64 heads 0.37 / 0.52, 80 heads 0.42 / 0.52;  T = 4096: 96 heads 0.96 / 1.05, 128: 1.07 / 1.06;
+  //             T = 8192: 128 heads 2.04 / 2.12;                       T = 16384: 128 heads 4.08 / 4.19
+  //   d =  96:  T = 1024: 48 heads 0.158 / 0.202, 64: 0.176 / 0.202;   T = 2048: 64 heads 0.27 / 0.40, 96: 0.42 / 0.40;
+  //             T = 4096: 96 heads 0.71 / 0.80, 128: 0.86 / 0.80;      T = 16384: 128 heads 3.20 / 3.17
+  //   d =  64:  T = 1024: 128 heads 0.140 / 0.143, 192: 0.198 / 0.144; T = 2048: 128 heads 0.23 / 0.28, 192: 0.35 / 0.28;
+  //             T = 4096: 192 heads 0.63 / 0.58, 256: 0.74 / 0.58, 320: 0.97 / 0.77;
+  //             T = 16384: 192 heads 2.29 / 2.28, 256: 2.81 / 2.29, 320: 3.77 / 3.04
+  //   d =  32:  T = 1024: 256 heads 0.112 / 0.117, 512: 0.189 / 0.138; T = 2048: 320 heads 0.25 / 0.27, 512: 0.38 / 0.27;
+  //             T = 16384: 320 heads 1.83 / 2.13, 400: 2.61 / 2.13, 512: 2.77 / 2.14
+  // With u, the normalised read-out and the feature map the block kernel is the one of the options:
+  //   d = 128:  T = 2048: 64 heads 0.59 / 0.82;  T = 4096: 96 heads 1.63 / 1.65;  T = 16384: 96 heads 6.16 / 6.57, 128: 7.78 / 6.56
+  //   d =  96:  T = 2048: 64 heads 0.48 / 0.69;  T = 4096: 96 heads 1.42 / 1.38
+  //   d =  64:  T = 2048: 128 heads 0.41 / 0.50, 192: 0.56 / 0.50;  T = 4096: 192 heads 1.07 / 1.00, 320: 1.95 / 1.38;
+  //             T = 16384: 192 heads 4.16 / 3.95, 320: 7.86 / 5.49
+  //   d =  32:  T = 2048: 320 heads 0.42 / 0.51;  T = 16384: 320 heads 3.11 / 4.03, 512: 4.90 / 4.05
+  // The thresholds lie above the present crossovers in places, by up to 1.43 times in the time of a call: they were measured
   // when the block kernel took longer, and they stay because every segment restarts from a float64 inverse, which calls that
-  // moved to the block kernel would lose.  Error of A, time-parallel / block kernel, lambda0 = 0.1, Gaussian keys: d = 64, 512
-  // tokens 7e-8 / 3e-7, 4096 7e-8 / 2.9e-7, 16384 1.2e-7 / 5.2e-7, 131072 1e-6 / 2.6e-5; o and S differ from 16384 tokens on
-  // (3.3e-7 / 6.0e-7).
+  // moved to the block kernel would lose.  Error of A, time-parallel / block kernel, lambda0 = 0.1, Gaussian keys, 16 heads of 64: 4096
+  // tokens 1.3e-7 / 2.7e-7, 16384 1.9e-7 / 5.2e-7, 131072 5e-7 / 1.5e-6; of S 3.3e-7 / 4.0e-7, 3.5e-7 / 5.9e-7, 6e-7 / 1.5e-6.
+  // (Segments are as few as is fastest all the same, see plan_segments: half as many cost A 1.05 to 1.4 times its error, the block
+  // kernel two to three times.  opts->segments asks for more.)
   const int t_128 = d == 96 ? 4096 : 8192;   // from here 128 heads still gain at d >= 96
   long long few = d >= 96 ? (T >= t_128 ? 128 : (T >= 4096 ? 96 : 64))
                           : (d >= 64 ? (T >= 4096 ? 320 : 192) : 512);
   // Value heads of another size than the key heads: the same thresholds by the key head size, a notch higher
-  // where measured (the S rows kernel of the segment modes takes the row tiles of S in turn).  T = 4096, now: d_k = 64,
-  // d_v = 128: 128 heads 0.75 / 0.84, 160: 0.93 / 0.82, 384: 1.94 / 1.24; d_v = 16: 192 heads 0.70 / 0.76, 384: 1.35 / 0.89; d_k =
-  // 128, d_v = 64: 96 heads 1.07 / 1.10, 128: 1.27 / 1.12; d_v = 16: 128 heads 1.20 / 1.19; d_k = 32, d_v = 128: 128 heads 0.52 /
-  // 0.68, 192: 0.76 / 0.68, 1280: 3.07 / 2.37.
+  // where measured (the S rows kernel of the segment modes takes the row tiles of S in turn).  T = 4096: d_k = 64, d_v = 128:
+  // 128 heads 0.56 / 0.64, 160: 0.72 / 0.64, 384: 1.68 / 1.21; d_v = 16: 192 heads 0.57 / 0.56, 384: 1.08 / 0.68; d_k = 128, d_v =
+  // 64: 96 heads 0.86 / 0.86, 128: 1.06 / 0.86; d_v = 16: 128 heads 1.03 / 1.13; d_k = 32, d_v = 128: 128 heads 0.40 / 0.54, 192:
+  // 0.61 / 0.54, 1280: 2.95 / 2.33.
   if (d != d_v) {
     if (d == 64 && T >= 4096) few = 384;
     if (d == 128 && T >= 4096) few = 128;
     if (d == 32 && d_v == 128) few = 1280;
   }
-  // Short sequences (half the length), T = 512: 48 heads at d = 64 0.087 against 0.089 ms, 64: 0.093 against 0.088; 64 heads
-  // at d = 32 0.061 against 0.071, 128: 0.098 against 0.073; 2 heads at d = 128 0.127 against 0.149, 16: 0.163 against 0.149.
+  // Short sequences (half the length), T = 512: 48 heads at d = 64 0.065 against 0.074 ms, 64: 0.070 against 0.074; 64 heads
+  // at d = 32 0.047 against 0.060, 128: 0.070 against 0.060; 2 heads at d = 128 0.103 against 0.132, 16: 0.117 against 0.133, 32:
+  // 0.139 against 0.132.
   // Not at d = 96, whose Gram sums and boundary inverses run in the d = 128 layout.
   const long long few_short = d >= 96 ? 32 : (d >= 64 ? 64 : 256);
   const int t_short = d == 96 ? 1024 : 512;

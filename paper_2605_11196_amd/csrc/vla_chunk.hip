@@ -607,31 +607,35 @@ static int rounds(int n_heads, int resident) { return (n_heads + resident - 1) /
 // and holds twice the waves per head, so it wins as long as its workgroups are resident in one round, and beyond that
 // where the other kernel leaves a compute unit with fewer waves than SIMDs' worth of work.  Waves of 16 columns, one term
 // and three terms, this file's kernel / that one:
-//   d = 128: 16 heads 0.189 / 0.152 and 0.221 / 0.164, 256 heads 0.198 / 0.166 and 0.229 / 0.185, 512 heads 0.282 / 0.331
-//            and 0.364 / 0.368, 768 heads (three terms) 0.705 / 0.561
-//     d_v = 96: 256 heads 0.186 / 0.147 and 0.226 / 0.166, 512 heads 0.296 / 0.297 and 0.370 / 0.340, 768 heads 0.522 / 0.452
-//     and 0.659 / 0.512; d_v = 64: 256 heads 0.171 / 0.142 and 0.198 / 0.155, 512 heads 0.228 / 0.276 and 0.275 / 0.320, 768
-//     heads 0.406 / 0.434 and 0.539 / 0.477; d_v = 16: 256 heads 0.153 / 0.151 and 0.176 / 0.205 (one wave stages every token)
-//   d =  96: 256 heads 0.157 / 0.126 and 0.189 / 0.141, 512 heads 0.239 / 0.248 and 0.302 / 0.294, 768 heads 0.461 / 0.391
-//            and 0.559 / 0.443, 2048 heads 0.938 / 1.026 and 1.191 / 1.147
-//     d_v = 128: 256 heads 0.201 / 0.140 and 0.253 / 0.152, 2048 heads 1.41 / 1.09 and 2.01 / 1.25
-//     d_v = 64: 768 heads 0.466 / 0.375 and 0.572 / 0.425, 2048 heads 0.967 / 0.991 and 1.21 / 1.12; d_v = 32: 768 heads
-//     0.359 / 0.256 and 0.472 / 0.385, 2048 heads 0.771 / 0.622 and 0.957 / 1.018
+//   d = 128 (three terms): 16 heads 0.286 / 0.154, 256 heads 0.302 / 0.178, 512 heads 0.366 / 0.338, 768 heads 0.655 / 0.523
+//     d_v = 96: 256 heads 0.243 / 0.141 and 0.298 / 0.160, 512 heads 0.283 / 0.251 and 0.364 / 0.307, 768 heads 0.515 / 0.376
+//     and 0.655 / 0.470; d_v = 64: 256 heads 0.187 / 0.123 and 0.228 / 0.142, 512 heads 0.218 / 0.218 and 0.275 / 0.280, 768
+//     heads 0.387 / 0.343 and 0.537 / 0.428; d_v = 32: 256 heads 0.168 / 0.122 and 0.209 / 0.144, 512 heads 0.200 / 0.225 and
+//     0.260 / 0.290; d_v = 16 has none (one wave staged every token: 256 heads 0.153 / 0.151 and 0.176 / 0.205)
+//   d =  96: 256 heads 0.199 / 0.115 and 0.250 / 0.130, 512 heads 0.231 / 0.211 and 0.296 / 0.254, 768 heads 0.447 / 0.319
+//            and 0.561 / 0.386, 2048 heads 0.917 / 0.834 and 1.174 / 1.000
+//     d_v = 128, one term: 256 heads 0.273 / 0.130, 512 heads 0.314 / 0.234, 2048 heads 1.247 / 0.920
+//     d_v = 64: 256 heads 0.205 / 0.109 and 0.253 / 0.123, 768 heads 0.454 / 0.303 and 0.564 / 0.372, 2048 heads 0.939 / 0.796
+//     and 1.188 / 0.974; d_v = 32, three terms: 256 heads 0.196 / 0.114, 512 heads 0.235 / 0.221, 768 heads 0.456 / 0.330, 2048
+//     heads 0.932 / 0.865; d_v = 16: 512 heads 0.168 / 0.128 and 0.207 / 0.235, 2048 heads 0.671 / 0.621 and 0.830 / 0.945
 //     The first block of each chain stands alone, so where this one has half the rounds of workgroups, two of its heads
-//     beside each other win on the shortest sequences.  257 heads, 16 and 32 tokens, in us: 96 x 96, three terms 16 / 19 and
-//     26 / 28 (48 tokens: 35 / 36); 96 x 64, three terms 16 / 18 and 27 / 27; 96 x 128, one term 17 / 19 and 28 / 29.
-//   d =  64: 16 heads 0.123 / 0.089 and 0.126 / 0.092, 256 heads 0.123 / 0.095 and 0.128 / 0.097, 512 heads 0.146 / 0.130
-//            and 0.161 / 0.144, 640 heads 0.169 / 0.168 and 0.192 / 0.241
-//     d_v = 16: 512 heads 0.125 / 0.109 and 0.137 / 0.206; d_v = 96: 256 heads 0.140 / 0.101 and 0.162 / 0.106, 512 heads
-//     0.174 / 0.147 and 0.208 / 0.222; d_v = 128: 256 heads 0.131 / 0.104 and 0.163 / 0.115, 512 heads 0.163 / 0.160 and
-//     0.202 / 0.235
-//   d =  32: 256 heads 0.104 / 0.074 and 0.105 / 0.078, 1024 heads 0.136 / 0.127 and 0.148 / 0.138, 1536 heads 0.175 / 0.203
-//            and 0.197 / 0.253
-//     d_v = 64: 512 heads 0.139 / 0.105 and 0.150 / 0.108, 768 heads 0.143 / 0.131 and 0.155 / 0.142, 1024 heads 0.155 / 0.156
-//     and 0.174 / 0.235; d_v = 96: 512 heads 0.164 / 0.110 and 0.176 / 0.113, 768 heads 0.167 / 0.146 and 0.189 / 0.161;
-//     d_v = 128: 256 heads 0.133 / 0.087 and 0.160 / 0.091, 512 heads 0.180 / 0.130 and 0.201 / 0.140, 768 heads 0.185 / 0.200
-// The lines below do not reach every count at which that kernel is ahead: 513 to 768 heads of 96 and, with three terms, of
-// 128 x 64 to 128 x 128 stay here by 9 to 27 %, 512 heads of 32 x 128 and 64 x 96 and 768 of 32 x 64 and 32 x 96 by 8 to 30 %.
+//     beside each other win on the shortest sequences.  257 heads, 16 and 32 tokens, in us, before the C x C sections by panels:
+//     96 x 96, three terms 16 / 19 and 26 / 28 (48 tokens: 35 / 36); 96 x 64, three terms 16 / 18 and 27 / 27; 96 x 128, one term
+//     17 / 19 and 28 / 29.
+//   d =  64 (three terms): 16 heads 0.118 / 0.080, 256 heads 0.121 / 0.084, 512 heads 0.147 / 0.122, 640 heads 0.177 / 0.192
+//     d_v = 16: 512 heads 0.109 / 0.089 and 0.126 / 0.172; d_v = 32: 512 heads 0.121 / 0.103 and 0.140 / 0.164; d_v = 96: 256 heads
+//     0.134 / 0.087 and 0.165 / 0.093, 512 heads 0.168 / 0.129 and 0.199 / 0.184; d_v = 128: 256 heads 0.128 / 0.092 and
+//     0.159 / 0.100, 512 heads 0.160 / 0.141 and 0.197 / 0.159, 640 heads 0.191 / 0.206 and 0.237 / 0.238
+//   d =  32: 256 heads 0.116 / 0.063 and 0.131 / 0.065, 1024 heads 0.120 / 0.102 and 0.135 / 0.110, 1536 heads 0.158 / 0.161
+//            and 0.180 / 0.196
+//     d_v = 64: 512 heads 0.126 / 0.086 and 0.141 / 0.092, 768 heads 0.128 / 0.106 and 0.145 / 0.118, 1024 heads 0.135 / 0.126
+//     and 0.157 / 0.188; d_v = 96: 512 heads 0.151 / 0.092 and 0.167 / 0.097, 768 heads 0.154 / 0.119 and 0.178 / 0.128;
+//     d_v = 128: 256 heads 0.137 / 0.077 and 0.158 / 0.079, 512 heads 0.170 / 0.108 and 0.195 / 0.116, 768 heads 0.175 / 0.166 and
+//     0.204 / 0.179, 1024 heads 0.187 / 0.262 and 0.224 / 0.288
+// The lines below do not reach every count at which that kernel is ahead, by the times above: beyond 256 heads 128 x 96 and, with
+// three terms, 128 x 128 at any count (by 2 to 28 %), 128 x 64 and 128 x 32 from 513 to 768 (3 to 20 %), 96 x 96, 96 x 64 and 96 x 16
+// with one term and 96 x 32 with three (6 to 33 %); 512 heads of 64 x 96 and 64 x 128 (8 to 24 %), 513 to 1024 of 32 x 64 and 32 x 96 (7
+// to 28 %), 257 to 768 of 32 x 128 (5 to 40 %).
 static bool pipe_narrow(int d_k, int d_v, int n_heads, int T, int terms) {
   switch (d_k) {
     case 128: return n_heads <= 256 && d_v > 16;
@@ -646,8 +650,9 @@ static bool pipe_narrow(int d_k, int d_v, int n_heads, int T, int terms) {
     default: return false;
   }
 }
-// Its waves of 32 columns, one term: 512 heads of 128 0.290 / 0.255, 768 0.531 / 0.394, 2048 1.092 / 0.985 (d_v = 64: 0.889 /
-// 1.150, not taken); 257 heads of 64 0.142 / 0.117, 1024 0.211 / 0.180, 1280 0.328 / 0.259, 2048 0.413 / 0.365.
+// Its waves of 32 columns, one term, where the ones of 16 take more rounds, 16 / 32 columns: 300 heads of 128 0.272 / 0.222, 512
+// 0.289 / 0.238, 768 0.439 / 0.386, 2048 1.174 / 0.950 (d_v = 64, against this file's kernel: 0.889 / 1.150, not taken); 257 heads of
+// 64 0.102 / 0.099, 1024 0.202 / 0.163, 1280 0.242 / 0.229, 2048 0.391 / 0.336.
 static bool pipe_wide(int d_k, int d_v, int n_heads, int terms) {
   return terms == 1 && d_k == d_v && (d_k == 64 || d_k == 128) && n_heads > 256;
 }
@@ -655,13 +660,14 @@ static bool pipe_wide(int d_k, int d_v, int n_heads, int terms) {
 // What is left for the kernel here: waves of 16 columns instead of 32?  Such a wave has half the splits and products
 // between two serial sections but as much of everything else, so it pays while it runs on a SIMD that would be idle: as long
 // as the narrow workgroups are resident in one round.  Wide / narrow waves, one term and three terms:
-//   d = 128 (4 / 8 waves): d_v = 64: 256 heads 0.190 / 0.171 and 0.229 / 0.198, 512 heads 0.226 / 0.336 and 0.276 / 0.406
-//   d =  64 (2 / 4 waves), three terms: 768 heads 0.235 / 0.206, 1024 heads 0.415 / 0.357, 2048 heads 0.694 / 0.561
-//     d_v = 96: 768 heads 0.234 / 0.217 and 0.280 / 0.264, 1024 heads 0.249 / 0.372 and 0.504 / 0.432
+//   d = 128 (4 / 8 waves): d_v = 16: 256 heads 0.156 / 0.150 and 0.191 / 0.172, 512 heads 0.185 / 0.279 and 0.237 / 0.345
+//   d =  64 (2 / 4 waves), one term: 768 heads of d_v = 16 0.156 / 0.128, of 96 0.228 / 0.205, of 128 0.267 / 0.200; 1024 heads 0.164 /
+//     0.154, 0.245 / 0.355, 0.287 / 0.341; 1536 heads of 16 0.208 / 0.274.  Three terms narrow always (768 heads of d_v = 96 0.280 /
+//     0.264, 1024 0.504 / 0.432 before the C x C sections by panels)
 //   d =  32 (1 / 2 waves):
-//     d_v = 64: 1024 heads 0.162 / 0.153 and 0.183 / 0.165, 1280 heads (three terms) 0.240 / 0.217, 1536: 0.242 / 0.304,
-//               3072: 0.479 / 0.514, 2048 heads (one term) 0.223 / 0.318
-//     d_v = 128: 1024 heads 0.713 / 0.195 (the wide wave's slab of S does not fit its registers)
+//     d_v = 64: 1024 heads 0.156 / 0.135 and 0.176 / 0.158, 1280 heads (three terms) 0.223 / 0.198, 1536: 0.225 / 0.290,
+//               3072: 0.447 / 0.479, 2048 heads (one term) 0.205 / 0.287
+//     d_v = 128: 1024 heads 0.713 / 0.188 (the wide wave's slab of S does not fit its registers)
 static bool narrow_waves(int d_k, int d_v, int n_heads, int terms) {
   switch (d_k) {
     case 128: return n_heads <= 256;
@@ -677,13 +683,12 @@ static bool narrow_waves(int d_k, int d_v, int n_heads, int terms) {
 // Three-term operands leave three workgroups of d = 64 and six of d = 32 (wide waves) a compute unit, FP32 products four
 // and eight: those win where they save a round.  Square heads then take several heads per workgroup
 // (vla_chunk_multihead.hip), others products on the FP32 instruction here.  float32, split / several heads:
-//   d = 64: 768 heads 0.206 / 0.278, 1024: 0.357 / 0.280, 1536: 0.398 / 0.552, 2048: 0.561 / 0.563, 3072: 0.790 / 0.837
-//           (with the feature map, bf16: 1024: 0.363 / 0.273, 2048: 0.589 / 0.547, 3072: 0.797 / 0.824)
-//   d = 32: 1024 heads 0.145 / 0.160, 1536: 0.196 / 0.219, 2048: 0.320 / 0.222, 3072: 0.385 / 0.431, 4096: 0.560 / 0.441
+//   d = 64: 768 heads 0.188 / 0.282, 1024: 0.329 / 0.278, 1536: 0.400 / 0.577, 2048: 0.567 / 0.569, 3072: 0.767 / 0.841
+//   d = 32: 1024 heads 0.135 / 0.156, 1536: 0.180 / 0.216, 2048: 0.312 / 0.221, 3072: 0.364 / 0.426
 // and, split / FP32 products here:
-//   64 x 16: 1024 heads 0.310 / 0.222, 2048: 0.475 / 0.524     64 x 32: 1024 heads 0.327 / 0.247, 2048: 0.510 / 0.576
-//   64 x 96: 769 heads 0.385 / 0.358, 1024: 0.432 / 0.373      64 x 128: 769 heads 0.384 / 0.413, 896: 0.426 / 0.430, 1024: 0.458 / 0.437
-//   32 x 16: 2048 heads 0.308 / 0.195    32 x 64: 1536 heads 0.242 / 0.276, 2048: 0.370 / 0.288, 3072: 0.479 / 0.542, 4096: 0.658 / 0.559
+//   64 x 16: 768 heads 0.150 / 0.197, 1024: 0.273 / 0.222, 2048: 0.443 / 0.506     64 x 32: 1024 heads 0.311 / 0.246, 2048: 0.493 / 0.571
+//   64 x 96: 768 heads 0.252 / 0.358, 1024: 0.427 / 0.360      64 x 128: 768 heads 0.252 / 0.426, 1024: 0.425 / 0.428
+//   32 x 16: 1536 heads 0.156 / 0.167, 2048: 0.272 / 0.174    32 x 64: 1536 heads 0.225 / 0.255, 2048: 0.345 / 0.268, 3072: 0.447 / 0.505
 static bool fewer_rounds_unsplit(int d_k, int n_heads) {
   if (d_k == 32) return rounds(n_heads, 2048) < rounds(n_heads, 1536);
   if (d_k == 64) return 11 * rounds(n_heads, 1024) < 8 * rounds(n_heads, 768);   // a round of each: 0.28 and 0.20 ms

@@ -678,7 +678,11 @@ hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
   return io_dtype == 1 ? launch<D, DV, SL, DB, SPLIT, uint16_t>(a, stream) : launch<D, DV, SL, DB, SPLIT, float>(a, stream);
 }
 // Which calls the kernel with the A chain and the S chain on waves of their own (vla_chunk_general_pipe.hip) takes.  T = 256,
-// this file's kernel / that one with waves of 16 columns (/ of 32), ms; bf16, every option on, unless said otherwise:
+// this file's kernel (before its C x C sections by panels: 0.95 to 0.98 of the times since) / that one with waves of 16 columns (/ of
+// 32), ms; bf16, every option on, unless said otherwise.  Heads of 64 up to 256 and of 32 up to 512 (d_v <= d) were on FP32 products
+// there and are on split ones here: error against float64 of o 0.84 to 0.92 of what it was, of S 0.83 to 0.89, of A 0.96 to 1.0 (14 pairs of
+// sizes, five sets of options; u = k^ with the feature map, 1000 tokens, A 1.6e-7 -> 2.0e-7, S 4.5e-7 -> 4.7e-7, o 6.0e-7 -> 5.6e-7).
+// Heads of 128 x 16 spill (float32, u 205 registers), and win all the same: 256 heads, 64 tokens 0.0430 / 0.0409.
 //   d = 128: 64 heads 0.164 / 0.114, 256 heads 0.179 / 0.128, 512 heads 0.307 / 0.238 / 0.201, 2048 heads 1.160 / 0.918 /
 //            0.792; float32 256 heads 0.172 / 0.132, 2048 heads 1.253 / 0.993 / 1.006 (three-term u leaves one workgroup of
 //            wide waves a compute unit); no u, 2048 heads 0.951 / 0.799 / 0.845 (registers spill)

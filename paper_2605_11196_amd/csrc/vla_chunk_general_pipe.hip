@@ -14,8 +14,8 @@
 //
 // What bounds it: with both states on every wave (vla_chunk_general.hip) a block is the sum of the two chains behind six
 // barriers, the matrix unit 31 % and the vector unit 50 % of the cycles.  Here four waves of two heads share a SIMD: in a
-// block 363 matrix and some 1300 vector instructions a head and SIMD, about 24000 of its 29800 cycles.  2048 heads of 128, 8192 tokens,
-// bf16, every option: 35.9 -> 25.2 ms (16.8 us -> 11.8 us a block of two heads).  Of that: directions in bf16 stay one term
+// block 418 matrix and some 1320 other vector instructions a head and SIMD; matrix pipes busy 57 % of the cycles, vector issue 42 %
+// beside them, LDS 48 %.  2048 heads of 128, 8192 tokens, bf16, every option: 35.9 -> 25.2 ms (16.8 us -> 11.8 us a block of two heads).  Of that: directions in bf16 stay one term
 // (three products with A instead of six), the residuals of the splits go to the matrix unit (split3_cut_matrix), the Gram
 // matrices are formed from a wave's own columns, without the barrier that a whole Y needs.  k^ is kept once more in float32 for the refresh terms and
 // the key sum (256 heads of 128, 512 tokens 0.258 -> 0.231 ms, 2048 heads 1.63 -> 1.59), and the key sum as split terms.
@@ -636,7 +636,7 @@ __global__ void __launch_bounds__(64 * (NWA + NWS), WPE) chunk_general_pipe_kern
     constexpr int kHalf = (NKB + 1) / 2;
     for (int blk = 0; blk < nblk; ++blk) {
       fresh();
-      // opaque: the compiler would peel the first block and keep twice the values over the loop (118 spilled registers for 61)
+      // opaque: the compiler would peel the first block and keep twice the values over the loop (some 60 more registers spilled; 51 are)
       int done = blk;
       asm volatile("" : "+s"(done));
       if (done > 0) s_update(blk - 1);

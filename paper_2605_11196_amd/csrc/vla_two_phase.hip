@@ -877,11 +877,9 @@ hipError_t launch_s_rows_lds_n(const ForwardArgs& a, hipStream_t stream) {
       if (hs <= 256) return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, true, 2>);
     }
     // Three-term operands of d = 64 take 44 KB, three workgroups per compute unit: beyond 768 pairs a last round that
-    // is nearly empty costs float32 calls more than the FP32 products do (33 KB, four workgroups).  16 heads, T = 65536,
-    // 1024 pairs: 1.12 to 1.13 ms against 1.17 with split products here and the maps apart; 24 heads, T = 4096, 384
-    // pairs: 0.208 against 0.190.
-    // Not mapped bf16 calls, whose maps are apart in any case: 16 heads, T = 65536: 1.083 split, 1.107 FP32; 320 heads,
-    // T = 4096: 1.25 and 1.30.
+    // is nearly empty costs float32 calls more than the FP32 products do (33 KB, four workgroups).  FP32 / split here, ms: 16 heads,
+    // T = 65536 in 64 segments 0.997 / 1.013; 192 heads, T = 4096, 960 pairs 0.762 / 0.768; two-phase, T = 512, 800 heads 0.296 / 0.302,
+    // 1024 0.319 / 0.323, 1500 0.512 / 0.504.
     if constexpr (D == 64 && sizeof(IO) == 4 && !RECT && !MAP) {
       if (hs > 768) return reinterpret_cast<const void*>(&s_rows_lds_kernel<D, NJV, RECT, IO, MAP, kNt, false, kWps>);
     }
@@ -1005,12 +1003,15 @@ hipError_t launch_two_phase(const ForwardArgs& a, int d, int io_dtype, hipStream
 // 256 pairs from d = 96, 512 at d = 64, 1024 at d = 32), in segments of at least 2 blocks up to one pair per compute unit and of
 // 16 blocks beyond.  The boundary inverses and the composition of the maps cost time per segment.  16 heads, bf16, ms:
 // d = 128, T = 32768: 16 segments 1.22, 32 1.30, 64 1.55;  d = 64, T = 32768: 16 0.56, 32 0.45, 48 0.50, 64 0.50, T = 131072: 32
-// 1.58, 48 1.75, 64 1.62;  d = 32, T = 131072: 32 1.02, 64 0.78.
+// 1.58, 48 1.75, 64 1.62, T = 4096: 8 0.162, 12 0.126, 16 0.108, 24 0.119, 32 0.111;  d = 32, T = 131072: 32 1.02, 64 0.78.
 // Few heads: the composition walks the segments of a head one after another, so their count stops at about the square
 // root of the blocks times 2.5 (2 from d = 96).  One head, d = 64: T = 4096 16 segments 0.104, 32 0.084, 64 0.090, 128 0.129;
 // T = 32768 64 0.205, 128 0.181, 256 0.233;  d = 128, T = 4096: 16 0.246, 32 0.218, 64 0.257;  T = 32768 64 0.515, 96 0.506, 256 0.741.
 // Head counts that leave more than an eighth of a round empty take up to two.  T = 4096: 192 heads of 64 2 segments 0.79, 3 0.75,
-// 4 0.64, 5 0.68;  320 heads 2 1.17, 3 1.02;  90 heads of 128 2 1.19, 5 1.06;  96 heads of 96, T = 8192 2 1.84, 5 1.44.
+// 4 0.64, 5 0.68;  320 heads 2 1.17, 3 1.02;  90 heads of 128 2 1.19, 5 1.06;  96 heads of 96, T = 8192 2 1.84, 5 1.44.  Those that
+// fill it do not, though that leaves one segment (the A chain alone, without a restart from an inverse) to 224 to 256 heads from d =
+// 96 and 448 to 512 of 64: 240 heads of 128 1 segment 1.48, 2 2.04, 4 2.19, of 96 1.50, 1.54, 1.76;  240 of 64 2 0.74, 4 0.76;  480
+// of 64 1 1.27, 2 1.41;  112 of 128 2 1.06, 4 1.10, of 96 2 0.86, 4 0.84, of 64 4 0.40, 8 0.42.
 //
 // With the options (`general`: the A chain runs on the option kernel, three workgroups per compute unit at
 // d = 64) a resident round is 768 pairs at d = 64, and the longer chain favours segments of 32 blocks there too
