@@ -114,14 +114,6 @@ def _refuse_state(name, shape, dev):
     raise ValueError(f"{name} must be a contiguous float32 tensor of shape {shape} on {dev}")
 
 
-def _like_v(torch, v, shape, dev):
-    """The output tensor: v's shape and type, on q's device `dev` (empty_like: 1.4 us, empty with all three spelled out 2.3, for v
-    from another device and with further dimensions of one element)."""
-    if v.dim() == len(shape) and v.device == dev:
-        return torch.empty_like(v, memory_format=torch.contiguous_format)
-    return torch.empty(shape, dtype=v.dtype, device=dev)
-
-
 def _on_device(torch, dev):
     """`dev` as the current device; entering it costs a microsecond, so only where another one is current."""
     return _SAME_DEVICE if dev.index == torch.cuda.current_device() else torch.cuda.device(dev)
@@ -233,7 +225,9 @@ def vla_decode_step(q, k, v, S, A, *, eps=None, stream=None, u=None, u_scale=Non
         if u is not None:
             u = u.contiguous()
             op.u = u.data_ptr()
-        o = _like_v(torch, v, (B, H, dv), dev)
+        # empty_like takes 1.4 us, empty with shape, type and device 2.3: for v from another device or with further dimensions of one
+        o = (torch.empty_like(v, memory_format=torch.contiguous_format) if v.dim() == 3 and v.device == dev
+             else torch.empty((B, H, dv), dtype=q.dtype, device=dev))
         if outside is not None:
             o.record_stream(outside)
         rc = _lib.vla_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), S.data_ptr(), A.data_ptr(), o.data_ptr(),
@@ -285,7 +279,8 @@ def vla_forward(q, k, v, S0=None, A0=None, *, lambda0=None, eps=None, mode=None,
     with context:
         q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
         u = None if u is None else u.contiguous()
-        o = _like_v(torch, v, (B, H, T, dv), dev)
+        o = (torch.empty_like(v, memory_format=torch.contiguous_format) if v.dim() == 4 and v.device == dev
+             else torch.empty((B, H, T, dv), dtype=q.dtype, device=dev))
         S_T = torch.empty((B, H, dv, dk), dtype=torch.float32, device=dev) if return_state else None
         A_T = torch.empty((B, H, dk, dk), dtype=torch.float32, device=dev) if return_state else None
         zkey_T = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if return_zkey else None
