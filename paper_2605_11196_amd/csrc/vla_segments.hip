@@ -255,14 +255,15 @@ __device__ __forceinline__ void gram_sum(const ForwardArgs& a, double* G) {
 // tile rows.
 //
 // Bound by the staging's vector instructions (about 10 an element) beside 15 matrix ones per tile and 64 tokens.  16 heads of 64,
-// 131072 tokens, bf16: 195 us in float64 (v_mfma_f64_16x16x4_f64, 64 cycles each), 118 here (13 products 114, 16 122); 16 heads of
-// 128, 32768 tokens 188 and 95 (13 products 89, 16 104).
+// 131072 tokens, bf16: 195 us in float64 (v_mfma_f64_16x16x4_f64, 64 cycles each), 119 here (13 products 114, 16 122); 16 heads of
+// 128, 32768 tokens 188 and 95 (13 products 89, 16 104).  D = 64 keeps three workgroups per compute unit, though some registers spill:
+// with two, 320 heads, 512 tokens, 960 workgroups, the whole call 178 -> 188 us.
 typedef int i4 __attribute__((ext_vector_type(4)));
 
 constexpr int fixed_threads(int d) { return d >= 96 ? 512 : 256; }
 
 template <int D, typename IO>
-__global__ void __launch_bounds__(fixed_threads(D), D >= 64 ? 2 : 3) gram_fixed_kernel(ForwardArgs a, double* G, int shift) {
+__global__ void __launch_bounds__(fixed_threads(D), D >= 96 ? 2 : 3) gram_fixed_kernel(ForwardArgs a, double* G, int shift) {
   constexpr int NS = D / 16;                        // column strips
   constexpr int KG = D == 32 ? 2 : 1;               // waves across the tokens of a tile
   constexpr int TT = 64 * KG;                       // tokens of a tile

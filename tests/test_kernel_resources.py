@@ -112,6 +112,7 @@ KNOWN = {
         (96, 6, 6, 3, "f32", 3, 3): (8, 1), (96, 6, 6, 3, "bf16", 1, 3): (20, 16),
     },
     "gram_fixed_kernel": {
+        (64, "f32"): (104, 57), (64, "bf16"): (24, 5),
         (128, "f32"): (140, 124), (128, "bf16"): (16, 5), (96, "f32"): (24, 9),
     },
     "gram_kernel": {}, "gram_given_a0_kernel": {}, "boundary_kernel": {},
