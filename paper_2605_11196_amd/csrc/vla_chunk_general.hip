@@ -687,6 +687,8 @@ hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
 //            0.792; float32 256 heads 0.172 / 0.132, 2048 heads 1.253 / 0.993 / 1.006 (three-term u leaves one workgroup of
 //            wide waves a compute unit); no u, 2048 heads 0.951 / 0.799 / 0.845 (registers spill)
 //     d_v = 96: 2048 heads 1.149 / 0.882;  d_v = 64: 256 heads 0.178 / 0.116, 2048 heads 0.922 / 0.815, 16 tokens 0.080 / 0.084;
+//     float32, u, now: 17 to 48 tokens, 2048 heads 0.120 / 0.126 and 0.171 / 0.177, 4096 heads 0.236 / 0.256 and 0.334 / 0.346, 768
+//     heads, 32 tokens 0.053 / 0.049;
 //     d_v = 32: 256 heads 0.178 / 0.120, 512 heads, float32 0.246 / 0.244, 2048 heads, float32 0.907 / 0.950;
 //     d_v = 16: 256 heads 0.168 / 0.139, 512 heads 0.243 / 0.270
 //   d =  96: 256 heads 0.147 / 0.105, 2048 heads 1.146 / 0.768, 2048 heads, 16 tokens 0.102 / 0.076; every d_v alike
@@ -700,7 +702,10 @@ hipError_t launch_as(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
 //     (with the normalised read-out 0.0148 / 0.0159; two blocks 0.0223 / 0.0225, without u, 513 heads 0.0132 / 0.0127)
 bool pipe_narrow(const ForwardArgs& a, int d, int d_v, int io_dtype) {
   switch (d) {
-    case 128: return a.n_heads <= 256 || d_v >= 96 || (d_v == 64 && a.T > 16);
+    case 128: {
+      const int few_blocks = io_dtype == 0 && a.u != nullptr && a.n_heads > 1024 ? 48 : 16;
+      return a.n_heads <= 256 || d_v >= 96 || (d_v == 64 && a.T > few_blocks);
+    }
     case 96: return true;
     case 64: return a.n_heads <= 256 || (a.n_heads <= 512 && d_v <= 64);
     case 32: {

@@ -377,7 +377,7 @@ def test_option_block_kernel_on_both_sides_of_its_head_counts(d, heads, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d,d_v,heads", [(32, 16, 3), (32, 128, 3), (32, 128, 513), (32, 64, 769), (64, 32, 3), (64, 64, 513), (64, 96, 257), (96, 64, 3),
+@pytest.mark.parametrize("d,d_v,heads", [(32, 16, 3), (32, 128, 3), (32, 128, 513), (32, 64, 769), (64, 32, 3), (64, 64, 513), (64, 96, 257), (96, 64, 3), (128, 64, 1025),
                                          (128, 16, 3), (128, 96, 3), (128, 128, 257)])
 def test_option_chains_on_waves_of_their_own(d, d_v, heads, dtype):
     """Every staging layout and both wave widths, from one token to ragged third blocks, state and phase carried in; the
