@@ -534,14 +534,15 @@ __global__ void __launch_bounds__(64 * NW, 2) chunk_kernel(ForwardArgs a) {
 //   float32 numbers lets three waves on a SIMD, so that this begins where two rounds of four workgroups would do: 1700 heads 355 / 352,
 //   1800 391 / 365, 2048 424 / 370, but 1200 (five together, one round) 240 / 305, 2500 463 / 517.
 //   A second round of between a quarter and half of the places: two of its workgroups go where two end together, and none to the
-//   next.  128 x 96, one term: 640 heads 532 / 507, 768 555 / 508, 900 564 / 563;  16 x 128, 256 tokens: 2500 heads 232 / 232,
-//   3072 280 / 242, 3500 292 / 293.
+//   next.  64 x 96, one term: 1280 heads 394 / 384, 1536 471 / 447; 32 x 128, one term 1500 355 / 341, three 410 / 392 (one term,
+//   1400 heads, T = 1024 648 / 672); 128 x 96, one term: 640 heads 532 / 507, 768 555 / 508, 900 564 / 563;  16 x 128, 256 tokens: 2500
+//   heads 232 / 232, 3072 280 / 242, 3500 292 / 293.
 // One block does not pay for it: 64 x 128, 3072 heads, 16 tokens 43.8 / 45.8.
-enum LastRound { kAny, kFull, kThreeQuarters, kHalf };
+enum LastRound { kAny, kFullOrHalf, kThreeQuarters, kHalf };
 constexpr LastRound loop_rule(int d, int d_v, int nw, bool f32, bool one_term) {
   if (d == 16) return d_v == 128 ? kHalf : kAny;
-  if (nw == 2 && d == 32) return d_v == 128 ? kFull : d_v == 96 && f32 ? kThreeQuarters : kAny;
-  if (nw == 2 && d == 64) return one_term && d_v > d ? kFull : kAny;
+  if (nw == 2 && d == 32) return d_v == 128 ? kFullOrHalf : d_v == 96 && f32 ? kThreeQuarters : kAny;
+  if (nw == 2 && d == 64) return one_term && d_v > d ? kFullOrHalf : kAny;
   return d == 128 && d_v == 96 && one_term ? kHalf : kAny;
 }
 // workgroups that the compute units hold together, by registers (two waves per SIMD; 32 x 96 of float32 numbers: as if two)
@@ -550,9 +551,10 @@ inline bool takes_turns(LastRound rule, int n_heads, int T, int resident) {
   if (rule == kAny || n_heads <= resident || T < 64) return false;
   const int last = (n_heads - 1) % resident + 1;
   const bool second = n_heads <= 2 * resident;
-  if (rule == kFull) return 32 * last >= 31 * resident;
+  const bool half = second && 4 * last >= resident && 2 * last <= resident;
+  if (rule == kFullOrHalf) return half || 32 * last >= 31 * resident;
   if (rule == kThreeQuarters) return second && 4 * last > 3 * resident;
-  return second && 4 * last >= resident && 2 * last <= resident;
+  return half;
 }
 
 template <int D, int DV, int NW, typename IO, bool FMAP, bool SPLIT>

@@ -574,7 +574,7 @@ def test_waves_of_16_and_of_32_columns(d, d_v, heads, dtype):
 
 @pytest.mark.parametrize("d,d_v,heads,resident,dtype", [
     (64, 96, 2047, 1024, "bf16"), (64, 96, 3072, 1024, "bf16"), (64, 128, 2040, 1024, "bf16"), (32, 128, 2048, 1024, "bf16"),
-    (32, 128, 2040, 1024, "f32"), (32, 96, 1793, 1024, "f32"), (128, 96, 640, 512, "bf16"), (128, 96, 768, 512, "bf16"),
+    (32, 128, 2040, 1024, "f32"), (32, 128, 1280, 1024, "f32"), (64, 96, 1536, 1024, "bf16"), (32, 96, 1793, 1024, "f32"), (128, 96, 640, 512, "bf16"), (128, 96, 768, 512, "bf16"),
     (16, 128, 2560, 2048, "f32"), (16, 128, 3072, 2048, "bf16")])
 def test_workgroups_that_go_through_the_heads_in_turn(d, d_v, heads, resident, dtype):
     """The block kernel where a workgroup takes the heads h, h + resident, ...: odd and even numbers of blocks before the next
