@@ -473,13 +473,19 @@ hipError_t launch(const ForwardArgs& a, int io_dtype, hipStream_t stream) {
 
 // Waves of 16 columns up to d = 96, of 32 at d = 128 (three-term keys leave no registers with 16 waves: 16 heads, T = 32768,
 // float32 1.43 against 1.51 ms; bf16 1.22 and 1.25).  d = 64 on two A waves of 32 columns: 16 heads, T = 131072 1.58 -> 1.73 ms.
+// Five slots a wave (heads of 32, d_v beyond 96) spill registers where they are compiled for four waves a SIMD.  Up to 256 pairs
+// of head and segment, one a compute unit, they are compiled for two: 16 heads, T = 4096, float32 152 -> 141 us, bf16 137 -> 130;
+// one head, T = 512, float32 46.1 -> 44.7.  With more pairs than that the workgroups that fit count: 1024 pairs (16 heads,
+// T = 16384) on two 289 -> 294, bf16 233 -> 253.
 hipError_t launch_a_map(const ForwardArgs& a, int d, int io_dtype, hipStream_t stream) {
   const int dv = a.d_v > 0 ? a.d_v : d;
+  const bool few = static_cast<long long>(a.n_heads) * a.n_seg <= 256;
   switch (d) {
     case 32:
       return dv <= 32   ? launch<32, 2, 2, 2, 4>(a, io_dtype, stream)
              : dv == 64 ? launch<32, 2, 2, 3, 4>(a, io_dtype, stream)
              : dv == 96 ? launch<32, 2, 2, 4, 4>(a, io_dtype, stream)
+             : few      ? launch<32, 2, 2, 5, 2>(a, io_dtype, stream)
                         : launch<32, 2, 2, 5, 4>(a, io_dtype, stream);
     case 64: return dv <= 64 ? launch<64, 4, 4, 2, 4>(a, io_dtype, stream) : launch<64, 4, 4, 3, 4>(a, io_dtype, stream);
     case 96: return dv <= 96 ? launch<96, 6, 6, 2, 3>(a, io_dtype, stream) : launch<96, 6, 6, 3, 3>(a, io_dtype, stream);

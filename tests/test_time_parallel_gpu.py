@@ -330,6 +330,15 @@ def test_maps_beside_the_a_chain_in_every_slot_layout(d, d_v, dtype, feature_map
         check_parity(q, k, v, S0, A0, dtype=dtype, mode=TP, segments=segments, feature_map=feature_map)
 
 
+@pytest.mark.parametrize("dtype,feature_map", [("f32", False), ("bf16", False), ("bf16", True)])
+@pytest.mark.parametrize("heads", [128, 129])
+def test_maps_of_five_slots_in_up_to_one_workgroup_a_compute_unit_and_in_more(heads, dtype, feature_map):
+    """Two segments of a head: 256 pairs and the first count above."""
+    q, k, _ = vla_inputs.gaussian_qkv(1, heads, 53, 32, seed=heads)
+    v = np.random.default_rng(heads).standard_normal((1, heads, 53, 128)).astype(np.float32)
+    check_parity(q, k, v, None, None, dtype=dtype, mode=TP, segments=2, feature_map=feature_map)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,T,segments,lambda0", [
     (32, 16 * 9 + 5, 3, 0.1), (64, 16 * 12 + 1, 3, 0.1), (96, 16 * 8 + 15, 2, 0.1), (128, 16 * 9, 3, 0.1),   # ragged tiles of 64 and 128 tokens
